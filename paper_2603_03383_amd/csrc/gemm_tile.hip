@@ -1,0 +1,295 @@
+// GEMM for more than 64 rows (several sequences verified together): sum_k X[m][k] * W[n][k], bf16 or fp16 in (element
+// type E), fp32 out.  From ~100 rows on a weight is used often enough that the matrix cores, and the bytes a CU can
+// request, matter as much as the HBM stream, so this kernel is built around operand reuse and a deep, barrier-light
+// pipeline:
+//   * a workgroup owns BM = 32 WR MT rows x BN = 32 WC NT columns (up to 256 x 128, so every weight is fetched once per
+//     row block) and consists of TWO groups of WR x WC = 4 waves; a round brings 64 features of X and W to LDS and
+//     group g multiplies features 32g .. 32g + 31 of it.  The two groups share a CU's SIMDs, so one group's LDS reads
+//     and waits overlap the other's MFMAs, and the K split inside the workgroup costs one exchange through LDS at the
+//     end instead of a partial-sum slot in memory;
+//   * both operands go straight to LDS (`global_load_lds`, 16 B per lane, no registers) into a ring of NS rounds; a wave
+//     waits for its own loads of a round with a counted vmcnt and one workgroup barrier per round makes them everyone's.
+//     The loads are written as inline assembly because the compiler, once it sees loads that write LDS, drains all
+//     of them before every LDS read;
+//   * X is read row-major, 128 B (one cache line) of eight rows per instruction; the 16-byte chunks of a row are XOR-ed
+//     with the row number on the way in (through the per-lane source addresses), which makes the operand reads bank
+//     conflict free without padding.  W arrives in the packed order (common.h): 4 KiB per tile and round, contiguous;
+//   * the MFMA is issued as W x X^T: a lane then holds four consecutive output columns of ONE row per register quad, so
+//     sums leave as 16-byte (fp32) or 8-byte (SwiGLU output) stores.
+// What bounds it: a CU keeps about 64 KiB of loads in flight whatever the ring holds (measured: rings of 3, 4 and 6 rounds
+// run alike), which at HBM latency is ~50 GB/s of X and W together (135 GB/s when every line is an L2 hit); hence the
+// tall tiles.  Measured on [M, K] x [N, K]^T, us per launch, before (128 x 256 tiles, operands through registers) / now:
+// 192 rows: 12288 x 4096: 55 / 35, 22016 x 4096 (with SwiGLU): 88 / 57, 4096 x 4096: 20.6 / 16.4, 4096 x 11008: 38 / 30.
+// 96 rows had no kernel but the portable one (800 / 26, 840 / 42, 810 / 12, 2170 / 23).
+#include "kernels.h"
+
+namespace mdz {
+
+typedef f32x16_t f32x16;
+typedef u32x4_t u32x4;
+
+namespace {
+constexpr int kRound = 64;  // features per round
+
+__device__ inline float silu_tile(float v) { return v / (1.0f + expf(-v)); }
+
+#define MDZ_LDS_ADDR(p) ((uint32_t)(uintptr_t)((__attribute__((address_space(3))) void*)(p)))
+
+// One wave brings 64 x 16 B from base + voff (per lane) to LDS address `lds` + 16 * lane.  base and lds are wave-uniform.
+__device__ inline void load_to_lds(const void* base, uint32_t voff, uint32_t lds) {
+  const uint64_t p = (uint64_t)base;
+  const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p) |
+                     ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32);
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane((int)lds)),
+               "v"(voff), "s"(u)
+               : "memory");
+}
+template <int N>
+__device__ inline void wait_loads() {  // all but the N youngest loads of this wave have landed
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ inline void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+}  // namespace
+
+// SWIGLU (gate/up matrix, NT == 2: a wave's two tiles are the gate and the up columns of the same 32 features): an unsplit
+// launch writes SiLU(gate) * up as E instead of the sums.
+template <typename E, int WR, int WC, int MT, int NT, int NS, bool SWIGLU>
+__global__ void __launch_bounds__(512, 2)
+    gemm_tile_kernel(const E* __restrict__ X, int M, int K, const E* __restrict__ Wp, int n_tiles, float* __restrict__ P,
+                     int64_t ldp, int64_t part_stride, int nb_m, int nb_n, int ksplit, E* __restrict__ U) {
+  static_assert(WR * WC == 4, "a group has four waves, one per SIMD");
+  static_assert(!SWIGLU || NT == 2, "gate and up tiles of a pair in one wave");
+  constexpr int XT = WR * MT, WT = WC * NT;            // 32-row and 32-column tiles of the workgroup
+  constexpr int UX = XT * 4, UT = (XT + WT) * 4;       // 1 KiB pieces of a round: X (8 rows x 128 B each), then W
+  constexpr int L = (UT + 7) / 8;                      // loads per wave and round (a few repeat the last piece)
+  constexpr uint32_t kSlot = UT * 1024;
+  static_assert(NS * kSlot >= 4 * MT * NT * 4096, "the groups' exchange fits the ring");
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds_raw[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Workgroups are dealt round-robin to the 8 XCDs: column blocks are dealt the same way and the row blocks of a column
+  // block follow each other on one XCD, so they share its weights through that XCD's L2.
+  const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
+  const int bn = (seq / nb_m) * 8 + xcd, bm = seq % nb_m;
+  if (bn >= nb_n) return;
+  const int n_rounds = K / kRound;
+  const int r_lo = (int)((int64_t)blockIdx.z * n_rounds / ksplit), r_hi = (int)((int64_t)(blockIdx.z + 1) * n_rounds / ksplit);
+  const int nst256 = (K + kStageFeatures - 1) / kStageFeatures;
+  const int grp = wave >> 2, wr = (wave & 3) / WC, wc = (wave & 3) % WC;
+
+  f32x16 acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  const uint32_t lds0 = MDZ_LDS_ADDR(lds_raw);
+  // rows beyond M re-read row M-1 and tiles beyond n_tiles re-read tile 0; neither is stored.  Rounds past the range
+  // repeat its last one and are never multiplied, so the wait counts below are the same in every trip.
+  auto load_round = [&](int r, int slot) {
+#pragma unroll
+    for (int q = 0; q < L; ++q) {
+      int u = q * 8 + wave;
+      u = u < UT ? u : UT - 1;
+      const uint32_t dst = lds0 + slot * kSlot + u * 1024;
+      if (u < UX) {
+        const int row8 = u * 8 + (lane >> 3), c = (lane & 7) ^ (row8 & 7);
+        const int row = min(bm * XT * 32 + row8, M - 1);
+        load_to_lds(X + (int64_t)r * kRound, (uint32_t)row * (uint32_t)K * 2 + c * 16, dst);
+      } else {
+        const int v = u - UX;
+        int tile = bn * WT + (v >> 2);
+        tile = tile < n_tiles ? tile : 0;
+        const int ks = r * 4 + (v & 3);
+        // packed order [band of 4 tiles][stage of 256 features][tile in band][16 k-steps][lane]
+        const int64_t unit = (((int64_t)(tile >> 2) * nst256 + (ks >> 4)) * kBandTiles + (tile & 3)) * 16 + (ks & 15);
+        load_to_lds(reinterpret_cast<const uint8_t*>(Wp) + unit * 1024, lane * 16, dst);
+      }
+    }
+  };
+
+  const int n = r_hi - r_lo;
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s) load_round(r_lo + min(s, n - 1), s);
+  int slot = 0;
+  for (int s = 0; s < n; ++s) {
+    const int prev = slot == 0 ? NS - 1 : slot - 1;
+    wait_loads<(NS - 2) * L>();
+    __builtin_amdgcn_s_barrier();  // round s is in LDS for everyone, and everyone has read round s - 1
+    __builtin_amdgcn_sched_barrier(0);
+    const uint8_t* base = lds_raw + slot * kSlot;
+    u32x4 a[2][MT], b[2][NT];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        b[ks][j] = *reinterpret_cast<const u32x4*>(base + (UX + (wc * NT + j) * 4 + grp * 2 + ks) * 1024 + lane * 16);
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+        a[ks][i] = *reinterpret_cast<const u32x4*>(base + ((wr * MT + i) * 32 + (lane & 31)) * 128 +
+                                                   ((grp * 4 + ks * 2 + (lane >> 5)) ^ (lane & 7)) * 16);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_round(r_lo + min(s + NS - 1, n - 1), prev);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = Elem16<E>::mfma(b[ks][j], a[ks][i], acc[i][j]);
+    wait_lds();  // this wave's reads of the slot are in registers before the next barrier lets it be overwritten
+    __builtin_amdgcn_sched_barrier(0);
+    slot = slot + 1 == NS ? 0 : slot + 1;
+  }
+  wait_loads<0>();
+  __syncthreads();
+
+  // The groups exchange halves through LDS: group 0 finishes the even row tiles, group 1 the odd ones (sums of group 0
+  // first, whoever adds them).
+  float* xch = reinterpret_cast<float*>(lds_raw);
+  auto cell = [&](int i, int j, int q) { return xch + ((((i * NT + j) * 4 + q) * 4 + (wave & 3)) * 64 + lane) * 4; };
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+    if ((i & 1) != grp) {
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<float4*>(cell(i, j, q)) =
+              float4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+    }
+  __syncthreads();
+  // D layout of W x X^T: lane holds row m = lane % 32 of the tile; register 4q + e is column 8q + 4 (lane / 32) + e.
+  float* out = SWIGLU ? nullptr : P + (int64_t)blockIdx.z * part_stride;
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+    if ((i & 1) == grp) {
+      const int m = (bm * XT + wr * MT + i) * 32 + (lane & 31);
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 o = *reinterpret_cast<const float4*>(cell(i, j, q));
+          acc[i][j][4 * q] += o.x, acc[i][j][4 * q + 1] += o.y, acc[i][j][4 * q + 2] += o.z, acc[i][j][4 * q + 3] += o.w;
+        }
+      if (m >= M) continue;
+      if constexpr (SWIGLU) {
+        const int tile = bn * WT + wc * 2;  // gate tile; its features are 16 tile .. + 31 of [M][16 n_tiles]
+        if (tile + 1 < n_tiles) {
+          E* u = U + (int64_t)m * (n_tiles * 16) + tile * 16 + 4 * (lane >> 5);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = silu_tile(acc[i][0][4 * q + e]) * acc[i][1][4 * q + e];
+            *reinterpret_cast<uint2*>(u + 8 * q) = uint2{Elem16<E>::pack2(v[0], v[1]), Elem16<E>::pack2(v[2], v[3])};
+          }
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          const int tile = bn * WT + wc * NT + j;
+          if (tile < n_tiles) {
+            float* o = out + (int64_t)m * ldp + tile * 32 + 4 * (lane >> 5);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              *reinterpret_cast<float4*>(o + 8 * q) =
+                  float4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+          }
+        }
+      }
+    }
+}
+
+namespace {
+struct TilePlan {
+  int bm, bn, ksplit;  // rows and columns of a workgroup's tile, K splits
+  int nb_m, nb_n;
+};
+
+// Tile and split by a small model of the launch: a workgroup's time is the larger of its requests at 50 GB/s and its
+// MFMAs at 4.5 TFLOP/s (what a CU sustains in this kernel's loop on real data) plus ~4 us of start and tail, workgroups run
+// in rounds of one per CU, the launch cannot beat the HBM stream of W, and every partial-sum slot is written here and read
+// back by the consumer.  The constants are measured on MI355X; the choice only moves work between equal results.
+TilePlan plan_tile(int M, int N, int K, int max_split, bool swiglu) {
+  TilePlan best{};
+  double best_t = 1e30;
+  const int n_rounds = K / kRound, cus = num_cus();
+  const int bms[3] = {128, 192, 256}, bns[2] = {128, 64};
+  for (int bm : bms)
+    for (int bn : bns) {
+      if (swiglu && bn != 128) continue;
+      const int nb_m = (M + bm - 1) / bm, nb_n = (N + bn - 1) / bn;
+      for (int ks = 1; ks <= 8 && ks <= max_split && ks <= n_rounds; ++ks) {
+        const int64_t wgs = (int64_t)nb_m * nb_n * ks;
+        const double feats = (double)((n_rounds + ks - 1) / ks) * kRound;
+        const double load = feats * (bm + bn) * 2 / 50e3, mfma = feats * bm * bn * 2 / 4.5e6;  // us
+        const double rounds = (double)((wgs + cus - 1) / cus);
+        double t = rounds * ((load > mfma ? load : mfma) + 4.0);
+        const double hbm = (double)N * K * 2 / 5.5e6 + 4.0;
+        if (t < hbm) t = hbm;
+        t += (double)ks * M * N * 4 * (1.0 / 5e6 + 1.0 / 4e6);
+        if (t < best_t - 1e-9) best_t = t, best = TilePlan{bm, bn, ks, nb_m, nb_n};
+      }
+    }
+  return best;
+}
+}  // namespace
+
+bool gemm_tile_supported(int dtype, int M, int N, int K) {
+  return is_16bit(dtype) && M > 64 && N % 32 == 0 && K % kRound == 0 && K >= kRound && (int64_t)M * K < (int64_t)1 << 31;
+}
+
+// partial-sum slots launch_gemm_tile will write for this problem (sizes the slot workspace)
+int gemm_tile_slots(int M, int N, int K, int max_split) { return plan_tile(M, N, K, max_split, false).ksplit; }
+
+template <typename E, bool SWIGLU>
+static int launch_gemm_tile_t(const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp, int64_t part_stride,
+                              int max_split, Partials* res, void* U, hipStream_t st) {
+  const TilePlan p = plan_tile(M, N, K, max_split, SWIGLU);
+  if (res) {
+    res->n = p.ksplit;
+    res->split_grid = 0;
+    res->band_cols = p.bn;
+    res->n_stages = 1;
+    res->split_units = 0;
+  }
+  const dim3 grid((p.nb_n + 7) / 8 * 8 * p.nb_m, 1, p.ksplit);
+#define MDZ_TILE_CASE(MT, NT, NS)                                                                                        \
+  if (p.bm == 64 * MT && p.bn == 64 * NT) {                                                                              \
+    constexpr int lds_bytes = NS * (2 * MT + 2 * NT) * 4 * 1024;                                                         \
+    static_assert(lds_bytes <= 160 * 1024, "LDS of a CU");                                                               \
+    MDZ_SET_LDS_ONCE((gemm_tile_kernel<E, 2, 2, MT, NT, NS, SWIGLU>), lds_bytes);                                        \
+    launch_timed(PROF_GEMM_LARGE, gemm_tile_kernel<E, 2, 2, MT, NT, NS, SWIGLU>, grid, 512, lds_bytes, st, (const E*)X, M, \
+                 K, (const E*)Wp, N / 32, P, ldp, part_stride, p.nb_m, p.nb_n, p.ksplit, (E*)U);                         \
+    MDZ_LAUNCH_CHECK();                                                                                                  \
+    return MDZ_OK;                                                                                                       \
+  }
+  MDZ_TILE_CASE(2, 2, 4)
+  MDZ_TILE_CASE(3, 2, 3)
+  MDZ_TILE_CASE(4, 2, 3)
+  if constexpr (!SWIGLU) {
+    MDZ_TILE_CASE(2, 1, 5)
+    MDZ_TILE_CASE(3, 1, 4)
+    MDZ_TILE_CASE(4, 1, 4)
+  }
+#undef MDZ_TILE_CASE
+  MDZ_FAIL(MDZ_EUNSUPPORTED, "gemm: no tile kernel for a %d x %d tile", p.bm, p.bn);
+}
+
+int launch_gemm_tile(int dtype, const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp,
+                     int64_t part_stride, int max_split, Partials* res, hipStream_t st) {
+  MDZ_WITH_ELEM16(dtype, return (launch_gemm_tile_t<E, false>(X, Wp, P, M, N, K, ldp, part_stride, max_split, res, nullptr, st)));
+}
+
+// gate/up GEMM with the SwiGLU in its epilogue: U [M][N / 2] of the storage type
+bool gemm_tile_swiglu_supported(int dtype, int M, int N, int K) { return gemm_tile_supported(dtype, M, N, K) && N % 64 == 0; }
+
+int launch_gemm_tile_swiglu(int dtype, const void* X, const void* Wp, void* U, int M, int N, int K, hipStream_t st) {
+  MDZ_WITH_ELEM16(dtype, return (launch_gemm_tile_t<E, true>(X, Wp, nullptr, M, N, K, N, 0, 1, nullptr, U, st)));
+}
+
+}  // namespace mdz

@@ -46,49 +46,35 @@ void gemm_mfma_describe(int M, int N, int K, int max_split, Partials* res, int* 
 int launch_gemm_mfma(int dtype, const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp,
                      int64_t part_stride, int max_split, Partials* res, hipStream_t st);
 
-bool gemm_large_supported(int dtype, int M, int N, int K);
-int gemm_large_slots(int M, int N, int K);
-int launch_gemm_large(int dtype, const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp,
-                      int64_t part_stride, Partials* res, hipStream_t st);
+bool gemm_tile_supported(int dtype, int M, int N, int K);
+int gemm_tile_slots(int M, int N, int K, int max_split);
+int launch_gemm_tile(int dtype, const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp,
+                     int64_t part_stride, int max_split, Partials* res, hipStream_t st);
 
 bool gemm_mfma_swiglu_supported(int dtype, int M, int N, int K);
 int launch_gemm_mfma_swiglu(int dtype, const void* X, const void* Wp, void* U, int M, int N, int K, hipStream_t st);
 bool gemm_mfma_argmax_supported(int dtype, int M, int N, int K);
 int gemm_mfma_argmax_cands(int M, int N, int K);
 int launch_gemm_mfma_argmax(int dtype, const void* X, const void* Wp, int M, int N, int K, ArgCand* cand, hipStream_t st);
-bool gemm_large_swiglu_supported(int dtype, int M, int N, int K);
-int launch_gemm_large_swiglu(int dtype, const void* X, const void* Wp, void* U, int M, int N, int K, hipStream_t st);
+bool gemm_tile_swiglu_supported(int dtype, int M, int N, int K);
+int launch_gemm_tile_swiglu(int dtype, const void* X, const void* Wp, void* U, int M, int N, int K, hipStream_t st);
 
 int launch_gemm(int dtype, const void* X, const void* Wp, float* out, int M, int N, int K, int64_t ld, int max_split,
                 Partials* res, hipStream_t st) {
   *res = single_slot(out, (int64_t)M * ld, ld);
-  // several sequences at once: the MFMA-bound kernel (it splits K only when the caller's consumer reduces slots)
-  if (gemm_large_supported(dtype, M, N, K) && (max_split > 1 || gemm_large_slots(M, N, K) == 1))
-    return launch_gemm_large(dtype, X, Wp, out, M, N, K, ld, res->stride, res, st);
-  const int rows_per_launch = M <= 64 ? M : 64;
-  if (gemm_mfma_supported(dtype, rows_per_launch, N, K) && (M <= 64 || M % 64 == 0)) {
-    // More than 64 rows (several sequences): one launch per block of 64 rows.  Every launch uses the same plan, so
-    // the slot counts are identical; the first launch streams the matrix from HBM, the following ones mostly from
-    // the memory-side cache.
-    for (int m0 = 0; m0 < M; m0 += rows_per_launch) {
-      int rc = launch_gemm_mfma(dtype, (const char*)X + (int64_t)m0 * K * 2, Wp, out + (int64_t)m0 * ld, rows_per_launch, N,
-                                K, ld, res->stride, max_split, res, st);
-      if (rc) return rc;
-    }
-    return MDZ_OK;
-  }
+  if (gemm_tile_supported(dtype, M, N, K))  // more than 64 rows: several sequences at once
+    return launch_gemm_tile(dtype, X, Wp, out, M, N, K, ld, res->stride, max_split, res, st);
+  if (gemm_mfma_supported(dtype, M, N, K)) return launch_gemm_mfma(dtype, X, Wp, out, M, N, K, ld, res->stride, max_split, res, st);
   return launch_gemm_generic(dtype, X, Wp, out, M, N, K, ld, false, st);
 }
 
-// split-K is only worth its partial-sum traffic for skinny problems
-static int max_split_for(int rows) { return (rows <= 64 || rows % 64 == 0) ? 12 : 1; }
+// most partial-sum slots a consumer of a layer GEMM's output is given (the fused norm requests twelve together)
+constexpr int kMaxLayerSlots = 12;
 // fp32 elements of partial-sum workspace a [rows, N] = [rows, K] x [N, K] GEMM needs
 static int64_t gemm_part_elems(int dtype, int rows, int N, int K) {
-  if (gemm_large_supported(dtype, rows, N, K)) return (int64_t)gemm_large_slots(rows, N, K) * rows * N;
-  const int per = rows <= 64 ? rows : 64;
-  const int slots = (gemm_mfma_supported(dtype, per, N, K) && (rows <= 64 || rows % 64 == 0))
-                        ? gemm_mfma_slots(per, N, K, max_split_for(rows))
-                        : 1;
+  int slots = 1;
+  if (gemm_tile_supported(dtype, rows, N, K)) slots = gemm_tile_slots(rows, N, K, kMaxLayerSlots);
+  else if (gemm_mfma_supported(dtype, rows, N, K)) slots = gemm_mfma_slots(rows, N, K, kMaxLayerSlots);
   return (int64_t)slots * rows * N;
 }
 
@@ -263,7 +249,7 @@ static int run_layer(const mdz_model_desc& m, const mdz_layer_weights& lw, int l
                      void* xn_next, hipStream_t st) {
   const TreeTables* t = host_tree(m.tree);
   const int rows = B * t->T;
-  const int ms = max_split_for(rows);
+  const int ms = kMaxLayerSlots;
   const KvGeom g = geom(kv, m.n_heads / kv_heads(m));
   int rc;
   float* cs = (float*)(ws + w.rope_cs);
@@ -284,8 +270,8 @@ static int run_layer(const mdz_model_desc& m, const mdz_layer_weights& lw, int l
   if ((rc = launch_gemm(m.dtype, att, lw.wo, part, rows, m.d, m.d, m.d, ms, &pr, st))) return rc;
   if ((rc = launch_residual_rmsnorm(m.dtype, x, pr, lw.g_ffn, xn, rows, m.d, m.rms_eps, st, fdt))) return rc;
   // SwiGLU in the GEMM's epilogue where a workgroup ends up with whole gate/up column pairs
-  if (gemm_large_swiglu_supported(fdt, rows, 2 * m.ffn, m.d)) {
-    if ((rc = launch_gemm_large_swiglu(fdt, xn, lw.wgateup, u, rows, 2 * m.ffn, m.d, st))) return rc;
+  if (gemm_tile_swiglu_supported(fdt, rows, 2 * m.ffn, m.d)) {
+    if ((rc = launch_gemm_tile_swiglu(fdt, xn, lw.wgateup, u, rows, 2 * m.ffn, m.d, st))) return rc;
   } else if (rows <= 64 && gemm_mfma_swiglu_supported(fdt, rows, 2 * m.ffn, m.d)) {
     if ((rc = launch_gemm_mfma_swiglu(fdt, xn, lw.wgateup, u, rows, 2 * m.ffn, m.d, st))) return rc;
   } else {
@@ -521,11 +507,11 @@ int medusa_heads(const mdz_model_desc* model, const mdz_weights* w, const void* 
     stacked = (const char*)w->head_w1[k] == (const char*)w->head_w1[0] + k * w1_bytes;
   if (stacked) {
     const int n_all = t->K * m.d;
-    if ((rc = launch_gemm(m.dtype, h, w->head_w1[0], part, B, n_all, m.d, n_all, max_split_for(B), &pr, st))) return rc;
+    if ((rc = launch_gemm(m.dtype, h, w->head_w1[0], part, B, n_all, m.d, n_all, kMaxLayerSlots, &pr, st))) return rc;
     if ((rc = launch_head_residual(m.dtype, h, pr, -1, b1s, t->K, z, B, m.d, st))) return rc;
   } else {
     for (int k = 0; k < t->K; ++k)
-      if ((rc = launch_gemm(m.dtype, h, w->head_w1[k], part + k * head_part, B, m.d, m.d, m.d, max_split_for(B), &pr, st)))
+      if ((rc = launch_gemm(m.dtype, h, w->head_w1[k], part + k * head_part, B, m.d, m.d, m.d, kMaxLayerSlots, &pr, st)))
         return rc;
     pr.p = part;
     if ((rc = launch_head_residual(m.dtype, h, pr, head_part, b1s, t->K, z, B, m.d, st))) return rc;
