@@ -1,4 +1,4 @@
-// Tree-masked attention for 16-bit storage (bf16 or fp16, element type E), 64-node tree, head_dim 128, on gfx950 MFMA
+// Tree-masked attention for 16-bit storage (bf16 or fp16, element type E), trees of 64 or 15 nodes, head_dim 128, on gfx950 MFMA
 // (Section 3.2: all T candidates attend in one pass; node i sees the whole prefix plus the tree slots
 // its row of the static visibility matrix allows).
 //
@@ -26,7 +26,6 @@ typedef f32x16_t f32x16;
 typedef u32x4_t u32x4;
 
 constexpr int kHD = 128;         // head_dim
-constexpr int kTQ = 64;          // queries (tree nodes)
 constexpr int kQRow = kHD * 2 + 16;  // bytes per staged Q row
 constexpr float kLazyLog2 = 8.f;  // see the key loop: how far a block's maximum may exceed the running reference
 
@@ -106,7 +105,10 @@ __device__ inline void rope16(const float* cs_row, int seg, float (&lo)[16], flo
 // (sequence, head, split) being two workgroups (blockIdx.z = 2 * sequence + half): half the accumulators, so two
 // workgroups share a CU and twice as many loads are in flight per CU, at the price of K and V passing through the
 // CU twice (the second time from L2: the halves are a multiple of 8 workgroups apart, i.e. on one XCD).
-template <typename E, bool Q8, int NU>
+// TQ: nodes of the tree = queries of a sequence (64, or 15: one group of 32 of which the last 17 are padding that is
+// never stored.  Six sequences of 40 .. 1500 keys x 32 heads take 30 us per layer; the portable kernel took 928 us
+// for them).
+template <typename E, bool Q8, int NU, int TQ>
 __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
     attn_tree_mfma_kernel(int tree, const E* __restrict__ q, const Partials qkv, const float* __restrict__ cs,
                           KvGeom g, E* __restrict__ kc, E* __restrict__ vc, int layer,
@@ -120,12 +122,14 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
   constexpr int kQW = 32 * NU;          // queries of this workgroup
   constexpr int kOPadN = kQW + 2;       // LDS row stride of the merge buffer (floats): conflict-free writes and reads
   const int split = blockIdx.x, n_splits = gridDim.x, h = blockIdx.y;
-  const int b = NU == 2 ? blockIdx.z : blockIdx.z >> 1;
-  const int q0 = NU == 2 ? 0 : (blockIdx.z & 1) * 32;  // first query of this workgroup
+  constexpr int kHalves = TQ > kQW ? 2 : 1;  // workgroups that share a sequence's queries
+  constexpr int kRows = TQ < kQW ? TQ : kQW;  // queries of this workgroup that exist
+  const int b = blockIdx.z / kHalves;
+  const int q0 = (blockIdx.z % kHalves) * 32;  // first query of this workgroup
   const int hk = h / g.group;  // the key/value head that query head h reads (grouped-query attention)
   const int d = q_heads(g) * kHD, dkv = g.n_heads * kHD;
   const int S = min(max(seq_len[b], 0), max_prefix);
-  const int n_slots = S + kTQ;
+  const int n_slots = S + TQ;
   const int nb = (n_slots + 31) >> 5;
   int blk_begin, blk_end;
   if (qkv.p != nullptr && n_splits > 1) {  // last split: every block with a tree slot; the others: prefix-only blocks
@@ -188,13 +192,14 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
       int idx = threadIdx.x + i * 256;
       int row = idx >> 4, col = idx & 15;
       *reinterpret_cast<u32x4*>(q_lds + row * kQRow + col * 16) =
-          *reinterpret_cast<const u32x4*>(q + (int64_t)(b * kTQ + q0 + row) * d + h * kHD + col * 8);
+          *reinterpret_cast<const u32x4*>(q + (int64_t)(b * TQ + q0 + min(row, kRows - 1)) * d + h * kHD + col * 8);
     }
   } else {
     // thread (row = t/4, seg = t%4): features [16 seg, +16) and their rotary partners of one row.  K / V rows: tree
-    // node `row` (all 64, by all threads); Q rows: query q0 + row (the first 32 NU rows of threads).
+    // node `row` (all TQ, by the first TQ rows of threads); Q rows: query q0 + row (the first 32 NU rows of threads, the
+    // padding as copies of the last query).
     const int row = threadIdx.x >> 2, seg = threadIdx.x & 3;
-    const int64_t grow_kv = (int64_t)b * kTQ + row, grow_q = (int64_t)b * kTQ + q0 + row;
+    const int64_t grow_kv = (int64_t)b * TQ + min(row, TQ - 1), grow_q = (int64_t)b * TQ + q0 + min(row, kRows - 1);
     const float* cs_kv = cs + grow_kv * kHD;  // 64 pairs x 2
     auto stage_q = [&](float (&lo)[16], float (&hi)[16]) {
       uint8_t* qrow = q_lds + row * kQRow;
@@ -269,8 +274,10 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
       } else {
         float lo[2][16], hi[2][16];
         const int cols[2] = {d + hk * kHD, d + dkv + hk * kHD};
-        qkv_gather<2>(qkv, grow_kv, cols, seg, lo, hi);
-        write_kv(lo[0], hi[0], lo[1], hi[1]);
+        if (row < TQ) {
+          qkv_gather<2>(qkv, grow_kv, cols, seg, lo, hi);
+          write_kv(lo[0], hi[0], lo[1], hi[1]);
+        }
         if (row < kQW) {
           float ql[1][16], qh[1][16];
           const int qcols[1] = {h * kHD};
@@ -292,7 +299,7 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
   const uint8_t* qfrag = q_lds + qi * kQRow + gh * 16;
   uint64_t mq[NU];
 #pragma unroll
-  for (int u = 0; u < NU; ++u) mq[u] = t.anc_mask[q0 + 32 * u + qi];
+  for (int u = 0; u < NU; ++u) mq[u] = t.anc_mask[min(q0 + 32 * u + qi, TQ - 1)];
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)kHD);
 
   float m_run[NU], l_run[NU];
@@ -456,10 +463,11 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
     for (int w = 0; w < 4; ++w) a += wt[w] * o_lds[(w * kHD + f) * kOPadN + qq];
     acc[j] = a;
   }
-  const int q_out = q0 + qq;  // the query's row among the 64 of its sequence
+  const int q_out = q0 + qq;  // the query's row among those of its sequence
+  if (kRows < kQW && qq >= kRows) return;
   if (n_splits == 1) {
     const float inv = 1.0f / L;
-    E* dst = att_out + (int64_t)(b * kTQ + q_out) * d + h * kHD + s4;
+    E* dst = att_out + (int64_t)(b * TQ + q_out) * d + h * kHD + s4;
 #pragma unroll
     for (int jj = 0; jj < 8; ++jj) {
       if constexpr (kEW == 4)
@@ -470,7 +478,7 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
     }
   } else {
     const int64_t pidx = ((int64_t)(b * q_heads(g) + h) * n_splits + split);
-    float* po = part_o + (pidx * kTQ + q_out) * kHD + s4;
+    float* po = part_o + (pidx * TQ + q_out) * kHD + s4;
 #pragma unroll
     for (int jj = 0; jj < 8; ++jj) {
       if constexpr (kEW == 4)
@@ -479,8 +487,8 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
         *reinterpret_cast<float2*>(po + 16 * jj) = float2{acc[2 * jj], acc[2 * jj + 1]};
     }
     if (threadIdx.x % kTPQ == 0) {
-      part_ml[(pidx * 2 + 0) * kTQ + q_out] = M;
-      part_ml[(pidx * 2 + 1) * kTQ + q_out] = L;
+      part_ml[(pidx * 2 + 0) * TQ + q_out] = M;
+      part_ml[(pidx * 2 + 1) * TQ + q_out] = L;
     }
   }
   MDZ_STAMP(4);
@@ -488,13 +496,14 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
 
 // Merges the key-splits of 16 queries of one (sequence, head): fixed order, exact same weighting rule as above.
 // Thread (q = t/16, c = t%16) owns features 8c .. 8c+7 of query 16*blockIdx.z + q.
-template <typename E>
+template <typename E, int TQ>
 __global__ void __launch_bounds__(256)
     attn_combine_kernel(int n_heads, int n_splits, const float* __restrict__ part_o, const float* __restrict__ part_ml,
                         E* __restrict__ att_out) {
   const int h = blockIdx.x, b = blockIdx.y;
   const int d = n_heads * kHD;
   const int qq = blockIdx.z * 16 + (threadIdx.x >> 4), f0 = (threadIdx.x & 15) * 8;
+  if (TQ % 16 != 0 && qq >= TQ) return;
   const int64_t p0 = (int64_t)(b * n_heads + h) * n_splits;
   float M = -INFINITY;
   float L = 0.f;
@@ -511,9 +520,9 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
     for (int s = 0; s < kTogether; ++s)
       if (s0 + s < n_splits) {
-        ms[s] = part_ml[((p0 + s0 + s) * 2 + 0) * kTQ + qq];
-        ls[s] = part_ml[((p0 + s0 + s) * 2 + 1) * kTQ + qq];
-        const float4* po = reinterpret_cast<const float4*>(part_o + ((p0 + s0 + s) * kTQ + qq) * kHD + f0);
+        ms[s] = part_ml[((p0 + s0 + s) * 2 + 0) * TQ + qq];
+        ls[s] = part_ml[((p0 + s0 + s) * 2 + 1) * TQ + qq];
+        const float4* po = reinterpret_cast<const float4*>(part_o + ((p0 + s0 + s) * TQ + qq) * kHD + f0);
         v0[s] = po[0], v1[s] = po[1];
       }
     float Mg = M;
@@ -540,11 +549,12 @@ __global__ void __launch_bounds__(256)
   uint32_t pk[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) pk[j] = Elem16<E>::pack2(acc[2 * j] * inv, acc[2 * j + 1] * inv);
-  *reinterpret_cast<u32x4*>(att_out + (int64_t)(b * kTQ + qq) * d + h * kHD + f0) = u32x4{pk[0], pk[1], pk[2], pk[3]};
+  *reinterpret_cast<u32x4*>(att_out + (int64_t)(b * TQ + qq) * d + h * kHD + f0) = u32x4{pk[0], pk[1], pk[2], pk[3]};
 }
 
 bool attn_mfma_supported(int dtype, int tree, const KvGeom& g) {
-  return is_16bit(dtype) && g.tiled && g.head_dim == kHD && host_tree(tree)->T == kTQ;
+  return is_16bit(dtype) && g.tiled && g.head_dim == kHD &&
+         (host_tree(tree)->T == 64 || (host_tree(tree)->T == 15 && !g.quant));
 }
 
 // Key-splits per (sequence, head).  fused: the kernel starts from the QKV partial sums, so one split is the tree
@@ -565,7 +575,7 @@ static int attn_splits(int B, int n_heads, int max_prefix, bool fused) {
     if (ps > 31) ps = 31;
     return ps >= 1 ? ps + 1 : 1;
   }
-  int nb = (max_prefix + kTQ + 31) / 32;
+  int nb = (max_prefix + 64 + 31) / 32;
   int by_len = nb / 8;                        // >= 2 blocks per wave
   int by_fill = (512 + pairs - 1) / pairs;    // aim at ~512 workgroups
   int s = by_len < by_fill ? by_len : by_fill;
@@ -577,10 +587,10 @@ static int attn_splits(int B, int n_heads, int max_prefix, bool fused) {
 int64_t attn_mfma_scratch_bytes(int B, int n_heads, int max_prefix) {
   int s = attn_splits(B, n_heads, max_prefix, true), s2 = attn_splits(B, n_heads, max_prefix, false);
   s = s > s2 ? s : s2;
-  return s == 1 ? 0 : (int64_t)B * n_heads * s * (kTQ * kHD + 2 * kTQ) * 4;
+  return s == 1 ? 0 : (int64_t)B * n_heads * s * (64 * kHD + 2 * 64) * 4;
 }
 
-template <typename E, bool Q8, int NU>
+template <typename E, bool Q8, int NU, int TQ>
 static int launch_attention_mfma_t(int tree, const void* q, const Partials* qkv, const float* cs, const KvGeom& g, void* kc,
                                    void* vc, int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out,
                                    void* scratch, int64_t scratch_bytes, hipStream_t st) {
@@ -588,20 +598,20 @@ static int launch_attention_mfma_t(int tree, const void* q, const Partials* qkv,
   // the merge buffer [4][128][32 NU + 2] + [4][2][32 NU] floats overlays the staged Q tile
   constexpr int lds_bytes = 4 * kHD * (32 * NU + 2) * 4 + 4 * 2 * 32 * NU * 4;
   static_assert(lds_bytes >= 32 * NU * kQRow && lds_bytes * (3 - NU) <= 160 * 1024, "LDS budget of the tree kernel");
-  MDZ_SET_LDS_ONCE((attn_tree_mfma_kernel<E, Q8, NU>), lds_bytes);
+  MDZ_SET_LDS_ONCE((attn_tree_mfma_kernel<E, Q8, NU, TQ>), lds_bytes);
   const int nq = q_heads(g);
   const int splits = attn_splits(B, nq, max_prefix, qkv != nullptr);
   MDZ_REQUIRE(scratch_bytes >= attn_mfma_scratch_bytes(B, nq, max_prefix), MDZ_EWORKSPACE,
               "attention: scratch too small");
   float* part_o = (float*)scratch;
-  float* part_ml = part_o + (int64_t)B * nq * splits * kTQ * kHD;
-  dim3 grid(splits, nq, B * (3 - NU));  // NU = 1: blockIdx.z = 2 * sequence + half
+  float* part_ml = part_o + (int64_t)B * nq * splits * TQ * kHD;
+  dim3 grid(splits, nq, B * (TQ > 32 * NU ? 2 : 1));  // two workgroups share a sequence: blockIdx.z = 2 * sequence + half
   const Partials none = single_slot(nullptr, 0, 0);
-  launch_timed(PROF_ATTN, attn_tree_mfma_kernel<E, Q8, NU>, grid, 256, lds_bytes, st, tree, (const E*)q, qkv ? *qkv : none, cs, g,
+  launch_timed(PROF_ATTN, attn_tree_mfma_kernel<E, Q8, NU, TQ>, grid, 256, lds_bytes, st, tree, (const E*)q, qkv ? *qkv : none, cs, g,
                (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml);
   MDZ_LAUNCH_CHECK();
   if (splits > 1) {
-    launch_timed(PROF_ATTN, attn_combine_kernel<E>, dim3(nq, B, kTQ / 16), 256, 0, st, nq, splits, part_o, part_ml, (E*)att_out);
+    launch_timed(PROF_ATTN, attn_combine_kernel<E, TQ>, dim3(nq, B, (TQ + 15) / 16), 256, 0, st, nq, splits, part_o, part_ml, (E*)att_out);
     MDZ_LAUNCH_CHECK();
   }
   return MDZ_OK;
@@ -618,15 +628,16 @@ int launch_attention_mfma(int dtype, int tree, const void* q, const Partials* qk
   static const char* env = getenv("MDZ_ATTN_HALVES");  // development builds only: 1 = 32 queries per workgroup, 0 = 64
   if (env) halves = atoi(env) != 0;
 #endif
-#define MDZ_ATTN_CASE(Q8, NU)                                                                                          \
-  MDZ_WITH_ELEM16(dtype, return (launch_attention_mfma_t<E, Q8, NU>(tree, q, qkv, cs, g, kc, vc, layer, seq_len, B,    \
-                                                                    max_prefix, att_out, scratch, scratch_bytes, st)))
+#define MDZ_ATTN_CASE(Q8, NU, TQ)                                                                                         \
+  MDZ_WITH_ELEM16(dtype, return (launch_attention_mfma_t<E, Q8, NU, TQ>(tree, q, qkv, cs, g, kc, vc, layer, seq_len, B,  \
+                                                                        max_prefix, att_out, scratch, scratch_bytes, st)))
+  if (host_tree(tree)->T == 15) MDZ_ATTN_CASE(false, 1, 15);
   if (g.quant) {
-    if (halves) MDZ_ATTN_CASE(true, 1);
-    MDZ_ATTN_CASE(true, 2);
+    if (halves) MDZ_ATTN_CASE(true, 1, 64);
+    MDZ_ATTN_CASE(true, 2, 64);
   }
-  if (halves) MDZ_ATTN_CASE(false, 1);
-  MDZ_ATTN_CASE(false, 2);
+  if (halves) MDZ_ATTN_CASE(false, 1, 64);
+  MDZ_ATTN_CASE(false, 2, 64);
 #undef MDZ_ATTN_CASE
 }
 
