@@ -40,6 +40,9 @@ int launch_attention_generic(int dtype, int tree, const void* q, const KvGeom& g
                              int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out,
                              hipStream_t st);
 
+bool gemm_f32_supported(int dtype, int K);
+int launch_gemm_f32(const void* X, const void* Wp, float* Y, int M, int N, int K, int64_t ldy, hipStream_t st);
+
 bool gemm_mfma_supported(int dtype, int M, int N, int K);
 int gemm_mfma_slots(int M, int N, int K, int max_split);
 void gemm_mfma_describe(int M, int N, int K, int max_split, Partials* res, int* grid);
@@ -62,6 +65,10 @@ int launch_gemm_tile_swiglu(int dtype, const void* X, const void* Wp, void* U, i
 int launch_gemm(int dtype, const void* X, const void* Wp, float* out, int M, int N, int K, int64_t ld, int max_split,
                 Partials* res, hipStream_t st) {
   *res = single_slot(out, (int64_t)M * ld, ld);
+  // the fast kernels load 16 bytes at a time; operands that do not start on such a boundary take the portable one
+  if ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Wp)) & 15)
+    return launch_gemm_generic(dtype, X, Wp, out, M, N, K, ld, false, st);
+  if (gemm_f32_supported(dtype, K)) return launch_gemm_f32(X, Wp, out, M, N, K, ld, st);
   if (gemm_tile_supported(dtype, M, N, K))  // more than 64 rows: several sequences at once
     return launch_gemm_tile(dtype, X, Wp, out, M, N, K, ld, res->stride, max_split, res, st);
   if (gemm_mfma_supported(dtype, M, N, K)) return launch_gemm_mfma(dtype, X, Wp, out, M, N, K, ld, res->stride, max_split, res, st);
