@@ -2,197 +2,404 @@
 // autoregressive decode step (Section 4.1: the Time_AR that the paper's Overhead and Speedup are measured
 // against).  The node sees the prefix and itself, so the mask is "slot <= S".
 //
-// One workgroup = 4 waves handles one (sequence, head, key-split); a wave walks 32-key blocks of the tiled cache
-// (common.h) with the same contiguous 16-byte-per-lane loads as the tree kernel.  There is one query, so the
-// products are plain FMAs: in a K unit lane l holds 8 features of key l % 32, and the two half-waves hold the two
-// halves of every 16-feature step, so a score is a 64-term sum per lane plus one exchange with lane ^ 32.  In a V
-// unit lane l holds feature 32t + l % 32 for 8 keys; their probabilities come from the lanes that own those keys.
-// Waves merge through LDS, key-splits through a second small kernel, both in a fixed order.
-// Q8 = true: 8-bit rows (common.h): a block is 4 K units + 4 V units + 2 x 32 scales; a lane's 16 bytes of K unit j are
-// its 8 features of k-steps 2j and 2j+1, its 16 bytes of V unit t the 8 keys of s2 = 0 and of s2 = 1; the score of key
-// k is multiplied by the key's K scale and its probability by the key's V scale, in fp32.
+// One workgroup = 4 waves handles one (sequence, KEY/VALUE head, key-split): the query heads of a group are the columns of one
+// 32-column operand, so grouped heads read K and V once (one query head per workgroup read them `group` times: 92 us per
+// layer for 24 sequences of 90 .. 3000 keys with 8 key/value and 32 query heads, 37 us now).  A wave walks 32-key blocks of
+// the tiled cache (common.h) with contiguous 16-byte-per-lane loads that are MFMA A operands as they are; scores are
+// computed transposed (keys x queries), so the probabilities of 16 keys of one query sit in a lane and feed the second
+// MFMA from registers, exactly as in the tree kernel.  Columns beyond the group's heads are zero and never stored: the
+// matrix cores idle otherwise, the kernel is bound by the K / V stream and, at short prefixes, by its fixed chain.
+// The kernel starts from the QKV GEMM's partial sums: every workgroup reduces and rotates the queries of its group; the
+// split that owns the block of slot S also produces the node's K and V rows, writes them to the cache and puts them into
+// the block from LDS, so that no load waits for a store (a launch of its own took 4.9 us per layer).  Waves merge
+// through LDS, key-splits through a second small kernel, both in a fixed order.
+// Q8 = true: 8-bit rows (common.h): a block is 4 K units + 4 V units + 2 x 32 scales; codes convert exactly to E in registers,
+// the K scales multiply the scores and the V scales the probabilities, in fp32.
 #include "kernels.h"
 
 namespace mdz {
 
 typedef u32x4_t u32x4;
+typedef f32x16_t f32x16;
 
 namespace {
 constexpr int kHD = 128;
+constexpr int kQRow = kHD * 2 + 16;  // bytes per staged query row
+constexpr int kORow = kHD + 4;       // floats per merged output row
 
-__device__ inline float fast_exp2_attn(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ inline float half_max(float v) {  // max over the 32 lanes of a half-wave (both halves hold the same set)
-#pragma unroll
-  for (int o = 16; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-__device__ inline float half_sum(float v) {
-#pragma unroll
-  for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ inline void unpack8_fp8(u32x4 v, int half, float (&f)[8]) {  // the 8 codes in words 2*half, 2*half+1
-  const uint32_t w0 = half ? v.z : v.x, w1 = half ? v.w : v.y;
-  const auto a = __builtin_amdgcn_cvt_pk_f32_fp8(w0, false), b = __builtin_amdgcn_cvt_pk_f32_fp8(w0, true);
-  const auto c = __builtin_amdgcn_cvt_pk_f32_fp8(w1, false), d = __builtin_amdgcn_cvt_pk_f32_fp8(w1, true);
-  f[0] = a[0], f[1] = a[1], f[2] = b[0], f[3] = b[1], f[4] = c[0], f[5] = c[1], f[6] = d[0], f[7] = d[1];
-}
+__device__ inline float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+
 template <typename E>
-__device__ inline void unpack8(u32x4 v, float (&f)[8]) {
-  f[0] = Elem16<E>::lo(v.x), f[1] = Elem16<E>::hi(v.x);
-  f[2] = Elem16<E>::lo(v.y), f[3] = Elem16<E>::hi(v.y);
-  f[4] = Elem16<E>::lo(v.z), f[5] = Elem16<E>::hi(v.z);
-  f[6] = Elem16<E>::lo(v.w), f[7] = Elem16<E>::hi(v.w);
-  // Keeps the conversions as instructions of their own.  For fp16 the compiler otherwise folds them into
-  // mixed-precision FMAs (v_fma_mix_f32), which made this kernel three times slower than its bf16 twin.
+__device__ inline u32x4 fp8x8_to_elem16(u32x4 v, int half) {  // 8 E4M3 codes (words 2 * half, 2 * half + 1) -> 8 elements
+  const uint32_t w0 = half ? v.z : v.x, w1 = half ? v.w : v.y;
+  return u32x4{Elem16<E>::from_fp8x2(w0, false), Elem16<E>::from_fp8x2(w0, true), Elem16<E>::from_fp8x2(w1, false),
+               Elem16<E>::from_fp8x2(w1, true)};
+}
+
+// Two adjacent columns and their rotary partners (64 columns on) of one row of the QKV partial sums.  load() requests the
+// first kEarly slots, sum() adds the slots in order (and fetches what lies beyond kEarly, which one row never needs).
+struct PairSums {
+  static constexpr int kEarly = 4;
+  float2 a[kEarly], p[kEarly];
+  const float* src;
+  int n;
+  __device__ inline void load(const Partials& part, int64_t row, int col) {
+    n = part.count(col);
+    src = part.p + row * part.ld + col;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(f[i]));
+    for (int s = 0; s < kEarly; ++s)
+      if (s < n) {
+        a[s] = *reinterpret_cast<const float2*>(src + (int64_t)s * part.stride);
+        p[s] = *reinterpret_cast<const float2*>(src + (int64_t)s * part.stride + 64);
+      }
+  }
+  __device__ inline void sum(const Partials& part, float2& ra, float2& rp) const {
+    ra = rp = float2{0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < kEarly; ++s)
+      if (s < n) ra.x += a[s].x, ra.y += a[s].y, rp.x += p[s].x, rp.y += p[s].y;
+    for (int s = kEarly; s < n; ++s) {
+      const float2 va = *reinterpret_cast<const float2*>(src + (int64_t)s * part.stride);
+      const float2 vp = *reinterpret_cast<const float2*>(src + (int64_t)s * part.stride + 64);
+      ra.x += va.x, ra.y += va.y, rp.x += vp.x, rp.y += vp.y;
+    }
+  }
+};
+__device__ inline void rotate(const float4& t, float2& a, float2& p) {  // t: cos, sin of the two pairs
+  const float2 ra = {a.x * t.x - p.x * t.y, a.y * t.z - p.y * t.w};
+  p = float2{p.x * t.x + a.x * t.y, p.y * t.z + a.y * t.w};
+  a = ra;
 }
 }  // namespace
 
+// qkv.p == NULL: q [B][d] holds the rotated queries and the cache already holds the node's row (separate RoPE kernel).
 template <typename E, bool Q8>
-__global__ void __launch_bounds__(256)
-    attn_decode_kernel(const E* __restrict__ q, KvGeom g, const E* __restrict__ kc, const E* __restrict__ vc,
-                       int layer, const int32_t* __restrict__ seq_len, int max_prefix, E* __restrict__ att_out,
-                       float* __restrict__ part_o, float* __restrict__ part_ml) {
-  __shared__ float o_lds[4][kHD];
-  __shared__ float ml_lds[4][2];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int key = lane & 31, half = lane >> 5;
-  const int split = blockIdx.x, n_splits = gridDim.x, h = blockIdx.y, b = blockIdx.z;
-  const int d = q_heads(g) * kHD;
+__global__ void __launch_bounds__(256, 2)
+    attn_decode_kernel(const E* __restrict__ q, const Partials qkv, const float* __restrict__ cs, KvGeom g, E* __restrict__ kc,
+                       E* __restrict__ vc, int layer, const int32_t* __restrict__ seq_len, int max_prefix,
+                       E* __restrict__ att_out, float* __restrict__ part_o, float* __restrict__ part_ml) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int qi = lane & 31, gh = lane >> 5;
+  const int split = blockIdx.x, n_splits = gridDim.x, b = blockIdx.z;
+  const int chunks = (g.group + 31) >> 5;  // groups of more than 32 query heads take several workgroups
+  const int hk = blockIdx.y / chunks, h0 = hk * g.group + (blockIdx.y % chunks) * 32;
+  const int nq = min(32, g.group - (blockIdx.y % chunks) * 32);  // query heads of this workgroup: h0 .. h0 + nq - 1
+  const int d = q_heads(g) * kHD, dkv = g.n_heads * kHD;
   const int S = min(max(seq_len[b], 0), max_prefix);
-  const int n_slots = S + 1;  // the prefix and the node itself
-  const int nb = (n_slots + 31) >> 5;
+  const int nb = (S + 1 + 31) >> 5;
   const int blk_begin = (int)((int64_t)split * nb / n_splits), blk_end = (int)((int64_t)(split + 1) * nb / n_splits);
 
-  // the lane's 64 query features: 16*ks + 8*half + e, pre-scaled by log2(e) / sqrt(head_dim)
-  const float scale_log2 = 1.4426950408889634f / sqrtf((float)kHD);
-  float qf[8][8];
-  const u32x4* qp = reinterpret_cast<const u32x4*>(q + (int64_t)b * d + h * kHD);
-#pragma unroll
-  for (int ks = 0; ks < 8; ++ks) {
-    unpack8<E>(qp[2 * ks + half], qf[ks]);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) qf[ks][e] *= scale_log2;
-  }
-
-  // query head h reads key/value head h / group.  16-bit rows: unit i of block blk at kp[blk*512 + i*64]; 8-bit
-  // rows: at kp[blk*264 + i*64], the scale of key `key` at ksc[blk*1056 + key]
+  // 16-bit rows: block blk, unit i at kp[blk*512 + i*64].  8-bit rows: at kp[blk*264 + i*64], the four scales of keys
+  // 8j + 4gh .. +3 at ks_p[blk*264 + 2j]
   constexpr int kBlkPieces = Q8 ? kKv8BlockBytes / 16 : 512;
   const u32x4* kp;
   const u32x4* vp;
-  const float* ksc = nullptr;
-  const float* vsc = nullptr;
+  const u32x4* ks_p = nullptr;
+  const u32x4* vs_p = nullptr;
   if constexpr (Q8) {
-    const int64_t hb = kv8_head_base(g, layer, b, h / g.group);
-    const uint8_t* k0 = reinterpret_cast<const uint8_t*>(kc) + hb;
-    const uint8_t* v0 = reinterpret_cast<const uint8_t*>(vc) + hb;
-    kp = reinterpret_cast<const u32x4*>(k0) + lane, vp = reinterpret_cast<const u32x4*>(v0) + lane;
-    ksc = reinterpret_cast<const float*>(k0 + 4096) + key, vsc = reinterpret_cast<const float*>(v0 + 4096) + key;
+    const int64_t hb = kv8_head_base(g, layer, b, hk);
+    const u32x4* k0 = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(kc) + hb);
+    const u32x4* v0 = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(vc) + hb);
+    kp = k0 + lane, vp = v0 + lane;
+    ks_p = k0 + 256 + gh, vs_p = v0 + 256 + gh;
   } else {
-    const int64_t head_base = kv_head_base(g, layer, b, h / g.group);
+    const int64_t head_base = kv_head_base(g, layer, b, hk);
     kp = reinterpret_cast<const u32x4*>(kc + head_base) + lane;
     vp = reinterpret_cast<const u32x4*>(vc + head_base) + lane;
   }
+  // K and V double buffered one block ahead; every load is unconditional (past the wave's last block it repeats it)
+  u32x4 kb[2][8], vb[2][8];
+  auto load_kv = [&](int blk, u32x4 (&kd)[8], u32x4 (&vd)[8]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      kd[i] = (Q8 && i >= 4) ? ks_p[(int64_t)blk * kBlkPieces + 2 * (i - 4)] : kp[(int64_t)blk * kBlkPieces + i * 64];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      vd[i] = (Q8 && i >= 4) ? vs_p[(int64_t)blk * kBlkPieces + 2 * (i - 4)] : vp[(int64_t)blk * kBlkPieces + i * 64];
+  };
+  // Requested first (loads return in order): the partial sums of two rotary pairs of one query head per thread, and, in the
+  // split that owns the block of slot S, the node's K row (threads 192 .. 223) and V row (224 .. 255).
+  const bool fused = qkv.p != nullptr, owner = blk_begin < blk_end && blk_end == nb;
+  const float* csr = cs + (int64_t)b * kHD;  // [64 pairs][cos, sin]
+  const int f = (tid & 31) * 2;              // first of the thread's two features; partners 64 further
+  PairSums qs, kvs;
+  float4 rot = {};
+  if (fused) {
+    rot = *reinterpret_cast<const float4*>(csr + 2 * f);
+    if ((tid >> 5) < nq) qs.load(qkv, b, (h0 + (tid >> 5)) * kHD + f);
+    if (owner && tid >= 192) kvs.load(qkv, b, d + (tid < 224 ? 0 : dkv) + hk * kHD + f);
+  }
+  const int n_mine = blk_begin + wave < blk_end ? (blk_end - blk_begin - wave + 3) >> 2 : 0;
+  const int first = blk_begin + wave, last = first + 4 * (n_mine - 1);
+  // The first block waits for nothing below: the node's own row, if it falls into it, is put in from LDS.
+  __builtin_amdgcn_sched_barrier(0);
+  if (n_mine > 0) load_kv(first, kb[0], vb[0]);
+  __builtin_amdgcn_sched_barrier(0);
 
-  float m_run = -INFINITY, l_run = 0.f;
-  float o[4] = {0.f, 0.f, 0.f, 0.f};  // feature 32t + key, over the keys this half-wave owns
-  for (int blk = blk_begin + wave; blk < blk_end; blk += 4) {
-    constexpr int kUnits = Q8 ? 4 : 8;
-    u32x4 kd[kUnits], vd[kUnits];
-#pragma unroll
-    for (int i = 0; i < kUnits; ++i) kd[i] = kp[(int64_t)blk * kBlkPieces + i * 64];
-#pragma unroll
-    for (int i = 0; i < kUnits; ++i) vd[i] = vp[(int64_t)blk * kBlkPieces + i * 64];
-    float k_scale = 1.f, v_scale = 1.f;
-    if constexpr (Q8) k_scale = ksc[(int64_t)blk * (kKv8BlockBytes / 4)], v_scale = vsc[(int64_t)blk * (kKv8BlockBytes / 4)];
-    float s = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      float kf[8];
-      if constexpr (Q8)
-        unpack8_fp8(kd[ks >> 1], ks & 1, kf);
-      else
-        unpack8<E>(kd[ks], kf);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s += qf[ks][e] * kf[e];
+  // queries -> LDS, rows beyond nq zero
+  uint8_t* q_lds = lds_raw;
+  uint8_t* kv_lds = lds_raw + 32 * kQRow;  // the node's K row, then its V row: 128 elements (8-bit rows: 128 codes, scale)
+  if (!fused) {
+    for (int i = tid; i < 32 * 16; i += 256) {
+      const int row = i >> 4, c = i & 15;
+      u32x4 v = {0, 0, 0, 0};
+      if (row < nq) v = *reinterpret_cast<const u32x4*>(q + (int64_t)b * d + (h0 + row) * kHD + c * 8);
+      *reinterpret_cast<u32x4*>(q_lds + row * kQRow + c * 16) = v;
     }
-    s += __shfl_xor(s, 32, 64);  // both half-waves now hold the score of key `key`
-    s *= k_scale;
-    s = (blk * 32 + key < n_slots) ? s : -INFINITY;
-    const float m_new = fmaxf(m_run, half_max(s));  // finite: a block in range holds at least one visible slot
-    const float p = fast_exp2_attn(s - m_new);
-    const float alpha = fast_exp2_attn(m_run - m_new);
-    l_run = l_run * alpha + half_sum(p);
-    m_run = m_new;
+  } else {
+    for (int row = tid >> 5; row < 32; row += 8) {
+      uint32_t lo = 0, hi = 0;
+      if (row < nq) {
+        if (row >= 8) qs.load(qkv, b, (h0 + row) * kHD + f);
+        float2 a, p;
+        qs.sum(qkv, a, p);
+        rotate(rot, a, p);
+        lo = Elem16<E>::pack2(a.x, a.y), hi = Elem16<E>::pack2(p.x, p.y);
+      }
+      *reinterpret_cast<uint32_t*>(q_lds + row * kQRow + 2 * f) = lo;
+      *reinterpret_cast<uint32_t*>(q_lds + row * kQRow + 128 + 2 * f) = hi;
+    }
+    if (owner && tid >= 192) {  // the node's K and V rows: to LDS for the block below, and to the cache
+      const bool is_k = tid < 224;
+      uint8_t* stage = kv_lds + (is_k ? 0 : kQRow);
+      float2 a, p;
+      kvs.sum(qkv, a, p);
+      if (is_k) rotate(rot, a, p);
+      if constexpr (Q8) {
+        float am = fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(p.x), fabsf(p.y)));
 #pragma unroll
-    for (int t = 0; t < 4; ++t) o[t] *= alpha;
-    // V unit (2t + s2): feature 32t + key, keys 16*s2 + 8*(e/4) + 4*half + e%4; the probability of key k lives in lane k
-    const float pv = Q8 ? (blk * 32 + key < n_slots ? p * v_scale : 0.f) : p;  // the key's V scale rides on its probability
+        for (int o = 16; o > 0; o >>= 1) am = fmaxf(am, __shfl_xor(am, o, 64));  // over the 32 threads of the row
+        const float sc = kv8_scale_of(am);
+        const uint32_t w = kv8_pack4(a.x, a.y, p.x, p.y, sc);
+        *reinterpret_cast<uint16_t*>(stage + f) = (uint16_t)w;
+        *reinterpret_cast<uint16_t*>(stage + 64 + f) = (uint16_t)(w >> 16);
+        uint8_t* dst = reinterpret_cast<uint8_t*>(is_k ? kc : vc) + kv8_head_base(g, layer, b, hk);
 #pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
-      float pe[8];
+        for (int e = 0; e < 4; ++e) {
+          const int i = f + (e & 1) + (e >> 1) * 64;
+          dst[is_k ? kv8_k_code(S, i) : kv8_v_code(S, i)] = (uint8_t)(w >> (8 * e));
+        }
+        if ((tid & 31) == 0) {
+          *reinterpret_cast<float*>(dst + kv8_scale(S)) = sc;
+          *reinterpret_cast<float*>(stage + 128) = sc;
+        }
+      } else {
+        const uint32_t lo = Elem16<E>::pack2(a.x, a.y), hi = Elem16<E>::pack2(p.x, p.y);
+        *reinterpret_cast<uint32_t*>(stage + 2 * f) = lo;
+        *reinterpret_cast<uint32_t*>(stage + 128 + 2 * f) = hi;
+        if (is_k) {  // adjacent features of one key are adjacent in the tiled K layout
+          *reinterpret_cast<uint32_t*>(kc + k_index(g, layer, b, hk, S, f)) = lo;
+          *reinterpret_cast<uint32_t*>(kc + k_index(g, layer, b, hk, S, f + 64)) = hi;
+        } else {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) pe[e] = __shfl(pv, 16 * s2 + 8 * (e >> 2) + 4 * half + (e & 3), 64);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        float vf[8];
-        if constexpr (Q8)
-          unpack8_fp8(vd[t], s2, vf);
-        else
-          unpack8<E>(vd[2 * t + s2], vf);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[t] += pe[e] * vf[e];
+          for (int e = 0; e < 2; ++e) {
+            vc[v_index(g, layer, b, hk, S, f + e)] = E{(uint16_t)(lo >> (16 * e))};
+            vc[v_index(g, layer, b, hk, S, f + 64 + e)] = E{(uint16_t)(hi >> (16 * e))};
+          }
+        }
       }
     }
   }
+  __syncthreads();
+
+  // Puts the node's own row, staged in LDS, into the block that holds slot S (its cache copy may not have arrived yet).
+  const int own_blk = fused ? S >> 5 : -1, own = S & 31;
+  auto put_own = [&](u32x4 (&kd)[8], u32x4 (&vd)[8]) {
+    if constexpr (Q8) {
+      if (qi == own) {
 #pragma unroll
-  for (int t = 0; t < 4; ++t) o[t] += __shfl_xor(o[t], 32, 64);  // the two half-waves own disjoint keys
+        for (int j = 0; j < 4; ++j) {
+          const uint2 lo = *reinterpret_cast<const uint2*>(kv_lds + 32 * j + 8 * gh);
+          const uint2 hi = *reinterpret_cast<const uint2*>(kv_lds + 32 * j + 16 + 8 * gh);
+          kd[j] = u32x4{lo.x, lo.y, hi.x, hi.y};
+        }
+      }
+      const bool mine = ((own >> 2) & 1) == gh;  // V units and scales: the half-wave that holds key `own`
+      const int byte = 8 * (own >> 4) + 4 * ((own >> 3) & 1) + (own & 3);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const uint32_t code = kv_lds[kQRow + 32 * t + qi];
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+          if (mine && w == byte >> 2) vd[t][w] = (vd[t][w] & ~(0xFFu << (8 * (byte & 3)))) | code << (8 * (byte & 3));
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (mine && t == own >> 3 && e == (own & 3)) {
+            kd[4 + t][e] = *reinterpret_cast<const uint32_t*>(kv_lds + 128);
+            vd[4 + t][e] = *reinterpret_cast<const uint32_t*>(kv_lds + kQRow + 128);
+          }
+      }
+    } else {
+      if (qi == own) {
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) kd[ks] = *reinterpret_cast<const u32x4*>(kv_lds + 32 * ks + 16 * gh);
+      }
+      const bool mine = ((own >> 2) & 1) == gh;
+      const int e = 4 * ((own >> 3) & 1) + (own & 3), sh = 16 * (e & 1);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const uint32_t v = *reinterpret_cast<const uint16_t*>(kv_lds + kQRow + 2 * (32 * t + qi));
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+          for (int w = 0; w < 4; ++w)
+            if (mine && s2 == own >> 4 && w == e >> 1) vd[2 * t + s2][w] = (vd[2 * t + s2][w] & ~(0xFFFFu << sh)) | v << sh;
+      }
+    }
+  };
+
+  const uint8_t* qfrag = q_lds + qi * kQRow + gh * 16;  // B operand of scores^T: query qi, features 16 ks + 8 gh .. +7
+  const float scale_log2 = 1.4426950408889634f / sqrtf((float)kHD);
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x16 o[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[t][r] = 0.f;
+
+  auto process = [&](int blk, const u32x4 (&kd)[8], const u32x4 (&vd)[8]) {
+    // Compiler barrier: keeps the (loop-invariant) query operands in LDS instead of in 32 registers this kernel lacks
+    asm volatile("" ::: "memory");
+    f32x16 sc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      const u32x4 ka = Q8 ? fp8x8_to_elem16<E>(kd[ks >> 1], ks & 1) : kd[ks];
+      sc = Elem16<E>::mfma(ka, *reinterpret_cast<const u32x4*>(qfrag + ks * 32), sc);
+    }
+    // register r is key 8*(r/4) + 4*gh + r%4 of the block; its scale is component r%4 of scale piece r/4
+    float bmax = -INFINITY;
+    const int left = S + 1 - blk * 32 - 4 * gh;  // keys of this half-wave's numbering that are visible
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float s = sc[r] * (Q8 ? __uint_as_float(kd[4 + (r >> 2)][r & 3]) * scale_log2 : scale_log2);
+      s = 8 * (r >> 2) + (r & 3) < left ? s : -INFINITY;
+      sc[r] = s;
+      bmax = fmaxf(bmax, s);
+    }
+    bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));  // finite: a block in range holds at least one visible slot
+    const float m_new = fmaxf(m_run, bmax);
+    const float alpha = exp2_fast(m_run - m_new);
+    float sum = 0.f;
+    uint32_t pk[8];
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+      float p0 = exp2_fast(sc[r] - m_new), p1 = exp2_fast(sc[r + 1] - m_new);
+      sum += p0 + p1;
+      if constexpr (Q8) {  // a slot that no row was ever written to may hold any finite scale; its probability is zero
+        p0 *= __uint_as_float(vd[4 + (r >> 2)][r & 3]), p1 *= __uint_as_float(vd[4 + (r >> 2)][(r & 3) + 1]);
+      }
+      pk[r >> 1] = Elem16<E>::pack2(p0, p1);
+    }
+    l_run = l_run * alpha + sum;
+    if (__any(m_new != m_run)) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[t][r] *= alpha;
+    }
+    m_run = m_new;
+    const u32x4 pf[2] = {u32x4{pk[0], pk[1], pk[2], pk[3]}, u32x4{pk[4], pk[5], pk[6], pk[7]}};
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) {
+        const u32x4 va = Q8 ? fp8x8_to_elem16<E>(vd[t], s2) : vd[t * 2 + s2];
+        o[t] = Elem16<E>::mfma(va, pf[s2], o[t]);
+      }
+  };
+  if (n_mine > 0) {
+    for (int it = 0; it < n_mine; it += 2) {
+      const int blk = first + 4 * it;
+      load_kv(min(blk + 4, last), kb[1], vb[1]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (blk == own_blk) put_own(kb[0], vb[0]);
+      process(blk, kb[0], vb[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      load_kv(min(blk + 8, last), kb[0], vb[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (it + 1 < n_mine) {
+        if (blk + 4 == own_blk) put_own(kb[1], vb[1]);
+        process(blk + 4, kb[1], vb[1]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
 
   // ---- merge the four waves (fixed order), then store or hand the partial result to the combine kernel
-  if (half == 0) {
+  __syncthreads();  // every wave has its query operands; the merge buffer overlays them
+  float* o_lds = reinterpret_cast<float*>(lds_raw);  // [4][nq][kORow]
+  float* m_lds = o_lds + 4 * nq * kORow;             // [4][nq]
+  float* l_lds = m_lds + 4 * nq;
+  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  if (qi < nq) {
+    if (gh == 0) m_lds[wave * nq + qi] = m_run, l_lds[wave * nq + qi] = l_tot;
+    float* dst = o_lds + (wave * nq + qi) * kORow + 4 * gh;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) o_lds[wave][32 * t + key] = o[t];
-    if (key == 0) ml_lds[wave][0] = m_run, ml_lds[wave][1] = l_run;
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        *reinterpret_cast<float4*>(dst + 32 * t + 8 * c) = float4{o[t][4 * c], o[t][4 * c + 1], o[t][4 * c + 2], o[t][4 * c + 3]};
   }
   __syncthreads();
-  if (threadIdx.x < kHD) {
-    const int f = threadIdx.x;
+  for (int i = tid; i < nq * 32; i += 256) {  // thread: 4 features of one query head
+    const int qq = i >> 5, f = (i & 31) * 4;
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) M = fmaxf(M, ml_lds[w][0]);
+    for (int w = 0; w < 4; ++w) M = fmaxf(M, m_lds[w * nq + qq]);
     const float M_safe = M == -INFINITY ? 0.f : M;
-    float L = 0.f, acc = 0.f;
+    float L = 0.f;
+    float4 a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float wt = fast_exp2_attn(ml_lds[w][0] - M_safe);
-      L += wt * ml_lds[w][1];
-      acc += wt * o_lds[w][f];
+      const float wt = exp2_fast(m_lds[w * nq + qq] - M_safe);
+      const float4 v = *reinterpret_cast<const float4*>(o_lds + (w * nq + qq) * kORow + f);
+      L += wt * l_lds[w * nq + qq];
+      a.x += wt * v.x, a.y += wt * v.y, a.z += wt * v.z, a.w += wt * v.w;
     }
     if (n_splits == 1) {
-      att_out[(int64_t)b * d + h * kHD + f] = from_float<E>(acc / L);
+      const float inv = 1.0f / L;
+      *reinterpret_cast<uint2*>(att_out + (int64_t)b * d + (h0 + qq) * kHD + f) =
+          uint2{Elem16<E>::pack2(a.x * inv, a.y * inv), Elem16<E>::pack2(a.z * inv, a.w * inv)};
     } else {
-      const int64_t pidx = (int64_t)(b * q_heads(g) + h) * n_splits + split;
-      part_o[pidx * kHD + f] = acc;
+      const int64_t pidx = (int64_t)(b * q_heads(g) + h0 + qq) * n_splits + split;
+      *reinterpret_cast<float4*>(part_o + pidx * kHD + f) = a;
       if (f == 0) part_ml[pidx * 2] = M, part_ml[pidx * 2 + 1] = L;
     }
   }
 }
 
+// One workgroup per (query head, sequence), one thread per feature; the splits' loads are requested eight at a time.
 template <typename E>
 __global__ void __launch_bounds__(128)
     attn_decode_combine_kernel(int n_heads, int n_splits, const float* __restrict__ part_o, const float* __restrict__ part_ml,
                                E* __restrict__ att_out) {
   const int h = blockIdx.x, b = blockIdx.y, f = threadIdx.x;
   const int64_t p0 = (int64_t)(b * n_heads + h) * n_splits;
-  float M = -INFINITY;
-  for (int s = 0; s < n_splits; ++s) M = fmaxf(M, part_ml[(p0 + s) * 2]);
-  float L = 0.f, acc = 0.f;
-  for (int s = 0; s < n_splits; ++s) {
-    const float w = fast_exp2_attn(part_ml[(p0 + s) * 2] - M);
-    L += w * part_ml[(p0 + s) * 2 + 1];
-    acc += w * part_o[(p0 + s) * kHD + f];
+  float M = -INFINITY, L = 0.f, acc = 0.f;
+  constexpr int kTogether = 8;
+  for (int s0 = 0; s0 < n_splits; s0 += kTogether) {
+    float ms[kTogether], ls[kTogether], v[kTogether];
+#pragma unroll
+    for (int s = 0; s < kTogether; ++s) {
+      const int64_t p = p0 + min(s0 + s, n_splits - 1);
+      ms[s] = part_ml[p * 2], ls[s] = part_ml[p * 2 + 1], v[s] = part_o[p * kHD + f];
+    }
+    float Mg = M;
+#pragma unroll
+    for (int s = 0; s < kTogether; ++s) Mg = fmaxf(Mg, ms[s]);
+    const float r = M == -INFINITY ? 0.f : exp2_fast(M - Mg);
+    L *= r, acc *= r;
+    M = Mg;
+#pragma unroll
+    for (int s = 0; s < kTogether; ++s)
+      if (s0 + s < n_splits) {
+        const float w = ms[s] == -INFINITY ? 0.f : exp2_fast(ms[s] - M);  // (an empty split, possibly before any other)
+        L += w * ls[s];
+        acc += w * v[s];
+      }
   }
   att_out[((int64_t)b * n_heads + h) * kHD + f] = from_float<E>(acc / L);
 }
@@ -201,49 +408,56 @@ bool attn_decode_supported(int dtype, int tree, const KvGeom& g) {
   return is_16bit(dtype) && g.tiled && g.head_dim == kHD && host_tree(tree)->T == 1;
 }
 
-static int decode_splits(int B, int n_heads, int max_prefix) {
-  const int nb = (max_prefix + 1 + 31) / 32;
-  int by_len = nb / 4;                                     // >= one block per wave
-  int by_fill = (512 + B * n_heads - 1) / (B * n_heads);   // aim at ~512 workgroups
-  int s = by_len < by_fill ? by_len : by_fill;
+// Key-splits: enough workgroups to give every CU two (they fit), but at least seven blocks each, i.e. two per wave (one
+// sequence of 1024 keys, 32 heads: 12.5 us with 5 splits, 13.7 with 2, 13.9 with 3, 15.1 with 9, merge included).
+// Dealing equal parts of a ragged batch out by its device-side lengths was measured too: 24 sequences of 90 .. 3000 keys
+// gain 1 us of 37 (the HBM stream bounds them), a single sequence loses 1 us to finding its part.
+static int decode_splits(int B, int kv_heads, int max_prefix) {
+  const int nb = (max_prefix + 1 + 31) / 32, pairs = B * kv_heads;
+  const int by_len = (nb + 6) / 7, by_fill = (2 * num_cus() + pairs - 1) / pairs;
+  const int s = by_len < by_fill ? by_len : by_fill;
   return s > 32 ? 32 : s < 1 ? 1 : s;
 }
 
-int64_t attn_decode_scratch_bytes(int B, int n_heads, int max_prefix) {
-  const int s = decode_splits(B, n_heads, max_prefix);
+int64_t attn_decode_scratch_bytes(int B, int n_heads, int kv_heads, int max_prefix) {
+  const int s = decode_splits(B, kv_heads, max_prefix);
   return s == 1 ? 0 : (int64_t)B * n_heads * s * (kHD + 2) * 4;
 }
 
 template <typename E, bool Q8>
-static int launch_attention_decode_t(const void* q, const KvGeom& g, const void* kc, const void* vc, int layer,
-                                     const int32_t* seq_len, int B, int max_prefix, void* att_out, void* scratch,
+static int launch_attention_decode_t(const void* q, const Partials* qkv, const float* cs, const KvGeom& g, void* kc, void* vc,
+                                     int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out, void* scratch,
                                      int64_t scratch_bytes, hipStream_t st) {
-  ProfScope prof_(PROF_ATTN, st);
   if (B == 0) return MDZ_OK;
-  const int nq = q_heads(g);
-  const int splits = decode_splits(B, nq, max_prefix);
-  MDZ_REQUIRE(scratch_bytes >= attn_decode_scratch_bytes(B, nq, max_prefix), MDZ_EWORKSPACE,
+  const int nq = q_heads(g), splits = decode_splits(B, g.n_heads, max_prefix), chunks = (g.group + 31) / 32;
+  MDZ_REQUIRE(scratch_bytes >= attn_decode_scratch_bytes(B, nq, g.n_heads, max_prefix), MDZ_EWORKSPACE,
               "decode attention: scratch too small");
   float* part_o = (float*)scratch;
   float* part_ml = part_o + (int64_t)B * nq * splits * kHD;
-  attn_decode_kernel<E, Q8><<<dim3(splits, nq, B), 256, 0, st>>>((const E*)q, g, (const E*)kc, (const E*)vc, layer, seq_len,
-                                                             max_prefix, (E*)att_out, part_o, part_ml);
+  const int cols = g.group < 32 ? g.group : 32;
+  const int merge_bytes = 4 * cols * (kORow + 2) * 4, q_bytes = 34 * kQRow;
+  const int lds_bytes = merge_bytes > q_bytes ? merge_bytes : q_bytes;
+  MDZ_SET_LDS_ONCE((attn_decode_kernel<E, Q8>), 4 * 32 * (kORow + 2) * 4);
+  const Partials none = single_slot(nullptr, 0, 0);
+  launch_timed(PROF_ATTN, attn_decode_kernel<E, Q8>, dim3(splits, g.n_heads * chunks, B), 256, lds_bytes, st, (const E*)q,
+               qkv ? *qkv : none, cs, g, (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml);
   MDZ_LAUNCH_CHECK();
   if (splits > 1) {
-    attn_decode_combine_kernel<E><<<dim3(nq, B), 128, 0, st>>>(nq, splits, part_o, part_ml, (E*)att_out);
+    launch_timed(PROF_ATTN, attn_decode_combine_kernel<E>, dim3(nq, B), 128, 0, st, nq, splits, part_o, part_ml, (E*)att_out);
     MDZ_LAUNCH_CHECK();
   }
   return MDZ_OK;
 }
 
-int launch_attention_decode(int dtype, const void* q, const KvGeom& g, const void* kc, const void* vc, int layer,
-                            const int32_t* seq_len, int B, int max_prefix, void* att_out, void* scratch,
+// qkv: the QKV GEMM's partial sums (RoPE, the cache row and the attention in one kernel), or NULL: q holds rotated queries
+int launch_attention_decode(int dtype, const void* q, const Partials* qkv, const float* cs, const KvGeom& g, void* kc, void* vc,
+                            int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out, void* scratch,
                             int64_t scratch_bytes, hipStream_t st) {
   if (g.quant)
-    MDZ_WITH_ELEM16(dtype, return (launch_attention_decode_t<E, true>(q, g, kc, vc, layer, seq_len, B, max_prefix, att_out,
-                                                                      scratch, scratch_bytes, st)));
-  MDZ_WITH_ELEM16(dtype, return (launch_attention_decode_t<E, false>(q, g, kc, vc, layer, seq_len, B, max_prefix, att_out,
-                                                                     scratch, scratch_bytes, st)));
+    MDZ_WITH_ELEM16(dtype, return (launch_attention_decode_t<E, true>(q, qkv, cs, g, kc, vc, layer, seq_len, B, max_prefix,
+                                                                      att_out, scratch, scratch_bytes, st)));
+  MDZ_WITH_ELEM16(dtype, return (launch_attention_decode_t<E, false>(q, qkv, cs, g, kc, vc, layer, seq_len, B, max_prefix,
+                                                                     att_out, scratch, scratch_bytes, st)));
 }
 
 }  // namespace mdz

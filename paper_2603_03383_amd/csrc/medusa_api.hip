@@ -92,13 +92,13 @@ int launch_attention_mfma(int dtype, int tree, const void* q, const Partials* qk
                           void* scratch, int64_t scratch_bytes, hipStream_t st);
 
 bool attn_decode_supported(int dtype, int tree, const KvGeom& g);
-int64_t attn_decode_scratch_bytes(int B, int n_heads, int max_prefix);
-int launch_attention_decode(int dtype, const void* q, const KvGeom& g, const void* kc, const void* vc, int layer,
-                            const int32_t* seq_len, int B, int max_prefix, void* att_out, void* scratch,
+int64_t attn_decode_scratch_bytes(int B, int n_heads, int kv_heads, int max_prefix);
+int launch_attention_decode(int dtype, const void* q, const Partials* qkv, const float* cs, const KvGeom& g, void* kc, void* vc,
+                            int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out, void* scratch,
                             int64_t scratch_bytes, hipStream_t st);
 
 int64_t tree_attention_scratch_bytes(int dtype, int tree, const KvGeom& g, int B, int max_prefix) {
-  if (attn_decode_supported(dtype, tree, g)) return attn_decode_scratch_bytes(B, q_heads(g), max_prefix);
+  if (attn_decode_supported(dtype, tree, g)) return attn_decode_scratch_bytes(B, q_heads(g), g.n_heads, max_prefix);
   return attn_mfma_supported(dtype, tree, g) ? attn_mfma_scratch_bytes(B, q_heads(g), max_prefix) : 0;
 }
 
@@ -106,7 +106,8 @@ int launch_tree_attention(int dtype, int tree, const void* q, const KvGeom& g, c
                           int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out, void* scratch,
                           int64_t scratch_bytes, hipStream_t st) {
   if (attn_decode_supported(dtype, tree, g))
-    return launch_attention_decode(dtype, q, g, kc, vc, layer, seq_len, B, max_prefix, att_out, scratch, scratch_bytes, st);
+    return launch_attention_decode(dtype, q, nullptr, nullptr, g, (void*)kc, (void*)vc, layer, seq_len, B, max_prefix, att_out,
+                                   scratch, scratch_bytes, st);
   if (attn_mfma_supported(dtype, tree, g))
     return launch_attention_mfma(dtype, tree, q, nullptr, nullptr, g, (void*)kc, (void*)vc, layer, seq_len, B, max_prefix,
                                  att_out, scratch, scratch_bytes, st);
@@ -123,6 +124,9 @@ int launch_rope_attention(int dtype, int tree, const Partials& qkv, const float*
       (qkv.split_grid == 0 || qkv.band_cols % 128 == 0))
     return launch_attention_mfma(dtype, tree, nullptr, &qkv, cs, g, kc, vc, layer, seq_len, B, max_prefix, att_out, scratch,
                                  scratch_bytes, st);
+  if (!unfused && attn_decode_supported(dtype, tree, g))
+    return launch_attention_decode(dtype, nullptr, &qkv, cs, g, kc, vc, layer, seq_len, B, max_prefix, att_out, scratch,
+                                   scratch_bytes, st);
   int rc = launch_rope_kvwrite(dtype, tree, qkv, cs, q_scratch, g, kc, vc, layer, seq_len, B, max_prefix, st);
   if (rc) return rc;
   return launch_tree_attention(dtype, tree, q_scratch, g, kc, vc, layer, seq_len, B, max_prefix, att_out, scratch,
