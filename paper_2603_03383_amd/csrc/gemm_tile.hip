@@ -11,15 +11,19 @@
 //     waits for its own loads of a round with a counted vmcnt and one workgroup barrier per round makes them everyone's.
 //     The loads are written as inline assembly because the compiler, once it sees loads that write LDS, drains all
 //     of them before every LDS read;
+//   * the operands of a k-step are read from LDS while the previous k-step multiplies (two register sets), so that after a
+//     barrier the matrix cores have work while all eight waves read LDS at once;
 //   * X is read row-major, 128 B (one cache line) of eight rows per instruction; the 16-byte chunks of a row are XOR-ed
 //     with the row number on the way in (through the per-lane source addresses), which makes the operand reads bank
 //     conflict free without padding.  W arrives in the packed order (common.h): 4 KiB per tile and round, contiguous;
 //   * the MFMA is issued as W x X^T: a lane then holds four consecutive output columns of ONE row per register quad, so
 //     sums leave as 16-byte (fp32) or 8-byte (SwiGLU output) stores.
-// What bounds it: a CU keeps about 64 KiB of loads in flight whatever the ring holds (measured: rings of 3, 4 and 6 rounds
-// run alike), which at HBM latency is ~50 GB/s of X and W together (135 GB/s when every line is an L2 hit); hence the
-// tall tiles.  Measured on [M, K] x [N, K]^T, us per launch, before (128 x 256 tiles, operands through registers) / now:
-// 192 rows: 12288 x 4096: 55 / 35, 22016 x 4096 (with SwiGLU): 88 / 57, 4096 x 4096: 20.6 / 16.4, 4096 x 11008: 38 / 30.
+// What bounds it: below ~300 rows the loads (a CU keeps about 64 KiB in flight whatever the ring holds: rings of 3, 4 and 6
+// rounds run alike), hence the tall tiles; at 1024 rows the LDS, which a round of the 256 x 128 tile asks for 96 KiB of
+// operand reads and 48 KiB of incoming loads beside 1024 clocks of MFMAs (1024 x 22016 x 4096: 196 us; without the loads
+// 145, without the MFMAs 146).  Measured on [M, K] x [N, K]^T, us per launch, before (128 x 256 tiles, operands through registers) / now:
+// 192 rows: 12288 x 4096: 55 / 33, 22016 x 4096 (with SwiGLU): 88 / 55, 4096 x 4096: 20.6 / 17.4, 4096 x 11008: 38 / 28.6
+// (35 / 58.7 / 17.2 / 32.1 without the second register set; 1024 rows, without / with it: 128 / 122, 206 / 194, 42 / 40, 108 / 102).
 // 96 rows had no kernel but the portable one (800 / 26, 840 / 42, 810 / 12, 2170 / 23).
 #include "kernels.h"
 
@@ -110,40 +114,52 @@ __global__ void __launch_bounds__(512, 2)
     }
   };
 
+  // Operands of one k-step (16 of the group's 32 features of a round), LDS -> registers, and their products.
+  auto read_ops = [&](int slot, int ks, u32x4 (&a)[MT], u32x4 (&b)[NT]) {
+    const uint8_t* base = lds_raw + slot * kSlot;
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+      b[j] = *reinterpret_cast<const u32x4*>(base + (UX + (wc * NT + j) * 4 + grp * 2 + ks) * 1024 + lane * 16);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+      a[i] = *reinterpret_cast<const u32x4*>(base + ((wr * MT + i) * 32 + (lane & 31)) * 128 +
+                                             ((grp * 4 + ks * 2 + (lane >> 5)) ^ (lane & 7)) * 16);
+  };
+  auto multiply = [&](const u32x4 (&a)[MT], const u32x4 (&b)[NT]) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[i][j] = Elem16<E>::mfma(b[j], a[i], acc[i][j]);
+  };
+
   const int n = r_hi - r_lo;
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s) load_round(r_lo + min(s, n - 1), s);
+  wait_loads<(NS - 2) * L>();
+  __builtin_amdgcn_s_barrier();  // round 0 is in LDS for everyone
+  __builtin_amdgcn_sched_barrier(0);
+  u32x4 a0[MT], b0[NT], a1[MT], b1[NT];
+  read_ops(0, 0, a0, b0);
   int slot = 0;
   for (int s = 0; s < n; ++s) {
-    const int prev = slot == 0 ? NS - 1 : slot - 1;
+    const int prev = slot == 0 ? NS - 1 : slot - 1, next = slot + 1 == NS ? 0 : slot + 1;
+    read_ops(slot, 1, a1, b1);
+    __builtin_amdgcn_sched_barrier(0);
+    load_round(r_lo + min(s + NS - 1, n - 1), prev);  // (everyone had read round s - 1 before the last barrier)
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(a0, b0);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_lds();  // this wave's reads of the slot are in registers before the barrier lets it be overwritten
     wait_loads<(NS - 2) * L>();
-    __builtin_amdgcn_s_barrier();  // round s is in LDS for everyone, and everyone has read round s - 1
+    __builtin_amdgcn_s_barrier();  // round s + 1 is in LDS for everyone, and everyone has read round s
     __builtin_amdgcn_sched_barrier(0);
-    const uint8_t* base = lds_raw + slot * kSlot;
-    u32x4 a[2][MT], b[2][NT];
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-        b[ks][j] = *reinterpret_cast<const u32x4*>(base + (UX + (wc * NT + j) * 4 + grp * 2 + ks) * 1024 + lane * 16);
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-        a[ks][i] = *reinterpret_cast<const u32x4*>(base + ((wr * MT + i) * 32 + (lane & 31)) * 128 +
-                                                   ((grp * 4 + ks * 2 + (lane >> 5)) ^ (lane & 7)) * 16);
-    }
+    read_ops(next, 0, a0, b0);  // (behind the last round: a repeated one, never multiplied)
     __builtin_amdgcn_sched_barrier(0);
-    load_round(r_lo + min(s + NS - 1, n - 1), prev);
+    multiply(a1, b1);
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = Elem16<E>::mfma(b[ks][j], a[ks][i], acc[i][j]);
-    wait_lds();  // this wave's reads of the slot are in registers before the next barrier lets it be overwritten
-    __builtin_amdgcn_sched_barrier(0);
-    slot = slot + 1 == NS ? 0 : slot + 1;
+    slot = next;
   }
+  wait_lds();
   wait_loads<0>();
   __syncthreads();
 
