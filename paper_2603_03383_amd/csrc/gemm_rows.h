@@ -1,0 +1,30 @@
+// What the two many-row GEMMs (gemm_tile.hip, gemm_wide.hip) share: direct-to-LDS loads' helpers, and which of the two a product takes.
+#pragma once
+#include "kernels.h"
+
+namespace mdz {
+
+constexpr int kRound = 64;  // features per round of loads
+
+#define MDZ_LDS_ADDR(p) ((uint32_t)(uintptr_t)((__attribute__((address_space(3))) void*)(p)))
+
+__device__ inline float silu_tile(float v) { return v / (1.0f + expf(-v)); }
+template <int N>
+__device__ inline void wait_loads() {  // all but the N youngest loads of this wave have landed
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ inline void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// Modelled time of a launch in us, the reading of its partial-sum slots by the consumer included; `slots` (nullable) receives
+// their number.
+double gemm_tile_cost(int M, int N, int K, int max_split, bool swiglu, int* slots);
+double gemm_wide_cost(int M, int N, int K, int max_split, bool swiglu, int* slots);
+// the faster of the two by these models
+inline bool gemm_wide_preferred(int M, int N, int K, int max_split, bool swiglu) {
+  return gemm_wide_cost(M, N, K, max_split, swiglu, nullptr) < gemm_tile_cost(M, N, K, max_split, swiglu, nullptr);
+}
+int launch_gemm_wide(int dtype, const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp, int64_t part_stride,
+                     int max_split, Partials* res, hipStream_t st);
+int launch_gemm_wide_swiglu(int dtype, const void* X, const void* Wp, void* U, int M, int N, int K, hipStream_t st);
+
+}  // namespace mdz

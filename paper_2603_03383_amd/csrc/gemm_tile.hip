@@ -25,7 +25,7 @@
 // 192 rows: 12288 x 4096: 55 / 33, 22016 x 4096 (with SwiGLU): 88 / 55, 4096 x 4096: 20.6 / 17.4, 4096 x 11008: 38 / 28.6
 // (35 / 58.7 / 17.2 / 32.1 without the second register set; 1024 rows, without / with it: 128 / 122, 206 / 194, 42 / 40, 108 / 102).
 // 96 rows had no kernel but the portable one (800 / 26, 840 / 42, 810 / 12, 2170 / 23).
-#include "kernels.h"
+#include "gemm_rows.h"
 
 namespace mdz {
 
@@ -33,12 +33,6 @@ typedef f32x16_t f32x16;
 typedef u32x4_t u32x4;
 
 namespace {
-constexpr int kRound = 64;  // features per round
-
-__device__ inline float silu_tile(float v) { return v / (1.0f + expf(-v)); }
-
-#define MDZ_LDS_ADDR(p) ((uint32_t)(uintptr_t)((__attribute__((address_space(3))) void*)(p)))
-
 // One wave brings 64 x 16 B from base + voff (per lane) to LDS address `lds` + 16 * lane.  base and lds are wave-uniform.
 __device__ inline void load_to_lds(const void* base, uint32_t voff, uint32_t lds) {
   const uint64_t p = (uint64_t)base;
@@ -48,11 +42,6 @@ __device__ inline void load_to_lds(const void* base, uint32_t voff, uint32_t lds
                "v"(voff), "s"(u)
                : "memory");
 }
-template <int N>
-__device__ inline void wait_loads() {  // all but the N youngest loads of this wave have landed
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-__device__ inline void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 }  // namespace
 
 // SWIGLU (gate/up matrix, NT == 2: a wave's two tiles are the gate and the up columns of the same 32 features): an unsplit
@@ -224,6 +213,7 @@ namespace {
 struct TilePlan {
   int bm, bn, ksplit;  // rows and columns of a workgroup's tile, K splits
   int nb_m, nb_n;
+  double us;  // modelled
 };
 
 // Tile and split by a small model of the launch: a workgroup's time is the larger of its requests at 50 GB/s and its
@@ -248,7 +238,7 @@ TilePlan plan_tile(int M, int N, int K, int max_split, bool swiglu) {
         const double hbm = (double)N * K * 2 / 5.5e6 + 4.0;
         if (t < hbm) t = hbm;
         t += (double)ks * M * N * 4 * (1.0 / 5e6 + 1.0 / 4e6);
-        if (t < best_t - 1e-9) best_t = t, best = TilePlan{bm, bn, ks, nb_m, nb_n};
+        if (t < best_t - 1e-9) best_t = t, best = TilePlan{bm, bn, ks, nb_m, nb_n, t};
       }
     }
   return best;
@@ -259,8 +249,19 @@ bool gemm_tile_supported(int dtype, int M, int N, int K) {
   return is_16bit(dtype) && M > 64 && N % 32 == 0 && K % kRound == 0 && K >= kRound && (int64_t)M * K < (int64_t)1 << 31;
 }
 
+double gemm_tile_cost(int M, int N, int K, int max_split, bool swiglu, int* slots) {
+  const TilePlan p = plan_tile(M, N, K, max_split, swiglu);
+  if (slots) *slots = p.ksplit;
+  return p.us;
+}
+
 // partial-sum slots launch_gemm_tile will write for this problem (sizes the slot workspace)
-int gemm_tile_slots(int M, int N, int K, int max_split) { return plan_tile(M, N, K, max_split, false).ksplit; }
+int gemm_tile_slots(int M, int N, int K, int max_split) {
+  int slots = 1;
+  if (gemm_wide_preferred(M, N, K, max_split, false)) gemm_wide_cost(M, N, K, max_split, false, &slots);
+  else gemm_tile_cost(M, N, K, max_split, false, &slots);
+  return slots;
+}
 
 template <typename E, bool SWIGLU>
 static int launch_gemm_tile_t(const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp, int64_t part_stride,
@@ -298,6 +299,8 @@ static int launch_gemm_tile_t(const void* X, const void* Wp, float* P, int M, in
 
 int launch_gemm_tile(int dtype, const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp,
                      int64_t part_stride, int max_split, Partials* res, hipStream_t st) {
+  if (gemm_wide_preferred(M, N, K, max_split, false))
+    return launch_gemm_wide(dtype, X, Wp, P, M, N, K, ldp, part_stride, max_split, res, st);
   MDZ_WITH_ELEM16(dtype, return (launch_gemm_tile_t<E, false>(X, Wp, P, M, N, K, ldp, part_stride, max_split, res, nullptr, st)));
 }
 
@@ -305,6 +308,7 @@ int launch_gemm_tile(int dtype, const void* X, const void* Wp, float* P, int M, 
 bool gemm_tile_swiglu_supported(int dtype, int M, int N, int K) { return gemm_tile_supported(dtype, M, N, K) && N % 64 == 0; }
 
 int launch_gemm_tile_swiglu(int dtype, const void* X, const void* Wp, void* U, int M, int N, int K, hipStream_t st) {
+  if (gemm_wide_preferred(M, N, K, 1, true)) return launch_gemm_wide_swiglu(dtype, X, Wp, U, M, N, K, st);
   MDZ_WITH_ELEM16(dtype, return (launch_gemm_tile_t<E, true>(X, Wp, nullptr, M, N, K, N, 0, 1, nullptr, U, st)));
 }
 

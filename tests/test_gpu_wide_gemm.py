@@ -1,0 +1,49 @@
+"""Products of several hundred rows that take the 192 / 256 x 256 tiles (gemm_wide.hip): row counts around the tiles' edges, one and
+several bands of columns per workgroup, a last band of 96 columns, a contraction that is no whole number of packed stages, the
+SwiGLU epilogue with both row tiles, the K split.  Bounds: a product against float64 on the same 16-bit operands, fp32
+accumulation over ~2000 terms (1e-5 of the output scale); layers as in the parity tests."""
+import pytest
+import torch
+
+import paper_2603_03383_amd as P
+import workload as W
+from tests import gpu_util as G
+from tests.test_gpu_parity import _check_layer, _i32, _layer_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("tree,batch,vocab", [(W.TREE15, 13, 40032), (W.TREE1, 257, 20000), (W.TREE15, 18, 32000),
+                                              (W.TREE1, 400, 40032), (W.TREE64, 7, 32000), (W.TREE64, 16, 20000),
+                                              (W.TREE64, 16, 40032)],
+                         ids=lambda v: getattr(v, "name", v))
+def test_lm_head_logits(dtype, tree, batch, vocab):
+    """d 2112: 33 rounds of 64 features, 8.25 packed stages; 40032 columns: 156 bands of 256 and one of 96."""
+    w = W.CONFIGS["cfg2_layer_bf16"].with_(d=2112, n_heads=33, head_dim=64, ffn=64, vocab=vocab, dtype=dtype, tree=tree,
+                                           prefix=tuple(b % 3 for b in range(batch)), name=f"wide_lm{vocab}")
+    dm = G.device_model(w, heads=False)
+    T = dm.tree_info["T"]
+    kv = P.DeviceKV(dm, batch=batch, cap=2 + T)
+    buf = P.StepBuffers(dm, batch, 2, want_logits=True)
+    buf.tree_tokens.copy_(W.random_tokens(w, "wide_lm", (batch, T)).to(torch.int32))
+    P.run_step(dm, kv, buf, None, None, None, _i32(list(w.prefix)), with_heads=False)
+    torch.cuda.synchronize()
+    hid, lm = buf.hidden.reshape(batch * T, w.d).double(), W.lm_head(w, G.DEV).double()
+    logits = buf.logits.reshape(batch * T, vocab)
+    for r in range(0, batch * T, 256):
+        ref = hid[r:r + 256] @ lm.T
+        assert (logits[r:r + 256] - ref).abs().max() <= 1e-5 * max(1.0, float(ref.abs().max())), r
+    assert torch.equal(logits.gather(1, buf.node_argmax.reshape(-1, 1).long())[:, 0], logits.max(dim=1).values)
+
+
+@pytest.mark.parametrize("dtype,d,n_heads,ffn,tree,batch", [
+    ("bf16", 2048, 16, 4128, W.TREE64, 16),   # gate/up: 32 bands and one of 64 columns, 192-row tiles
+    ("fp16", 2048, 16, 5632, W.TREE64, 16),   # gate/up: 44 bands, 256-row tiles
+    ("bf16", 4096, 32, 11008, W.TREE64, 5),   # QKV with K in two parts, gate/up over 320 rows
+    ("bf16", 4096, 32, 11008, W.TREE15, 67),  # 1005 rows: QKV in whole bands, gate/up in two bands per workgroup
+])
+def test_layer(dtype, d, n_heads, ffn, tree, batch):
+    w = W.CONFIGS["cfg2_layer_bf16"].with_(d=d, n_heads=n_heads, ffn=ffn, dtype=dtype, tree=tree, name=f"wide_layer_{ffn}")
+    S_list = [(5 * b + 2) % 30 for b in range(batch)]
+    _check_layer(_layer_case(w, S_list, 30, x_seed=f"wide_x{batch}"), S_list, dtype)
