@@ -77,11 +77,12 @@ template <typename E, bool Q8>
 __global__ void __launch_bounds__(256, 2)
     attn_decode_kernel(const E* __restrict__ q, const Partials qkv, const float* __restrict__ cs, KvGeom g, E* __restrict__ kc,
                        E* __restrict__ vc, int layer, const int32_t* __restrict__ seq_len, int max_prefix,
-                       E* __restrict__ att_out, float* __restrict__ part_o, float* __restrict__ part_ml) {
+                       E* __restrict__ att_out, float* __restrict__ part_o, float* __restrict__ part_ml, bool ordered) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int qi = lane & 31, gh = lane >> 5;
-  const int split = blockIdx.x, n_splits = gridDim.x, b = blockIdx.z;
+  const int split = blockIdx.x, n_splits = gridDim.x;
+  const int b = ordered ? sequence_in_order(seq_len, gridDim.z, blockIdx.z) : blockIdx.z;
   const int chunks = (g.group + 31) >> 5;  // groups of more than 32 query heads take several workgroups
   const int hk = blockIdx.y / chunks, h0 = hk * g.group + (blockIdx.y % chunks) * 32;
   const int nq = min(32, g.group - (blockIdx.y % chunks) * 32);  // query heads of this workgroup: h0 .. h0 + nq - 1
@@ -439,8 +440,9 @@ static int launch_attention_decode_t(const void* q, const Partials* qkv, const f
   const int lds_bytes = merge_bytes > q_bytes ? merge_bytes : q_bytes;
   MDZ_SET_LDS_ONCE((attn_decode_kernel<E, Q8>), 4 * 32 * (kORow + 2) * 4);
   const Partials none = single_slot(nullptr, 0, 0);
+  const bool ordered = B > 1 && splits * g.n_heads * chunks * B > 2 * num_cus();  // more workgroups than fit at once: long ones first
   launch_timed(PROF_ATTN, attn_decode_kernel<E, Q8>, dim3(splits, g.n_heads * chunks, B), 256, lds_bytes, st, (const E*)q,
-               qkv ? *qkv : none, cs, g, (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml);
+               qkv ? *qkv : none, cs, g, (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, ordered);
   MDZ_LAUNCH_CHECK();
   if (splits > 1) {
     launch_timed(PROF_ATTN, attn_decode_combine_kernel<E>, dim3(nq, B), 128, 0, st, nq, splits, part_o, part_ml, (E*)att_out);

@@ -113,7 +113,7 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
     attn_tree_mfma_kernel(int tree, const E* __restrict__ q, const Partials qkv, const float* __restrict__ cs,
                           KvGeom g, E* __restrict__ kc, E* __restrict__ vc, int layer,
                           const int32_t* __restrict__ seq_len, int max_prefix, E* __restrict__ att_out,
-                          float* __restrict__ part_o, float* __restrict__ part_ml) {
+                          float* __restrict__ part_o, float* __restrict__ part_ml, bool ordered) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
   MDZ_STAMP(0);
   const TreeTables& t = c_trees[tree];
@@ -124,7 +124,7 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
   const int split = blockIdx.x, n_splits = gridDim.x, h = blockIdx.y;
   constexpr int kHalves = TQ > kQW ? 2 : 1;  // workgroups that share a sequence's queries
   constexpr int kRows = TQ < kQW ? TQ : kQW;  // queries of this workgroup that exist
-  const int b = blockIdx.z / kHalves;
+  const int b = ordered ? sequence_in_order(seq_len, gridDim.z / kHalves, blockIdx.z / kHalves) : blockIdx.z / kHalves;
   const int q0 = (blockIdx.z % kHalves) * 32;  // first query of this workgroup
   const int hk = h / g.group;  // the key/value head that query head h reads (grouped-query attention)
   const int d = q_heads(g) * kHD, dkv = g.n_heads * kHD;
@@ -607,8 +607,11 @@ static int launch_attention_mfma_t(int tree, const void* q, const Partials* qkv,
   float* part_ml = part_o + (int64_t)B * nq * splits * TQ * kHD;
   dim3 grid(splits, nq, B * (TQ > 32 * NU ? 2 : 1));  // two workgroups share a sequence: blockIdx.z = 2 * sequence + half
   const Partials none = single_slot(nullptr, 0, 0);
+  // More workgroups than a round of one per CU: long sequences first (per layer, 3 sequences of 200 .. 2500 keys: 46 -> 37 us, 16
+  // of 256 .. 4096: 155 -> 150; six whose workgroups fit at once lose 1 us of 30 to the sorting).
+  const bool ordered = B > 1 && (int64_t)grid.x * grid.y * grid.z > num_cus();
   launch_timed(PROF_ATTN, attn_tree_mfma_kernel<E, Q8, NU, TQ>, grid, 256, lds_bytes, st, tree, (const E*)q, qkv ? *qkv : none, cs, g,
-               (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml);
+               (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, ordered);
   MDZ_LAUNCH_CHECK();
   if (splits > 1) {
     launch_timed(PROF_ATTN, attn_combine_kernel<E, TQ>, dim3(nq, B, (TQ + 15) / 16), 256, 0, st, nq, splits, part_o, part_ml, (E*)att_out);

@@ -270,6 +270,23 @@ inline int64_t kv_elems(const KvGeom& g) {
   return (int64_t)g.n_layers * g.batch * g.n_heads * kv_cap_pad(g) * g.head_dim;
 }
 
+#if defined(__HIPCC__)
+// The sequence that takes place z in the launch order: longest first (ties: lower index first), within groups of 64 sequences.
+// A ragged batch has more workgroups than fit at once, and the hardware starts them in order: with the long ones in front the
+// short ones fill the gaps at the end.
+__device__ inline int sequence_in_order(const int32_t* seq_len, int B, int z) {
+  const int lane = threadIdx.x & 63, base = z & ~63, n = min(64, B - base);
+  if (n <= 1) return z;
+  const int len = lane < n ? seq_len[base + lane] : INT32_MIN;
+  int rank = 0;
+  for (int j = 0; j < n; ++j) {
+    const int other = __builtin_amdgcn_readlane(len, j);
+    rank += other > len || (other == len && j < lane);
+  }
+  return base + __builtin_ctzll(__ballot(lane < n && rank == z - base));
+}
+#endif
+
 // ---- 8-bit KV cache layout (MDZ_KV_FP8E4M3, head_dim 128) -----------------------------------------
 // The KV compression the paper points to for long sequences (Sections 4.2 and 5).  A row (one slot of one
 // key/value head) is 128 OCP FP8 E4M3 codes and one fp32 scale: scale = max|row| / 448 (1 for a zero row),
