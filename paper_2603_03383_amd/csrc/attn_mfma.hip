@@ -584,10 +584,10 @@ static int attn_splits(int B, int n_heads, int max_prefix, bool fused) {
   return s;
 }
 
-int64_t attn_mfma_scratch_bytes(int B, int n_heads, int max_prefix) {
+int64_t attn_mfma_scratch_bytes(int B, int n_heads, int T, int max_prefix) {
   int s = attn_splits(B, n_heads, max_prefix, true), s2 = attn_splits(B, n_heads, max_prefix, false);
   s = s > s2 ? s : s2;
-  return s == 1 ? 0 : (int64_t)B * n_heads * s * (64 * kHD + 2 * 64) * 4;
+  return s == 1 ? 0 : (int64_t)B * n_heads * s * (T * kHD + 2 * T) * 4;
 }
 
 template <typename E, bool Q8, int NU, int TQ>
@@ -601,7 +601,7 @@ static int launch_attention_mfma_t(int tree, const void* q, const Partials* qkv,
   MDZ_SET_LDS_ONCE((attn_tree_mfma_kernel<E, Q8, NU, TQ>), lds_bytes);
   const int nq = q_heads(g);
   const int splits = attn_splits(B, nq, max_prefix, qkv != nullptr);
-  MDZ_REQUIRE(scratch_bytes >= attn_mfma_scratch_bytes(B, nq, max_prefix), MDZ_EWORKSPACE,
+  MDZ_REQUIRE(scratch_bytes >= attn_mfma_scratch_bytes(B, nq, TQ, max_prefix), MDZ_EWORKSPACE,
               "attention: scratch too small");
   float* part_o = (float*)scratch;
   float* part_ml = part_o + (int64_t)B * nq * splits * TQ * kHD;

@@ -78,15 +78,15 @@ int launch_gemm(int dtype, const void* X, const void* Wp, float* out, int M, int
 // most partial-sum slots a consumer of a layer GEMM's output is given (the fused norm requests twelve together)
 constexpr int kMaxLayerSlots = 12;
 // fp32 elements of partial-sum workspace a [rows, N] = [rows, K] x [N, K] GEMM needs
-static int64_t gemm_part_elems(int dtype, int rows, int N, int K) {
+static int64_t gemm_part_elems(int dtype, int rows, int N, int K, int max_slots = kMaxLayerSlots) {
   int slots = 1;
-  if (gemm_tile_supported(dtype, rows, N, K)) slots = gemm_tile_slots(rows, N, K, kMaxLayerSlots);
-  else if (gemm_mfma_supported(dtype, rows, N, K)) slots = gemm_mfma_slots(rows, N, K, kMaxLayerSlots);
+  if (gemm_tile_supported(dtype, rows, N, K)) slots = gemm_tile_slots(rows, N, K, max_slots);
+  else if (gemm_mfma_supported(dtype, rows, N, K)) slots = gemm_mfma_slots(rows, N, K, max_slots);
   return (int64_t)slots * rows * N;
 }
 
 bool attn_mfma_supported(int dtype, int tree, const KvGeom& g);
-int64_t attn_mfma_scratch_bytes(int B, int n_heads, int max_prefix);
+int64_t attn_mfma_scratch_bytes(int B, int n_heads, int T, int max_prefix);
 int launch_attention_mfma(int dtype, int tree, const void* q, const Partials* qkv, const float* cs, const KvGeom& g, void* kc,
                           void* vc, int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out,
                           void* scratch, int64_t scratch_bytes, hipStream_t st);
@@ -99,7 +99,7 @@ int launch_attention_decode(int dtype, const void* q, const Partials* qkv, const
 
 int64_t tree_attention_scratch_bytes(int dtype, int tree, const KvGeom& g, int B, int max_prefix) {
   if (attn_decode_supported(dtype, tree, g)) return attn_decode_scratch_bytes(B, q_heads(g), g.n_heads, max_prefix);
-  return attn_mfma_supported(dtype, tree, g) ? attn_mfma_scratch_bytes(B, q_heads(g), max_prefix) : 0;
+  return attn_mfma_supported(dtype, tree, g) ? attn_mfma_scratch_bytes(B, q_heads(g), host_tree(tree)->T, max_prefix) : 0;
 }
 
 int launch_tree_attention(int dtype, int tree, const void* q, const KvGeom& g, const void* kc, const void* vc,
@@ -142,16 +142,18 @@ static int ffn_dtype(const mdz_model_desc& m) { return m.ffn_f16 ? (int)MDZ_FP16
 
 struct Workspace {
   int64_t rope_cs, x, xn, part, q, att, u, logits, h, z, hlogits, sel, sel_bytes, attn_scratch, total;
+  int max_slots;  // partial-sum slots that `part` holds for each of a layer's GEMMs
 };
 
 static int64_t align256(int64_t v) { return (v + 255) & ~int64_t(255); }
 
 // layer_only: what tree_verify_layer touches (no logits, no head buffers, no selection lists)
-static Workspace carve(const mdz_model_desc& m, int B, int max_prefix, bool layer_only = false) {
+static Workspace carve(const mdz_model_desc& m, int B, int max_prefix, bool layer_only = false, int max_slots = kMaxLayerSlots) {
   const TreeTables* t = host_tree(m.tree);
   const int64_t es = elem_bytes(m.dtype);
   const int64_t rows = (int64_t)B * t->T;
   Workspace w{};
+  w.max_slots = max_slots;
   int64_t off = 0;
   auto take = [&](int64_t bytes) {
     int64_t o = off;
@@ -165,7 +167,7 @@ static Workspace carve(const mdz_model_desc& m, int B, int max_prefix, bool laye
     int64_t layer_part = 0;
     const int shapes[4][2] = {{m.d + 2 * kv_width(m), m.d}, {m.d, m.d}, {2 * m.ffn, m.d}, {m.d, m.ffn}};
     for (auto& sh : shapes) {
-      int64_t e = gemm_part_elems(m.dtype, (int)rows, sh[0], sh[1]) * 4;
+      int64_t e = gemm_part_elems(m.dtype, (int)rows, sh[0], sh[1], max_slots) * 4;
       layer_part = e > layer_part ? e : layer_part;
     }
     // every head's first-layer sums at once: from separate GEMMs, or from one GEMM over the stacked matrices
@@ -260,7 +262,7 @@ static int run_layer(const mdz_model_desc& m, const mdz_layer_weights& lw, int l
                      void* xn_next, hipStream_t st) {
   const TreeTables* t = host_tree(m.tree);
   const int rows = B * t->T;
-  const int ms = kMaxLayerSlots;
+  const int ms = w.max_slots;
   const KvGeom g = geom(kv, m.n_heads / kv_heads(m));
   int rc;
   float* cs = (float*)(ws + w.rope_cs);
@@ -588,7 +590,9 @@ int tree_verify_layer_static(const mdz_model_desc* model, const mdz_layer_weight
                              const mdz_kv_desc* kv, const int32_t* seq_len, int B, int max_prefix, void* stream) {
   int rc = verify_layer_checked(model, lw, layer, x_inout, kv, seq_len, B, max_prefix);
   if (rc) return rc;
-  const Workspace L = carve(*model, B, max_prefix, /*layer_only=*/true);
+  // where the faster K splits do not fit the buffer, fewer partial sums do the same work
+  Workspace L = carve(*model, B, max_prefix, /*layer_only=*/true);
+  for (int slots = kMaxLayerSlots; L.total > kStaticScratchBytes && slots > 1;) L = carve(*model, B, max_prefix, true, --slots);
   MDZ_REQUIRE(L.total <= kStaticScratchBytes, MDZ_EWORKSPACE,
               "tree_verify_layer_static: this shape (B %d, max_prefix %d) needs %lld bytes of scratch, the built-in buffer "
               "holds %lld; use tree_verify_layer with a caller workspace",
