@@ -1,5 +1,7 @@
 // What the two many-row GEMMs (gemm_tile.hip, gemm_wide.hip) share: direct-to-LDS loads' helpers, and which of the two a product takes.
 #pragma once
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace mdz {
@@ -9,6 +11,18 @@ constexpr int kRound = 64;  // features per round of loads
 #define MDZ_LDS_ADDR(p) ((uint32_t)(uintptr_t)((__attribute__((address_space(3))) void*)(p)))
 
 __device__ inline float silu_tile(float v) { return v / (1.0f + expf(-v)); }
+template <int N, int I = 0, typename F>
+__device__ inline __attribute__((always_inline)) void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+// One wave brings 64 x 16 B from base + off (per lane) to LDS address `lds` + OFF + 16 * lane.  base and lds are wave-uniform.
+template <int OFF>
+__device__ inline void load_to_lds(const void* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_add_i32 m0, %0, %3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base), "n"(OFF) : "memory", "scc");
+}
 template <int N>
 __device__ inline void wait_loads() {  // all but the N youngest loads of this wave have landed
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");

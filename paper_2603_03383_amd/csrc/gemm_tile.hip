@@ -22,8 +22,9 @@
 // rounds run alike), hence the tall tiles; at 1024 rows the LDS, which a round of the 256 x 128 tile asks for 96 KiB of
 // operand reads and 48 KiB of incoming loads beside 1024 clocks of MFMAs (1024 x 22016 x 4096: 196 us; without the loads
 // 145, without the MFMAs 146).  Measured on [M, K] x [N, K]^T, us per launch, before (128 x 256 tiles, operands through registers) / now:
-// 192 rows: 12288 x 4096: 55 / 33, 22016 x 4096 (with SwiGLU): 88 / 55, 4096 x 4096: 20.6 / 17.4, 4096 x 11008: 38 / 28.6
-// (35 / 58.7 / 17.2 / 32.1 without the second register set; 1024 rows, without / with it: 128 / 122, 206 / 194, 42 / 40, 108 / 102).
+// 192 rows: 12288 x 4096: 55 / 32.5, 22016 x 4096 (with SwiGLU): 88 / 53, 4096 x 4096: 20.6 / 16.4, 4096 x 11008: 38 / 30
+// (35 / 58.7 / 17.2 / 32.1 without the second register set, 33.1 / 55.1 / 17.2 / 31.7 with the addresses of every load worked out
+// anew; 1024 rows, likewise: 128 / 121 / 117, 206 / 196 / 187, 42 / 40.5 / 39, 108 / 101 / 97).
 // 96 rows had no kernel but the portable one (800 / 26, 840 / 42, 810 / 12, 2170 / 23).
 #include "gemm_rows.h"
 
@@ -31,18 +32,6 @@ namespace mdz {
 
 typedef f32x16_t f32x16;
 typedef u32x4_t u32x4;
-
-namespace {
-// One wave brings 64 x 16 B from base + voff (per lane) to LDS address `lds` + 16 * lane.  base and lds are wave-uniform.
-__device__ inline void load_to_lds(const void* base, uint32_t voff, uint32_t lds) {
-  const uint64_t p = (uint64_t)base;
-  const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p) |
-                     ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32);
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane((int)lds)),
-               "v"(voff), "s"(u)
-               : "memory");
-}
-}  // namespace
 
 // SWIGLU (gate/up matrix, NT == 2: a wave's two tiles are the gate and the up columns of the same 32 features): an unsplit
 // launch writes SiLU(gate) * up as E instead of the sums.
@@ -54,7 +43,8 @@ __global__ void __launch_bounds__(512, 2)
   static_assert(!SWIGLU || NT == 2, "gate and up tiles of a pair in one wave");
   constexpr int XT = WR * MT, WT = WC * NT;            // 32-row and 32-column tiles of the workgroup
   constexpr int UX = XT * 4, UT = (XT + WT) * 4;       // 1 KiB pieces of a round: X (8 rows x 128 B each), then W
-  constexpr int L = (UT + 7) / 8;                      // loads per wave and round (a few repeat the last piece)
+  constexpr int LX = UX / 8, LW = WT / 2, L = LX + LW; // loads per wave and round
+  static_assert(LX * 8 == UX && L * 8 == UT, "the eight waves share the pieces of a round evenly");
   constexpr uint32_t kSlot = UT * 1024;
   static_assert(NS * kSlot >= 4 * MT * NT * 4096, "the groups' exchange fits the ring");
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds_raw[];
@@ -79,27 +69,34 @@ __global__ void __launch_bounds__(512, 2)
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const uint32_t lds0 = MDZ_LDS_ADDR(lds_raw);
-  // rows beyond M re-read row M-1 and tiles beyond n_tiles re-read tile 0; neither is stored.  Rounds past the range
-  // repeat its last one and are never multiplied, so the wait counts below are the same in every trip.
-  auto load_round = [&](int r, int slot) {
+  // Load cursor.  A load is two instructions: addresses are a scalar base of X and of W, advanced by additions from round to
+  // round, and per-lane offsets that do not change.  Rows beyond M re-read row M-1 and tiles beyond n_tiles the block's first
+  // tile; neither is stored.  Past the range the cursor stays on its last round, which is not multiplied again, so the
+  // wait counts below are the same in every trip.
+  const int n = r_hi - r_lo;
+  uint32_t xoff[LX], woff[LW];
 #pragma unroll
-    for (int q = 0; q < L; ++q) {
-      int u = q * 8 + wave;
-      u = u < UT ? u : UT - 1;
-      const uint32_t dst = lds0 + slot * kSlot + u * 1024;
-      if (u < UX) {
-        const int row8 = u * 8 + (lane >> 3), c = (lane & 7) ^ (row8 & 7);
-        const int row = min(bm * XT * 32 + row8, M - 1);
-        load_to_lds(X + (int64_t)r * kRound, (uint32_t)row * (uint32_t)K * 2 + c * 16, dst);
-      } else {
-        const int v = u - UX;
-        int tile = bn * WT + (v >> 2);
-        tile = tile < n_tiles ? tile : 0;
-        const int ks = r * 4 + (v & 3);
-        // packed order [band of 4 tiles][stage of 256 features][tile in band][16 k-steps][lane]
-        const int64_t unit = (((int64_t)(tile >> 2) * nst256 + (ks >> 4)) * kBandTiles + (tile & 3)) * 16 + (ks & 15);
-        load_to_lds(reinterpret_cast<const uint8_t*>(Wp) + unit * 1024, lane * 16, dst);
-      }
+  for (int q = 0; q < LX; ++q) {
+    const int row = min(bm * XT * 32 + (q * 8 + wave) * 8 + (lane >> 3), M - 1);
+    xoff[q] = (uint32_t)row * (uint32_t)K * 2 + ((lane & 7) ^ (lane >> 3)) * 16;
+  }
+#pragma unroll
+  for (int q = 0; q < LW; ++q) {
+    const int t = q * 2 + (wave >> 2);  // tile of the block; this wave loads its k-step (wave & 3) of every round
+    woff[q] = lane * 16 + (bn * WT + t < n_tiles ? t * 16384 : 0);
+  }
+  // packed order [band of 4 tiles][stage of 256 features][tile in band][16 k-steps][lane]
+  const uint8_t* xp = reinterpret_cast<const uint8_t*>(X) + (int64_t)r_lo * (kRound * 2);
+  const uint8_t* wp = reinterpret_cast<const uint8_t*>(Wp) + ((int64_t)(bn * WT >> 2) * nst256 + (r_lo >> 2)) * 65536 +
+                      ((bn * WT) & 3) * 16384 + (r_lo & 3) * 4096 + (wave & 3) * 1024;
+  int next_r = r_lo;
+  auto load_round = [&](int slot) {
+    const uint32_t dst = lds0 + slot * kSlot + wave * 1024;
+    static_for<LX>([&](auto q) { load_to_lds<decltype(q)::value * 8192>(xp, xoff[decltype(q)::value], dst); });
+    static_for<LW>([&](auto q) { load_to_lds<UX * 1024 + decltype(q)::value * 8192>(wp, woff[decltype(q)::value], dst); });
+    if (next_r + 1 < r_hi) {
+      ++next_r;
+      xp += kRound * 2, wp += (next_r & 3) ? 4096 : 4096 + 3 * 16384;
     }
   };
 
@@ -121,9 +118,8 @@ __global__ void __launch_bounds__(512, 2)
       for (int j = 0; j < NT; ++j) acc[i][j] = Elem16<E>::mfma(b[j], a[i], acc[i][j]);
   };
 
-  const int n = r_hi - r_lo;
 #pragma unroll
-  for (int s = 0; s < NS - 1; ++s) load_round(r_lo + min(s, n - 1), s);
+  for (int s = 0; s < NS - 1; ++s) load_round(s);
   wait_loads<(NS - 2) * L>();
   __builtin_amdgcn_s_barrier();  // round 0 is in LDS for everyone
   __builtin_amdgcn_sched_barrier(0);
@@ -134,7 +130,7 @@ __global__ void __launch_bounds__(512, 2)
     const int prev = slot == 0 ? NS - 1 : slot - 1, next = slot + 1 == NS ? 0 : slot + 1;
     read_ops(slot, 1, a1, b1);
     __builtin_amdgcn_sched_barrier(0);
-    load_round(r_lo + min(s + NS - 1, n - 1), prev);  // (everyone had read round s - 1 before the last barrier)
+    load_round(prev);  // (everyone had read round s - 1 before the last barrier)
     __builtin_amdgcn_sched_barrier(0);
     multiply(a0, b0);
     __builtin_amdgcn_sched_barrier(0);

@@ -11,10 +11,8 @@
 //   * A workgroup runs several bands of 256 columns one after the other without emptying the rings, or a K split of one band.
 // What bounds it now: power.  The clock falls from 2.4 to ~1.65 GHz and the loop then runs at 75 % of the MFMA rate of that
 // clock; fewer busy CUs run faster, so a launch takes no more of them than its rounds need.  Measured, us per launch, gemm_tile / this one:
-// 1024 rows: 12288 x 4096: 122 / 100 (and one partial sum instead of two), 22016 x 4096 with SwiGLU: 194 / 178, 128000 x 4096:
-// 1141 / 957 (1.12 PFLOP/s); 512 rows: 68 / 58, 123 / 101, 637 / 539; 320 rows: 53 / 46, 96 / 84, 495 / 435.
-#include <type_traits>
-
+// 1024 rows: 12288 x 4096: 117 / 100 (and one partial sum instead of two), 22016 x 4096 with SwiGLU: 187 / 178, 128000 x 4096:
+// 1082 / 957 (1.12 PFLOP/s); 512 rows: 65 / 58, 118 / 101, 602 / 539; 320 rows: 48 / 46, 95 / 84, 476 / 435.
 #include "gemm_rows.h"
 
 namespace mdz {
@@ -23,13 +21,6 @@ typedef f32x16_t f32x16;
 typedef u32x4_t u32x4;
 
 namespace {
-template <int N, int I = 0, typename F>
-__device__ inline __attribute__((always_inline)) void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<N, I + 1>(f);
-  }
-}
 __device__ inline void workgroup_barrier() {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
@@ -104,12 +95,8 @@ __global__ void __launch_bounds__(256, 1)
     for (int q = 0; q < LW; ++q) woff[q] = lane * 16 + (q & 1) * 32768 + (q >> 1) * second;
   };
   w_band();
-  auto dma = [&](const void* base, uint32_t off, uint32_t lds, auto qc) {
-    asm volatile("s_add_i32 m0, %0, %3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base), "n"(decltype(qc)::value * 4096)
-                 : "memory", "scc");
-  };
-  auto load_x = [&](auto q) { dma(xp, xoff[decltype(q)::value], x_lds, q); };
-  auto load_w = [&](auto q) { dma(wp, woff[decltype(q)::value], w_lds, q); };
+  auto load_x = [&](auto q) { load_to_lds<decltype(q)::value * 4096>(xp, xoff[decltype(q)::value], x_lds); };
+  auto load_w = [&](auto q) { load_to_lds<decltype(q)::value * 4096>(wp, woff[decltype(q)::value], w_lds); };
   auto next_x = [&]() {
     if (x_left > 0) {
       --x_left, ++xr, xp += kRound;
