@@ -37,6 +37,7 @@ double gemm_wide_cost(int M, int N, int K, int max_split, bool swiglu, int* slot
 inline bool gemm_wide_preferred(int M, int N, int K, int max_split, bool swiglu) {
   return gemm_wide_cost(M, N, K, max_split, swiglu, nullptr) < gemm_tile_cost(M, N, K, max_split, swiglu, nullptr);
 }
+bool gemm_tile_supported(int dtype, int M, int N, int K);
 int launch_gemm_wide(int dtype, const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp, int64_t part_stride,
                      int max_split, Partials* res, hipStream_t st);
 int launch_gemm_wide_swiglu(int dtype, const void* X, const void* Wp, void* U, int M, int N, int K, hipStream_t st);

@@ -30,10 +30,12 @@ __device__ inline void workgroup_barrier() {
 
 // SWIGLU (gate/up matrix, whole bands): of a wave's four tiles 0, 2 are gate and 1, 3 the up columns of the same features;
 // SiLU(gate) * up is written as E instead of the sums.
-template <typename E, int MT, bool SWIGLU>
+// ARGMAX (LM head of a verify pass that wants no logits, whole bands): a lane keeps the best (value, column) of its rows over the
+// workgroup's bands; two candidates per row and workgroup leave the kernel instead of the sums.
+template <typename E, int MT, bool SWIGLU, bool ARGMAX>
 __global__ void __launch_bounds__(256, 1)
     gemm_wide_kernel(const E* __restrict__ X, int M, int K, const E* __restrict__ Wp, int n_tiles, float* __restrict__ P,
-                     int64_t ldp, int64_t part_stride, int nb_m, int nb_n, int G, int ksplit, E* __restrict__ U) {
+                     int64_t ldp, int64_t part_stride, int nb_m, int nb_n, int G, int ksplit, E* __restrict__ U, ArgCand* __restrict__ cand) {
   constexpr int NT = 4, BM = 64 * MT;
   constexpr int LX = 2 * MT, LW = 4;                // loads of a wave: X of one round, W of half a round
   constexpr int HX = MT, LWIN = LW + HX;            // a window: W of half a round and half of a round's X
@@ -121,8 +123,12 @@ __global__ void __launch_bounds__(256, 1)
   };
 
   int cb = u_lo / n_rounds, cr = u_lo % n_rounds;
+  float best_v[MT];
+  int best_i[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) best_v[i] = -INFINITY, best_i[i] = kNoIndex;
   auto flush = [&]() {
-    float* out = SWIGLU ? nullptr : P + (int64_t)(w % ksplit) * part_stride;
+    float* out = SWIGLU || ARGMAX ? nullptr : P + (int64_t)(w % ksplit) * part_stride;
     auto pin = [&]() {  // holds the sums in accumulation registers until each is wanted; read out all at once they spill
 #pragma unroll
       for (int i = 0; i < MT; ++i)
@@ -133,6 +139,22 @@ __global__ void __launch_bounds__(256, 1)
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
       const int m = bm * BM + (wr * MT + i) * 32 + (lane & 31);
+      if constexpr (ARGMAX) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          pin();
+          const int tile = cb * 8 + wc * NT + j;
+          if (tile < n_tiles) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const int col = tile * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+              if (precedes(acc[i][j][r], col, best_v[i], best_i[i])) best_v[i] = acc[i][j][r], best_i[i] = col;
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        continue;
+      }
       if (m >= M) continue;
       if constexpr (SWIGLU) {
 #pragma unroll
@@ -247,6 +269,16 @@ __global__ void __launch_bounds__(256, 1)
     flush();
     cr = 0, ++cb;
   }
+  if constexpr (ARGMAX) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const int m = bm * BM + (wr * MT + i) * 32 + (lane & 31);
+      const float ov = __shfl_xor(best_v[i], 32, 64);  // the row's other columns
+      const int oi = __shfl_xor(best_i[i], 32, 64);
+      if (precedes(ov, oi, best_v[i], best_i[i])) best_v[i] = ov, best_i[i] = oi;
+      if (lane < 32 && m < M) cand[(int64_t)m * (2 * G) + 2 * w + wc] = ArgCand{best_v[i], best_i[i]};
+    }
+  }
   wait_lds();
   wait_loads<0>();  // no load may write LDS after the workgroup has given it back
 }
@@ -289,9 +321,9 @@ double gemm_wide_cost(int M, int N, int K, int max_split, bool swiglu, int* slot
   return p.us;
 }
 
-template <typename E, bool SWIGLU>
+template <typename E, bool SWIGLU, bool ARGMAX = false>
 static int launch_gemm_wide_t(const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp, int64_t part_stride,
-                              int max_split, Partials* res, void* U, hipStream_t st) {
+                              int max_split, Partials* res, void* U, hipStream_t st, ArgCand* cand = nullptr) {
   const WidePlan p = plan_wide(M, N, K, max_split, SWIGLU);
   if (res) {
     res->n = p.ksplit;
@@ -305,9 +337,9 @@ static int launch_gemm_wide_t(const void* X, const void* Wp, float* P, int M, in
   if (p.mt == MT) {                                                                                                        \
     constexpr int lds_bytes = 3 * 64 * MT * 128 + 4 * 16 * 1024;                                                           \
     static_assert(lds_bytes <= 160 * 1024, "LDS of a CU");                                                                 \
-    MDZ_SET_LDS_ONCE((gemm_wide_kernel<E, MT, SWIGLU>), lds_bytes);                                                        \
-    launch_timed(PROF_GEMM_LARGE, gemm_wide_kernel<E, MT, SWIGLU>, grid, 256, lds_bytes, st, (const E*)X, M, K, (const E*)Wp, \
-                 N / 32, P, ldp, part_stride, p.nb_m, p.nb_n, p.G, p.ksplit, (E*)U);                                       \
+    MDZ_SET_LDS_ONCE((gemm_wide_kernel<E, MT, SWIGLU, ARGMAX>), lds_bytes);                                                        \
+    launch_timed(PROF_GEMM_LARGE, gemm_wide_kernel<E, MT, SWIGLU, ARGMAX>, grid, 256, lds_bytes, st, (const E*)X, M, K, (const E*)Wp, \
+                 N / 32, P, ldp, part_stride, p.nb_m, p.nb_n, p.G, p.ksplit, (E*)U, cand);                                 \
     MDZ_LAUNCH_CHECK();                                                                                                    \
     return MDZ_OK;                                                                                                         \
   }
@@ -324,6 +356,16 @@ int launch_gemm_wide(int dtype, const void* X, const void* Wp, float* P, int M, 
 
 int launch_gemm_wide_swiglu(int dtype, const void* X, const void* Wp, void* U, int M, int N, int K, hipStream_t st) {
   MDZ_WITH_ELEM16(dtype, return (launch_gemm_wide_t<E, true>(X, Wp, nullptr, M, N, K, N, 0, 1, nullptr, U, st)));
+}
+
+// The LM head of a verify pass when only the per-row argmax is wanted: cand receives M x gemm_wide_argmax_cands(...) candidates.
+bool gemm_wide_argmax_supported(int dtype, int M, int N, int K) {
+  return gemm_tile_supported(dtype, M, N, K) && gemm_wide_preferred(M, N, K, 1, false);
+}
+int gemm_wide_argmax_cands(int M, int N, int K) { return 2 * plan_wide(M, N, K, 1, false).G; }
+
+int launch_gemm_wide_argmax(int dtype, const void* X, const void* Wp, int M, int N, int K, ArgCand* cand, hipStream_t st) {
+  MDZ_WITH_ELEM16(dtype, return (launch_gemm_wide_t<E, false, true>(X, Wp, nullptr, M, N, K, 0, 0, 1, nullptr, nullptr, st, cand)));
 }
 
 }  // namespace mdz

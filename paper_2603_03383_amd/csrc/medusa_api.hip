@@ -59,17 +59,24 @@ int launch_gemm_mfma_swiglu(int dtype, const void* X, const void* Wp, void* U, i
 bool gemm_mfma_argmax_supported(int dtype, int M, int N, int K);
 int gemm_mfma_argmax_cands(int M, int N, int K);
 int launch_gemm_mfma_argmax(int dtype, const void* X, const void* Wp, int M, int N, int K, ArgCand* cand, hipStream_t st);
+bool gemm_wide_argmax_supported(int dtype, int M, int N, int K);
+int gemm_wide_argmax_cands(int M, int N, int K);
+int launch_gemm_wide_argmax(int dtype, const void* X, const void* Wp, int M, int N, int K, ArgCand* cand, hipStream_t st);
 bool gemm_tile_swiglu_supported(int dtype, int M, int N, int K);
 int launch_gemm_tile_swiglu(int dtype, const void* X, const void* Wp, void* U, int M, int N, int K, hipStream_t st);
+
+static bool aligned16(const void* X, const void* Wp) {
+  return ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Wp)) & 15) == 0;
+}
 
 int launch_gemm(int dtype, const void* X, const void* Wp, float* out, int M, int N, int K, int64_t ld, int max_split,
                 Partials* res, hipStream_t st) {
   *res = single_slot(out, (int64_t)M * ld, ld);
-  // the fast kernels load 16 bytes at a time; operands that do not start on such a boundary take the portable one
-  if ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Wp)) & 15)
-    return launch_gemm_generic(dtype, X, Wp, out, M, N, K, ld, false, st);
-  if (gemm_f32_supported(dtype, K)) return launch_gemm_f32(X, Wp, out, M, N, K, ld, st);
-  if (gemm_tile_supported(dtype, M, N, K))  // more than 64 rows: several sequences at once
+  // the fp32 and the many-row kernels need operands that start on 16 bytes (direct-to-LDS loads, for the latter); others take the
+  // portable one
+  const bool aligned = aligned16(X, Wp);
+  if (aligned && gemm_f32_supported(dtype, K)) return launch_gemm_f32(X, Wp, out, M, N, K, ld, st);
+  if (aligned && gemm_tile_supported(dtype, M, N, K))  // more than 64 rows: several sequences at once
     return launch_gemm_tile(dtype, X, Wp, out, M, N, K, ld, res->stride, max_split, res, st);
   if (gemm_mfma_supported(dtype, M, N, K)) return launch_gemm_mfma(dtype, X, Wp, out, M, N, K, ld, res->stride, max_split, res, st);
   return launch_gemm_generic(dtype, X, Wp, out, M, N, K, ld, false, st);
@@ -283,7 +290,7 @@ static int run_layer(const mdz_model_desc& m, const mdz_layer_weights& lw, int l
   if ((rc = launch_gemm(m.dtype, att, lw.wo, part, rows, m.d, m.d, m.d, ms, &pr, st))) return rc;
   if ((rc = launch_residual_rmsnorm(m.dtype, x, pr, lw.g_ffn, xn, rows, m.d, m.rms_eps, st, fdt))) return rc;
   // SwiGLU in the GEMM's epilogue where a workgroup ends up with whole gate/up column pairs
-  if (gemm_tile_swiglu_supported(fdt, rows, 2 * m.ffn, m.d)) {
+  if (gemm_tile_swiglu_supported(fdt, rows, 2 * m.ffn, m.d) && aligned16(xn, lw.wgateup)) {
     if ((rc = launch_gemm_tile_swiglu(fdt, xn, lw.wgateup, u, rows, 2 * m.ffn, m.d, st))) return rc;
   } else if (rows <= 64 && gemm_mfma_swiglu_supported(fdt, rows, 2 * m.ffn, m.d)) {
     if ((rc = launch_gemm_mfma_swiglu(fdt, xn, lw.wgateup, u, rows, 2 * m.ffn, m.d, st))) return rc;
@@ -645,6 +652,14 @@ int tree_verify_step(const mdz_model_desc* model, const mdz_weights* w, const in
     if ((int64_t)rows * n_cand * (int64_t)sizeof(ArgCand) <= L.sel_bytes) {
       ArgCand* cand = (ArgCand*)(wsb + L.sel);
       if ((rc = launch_gemm_mfma_argmax(m.dtype, hid, w->lm_head, rows, m.vocab, m.d, cand, st))) return rc;
+      return launch_argmax_merge(cand, rows, n_cand, node_argmax, st);
+    }
+  }
+  if (!logits_opt && gemm_wide_argmax_supported(m.dtype, rows, m.vocab, m.d) && aligned16(hid, w->lm_head)) {
+    const int n_cand = gemm_wide_argmax_cands(rows, m.vocab, m.d);
+    if ((int64_t)rows * n_cand * (int64_t)sizeof(ArgCand) <= L.sel_bytes) {
+      ArgCand* cand = (ArgCand*)(wsb + L.sel);
+      if ((rc = launch_gemm_wide_argmax(m.dtype, hid, w->lm_head, rows, m.vocab, m.d, cand, st))) return rc;
       return launch_argmax_merge(cand, rows, n_cand, node_argmax, st);
     }
   }

@@ -37,6 +37,38 @@ def test_lm_head_logits(dtype, tree, batch, vocab):
     assert torch.equal(logits.gather(1, buf.node_argmax.reshape(-1, 1).long())[:, 0], logits.max(dim=1).values)
 
 
+@pytest.mark.parametrize("tree,batch,vocab", [(W.TREE15, 18, 40032), (W.TREE1, 400, 40032), (W.TREE64, 16, 20000), (W.TREE64, 16, 40032)],
+                         ids=lambda v: getattr(v, "name", v))
+def test_argmax_without_logits(tree, batch, vocab):
+    """The pass that keeps each row's best column itself gives the argmax of the pass that writes the logits, bit for bit; every
+    vocabulary row exists three times (the first of equal maxima wins), in other lanes, tiles and workgroups."""
+    w = W.CONFIGS["cfg2_layer_bf16"].with_(d=2112, n_heads=33, head_dim=64, ffn=64, vocab=vocab, tree=tree,
+                                           prefix=tuple(b % 3 for b in range(batch)), name=f"wide_argmax{vocab}")
+    dm = G.device_model(w, heads=False)
+    lm = W.lm_head(w, G.DEV)
+    third = vocab // 3
+    perm = torch.randperm(third, generator=torch.Generator().manual_seed(3)).to(G.DEV)
+    lm[third:2 * third], lm[2 * third:3 * third] = lm[:third][perm], lm[:third].flip(0)
+    dm.set_lm_head(lm)
+    dm.finalize()
+    T = dm.tree_info["T"]
+    found = []
+    for want in (True, False):
+        kv = P.DeviceKV(dm, batch=batch, cap=2 + T)
+        buf = P.StepBuffers(dm, batch, 2, want_logits=want)
+        buf.tree_tokens.copy_(W.random_tokens(w, "wide_argmax", (batch, T)).to(torch.int32))
+        buf.node_argmax.fill_(-7)
+        P.run_step(dm, kv, buf, None, None, None, _i32(list(w.prefix)), with_heads=False)
+        torch.cuda.synchronize()
+        found.append(buf.node_argmax.clone())
+        if want:
+            logits = buf.logits.reshape(batch * T, vocab)
+            ties = (logits == logits.max(dim=1, keepdim=True).values)
+            assert int((ties.sum(dim=1) >= 3).sum()) >= batch * T * 9 // 10  # (up to two rows at the end exist only once)
+            assert torch.equal(buf.node_argmax.reshape(-1).long(), ties.to(torch.uint8).argmax(dim=1))
+    assert torch.equal(found[0], found[1])
+
+
 @pytest.mark.parametrize("dtype,d,n_heads,ffn,tree,batch", [
     ("bf16", 2048, 16, 4128, W.TREE64, 16),   # gate/up: 32 bands and one of 64 columns, 192-row tiles
     ("fp16", 2048, 16, 5632, W.TREE64, 16),   # gate/up: 44 bands, 256-row tiles
