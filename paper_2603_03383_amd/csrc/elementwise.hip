@@ -112,55 +112,95 @@ __global__ void __launch_bounds__(256) residual_rmsnorm_kernel(float* __restrict
   for (int i = threadIdx.x; i < d; i += 256) xn[(int64_t)r * d + i] = from_float<TO>(xr[i] * rs * to_float(g[i]));
 }
 
-// Fast path for d == 4 * blockDim (d = 4096 with 1024 threads): every thread owns one float4 of the row, all
-// partial loads are issued at once, and the row never leaves registers between the two halves.
-template <typename T, typename TO = T>
+// Fast path for widths that are multiples of four, up to 8192: a thread owns NV float4 of the row (float4 number t + k * blockDim),
+// all partial loads are issued at once, and the row never leaves registers between the two halves.  Bound by one memory round
+// trip and the bytes of the slots through one CU (64 rows of 5120 with up to 12 slots: 41 us in the element-wise kernel
+// above, one dependent load after the other, 6.0 here; 64 rows of 2048: 28 / 4.8).  Two float4 per thread only where 1024 threads do not
+// reach around the row.  FULL: 1024 threads and a width of 4096 NV, known to the compiler (4096: 0.45 us less than without).
+template <typename T, typename TO, int NV, bool FULL>
 __global__ void __launch_bounds__(1024) residual_rmsnorm_vec4_kernel(float* __restrict__ x, Partials part,
                                                                      const T* __restrict__ g, TO* __restrict__ xn,
                                                                      int d, float eps, int rows, RopeJob rope) {
   if ((int)blockIdx.x >= rows) {
-    rope_table_entry((blockIdx.x - rows) * 1024 + threadIdx.x, rope.tree, rope.seq_len, rope.B, rope.max_prefix, rope.half,
+    rope_table_entry((blockIdx.x - rows) * (FULL ? 1024 : blockDim.x) + threadIdx.x, rope.tree, rope.seq_len, rope.B, rope.max_prefix, rope.half,
                      rope.log2_base, rope.cs, rope.status);
     return;
   }
   const float* P = part.p;
   const int64_t part_stride = part.stride, ldp = part.ld;
   __shared__ float red[16];
-  const int r = blockIdx.x, i = threadIdx.x * 4;
-  float4 v = *reinterpret_cast<const float4*>(x + (int64_t)r * d + i);
+  const int r = blockIdx.x, threads = FULL ? 1024 : blockDim.x;
+  int col[NV];
+  float4 v[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    col[k] = (threadIdx.x + k * threads) * 4;
+    v[k] = FULL || col[k] < d ? *reinterpret_cast<const float4*>(x + (int64_t)r * d + col[k]) : float4{0.f, 0.f, 0.f, 0.f};
+  }
   if (P) {
-    const int n_part = part.count(i);  // band widths are multiples of 32, so one count covers the float4
     // the first twelve slots (the most the streaming GEMM makes) are requested together, then added in slot order
     constexpr int kTogether = 12;
-    const float* src = P + (int64_t)r * ldp + i;
-    float4 p[kTogether];
+    int n_part[NV];
+    float4 p[NV][kTogether];
 #pragma unroll
-    for (int s = 0; s < kTogether; ++s)
-      if (s < n_part) p[s] = *reinterpret_cast<const float4*>(src + (int64_t)s * part_stride);
+    for (int k = 0; k < NV; ++k) {
+      n_part[k] = FULL || col[k] < d ? part.count(col[k]) : 0;  // band widths are multiples of 32, so one count covers the float4
+      const float* src = P + (int64_t)r * ldp + col[k];
 #pragma unroll
-    for (int s = 0; s < kTogether; ++s)
-      if (s < n_part) v.x += p[s].x, v.y += p[s].y, v.z += p[s].z, v.w += p[s].w;
-    for (int s = kTogether; s < n_part; ++s) {
-      const float4 q = *reinterpret_cast<const float4*>(src + (int64_t)s * part_stride);
-      v.x += q.x, v.y += q.y, v.z += q.z, v.w += q.w;
+      for (int s = 0; s < kTogether; ++s)
+        if (s < n_part[k]) p[k][s] = *reinterpret_cast<const float4*>(src + (int64_t)s * part_stride);
     }
-    *reinterpret_cast<float4*>(x + (int64_t)r * d + i) = v;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+#pragma unroll
+      for (int s = 0; s < kTogether; ++s)
+        if (s < n_part[k]) v[k].x += p[k][s].x, v[k].y += p[k][s].y, v[k].z += p[k][s].z, v[k].w += p[k][s].w;
+      for (int s = kTogether; s < n_part[k]; ++s) {
+        const float4 q = *reinterpret_cast<const float4*>(P + (int64_t)r * ldp + col[k] + (int64_t)s * part_stride);
+        v[k].x += q.x, v[k].y += q.y, v[k].z += q.z, v[k].w += q.w;
+      }
+      if (FULL || col[k] < d) *reinterpret_cast<float4*>(x + (int64_t)r * d + col[k]) = v[k];
+    }
   }
   if (!xn) return;
-  float ss = wave_sum(v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w);
+  auto squares = [](const float4& a) { return a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w; };
+  float own = squares(v[0]);
+#pragma unroll
+  for (int k = 1; k < NV; ++k) own += squares(v[k]);
+  const float ss = wave_sum(own);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   __syncthreads();
   float tot = 0.f;
 #pragma unroll
-  for (int w = 0; w < 16; ++w) tot += red[w];
+  for (int w = 0; w < 16; ++w) {  // (all sixteen read at once; a loop over the waves there are costs 0.4 us)
+    const float part_sum = red[w];
+    tot += w < threads >> 6 ? part_sum : 0.f;
+  }
   const float rs = 1.0f / sqrtf(tot / (float)d + eps);
-  const Quad<T> gi = *reinterpret_cast<const Quad<T>*>(g + i);  // gains and output: one 8- or 16-byte access each
-  Quad<TO> o;
-  o.v[0] = from_float<TO>(v.x * rs * to_float(gi.v[0]));
-  o.v[1] = from_float<TO>(v.y * rs * to_float(gi.v[1]));
-  o.v[2] = from_float<TO>(v.z * rs * to_float(gi.v[2]));
-  o.v[3] = from_float<TO>(v.w * rs * to_float(gi.v[3]));
-  *reinterpret_cast<Quad<TO>*>(xn + (int64_t)r * d + i) = o;
+#pragma unroll
+  for (int k = 0; k < NV; ++k)
+    if (FULL || col[k] < d) {
+      const Quad<T> gi = *reinterpret_cast<const Quad<T>*>(g + col[k]);  // gains and output: one 8- or 16-byte access each
+      Quad<TO> o;
+      o.v[0] = from_float<TO>(v[k].x * rs * to_float(gi.v[0]));
+      o.v[1] = from_float<TO>(v[k].y * rs * to_float(gi.v[1]));
+      o.v[2] = from_float<TO>(v[k].z * rs * to_float(gi.v[2]));
+      o.v[3] = from_float<TO>(v[k].w * rs * to_float(gi.v[3]));
+      *reinterpret_cast<Quad<TO>*>(xn + (int64_t)r * d + col[k]) = o;
+    }
+}
+
+template <typename T, typename TO>
+static void launch_norm_t(float* x, const Partials& part, const void* g, void* xn, int rows, int d, float eps, RopeJob rope,
+                          int entries, hipStream_t st) {
+  const bool vec = d % 4 == 0 && d <= 8192 && part.ld % 4 == 0 && part.stride % 4 == 0 && ((uintptr_t)g | (uintptr_t)xn) % 16 == 0;
+  const int nv = d > 4096 ? 2 : 1, threads = vec ? (d / 4 + 64 * nv - 1) / (64 * nv) * 64 : 256;
+  rope.n_blocks = (entries + threads - 1) / threads;
+  auto kernel = !vec ? residual_rmsnorm_kernel<T, TO>
+               : d == 4096 ? residual_rmsnorm_vec4_kernel<T, TO, 1, true>
+                 : nv == 1 ? residual_rmsnorm_vec4_kernel<T, TO, 1, false>
+                 : d == 8192 ? residual_rmsnorm_vec4_kernel<T, TO, 2, true> : residual_rmsnorm_vec4_kernel<T, TO, 2, false>;
+  launch_timed(PROF_NORM, kernel, rows + rope.n_blocks, threads, 0, st, x, part, (const T*)g, (TO*)xn, d, eps, rows, rope);
 }
 
 // out_dtype: element type of xn.  It differs from dtype (the gains' type) in one case only: a bf16 model whose
@@ -172,23 +212,9 @@ static int launch_norm_with_rope(int dtype, int out_dtype, float* x, const Parti
   if (out_dtype != dtype) {
     MDZ_REQUIRE(dtype == MDZ_BF16 && out_dtype == MDZ_FP16 && rope.n_blocks == 0, MDZ_EINVAL,
                 "norm: only bf16 gains with binary16 output may differ in type");
-    if (d == 4096 && part.ld % 4 == 0 && part.stride % 4 == 0 && ((uintptr_t)g | (uintptr_t)xn) % 16 == 0)
-      launch_timed(PROF_NORM, residual_rmsnorm_vec4_kernel<bf16_t, f16_t>, rows, 1024, 0, st, x, part, (const bf16_t*)g, (f16_t*)xn, d,
-                   eps, rows, rope);
-    else
-      launch_timed(PROF_NORM, residual_rmsnorm_kernel<bf16_t, f16_t>, rows, 256, 0, st, x, part, (const bf16_t*)g, (f16_t*)xn, d, eps,
-                   rows, rope);
-    MDZ_LAUNCH_CHECK();
-    return MDZ_OK;
-  }
-  if (d == 4096 && part.ld % 4 == 0 && part.stride % 4 == 0 && ((uintptr_t)g | (uintptr_t)xn) % 16 == 0) {
-    rope.n_blocks = (entries + 1023) / 1024;
-    MDZ_WITH_ELEM(dtype, (launch_timed(PROF_NORM, residual_rmsnorm_vec4_kernel<E>, rows + rope.n_blocks, 1024, 0, st, x, part,
-                                       (const E*)g, (E*)xn, d, eps, rows, rope)));
+    launch_norm_t<bf16_t, f16_t>(x, part, g, xn, rows, d, eps, rope, 0, st);
   } else {
-    rope.n_blocks = (entries + 255) / 256;
-    MDZ_WITH_ELEM(dtype, (launch_timed(PROF_NORM, residual_rmsnorm_kernel<E>, rows + rope.n_blocks, 256, 0, st, x, part,
-                                       (const E*)g, (E*)xn, d, eps, rows, rope)));
+    MDZ_WITH_ELEM(dtype, (launch_norm_t<E, E>(x, part, g, xn, rows, d, eps, rope, entries, st)));
   }
   MDZ_LAUNCH_CHECK();
   return MDZ_OK;
