@@ -480,7 +480,7 @@ def main():
         elems = w.n_layers * (2 * w.d * w.d + 2 * w.kv_heads * w.head_dim * w.d + 3 * w.d * w.ffn) + (0 if layer_only else w.vocab * w.d)
         flops = 2.0 * Bn * T * elems
         tf = flops / (gl["total_us"] / args.steps * 1e-6) / 1e12
-        out["roofline"] = {"kernel": "gemm_tile_kernel (every GEMM of the step at M = %d rows)" % (Bn * T), "bound": "mfma",
+        out["roofline"] = {"kernel": "gemm_wide_kernel and gemm_tile_kernel (every GEMM of the step at M = %d rows)" % (Bn * T), "bound": "mfma",
                            "achieved": tf, "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": tf / MFMA_PEAK_TFLOPS, "traffic": None,
                            "algorithmic_flops_per_launch": flops / (gl["launches"] / args.steps),
                            "launches_per_step": gl["launches"] / args.steps,

@@ -16,7 +16,7 @@ enum ProfTag {
   PROF_GEMM_N64,     // gemm_mfma_kernel<2,1,2,*>: 64-column bands, 64 rows (development plans only)
   PROF_GEMM_W32,     // gemm_mfma_kernel<4,1,1,*>: <= 32 rows (Medusa heads, autoregressive step)
   PROF_GEMM_N32,     // gemm_mfma_kernel<2,1,1,*>: <= 32 rows (development plans only)
-  PROF_GEMM_LARGE,   // gemm_tile_kernel: more than 64 rows (several sequences)
+  PROF_GEMM_LARGE,   // gemm_tile_kernel, gemm_wide_kernel: more than 64 rows (several sequences)
   PROF_ATTN,         // tree-masked attention (+ its combine pass)
   PROF_NORM,         // RMSNorm
   PROF_ROPE,         // RoPE table, RoPE + KV write
