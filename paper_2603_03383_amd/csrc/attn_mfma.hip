@@ -543,7 +543,7 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
     for (int s = 0; s < kTogether; ++s)
       if (s0 + s < n_splits) {
-        const float w = fast_exp2(ms[s] - M);
+        const float w = ms[s] == -INFINITY ? 0.f : fast_exp2(ms[s] - M);  // (an empty split, possibly before any other: M = -inf)
         L += w * ls[s];
         acc[0] += w * v0[s].x, acc[1] += w * v0[s].y, acc[2] += w * v0[s].z, acc[3] += w * v0[s].w;
         acc[4] += w * v1[s].x, acc[5] += w * v1[s].y, acc[6] += w * v1[s].z, acc[7] += w * v1[s].w;
