@@ -7,14 +7,17 @@
 // layer for 24 sequences of 90 .. 3000 keys with 8 key/value and 32 query heads, 37 us now).  A wave walks 32-key blocks of
 // the tiled cache (common.h) with contiguous 16-byte-per-lane loads that are MFMA A operands as they are; scores are
 // computed transposed (keys x queries), so the probabilities of 16 keys of one query sit in a lane and feed the second
-// MFMA from registers, exactly as in the tree kernel.  Columns beyond the group's heads are zero and never stored: the
+// MFMA from registers, as in the tree kernel, but as the 16-bit terms of their fp32 values (WeightTerms).  Columns beyond the group's heads are zero and never stored: the
 // matrix cores idle otherwise, the kernel is bound by the K / V stream and, at short prefixes, by its fixed chain.
 // The kernel starts from the QKV GEMM's partial sums: every workgroup reduces and rotates the queries of its group; the
 // split that owns the block of slot S also produces the node's K and V rows, writes them to the cache and puts them into
 // the block from LDS, so that no load waits for a store (a launch of its own took 4.9 us per layer).  Waves merge
 // through LDS, key-splits through a second small kernel, both in a fixed order.
-// Q8 = true: 8-bit rows (common.h): a block is 4 K units + 4 V units + 2 x 32 scales; codes convert exactly to E in registers,
-// the K scales multiply the scores and the V scales the probabilities, in fp32.
+// Q8 = true: 8-bit rows (common.h): a block is 4 K units + 4 V units + 2 x 32 scales; K codes convert exactly to E in registers and
+// the K scales multiply the scores in fp32.  The V scales multiply the probabilities in fp32 too; a scale is |row| / 448, so
+// that product is split into bf16 terms, which have fp32's range, and the V codes convert exactly to bf16, in fp16 models too.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace mdz {
@@ -259,6 +262,7 @@ __global__ void __launch_bounds__(256, 2)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[t][r] = 0.f;
 
+  using VE = std::conditional_t<Q8, bf16_t, E>;  // operand type of the product with V
   auto process = [&](int blk, const u32x4 (&kd)[8], const u32x4 (&vd)[8]) {
     // Compiler barrier: keeps the (loop-invariant) query operands in LDS instead of in 32 registers this kernel lacks
     asm volatile("" ::: "memory");
@@ -283,16 +287,14 @@ __global__ void __launch_bounds__(256, 2)
     bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));  // finite: a block in range holds at least one visible slot
     const float m_new = fmaxf(m_run, bmax);
     const float alpha = exp2_fast(m_run - m_new);
-    float sum = 0.f;
-    uint32_t pk[8];
+    float sum = 0.f, p[16];
 #pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      float p0 = exp2_fast(sc[r] - m_new), p1 = exp2_fast(sc[r + 1] - m_new);
-      sum += p0 + p1;
-      if constexpr (Q8) {  // a slot that no row was ever written to may hold any finite scale; its probability is zero
-        p0 *= __uint_as_float(vd[4 + (r >> 2)][r & 3]), p1 *= __uint_as_float(vd[4 + (r >> 2)][(r & 3) + 1]);
-      }
-      pk[r >> 1] = Elem16<E>::pack2(p0, p1);
+    for (int r = 0; r < 16; ++r) p[r] = exp2_fast(sc[r] - m_new) * WeightTerms<VE>::kScale;
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) sum += p[r] + p[r + 1];
+    if constexpr (Q8) {  // a slot that no row was ever written to may hold any finite scale; its probability is zero
+#pragma unroll
+      for (int r = 0; r < 16; ++r) p[r] *= __uint_as_float(vd[4 + (r >> 2)][r & 3]);
     }
     l_run = l_run * alpha + sum;
     if (__any(m_new != m_run)) {
@@ -302,14 +304,18 @@ __global__ void __launch_bounds__(256, 2)
         for (int r = 0; r < 16; ++r) o[t][r] *= alpha;
     }
     m_run = m_new;
-    const u32x4 pf[2] = {u32x4{pk[0], pk[1], pk[2], pk[3]}, u32x4{pk[4], pk[5], pk[6], pk[7]}};
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int i = 0; i < WeightTerms<VE>::kTerms; ++i) {
+      u32x4 pf[2];
+      next_weight_term<VE>(p, pf);
 #pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        const u32x4 va = Q8 ? fp8x8_to_elem16<E>(vd[t], s2) : vd[t * 2 + s2];
-        o[t] = Elem16<E>::mfma(va, pf[s2], o[t]);
-      }
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          const u32x4 va = Q8 ? fp8x8_to_elem16<VE>(vd[t], s2) : vd[t * 2 + s2];
+          o[t] = Elem16<VE>::mfma(va, pf[s2], o[t]);
+        }
+    }
   };
   if (n_mine > 0) {
     for (int it = 0; it < n_mine; it += 2) {

@@ -160,6 +160,33 @@ struct Elem16<f16_t> {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
   }
 };
+// A softmax weight as a sum of 16-bit terms, so that an MFMA over 16-bit operands multiplies V by the fp32 weight: term i is the
+// rounded rest after terms 0 .. i - 1.  Three bf16 terms are the 24 bits of an fp32 number.  Two binary16 terms are 22, and the
+// weights (at most 1) come scaled by 2^15, which keeps the terms of everything above 2^-29 out of binary16's subnormals and the
+// rest within 2^-40 of the largest weight; the factor is in the denominator too and cancels.
+template <typename E>
+struct WeightTerms;
+template <>
+struct WeightTerms<bf16_t> {
+  static constexpr int kTerms = 3;
+  static constexpr float kScale = 1.f;
+};
+template <>
+struct WeightTerms<f16_t> {
+  static constexpr int kTerms = 2;
+  static constexpr float kScale = 32768.f;
+};
+// takes the next term of 16 weights (registers w) as the MFMA's two B operands; w keeps what is left
+template <typename E>
+__device__ inline void next_weight_term(float (&w)[16], u32x4_t (&term)[2]) {
+#pragma unroll
+  for (int r = 0; r < 16; r += 2) {
+    const uint32_t t = Elem16<E>::pack2(w[r], w[r + 1]);
+    w[r] -= Elem16<E>::lo(t), w[r + 1] -= Elem16<E>::hi(t);
+    term[r >> 3][(r & 7) >> 1] = t;
+  }
+}
+
 // runs `body` with E bound to the element type of any storage dtype
 #define MDZ_WITH_ELEM(dtype, body)    \
   do {                                \
