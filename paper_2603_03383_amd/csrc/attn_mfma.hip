@@ -107,7 +107,8 @@ __device__ inline void rope16(const float* cs_row, int seg, float (&lo)[16], flo
 // CU twice (the second time from L2: the halves are a multiple of 8 workgroups apart, i.e. on one XCD).
 // TQ: nodes of the tree = queries of a sequence (64, or 15: one group of 32 of which the last 17 are padding that is
 // never stored.  Six sequences of 40 .. 1500 keys x 32 heads take 30 us per layer; the portable kernel took 928 us
-// for them).
+// for them).  Its softmax weights enter the product with V as the 16-bit terms of their fp32 values (WeightTerms, common.h): the
+// portable kernel multiplies fp32 weights, and a tree is served with the same precision whichever of the two its shape takes.
 template <typename E, bool Q8, int NU, int TQ>
 __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
     attn_tree_mfma_kernel(int tree, const E* __restrict__ q, const Partials qkv, const float* __restrict__ cs,
@@ -124,6 +125,8 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
   const int split = blockIdx.x, n_splits = gridDim.x, h = blockIdx.y;
   constexpr int kHalves = TQ > kQW ? 2 : 1;  // workgroups that share a sequence's queries
   constexpr int kRows = TQ < kQW ? TQ : kQW;  // queries of this workgroup that exist
+  constexpr bool kFp32Weights = TQ == 15;
+  static_assert(!kFp32Weights || (NU == 1 && !Q8), "fp32 weights: one group of queries, 16-bit rows");
   const int b = ordered ? sequence_in_order(seq_len, gridDim.z / kHalves, blockIdx.z / kHalves) : blockIdx.z / kHalves;
   const int q0 = (blockIdx.z % kHalves) * 32;  // first query of this workgroup
   const int hk = h / g.group;  // the key/value head that query head h reads (grouped-query attention)
@@ -342,6 +345,7 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
     const bool need_mask = rel0 + 32 > 0;  // wave-uniform: the block reaches past the prefix
     float alpha[NU];
     u32x4 pf[NU][2];
+    float weight[16];  // (fp32 weights: NU is 1)
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
       float bmax = -INFINITY;
@@ -370,7 +374,8 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
       // moved (and the accumulators rescaled: 128 registers through the vector ALU) only when a block's maximum
       // exceeds it by more than 2^kLazyLog2, so probabilities stay below 2^kLazyLog2 and, in a long prefix, almost
       // no block rescales.  o, l and m stay consistent, so the merges below need no change.
-      const float m_new = bmax > m_run[u] + kLazyLog2 ? bmax : m_run[u];
+      // (fp32 weights: always the maximum, so that they are at most 1.)
+      const float m_new = bmax > m_run[u] + (kFp32Weights ? 0.f : kLazyLog2) ? bmax : m_run[u];
       const float m_safe = m_new == -INFINITY ? 0.f : m_new;
       alpha[u] = m_new == m_run[u] ? 1.f : fast_exp2(m_run[u] - m_safe);
       float sum = 0.f;
@@ -378,6 +383,12 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
 #pragma unroll
       for (int r = 0; r < 16; r += 2) {
         float p0 = fast_exp2(sc[u][r] - m_safe), p1 = fast_exp2(sc[u][r + 1] - m_safe);
+        if constexpr (kFp32Weights) {
+          p0 *= WeightTerms<E>::kScale, p1 *= WeightTerms<E>::kScale;
+          weight[r] = p0, weight[r + 1] = p1;
+          sum += p0 + p1;
+          continue;
+        }
         sum += p0 + p1;
         if constexpr (Q8) p0 *= __uint_as_float(vd[4 + (r >> 2)][r & 3]), p1 *= __uint_as_float(vd[4 + (r >> 2)][(r & 3) + 1]);
         pk[r >> 1] = Elem16<E>::pack2(p0, p1);
@@ -394,6 +405,18 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
         for (int u = 0; u < NU; ++u)
 #pragma unroll
           for (int r = 0; r < 16; ++r) o[tt][u][r] *= alpha[u];
+    }
+    if constexpr (kFp32Weights) {
+#pragma unroll
+      for (int i = 0; i < WeightTerms<E>::kTerms; ++i) {
+        u32x4 term[2];
+        next_weight_term<E>(weight, term);
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt)
+#pragma unroll
+          for (int s2 = 0; s2 < 2; ++s2) o[tt][0] = Elem16<E>::mfma(vd[tt * 2 + s2], term[s2], o[tt][0]);
+      }
+      return;
     }
 #pragma unroll
     for (int tt = 0; tt < 4; ++tt)

@@ -1,4 +1,5 @@
-"""The softmax weights of the single-query attention are fp32 numbers: products with V lose nothing against fp32.  A layer in which everything around the attention is exact makes its output visible: x is +-1 (its norm is then +-1 in
+"""The softmax weights of the single-query attention and of the 15-node tree are fp32 numbers: products with V lose nothing against
+fp32.  A layer in which everything around the attention is exact makes its output visible: x is +-1 (its norm is then +-1 in
 both 16-bit types), every row of Wq, Wk, Wv has ONE nonzero entry, the rotary base is so large that the features in use do not
 turn, Wo is 1024 x identity and the feed-forward block adds zero.  So (x_out - x) / 1024 is the attention's 16-bit output.
 
@@ -18,7 +19,7 @@ from oracle import tree as OT
 pytestmark = pytest.mark.gpu
 
 HD, OUT = 128, 1024.0
-TREES = {"tree1": W.TREE1}
+TREES = {"tree1": W.TREE1, "tree15": W.TREE15}
 ACTIVE = np.r_[32:64, 96:128]  # features whose rotary angle is below 1e-15 at every position used here
 
 
@@ -93,3 +94,9 @@ def test_single_query(dtype, n_heads, kv_heads):
 def test_single_query_eight_bit_rows(dtype, v_std):
     """Value rows whose scales (largest entry / 448), times a weight, are far below binary16's normal range."""
     _check("tree1", dtype, 4, 2, [40, 0, 5, 100, 700, 31], 700, quant="fp8e4m3", v_std=v_std)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("n_heads,kv_heads", [(4, 4), (8, 2)])
+def test_fifteen_node_tree(dtype, n_heads, kv_heads):
+    _check("tree15", dtype, n_heads, kv_heads, [18, 0, 45, 600], 600)
