@@ -19,10 +19,17 @@ __device__ inline __attribute__((always_inline)) void static_for(F&& f) {
   }
 }
 // One wave brings 64 x 16 B from base + off (per lane) to LDS address `lds` + OFF + 16 * lane.  base and lds are wave-uniform.
+// The load takes its LDS address from m0, one wait state after a scalar write of it (the compiler inserts that for its own
+// loads; it does not look into assembly).  (clang warns that m0 is a reserved register: it is named so that a value the compiler
+// itself puts there is not taken to outlive the load.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <int OFF>
 __device__ inline void load_to_lds(const void* base, uint32_t off, uint32_t lds) {
-  asm volatile("s_add_i32 m0, %0, %3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base), "n"(OFF) : "memory", "scc");
+  asm volatile("s_add_i32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base), "n"(OFF)
+               : "memory", "scc", "m0");
 }
+#pragma clang diagnostic pop
 template <int N>
 __device__ inline void wait_loads() {  // all but the N youngest loads of this wave have landed
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");

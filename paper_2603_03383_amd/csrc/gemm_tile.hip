@@ -69,7 +69,7 @@ __global__ void __launch_bounds__(512, 2)
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const uint32_t lds0 = MDZ_LDS_ADDR(lds_raw);
-  // Load cursor.  A load is two instructions: addresses are a scalar base of X and of W, advanced by additions from round to
+  // Load cursor.  A load is two instructions and a wait state: addresses are a scalar base of X and of W, advanced by additions from round to
   // round, and per-lane offsets that do not change.  Rows beyond M re-read row M-1 and tiles beyond n_tiles the block's first
   // tile; neither is stored.  Past the range the cursor stays on its last round, which is not multiplied again, so the
   // wait counts below are the same in every trip.

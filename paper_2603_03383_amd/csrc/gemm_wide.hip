@@ -6,7 +6,7 @@
 //   * Loads go straight to LDS: X in a ring of three rounds (row-major, a cache line of eight rows per load, 16-byte chunks
 //     XOR-ed with the row number), W in a ring of four half rounds (packed order, common.h), 160 KiB together.
 //   * With one wave per SIMD nothing hides an instruction but the MFMA in front of it (32 clocks), so the loop is laid out by
-//     hand: behind every MFMA at most one LDS read and one load, a load being two instructions; operands are read one
+//     hand: behind every MFMA at most one LDS read and one load, a load being two instructions and a wait state; operands are read one
 //     k-step ahead.  (Address arithmetic per load and loads in bunches cost 3970 clocks per round instead of 2660.)
 //   * A workgroup runs several bands of 256 columns one after the other without emptying the rings, or a K split of one band.
 // What bounds it now: power.  The clock falls from 2.4 to ~1.65 GHz and the loop then runs at 75 % of the MFMA rate of that
@@ -74,7 +74,7 @@ __global__ void __launch_bounds__(256, 1)
   };
   zero_acc();
   const uint32_t lds0 = MDZ_LDS_ADDR(lds_raw);
-  // Load cursors.  A load is two instructions (m0, load): addresses are a scalar base per round or half round, advanced by
+  // Load cursors.  A load is two instructions (m0, load) and a wait state: addresses are a scalar base per round or half round, advanced by
   // additions, and per-lane offsets that do not change.  A cursor stays on the range's last piece when it gets there.
   const int64_t bs = (int64_t)nst256 * 65536;  // bytes of a band of 128 columns
   uint32_t xoff[LX], woff[LW];
