@@ -35,7 +35,10 @@ typedef u32x4_t u32x4;
 
 // SWIGLU (gate/up matrix, NT == 2: a wave's two tiles are the gate and the up columns of the same 32 features): an unsplit
 // launch writes SiLU(gate) * up as E instead of the sums.
-template <typename E, int WR, int WC, int MT, int NT, int NS, bool SWIGLU>
+// DIRECT = false: X or W does not start on 16 bytes (a caller's buffer; the C interface asks for no alignment).  The same ring is
+// filled through registers, from ordinary loads that are requested a round before they are written to LDS.  (128000 x 4096, us,
+// aligned / not: 135 rows 217 / 329, 192 rows 228 / 344, 1024 rows 882 (gemm_wide.hip) / 1561; the portable kernel takes 3854, 3990, 18800.)
+template <typename E, int WR, int WC, int MT, int NT, int NS, bool SWIGLU, bool DIRECT>
 __global__ void __launch_bounds__(512, 2)
     gemm_tile_kernel(const E* __restrict__ X, int M, int K, const E* __restrict__ Wp, int n_tiles, float* __restrict__ P,
                      int64_t ldp, int64_t part_stride, int nb_m, int nb_n, int ksplit, E* __restrict__ U) {
@@ -90,10 +93,26 @@ __global__ void __launch_bounds__(512, 2)
   const uint8_t* wp = reinterpret_cast<const uint8_t*>(Wp) + ((int64_t)(bn * WT >> 2) * nst256 + (r_lo >> 2)) * 65536 +
                       ((bn * WT) & 3) * 16384 + (r_lo & 3) * 4096 + (wave & 3) * 1024;
   int next_r = r_lo;
+  typedef u32x4 u32x4_any __attribute__((aligned(2)));
+  u32x4 held[DIRECT ? 1 : L];  // (through registers: the round after the newest one in LDS)
   auto load_round = [&](int slot) {
-    const uint32_t dst = lds0 + slot * kSlot + wave * 1024;
-    static_for<LX>([&](auto q) { load_to_lds<decltype(q)::value * 8192>(xp, xoff[decltype(q)::value], dst); });
-    static_for<LW>([&](auto q) { load_to_lds<UX * 1024 + decltype(q)::value * 8192>(wp, woff[decltype(q)::value], dst); });
+    if constexpr (DIRECT) {
+      const uint32_t dst = lds0 + slot * kSlot + wave * 1024;
+      static_for<LX>([&](auto q) { load_to_lds<decltype(q)::value * 8192>(xp, xoff[decltype(q)::value], dst); });
+      static_for<LW>([&](auto q) { load_to_lds<UX * 1024 + decltype(q)::value * 8192>(wp, woff[decltype(q)::value], dst); });
+    } else {
+      uint8_t* dst = lds_raw + slot * kSlot + wave * 1024 + lane * 16;
+#pragma unroll
+      for (int q = 0; q < L; ++q) *reinterpret_cast<u32x4*>(dst + (q < LX ? q * 8192 : UX * 1024 + (q - LX) * 8192)) = held[q];
+    }
+  };
+  auto next_round = [&]() {
+    if constexpr (!DIRECT) {
+#pragma unroll
+      for (int q = 0; q < LX; ++q) held[q] = *reinterpret_cast<const u32x4_any*>(xp + xoff[q]);
+#pragma unroll
+      for (int q = 0; q < LW; ++q) held[LX + q] = *reinterpret_cast<const u32x4_any*>(wp + woff[q]);
+    }
     if (next_r + 1 < r_hi) {
       ++next_r;
       xp += kRound * 2, wp += (next_r & 3) ? 4096 : 4096 + 3 * 16384;
@@ -119,8 +138,17 @@ __global__ void __launch_bounds__(512, 2)
   };
 
 #pragma unroll
-  for (int s = 0; s < NS - 1; ++s) load_round(s);
-  wait_loads<(NS - 2) * L>();
+  for (int s = 0; s < NS - 1; ++s) {
+    if constexpr (!DIRECT) next_round();
+    load_round(s);
+    if constexpr (DIRECT) next_round();
+  }
+  if constexpr (DIRECT) {
+    wait_loads<(NS - 2) * L>();
+  } else {
+    next_round();
+    wait_lds();
+  }
   __builtin_amdgcn_s_barrier();  // round 0 is in LDS for everyone
   __builtin_amdgcn_sched_barrier(0);
   u32x4 a0[MT], b0[NT], a1[MT], b1[NT];
@@ -131,11 +159,12 @@ __global__ void __launch_bounds__(512, 2)
     read_ops(slot, 1, a1, b1);
     __builtin_amdgcn_sched_barrier(0);
     load_round(prev);  // (everyone had read round s - 1 before the last barrier)
+    next_round();
     __builtin_amdgcn_sched_barrier(0);
     multiply(a0, b0);
     __builtin_amdgcn_sched_barrier(0);
     wait_lds();  // this wave's reads of the slot are in registers before the barrier lets it be overwritten
-    wait_loads<(NS - 2) * L>();
+    if constexpr (DIRECT) wait_loads<(NS - 2) * L>();
     __builtin_amdgcn_s_barrier();  // round s + 1 is in LDS for everyone, and everyone has read round s
     __builtin_amdgcn_sched_barrier(0);
     read_ops(next, 0, a0, b0);  // (behind the last round: a repeated one, never multiplied)
@@ -259,7 +288,7 @@ int gemm_tile_slots(int M, int N, int K, int max_split) {
   return slots;
 }
 
-template <typename E, bool SWIGLU>
+template <typename E, bool SWIGLU, bool DIRECT>
 static int launch_gemm_tile_t(const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp, int64_t part_stride,
                               int max_split, Partials* res, void* U, hipStream_t st) {
   const TilePlan p = plan_tile(M, N, K, max_split, SWIGLU);
@@ -275,9 +304,9 @@ static int launch_gemm_tile_t(const void* X, const void* Wp, float* P, int M, in
   if (p.bm == 64 * MT && p.bn == 64 * NT) {                                                                              \
     constexpr int lds_bytes = NS * (2 * MT + 2 * NT) * 4 * 1024;                                                         \
     static_assert(lds_bytes <= 160 * 1024, "LDS of a CU");                                                               \
-    MDZ_SET_LDS_ONCE((gemm_tile_kernel<E, 2, 2, MT, NT, NS, SWIGLU>), lds_bytes);                                        \
-    launch_timed(PROF_GEMM_LARGE, gemm_tile_kernel<E, 2, 2, MT, NT, NS, SWIGLU>, grid, 512, lds_bytes, st, (const E*)X, M, \
-                 K, (const E*)Wp, N / 32, P, ldp, part_stride, p.nb_m, p.nb_n, p.ksplit, (E*)U);                         \
+    MDZ_SET_LDS_ONCE((gemm_tile_kernel<E, 2, 2, MT, NT, NS, SWIGLU, DIRECT>), lds_bytes);                                        \
+    launch_timed(PROF_GEMM_LARGE, gemm_tile_kernel<E, 2, 2, MT, NT, NS, SWIGLU, DIRECT>, grid, 512, lds_bytes, st, (const E*)X, \
+                 M, K, (const E*)Wp, N / 32, P, ldp, part_stride, p.nb_m, p.nb_n, p.ksplit, (E*)U);                         \
     MDZ_LAUNCH_CHECK();                                                                                                  \
     return MDZ_OK;                                                                                                       \
   }
@@ -293,19 +322,29 @@ static int launch_gemm_tile_t(const void* X, const void* Wp, float* P, int M, in
   MDZ_FAIL(MDZ_EUNSUPPORTED, "gemm: no tile kernel for a %d x %d tile", p.bm, p.bn);
 }
 
+static bool starts_on_16(const void* X, const void* Wp) {  // what the direct-to-LDS loads need
+  return ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Wp)) & 15) == 0;
+}
+
 int launch_gemm_tile(int dtype, const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp,
                      int64_t part_stride, int max_split, Partials* res, hipStream_t st) {
+  if (!starts_on_16(X, Wp)) {
+    max_split = gemm_tile_slots(M, N, K, max_split);  // (the buffer is sized for the plan of aligned operands)
+    MDZ_WITH_ELEM16(dtype, return (launch_gemm_tile_t<E, false, false>(X, Wp, P, M, N, K, ldp, part_stride, max_split, res, nullptr, st)));
+  }
   if (gemm_wide_preferred(M, N, K, max_split, false))
     return launch_gemm_wide(dtype, X, Wp, P, M, N, K, ldp, part_stride, max_split, res, st);
-  MDZ_WITH_ELEM16(dtype, return (launch_gemm_tile_t<E, false>(X, Wp, P, M, N, K, ldp, part_stride, max_split, res, nullptr, st)));
+  MDZ_WITH_ELEM16(dtype, return (launch_gemm_tile_t<E, false, true>(X, Wp, P, M, N, K, ldp, part_stride, max_split, res, nullptr, st)));
 }
 
 // gate/up GEMM with the SwiGLU in its epilogue: U [M][N / 2] of the storage type
 bool gemm_tile_swiglu_supported(int dtype, int M, int N, int K) { return gemm_tile_supported(dtype, M, N, K) && N % 64 == 0; }
 
 int launch_gemm_tile_swiglu(int dtype, const void* X, const void* Wp, void* U, int M, int N, int K, hipStream_t st) {
+  if (!starts_on_16(X, Wp))
+    MDZ_WITH_ELEM16(dtype, return (launch_gemm_tile_t<E, true, false>(X, Wp, nullptr, M, N, K, N, 0, 1, nullptr, U, st)));
   if (gemm_wide_preferred(M, N, K, 1, true)) return launch_gemm_wide_swiglu(dtype, X, Wp, U, M, N, K, st);
-  MDZ_WITH_ELEM16(dtype, return (launch_gemm_tile_t<E, true>(X, Wp, nullptr, M, N, K, N, 0, 1, nullptr, U, st)));
+  MDZ_WITH_ELEM16(dtype, return (launch_gemm_tile_t<E, true, true>(X, Wp, nullptr, M, N, K, N, 0, 1, nullptr, U, st)));
 }
 
 }  // namespace mdz
