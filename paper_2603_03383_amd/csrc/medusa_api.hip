@@ -119,17 +119,17 @@ int launch_tree_attention(int dtype, int tree, const void* q, const KvGeom& g, c
   return launch_attention_generic(dtype, tree, q, g, kc, vc, layer, seq_len, B, max_prefix, att_out, st);
 }
 
-// QKV partial sums -> RoPE -> cache rows -> attention.  One fused kernel where the MFMA attention applies (the
+// QKV partial sums -> RoPE -> cache rows -> attention.  One fused kernel where the MFMA or the single-query attention applies (the
 // partial sums must then come in 128-column bands so that a head's columns share one slot count).
 int launch_rope_attention(int dtype, int tree, const Partials& qkv, const float* cs, void* q_scratch, const KvGeom& g,
                           void* kc, void* vc, int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out,
                           void* scratch, int64_t scratch_bytes, hipStream_t st) {
-  const bool unfused = g_force_unfused_rope.load(std::memory_order_relaxed) != 0;
-  if (!unfused && attn_mfma_supported(dtype, tree, g) && qkv.stride % 4 == 0 && qkv.ld % 4 == 0 &&
-      (qkv.split_grid == 0 || qkv.band_cols % 128 == 0))
+  const bool fused = g_force_unfused_rope.load(std::memory_order_relaxed) == 0 && qkv.stride % 4 == 0 && qkv.ld % 4 == 0 &&
+                     (qkv.split_grid == 0 || qkv.band_cols % 128 == 0);
+  if (fused && attn_mfma_supported(dtype, tree, g))
     return launch_attention_mfma(dtype, tree, nullptr, &qkv, cs, g, kc, vc, layer, seq_len, B, max_prefix, att_out, scratch,
                                  scratch_bytes, st);
-  if (!unfused && attn_decode_supported(dtype, tree, g))
+  if (fused && attn_decode_supported(dtype, tree, g))
     return launch_attention_decode(dtype, nullptr, &qkv, cs, g, kc, vc, layer, seq_len, B, max_prefix, att_out, scratch,
                                    scratch_bytes, st);
   int rc = launch_rope_kvwrite(dtype, tree, qkv, cs, q_scratch, g, kc, vc, layer, seq_len, B, max_prefix, st);

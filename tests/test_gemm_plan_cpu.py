@@ -72,3 +72,15 @@ def test_plan_rejects_shapes_the_streaming_kernel_does_not_take():
         P.medusa_gemm_plan(P.MDZ_FP32, 64, 4096, 4096, 8)
     with pytest.raises(P.MedusaError):
         P.medusa_gemm_slot_count(P.MDZ_BF16, 64, 4096, 4096, 8, 4096)
+
+
+@pytest.mark.parametrize("M", [1, 15, 24, 60, 64])
+@pytest.mark.parametrize("heads", [(1, 1), (2, 1), (3, 3), (8, 2), (16, 16), (32, 8), (32, 32), (40, 40), (48, 1)])
+def test_qkv_plans_keep_a_heads_columns_in_one_band(M, heads):
+    """The fused attention kernels read a head's 128 columns with one slot count (and take another path where that does not hold)."""
+    n_heads, kv_heads = heads
+    N, K = 128 * (n_heads + 2 * kv_heads), 128 * n_heads
+    plan = P.medusa_gemm_plan(P.MDZ_BF16, M, N, K, 12)
+    assert plan["band_cols"] % 128 == 0 or plan["max_slots"] == 1
+    for col in range(0, N, 128):
+        assert len({P.medusa_gemm_slot_count(P.MDZ_BF16, M, N, K, 12, c) for c in (col, col + 63, col + 64, col + 127)}) == 1
