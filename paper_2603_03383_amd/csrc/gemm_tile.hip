@@ -73,14 +73,15 @@ __global__ void __launch_bounds__(512, 2)
 
   const uint32_t lds0 = MDZ_LDS_ADDR(lds_raw);
   // Load cursor.  A load is two instructions and a wait state: addresses are a scalar base of X and of W, advanced by additions from round to
-  // round, and per-lane offsets that do not change.  Rows beyond M re-read row M-1 and tiles beyond n_tiles the block's first
-  // tile; neither is stored.  Past the range the cursor stays on its last round, which is not multiplied again, so the
+  // round, and per-lane offsets (from the block's first row) that do not change.  Rows beyond M re-read row M-1 and tiles beyond
+  // n_tiles the block's first tile; neither is stored.  Past the range the cursor stays on its last round, which is not multiplied again, so the
   // wait counts below are the same in every trip.
   const int n = r_hi - r_lo;
+  const int row0 = bm * XT * 32;
   uint32_t xoff[LX], woff[LW];
 #pragma unroll
   for (int q = 0; q < LX; ++q) {
-    const int row = min(bm * XT * 32 + (q * 8 + wave) * 8 + (lane >> 3), M - 1);
+    const int row = min((q * 8 + wave) * 8 + (lane >> 3), M - 1 - row0);
     xoff[q] = (uint32_t)row * (uint32_t)K * 2 + ((lane & 7) ^ (lane >> 3)) * 16;
   }
 #pragma unroll
@@ -89,7 +90,7 @@ __global__ void __launch_bounds__(512, 2)
     woff[q] = lane * 16 + (bn * WT + t < n_tiles ? t * 16384 : 0);
   }
   // packed order [band of 4 tiles][stage of 256 features][tile in band][16 k-steps][lane]
-  const uint8_t* xp = reinterpret_cast<const uint8_t*>(X) + (int64_t)r_lo * (kRound * 2);
+  const uint8_t* xp = reinterpret_cast<const uint8_t*>(X) + ((int64_t)row0 * K + (int64_t)r_lo * kRound) * 2;
   const uint8_t* wp = reinterpret_cast<const uint8_t*>(Wp) + ((int64_t)(bn * WT >> 2) * nst256 + (r_lo >> 2)) * 65536 +
                       ((bn * WT) & 3) * 16384 + (r_lo & 3) * 4096 + (wave & 3) * 1024;
   int next_r = r_lo;
@@ -271,7 +272,8 @@ TilePlan plan_tile(int M, int N, int K, int max_split, bool swiglu) {
 }  // namespace
 
 bool gemm_tile_supported(int dtype, int M, int N, int K) {
-  return is_16bit(dtype) && M > 64 && N % 32 == 0 && K % kRound == 0 && K >= kRound && (int64_t)M * K < (int64_t)1 << 31;
+  // (K: the byte offset of a row of a 256-row block is kept in 32 bits)
+  return is_16bit(dtype) && M > 64 && N % 32 == 0 && K % kRound == 0 && K >= kRound && K <= 1 << 22;
 }
 
 double gemm_tile_cost(int M, int N, int K, int max_split, bool swiglu, int* slots) {

@@ -77,10 +77,11 @@ __global__ void __launch_bounds__(256, 1)
   // Load cursors.  A load is two instructions (m0, load) and a wait state: addresses are a scalar base per round or half round, advanced by
   // additions, and per-lane offsets that do not change.  A cursor stays on the range's last piece when it gets there.
   const int64_t bs = (int64_t)nst256 * 65536;  // bytes of a band of 128 columns
+  X += (int64_t)bm * BM * K;  // the block's first row: offsets are relative to it
   uint32_t xoff[LX], woff[LW];
 #pragma unroll
   for (int q = 0; q < LX; ++q) {
-    const int row = min(bm * BM + (q * 4 + wave) * 8 + (lane >> 3), M - 1);
+    const int row = min((q * 4 + wave) * 8 + (lane >> 3), M - 1 - bm * BM);
     xoff[q] = (uint32_t)row * (uint32_t)K * 2 + ((lane & 7) ^ (lane >> 3)) * 16;
   }
   int xr = u_lo % n_rounds, x_left = u_hi - u_lo - 1;
