@@ -7,8 +7,9 @@
 // layer for 24 sequences of 90 .. 3000 keys with 8 key/value and 32 query heads, 37 us now).  A wave walks 32-key blocks of
 // the tiled cache (common.h) with contiguous 16-byte-per-lane loads that are MFMA A operands as they are; scores are
 // computed transposed (keys x queries), so the probabilities of 16 keys of one query sit in a lane and feed the second
-// MFMA from registers, as in the tree kernel, but as the 16-bit terms of their fp32 values (WeightTerms).  Columns beyond the group's heads are zero and never stored: the
-// matrix cores idle otherwise, the kernel is bound by the K / V stream and, at short prefixes, by its fixed chain.
+// MFMA from registers, as in the tree kernel, but as the 16-bit terms of their fp32 values (WeightTerms).  Columns beyond the
+// group's heads are zero and never stored: the matrix cores idle otherwise, the kernel is bound by the K / V stream and, at short
+// prefixes, by its fixed chain (many sequences of ungrouped heads: attn_decode_one_kernel below).
 // The kernel starts from the QKV GEMM's partial sums: every workgroup reduces and rotates the queries of its group; the
 // split that owns the block of slot S also produces the node's K and V rows, writes them to the cache and puts them into
 // the block from LDS, so that no load waits for a store (a launch of its own took 4.9 us per layer).  Waves merge
@@ -72,6 +73,112 @@ __device__ inline void rotate(const float4& t, float2& a, float2& p) {  // t: co
   const float2 ra = {a.x * t.x - p.x * t.y, a.y * t.z - p.y * t.w};
   p = float2{p.x * t.x + a.x * t.y, p.y * t.z + a.y * t.w};
   a = ra;
+}
+
+// Threads 192 .. 255 of the workgroup: the node's K row (192 .. 223) and V row from their QKV sums, two rotary pairs per thread
+// (features f, f + 1 and f + 64, f + 65), to the cache and to kv_lds (K row, then kQRow bytes on the V row: 128 elements; 8-bit
+// rows: 128 codes, scale).
+template <typename E, bool Q8>
+__device__ inline void write_own_row(const Partials& qkv, const PairSums& kvs, const float4& rot, uint8_t* kv_lds, const KvGeom& g,
+                                     E* kc, E* vc, int layer, int b, int hk, int S) {
+  const int tid = threadIdx.x, f = (tid & 31) * 2;
+  const bool is_k = tid < 224;
+  uint8_t* stage = kv_lds + (is_k ? 0 : kQRow);
+  float2 a, p;
+  kvs.sum(qkv, a, p);
+  if (is_k) rotate(rot, a, p);
+  if constexpr (Q8) {
+    float am = fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(p.x), fabsf(p.y)));
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) am = fmaxf(am, __shfl_xor(am, o, 64));  // over the 32 threads of the row
+    const float sc = kv8_scale_of(am);
+    const uint32_t w = kv8_pack4(a.x, a.y, p.x, p.y, sc);
+    *reinterpret_cast<uint16_t*>(stage + f) = (uint16_t)w;
+    *reinterpret_cast<uint16_t*>(stage + 64 + f) = (uint16_t)(w >> 16);
+    uint8_t* dst = reinterpret_cast<uint8_t*>(is_k ? kc : vc) + kv8_head_base(g, layer, b, hk);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = f + (e & 1) + (e >> 1) * 64;
+      dst[is_k ? kv8_k_code(S, i) : kv8_v_code(S, i)] = (uint8_t)(w >> (8 * e));
+    }
+    if ((tid & 31) == 0) {
+      *reinterpret_cast<float*>(dst + kv8_scale(S)) = sc;
+      *reinterpret_cast<float*>(stage + 128) = sc;
+    }
+  } else {
+    const uint32_t lo = Elem16<E>::pack2(a.x, a.y), hi = Elem16<E>::pack2(p.x, p.y);
+    *reinterpret_cast<uint32_t*>(stage + 2 * f) = lo;
+    *reinterpret_cast<uint32_t*>(stage + 128 + 2 * f) = hi;
+    if (is_k) {  // adjacent features of one key are adjacent in the tiled K layout
+      *reinterpret_cast<uint32_t*>(kc + k_index(g, layer, b, hk, S, f)) = lo;
+      *reinterpret_cast<uint32_t*>(kc + k_index(g, layer, b, hk, S, f + 64)) = hi;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        vc[v_index(g, layer, b, hk, S, f + e)] = E{(uint16_t)(lo >> (16 * e))};
+        vc[v_index(g, layer, b, hk, S, f + 64 + e)] = E{(uint16_t)(hi >> (16 * e))};
+      }
+    }
+  }
+}
+
+// Puts the node's own row, staged in LDS, into the units of the block that holds slot S (its cache copy may not have arrived
+// yet).  Lane (key, gh) of a K unit, lane (feature % 32 = key, gh) of a V unit; own = S % 32.
+template <bool Q8, int N>
+__device__ inline void put_own_row(const uint8_t* kv_lds, int key, int gh, int own, u32x4 (&kd)[N], u32x4 (&vd)[N]) {
+  const bool mine = ((own >> 2) & 1) == gh;  // V units: the half-wave that holds key `own`
+  if constexpr (Q8) {
+    if (key == own) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint2 lo = *reinterpret_cast<const uint2*>(kv_lds + 32 * j + 8 * gh);
+        const uint2 hi = *reinterpret_cast<const uint2*>(kv_lds + 32 * j + 16 + 8 * gh);
+        kd[j] = u32x4{lo.x, lo.y, hi.x, hi.y};
+      }
+    }
+    const int byte = 8 * (own >> 4) + 4 * ((own >> 3) & 1) + (own & 3);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const uint32_t code = kv_lds[kQRow + 32 * t + key];
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+        if (mine && w == byte >> 2) vd[t][w] = (vd[t][w] & ~(0xFFu << (8 * (byte & 3)))) | code << (8 * (byte & 3));
+    }
+  } else {
+    if (key == own) {
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) kd[ks] = *reinterpret_cast<const u32x4*>(kv_lds + 32 * ks + 16 * gh);
+    }
+    const int e = 4 * ((own >> 3) & 1) + (own & 3), sh = 16 * (e & 1);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const uint32_t v = *reinterpret_cast<const uint16_t*>(kv_lds + kQRow + 2 * (32 * t + key));
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+          if (mine && s2 == own >> 4 && w == e >> 1) vd[2 * t + s2][w] = (vd[2 * t + s2][w] & ~(0xFFFFu << sh)) | v << sh;
+    }
+  }
+}
+
+// 8 elements, or 8 E4M3 codes (words 2 * half, 2 * half + 1 of v), as floats
+template <typename E>
+__device__ inline void unpack8(u32x4 v, float (&f)[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) f[2 * i] = Elem16<E>::lo(v[i]), f[2 * i + 1] = Elem16<E>::hi(v[i]);
+  // Keeps the conversions as instructions of their own: for fp16 the compiler otherwise folds them into mixed-precision FMAs
+  // (v_fma_mix_f32), which run at a third of the speed here.
+#pragma unroll
+  for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(f[i]));
+}
+__device__ inline void unpack8_fp8(u32x4 v, int half, float (&f)[8]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const uint32_t w = v[2 * half + i];
+    const auto a = __builtin_amdgcn_cvt_pk_f32_fp8(w, false), c = __builtin_amdgcn_cvt_pk_f32_fp8(w, true);
+    f[4 * i] = a[0], f[4 * i + 1] = a[1], f[4 * i + 2] = c[0], f[4 * i + 3] = c[1];
+  }
 }
 }  // namespace
 
@@ -164,92 +271,22 @@ __global__ void __launch_bounds__(256, 2)
       *reinterpret_cast<uint32_t*>(q_lds + row * kQRow + 2 * f) = lo;
       *reinterpret_cast<uint32_t*>(q_lds + row * kQRow + 128 + 2 * f) = hi;
     }
-    if (owner && tid >= 192) {  // the node's K and V rows: to LDS for the block below, and to the cache
-      const bool is_k = tid < 224;
-      uint8_t* stage = kv_lds + (is_k ? 0 : kQRow);
-      float2 a, p;
-      kvs.sum(qkv, a, p);
-      if (is_k) rotate(rot, a, p);
-      if constexpr (Q8) {
-        float am = fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(p.x), fabsf(p.y)));
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) am = fmaxf(am, __shfl_xor(am, o, 64));  // over the 32 threads of the row
-        const float sc = kv8_scale_of(am);
-        const uint32_t w = kv8_pack4(a.x, a.y, p.x, p.y, sc);
-        *reinterpret_cast<uint16_t*>(stage + f) = (uint16_t)w;
-        *reinterpret_cast<uint16_t*>(stage + 64 + f) = (uint16_t)(w >> 16);
-        uint8_t* dst = reinterpret_cast<uint8_t*>(is_k ? kc : vc) + kv8_head_base(g, layer, b, hk);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int i = f + (e & 1) + (e >> 1) * 64;
-          dst[is_k ? kv8_k_code(S, i) : kv8_v_code(S, i)] = (uint8_t)(w >> (8 * e));
-        }
-        if ((tid & 31) == 0) {
-          *reinterpret_cast<float*>(dst + kv8_scale(S)) = sc;
-          *reinterpret_cast<float*>(stage + 128) = sc;
-        }
-      } else {
-        const uint32_t lo = Elem16<E>::pack2(a.x, a.y), hi = Elem16<E>::pack2(p.x, p.y);
-        *reinterpret_cast<uint32_t*>(stage + 2 * f) = lo;
-        *reinterpret_cast<uint32_t*>(stage + 128 + 2 * f) = hi;
-        if (is_k) {  // adjacent features of one key are adjacent in the tiled K layout
-          *reinterpret_cast<uint32_t*>(kc + k_index(g, layer, b, hk, S, f)) = lo;
-          *reinterpret_cast<uint32_t*>(kc + k_index(g, layer, b, hk, S, f + 64)) = hi;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 2; ++e) {
-            vc[v_index(g, layer, b, hk, S, f + e)] = E{(uint16_t)(lo >> (16 * e))};
-            vc[v_index(g, layer, b, hk, S, f + 64 + e)] = E{(uint16_t)(hi >> (16 * e))};
-          }
-        }
-      }
-    }
+    if (owner && tid >= 192) write_own_row<E, Q8>(qkv, kvs, rot, kv_lds, g, kc, vc, layer, b, hk, S);
   }
   __syncthreads();
 
-  // Puts the node's own row, staged in LDS, into the block that holds slot S (its cache copy may not have arrived yet).
   const int own_blk = fused ? S >> 5 : -1, own = S & 31;
   auto put_own = [&](u32x4 (&kd)[8], u32x4 (&vd)[8]) {
-    if constexpr (Q8) {
-      if (qi == own) {
+    put_own_row<Q8>(kv_lds, qi, gh, own, kd, vd);
+    if constexpr (Q8) {  // its scales: the half-wave that holds key `own`
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const uint2 lo = *reinterpret_cast<const uint2*>(kv_lds + 32 * j + 8 * gh);
-          const uint2 hi = *reinterpret_cast<const uint2*>(kv_lds + 32 * j + 16 + 8 * gh);
-          kd[j] = u32x4{lo.x, lo.y, hi.x, hi.y};
-        }
-      }
-      const bool mine = ((own >> 2) & 1) == gh;  // V units and scales: the half-wave that holds key `own`
-      const int byte = 8 * (own >> 4) + 4 * ((own >> 3) & 1) + (own & 3);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const uint32_t code = kv_lds[kQRow + 32 * t + qi];
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-          if (mine && w == byte >> 2) vd[t][w] = (vd[t][w] & ~(0xFFu << (8 * (byte & 3)))) | code << (8 * (byte & 3));
+      for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (mine && t == own >> 3 && e == (own & 3)) {
+          if (((own >> 2) & 1) == gh && t == own >> 3 && e == (own & 3)) {
             kd[4 + t][e] = *reinterpret_cast<const uint32_t*>(kv_lds + 128);
             vd[4 + t][e] = *reinterpret_cast<const uint32_t*>(kv_lds + kQRow + 128);
           }
-      }
-    } else {
-      if (qi == own) {
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) kd[ks] = *reinterpret_cast<const u32x4*>(kv_lds + 32 * ks + 16 * gh);
-      }
-      const bool mine = ((own >> 2) & 1) == gh;
-      const int e = 4 * ((own >> 3) & 1) + (own & 3), sh = 16 * (e & 1);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const uint32_t v = *reinterpret_cast<const uint16_t*>(kv_lds + kQRow + 2 * (32 * t + qi));
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-          for (int w = 0; w < 4; ++w)
-            if (mine && s2 == own >> 4 && w == e >> 1) vd[2 * t + s2][w] = (vd[2 * t + s2][w] & ~(0xFFFFu << sh)) | v << sh;
-      }
     }
   };
 
@@ -378,6 +415,173 @@ __global__ void __launch_bounds__(256, 2)
   }
 }
 
+// The same for ungrouped heads where more workgroups are asked for than the kernel above keeps resident (two per CU): one query
+// leaves 31 of the MFMA's 32 columns and most of that kernel's registers idle, and with many short sequences its time is the chain of
+// each workgroup, of which a CU then works on two.  Here the products are fp32 FMAs: lane (key, gh) of a K unit has half the
+// features of key `key`, lane (feature % 32, gh) of a V unit 16 of the 32 keys; four workgroups share a CU, and the next block's K
+// (V) is requested as soon as this block's registers are free.
+template <typename E, bool Q8>
+__global__ void __launch_bounds__(256, 4)
+    attn_decode_one_kernel(const E* __restrict__ q, const Partials qkv, const float* __restrict__ cs, KvGeom g, E* __restrict__ kc,
+                           E* __restrict__ vc, int layer, const int32_t* __restrict__ seq_len, int max_prefix,
+                           E* __restrict__ att_out, float* __restrict__ part_o, float* __restrict__ part_ml, bool ordered) {
+  __shared__ __attribute__((aligned(16))) float q_lds[kHD];
+  __shared__ __attribute__((aligned(16))) uint8_t kv_lds[2 * kQRow];
+  __shared__ __attribute__((aligned(16))) float p_lds[4][32];
+  __shared__ float o_lds[4][kHD], m_lds[4], l_lds[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int key = lane & 31, gh = lane >> 5;
+  const int split = blockIdx.x, n_splits = gridDim.x, h = blockIdx.y;
+  const int b = ordered ? sequence_in_order(seq_len, gridDim.z, blockIdx.z) : blockIdx.z;
+  const int d = g.n_heads * kHD;
+  const int S = min(max(seq_len[b], 0), max_prefix);
+  const int nb = (S + 1 + 31) >> 5;
+  const int blk_begin = (int)((int64_t)split * nb / n_splits), blk_end = (int)((int64_t)(split + 1) * nb / n_splits);
+
+  constexpr int kUnits = Q8 ? 4 : 8, kBlkPieces = Q8 ? kKv8BlockBytes / 16 : 512;
+  const uint8_t* kbase = reinterpret_cast<const uint8_t*>(kc) + (Q8 ? kv8_head_base(g, layer, b, h) : kv_head_base(g, layer, b, h) * 2);
+  const uint8_t* vbase = reinterpret_cast<const uint8_t*>(vc) + (Q8 ? kv8_head_base(g, layer, b, h) : kv_head_base(g, layer, b, h) * 2);
+  const u32x4* kp = reinterpret_cast<const u32x4*>(kbase) + lane;
+  const u32x4* vp = reinterpret_cast<const u32x4*>(vbase) + lane;
+  u32x4 kd[kUnits], vd[kUnits];
+  float k_scale = 1.f, v_scale = 1.f;  // 8-bit rows: of key `key`
+  auto load_k = [&](int blk) {
+#pragma unroll
+    for (int i = 0; i < kUnits; ++i) kd[i] = kp[(int64_t)blk * kBlkPieces + i * 64];
+    if constexpr (Q8) k_scale = *reinterpret_cast<const float*>(kbase + (int64_t)blk * kKv8BlockBytes + 4096 + key * 4);
+  };
+  auto load_v = [&](int blk) {
+#pragma unroll
+    for (int i = 0; i < kUnits; ++i) vd[i] = vp[(int64_t)blk * kBlkPieces + i * 64];
+    if constexpr (Q8) v_scale = *reinterpret_cast<const float*>(vbase + (int64_t)blk * kKv8BlockBytes + 4096 + key * 4);
+  };
+
+  // (order of requests and hand-over of the node's own row: as above)
+  const bool fused = qkv.p != nullptr, owner = blk_begin < blk_end && blk_end == nb;
+  const int f = (tid & 31) * 2;
+  PairSums sums;
+  float4 rot = {};
+  if (fused && (tid < 32 || (owner && tid >= 192))) {
+    rot = *reinterpret_cast<const float4*>(cs + (int64_t)b * kHD + 2 * f);
+    sums.load(qkv, b, (tid < 32 ? 0 : tid < 224 ? d : 2 * d) + h * kHD + f);
+  }
+  const int n_mine = blk_begin + wave < blk_end ? (blk_end - blk_begin - wave + 3) >> 2 : 0;
+  const int first = blk_begin + wave, last = first + 4 * (n_mine - 1);
+  __builtin_amdgcn_sched_barrier(0);
+  if (n_mine > 0) load_k(first), load_v(first);
+  __builtin_amdgcn_sched_barrier(0);
+  if (!fused) {
+    if (tid < kHD) q_lds[tid] = to_float(q[(int64_t)b * d + h * kHD + tid]);
+  } else if (tid < 32) {  // the query as the storage type holds it
+    float2 a, p;
+    sums.sum(qkv, a, p);
+    rotate(rot, a, p);
+    const uint32_t lo = Elem16<E>::pack2(a.x, a.y), hi = Elem16<E>::pack2(p.x, p.y);
+    q_lds[f] = Elem16<E>::lo(lo), q_lds[f + 1] = Elem16<E>::hi(lo);
+    q_lds[f + 64] = Elem16<E>::lo(hi), q_lds[f + 65] = Elem16<E>::hi(hi);
+  } else if (owner && tid >= 192) {
+    write_own_row<E, Q8>(qkv, sums, rot, kv_lds, g, kc, vc, layer, b, h, S);
+  }
+  __syncthreads();
+
+  const float scale_log2 = 1.4426950408889634f / sqrtf((float)kHD);
+  float m_run = -INFINITY, l_run = 0.f;  // l_run: of this lane's keys
+  float o[4] = {0.f, 0.f, 0.f, 0.f};     // feature 32 t + key, over the keys this half-wave holds
+  auto process = [&](int blk, auto is_last) {  // is_last: the wave's last block, the only one that can hold slot S and slots beyond it
+    if constexpr (decltype(is_last)::value) {
+      if (fused && blk == S >> 5) {
+        put_own_row<Q8>(kv_lds, key, gh, S & 31, kd, vd);
+        if constexpr (Q8) {
+          if (key == (S & 31)) {
+            k_scale = *reinterpret_cast<const float*>(kv_lds + 128);
+            v_scale = *reinterpret_cast<const float*>(kv_lds + kQRow + 128);
+          }
+        }
+      }
+    }
+    asm volatile("" ::: "memory");  // keeps the query in LDS, out of 64 registers
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {  // features 16 ks + 8 gh .. +7
+      float k8[8];
+      if constexpr (Q8) unpack8_fp8(kd[ks >> 1], ks & 1, k8);
+      else unpack8<E>(kd[ks], k8);
+      const float4 qa = *reinterpret_cast<const float4*>(q_lds + 16 * ks + 8 * gh);
+      const float4 qb = *reinterpret_cast<const float4*>(q_lds + 16 * ks + 8 * gh + 4);
+      part[0] += qa.x * k8[0], part[1] += qa.y * k8[1], part[2] += qa.z * k8[2], part[3] += qa.w * k8[3];
+      part[0] += qb.x * k8[4], part[1] += qb.y * k8[5], part[2] += qb.z * k8[6], part[3] += qb.w * k8[7];
+    }
+    float s = (part[0] + part[1]) + (part[2] + part[3]);
+    s = (s + __shfl_xor(s, 32, 64)) * (Q8 ? k_scale * scale_log2 : scale_log2);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!decltype(is_last)::value) load_k(blk + 4);
+    else s = blk * 32 + key <= S ? s : -INFINITY;
+    __builtin_amdgcn_sched_barrier(0);
+    float bmax = s;
+#pragma unroll
+    for (int x = 16; x > 0; x >>= 1) bmax = fmaxf(bmax, __shfl_xor(bmax, x, 64));
+    const float m_new = fmaxf(m_run, bmax);  // finite: a block in range holds at least one visible slot
+    const float alpha = exp2_fast(m_run - m_new), p = exp2_fast(s - m_new);
+    l_run = l_run * alpha + p;
+    m_run = m_new;
+    p_lds[wave][key] = Q8 ? p * v_scale : p;  // (a slot that no row was ever written to may hold any finite scale; its p is zero)
+    __builtin_amdgcn_wave_barrier();
+    float4 pk[4];  // keys 8 c + 4 gh .. +3
+#pragma unroll
+    for (int c = 0; c < 4; ++c) pk[c] = *reinterpret_cast<const float4*>(&p_lds[wave][8 * c + 4 * gh]);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      float a = o[t] * alpha;
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) {
+        float v8[8];
+        if constexpr (Q8) unpack8_fp8(vd[t], s2, v8);
+        else unpack8<E>(vd[2 * t + s2], v8);
+        const float4 pa = pk[2 * s2], pb = pk[2 * s2 + 1];
+        a += pa.x * v8[0], a += pa.y * v8[1], a += pa.z * v8[2], a += pa.w * v8[3];
+        a += pb.x * v8[4], a += pb.y * v8[5], a += pb.z * v8[6], a += pb.w * v8[7];
+      }
+      o[t] = a;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!decltype(is_last)::value) load_v(blk + 4);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (n_mine > 0) {
+    for (int blk = first; blk < last; blk += 4) process(blk, std::false_type{});
+    process(last, std::true_type{});
+  }
+
+  // ---- merge the four waves (fixed order), then store or hand the partial result to the combine kernel
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    o[t] += __shfl_xor(o[t], 32, 64);
+    if (gh == 0) o_lds[wave][32 * t + key] = o[t];
+  }
+#pragma unroll
+  for (int x = 16; x > 0; x >>= 1) l_run += __shfl_xor(l_run, x, 64);
+  if (lane == 0) m_lds[wave] = m_run, l_lds[wave] = l_run;
+  __syncthreads();
+  if (tid >= kHD) return;
+  float M = -INFINITY, L = 0.f, a = 0.f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) M = fmaxf(M, m_lds[w]);
+  const float M_safe = M == -INFINITY ? 0.f : M;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float wt = exp2_fast(m_lds[w] - M_safe);
+    L += wt * l_lds[w], a += wt * o_lds[w][tid];
+  }
+  if (n_splits == 1) {
+    att_out[(int64_t)b * d + h * kHD + tid] = from_float<E>(a / L);
+  } else {
+    const int64_t pidx = (int64_t)(b * g.n_heads + h) * n_splits + split;
+    part_o[pidx * kHD + tid] = a;
+    if (tid == 0) part_ml[pidx * 2] = M, part_ml[pidx * 2 + 1] = L;
+  }
+}
+
 // One workgroup per (query head, sequence), one thread per feature; the splits' loads are requested eight at a time.
 template <typename E>
 __global__ void __launch_bounds__(128)
@@ -447,8 +651,15 @@ static int launch_attention_decode_t(const void* q, const Partials* qkv, const f
   MDZ_SET_LDS_ONCE((attn_decode_kernel<E, Q8>), 4 * 32 * (kORow + 2) * 4);
   const Partials none = single_slot(nullptr, 0, 0);
   const bool ordered = B > 1 && splits * g.n_heads * chunks * B > 2 * num_cus();  // more workgroups than fit at once: long ones first
-  launch_timed(PROF_ATTN, attn_decode_kernel<E, Q8>, dim3(splits, g.n_heads * chunks, B), 256, lds_bytes, st, (const E*)q,
-               qkv ? *qkv : none, cs, g, (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, ordered);
+  // Ungrouped heads and more workgroups than the matrix-core kernel keeps resident: FMAs.  (Per layer with small GEMMs, matrix cores /
+  // FMAs: 64 sequences x 32 heads of S / 4 .. S keys, S = 16 94.2 / 77.9 us, 100 100.3 / 83.0, 500 149.0 / 140.4, 2000 309.8 / 308.3;
+  // 8-bit rows 95.3 / 76.8, 98.4 / 79.0, 124.3 / 105.1, 203.7 / 199.2; 32 at 4000 291.3 / 293.3, 8-bit 185.4 / 183.0.)
+  if (g.group == 1 && (int64_t)splits * g.n_heads * B > 2 * num_cus())
+    launch_timed(PROF_ATTN, attn_decode_one_kernel<E, Q8>, dim3(splits, g.n_heads, B), 256, 0, st, (const E*)q, qkv ? *qkv : none, cs,
+                 g, (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, ordered);
+  else
+    launch_timed(PROF_ATTN, attn_decode_kernel<E, Q8>, dim3(splits, g.n_heads * chunks, B), 256, lds_bytes, st, (const E*)q,
+                 qkv ? *qkv : none, cs, g, (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, ordered);
   MDZ_LAUNCH_CHECK();
   if (splits > 1) {
     launch_timed(PROF_ATTN, attn_decode_combine_kernel<E>, dim3(nq, B), 128, 0, st, nq, splits, part_o, part_ml, (E*)att_out);
