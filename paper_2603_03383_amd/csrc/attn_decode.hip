@@ -650,7 +650,10 @@ static int launch_attention_decode_t(const void* q, const Partials* qkv, const f
   const int lds_bytes = merge_bytes > q_bytes ? merge_bytes : q_bytes;
   MDZ_SET_LDS_ONCE((attn_decode_kernel<E, Q8>), 4 * 32 * (kORow + 2) * 4);
   const Partials none = single_slot(nullptr, 0, 0);
-  const bool ordered = B > 1 && splits * g.n_heads * chunks * B > 2 * num_cus();  // more workgroups than fit at once: long ones first
+  // More workgroups than fit at once: long sequences first, from 1536 keys on.  (Finding its place costs a workgroup 1 - 2 us: per layer,
+  // lengths S / 4 .. S, in order / not: 64 sequences x 32 heads at S = 100 83.1 / 77.9 us, 500 140.2 / 139.3, 1000 199.3 / 200.1, 2000
+  // 309.5 / 313.0; 49 at 2000 246.6 / 256.0; 49 x 8 key/value heads of 4 query heads at 500 77.6 / 73.1, 1000 84.7 / 80.1, 2000 110.9 / 111.2.)
+  const bool ordered = B > 1 && max_prefix >= 1536 && (int64_t)splits * g.n_heads * chunks * B > 2 * num_cus();
   // Ungrouped heads and more workgroups than the matrix-core kernel keeps resident: FMAs.  (Per layer with small GEMMs, matrix cores /
   // FMAs: 64 sequences x 32 heads of S / 4 .. S keys, S = 16 94.2 / 77.9 us, 100 100.3 / 83.0, 500 149.0 / 140.4, 2000 309.8 / 308.3;
   // 8-bit rows 95.3 / 76.8, 98.4 / 79.0, 124.3 / 105.1, 203.7 / 199.2; 32 at 4000 291.3 / 293.3, 8-bit 185.4 / 183.0.)

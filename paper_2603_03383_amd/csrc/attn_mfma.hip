@@ -634,9 +634,16 @@ static int launch_attention_mfma_t(int tree, const void* q, const Partials* qkv,
   float* part_ml = part_o + (int64_t)B * nq * splits * TQ * kHD;
   dim3 grid(splits, nq, B * (TQ > 32 * NU ? 2 : 1));  // two workgroups share a sequence: blockIdx.z = 2 * sequence + half
   const Partials none = single_slot(nullptr, 0, 0);
-  // More workgroups than a round of one per CU: long sequences first (per layer, 3 sequences of 200 .. 2500 keys: 46 -> 37 us, 16
-  // of 256 .. 4096: 155 -> 150; six whose workgroups fit at once lose 1 us of 30 to the sorting).
-  const bool ordered = B > 1 && (int64_t)grid.x * grid.y * grid.z > num_cus();
+  // Long sequences first, where the launch gains by it: finding its place costs a workgroup 1 - 2 us, and where all workgroups run at
+  // once the hardware's order pairs them better.  us per layer, lengths S / 4 .. S, in order / not, 64 nodes unless said otherwise:
+  //   one split, more workgroups than fit (32 heads): 32 sequences at S = 1000 135 / 124, 2000 194 / 188, 3000 255 / 256, 4000 315 / 328;
+  //     16 at 1000 64 / 62, 3000 131 / 134, 4000 168 / 174; 8-bit rows: 32 at 1000 119 / 117, 2000 157 / 162, 16 at 1000 57 / 59, 2000 75 / 84;
+  //     15 nodes, 32 at 250 35 / 33, 1000 81 / 85, 4000 257 / 268;
+  //   one split, all at once: 6 at 1000 31 / 27, 3000 64 / 58 (15 nodes gain: 12 at 1000 32 / 33, 3000 87 / 92);
+  //   several splits: 3 at 1000 24.5 / 23.6, 2000 26.9 / 28.9, 3000 34.5 / 38.0, 8-bit rows at 6000 38 / 44.
+  const int64_t wgs = (int64_t)grid.x * grid.y * grid.z;
+  const bool ordered = B > 1 && (splits > 1 ? wgs > num_cus() && max_prefix >= 1536
+                                            : wgs > (NU == 1 && TQ == 64 ? 2 : 1) * num_cus() && max_prefix >= (TQ == 64 && !Q8 ? 2560 : 1024));
   launch_timed(PROF_ATTN, attn_tree_mfma_kernel<E, Q8, NU, TQ>, grid, 256, lds_bytes, st, tree, (const E*)q, qkv ? *qkv : none, cs, g,
                (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, ordered);
   MDZ_LAUNCH_CHECK();
