@@ -51,6 +51,12 @@ int medusa_gemm_plan(int dtype, int M, int N, int K, int max_split, int32_t* gri
                      int32_t* max_slots);
 int medusa_gemm_slot_count(int dtype, int M, int N, int K, int max_split, int col);
 
+/* For X[M,K] x W[N,K]^T of more than 64 rows (16-bit, N % 32 == 0, K % 64 == 0), operands aligned: which of the two many-row
+ * kernels takes the product (`wide`: 0 = tiles of up to 256 x 128, 1 = tiles of 192 or 256 x 256), its tile, and into how many
+ * parts K is split.  swiglu: the gate/up product with its epilogue (max_split is then taken as 1). */
+int medusa_gemm_many_rows_plan(int dtype, int M, int N, int K, int max_split, int swiglu, int32_t* wide, int32_t* tile_rows,
+                               int32_t* tile_cols, int32_t* k_splits);
+
 /* ---- test hook --------------------------------------------------------------------------------------- */
 
 /* The layer runs RoPE + cache write either fused into the attention kernel's prologue (default) or as a kernel of

@@ -63,6 +63,7 @@ _SIGNATURES = {
     "medusa_tree_tables": (C.c_int, [C.c_int] + [C.c_void_p] * 5),
     "medusa_gemm_plan": (C.c_int, [C.c_int] * 5 + [C.c_void_p] * 4),
     "medusa_gemm_slot_count": (C.c_int, [C.c_int] * 6),
+    "medusa_gemm_many_rows_plan": (C.c_int, [C.c_int] * 6 + [C.c_void_p] * 4),
     "medusa_last_error": (C.c_char_p, []),
     "medusa_profile_begin": (C.c_int, [C.c_int]),
     "medusa_profile_end": (C.c_int, [C.c_char_p, C.c_int64]),
@@ -156,6 +157,12 @@ def medusa_gemm_slot_count(dtype: int, M: int, N: int, K: int, max_split: int, c
     n = lib().medusa_gemm_slot_count(dtype, M, N, K, max_split, col)
     _check(n)
     return n
+
+
+def medusa_gemm_many_rows_plan(dtype: int, M: int, N: int, K: int, max_split: int, swiglu: bool = False) -> dict:
+    vals = [C.c_int32() for _ in range(4)]
+    _check(lib().medusa_gemm_many_rows_plan(dtype, M, N, K, max_split, int(swiglu), *[C.byref(v) for v in vals]))
+    return dict(zip(("wide", "tile_rows", "tile_cols", "k_splits"), [v.value for v in vals]))
 
 
 def medusa_tree_tables(tree: int) -> dict:

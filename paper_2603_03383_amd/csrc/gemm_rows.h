@@ -44,6 +44,12 @@ double gemm_wide_cost(int M, int N, int K, int max_split, bool swiglu, int* slot
 inline bool gemm_wide_preferred(int M, int N, int K, int max_split, bool swiglu) {
   return gemm_wide_cost(M, N, K, max_split, swiglu, nullptr) < gemm_tile_cost(M, N, K, max_split, swiglu, nullptr);
 }
+struct ManyRowsPlan {
+  bool wide;
+  int tile_rows, tile_cols, k_splits;
+};
+ManyRowsPlan gemm_tile_plan(int M, int N, int K, int max_split, bool swiglu);
+ManyRowsPlan gemm_wide_plan(int M, int N, int K, int max_split, bool swiglu);
 bool gemm_tile_supported(int dtype, int M, int N, int K);
 int launch_gemm_wide(int dtype, const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp, int64_t part_stride,
                      int max_split, Partials* res, hipStream_t st);

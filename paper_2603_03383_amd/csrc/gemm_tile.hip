@@ -282,6 +282,11 @@ double gemm_tile_cost(int M, int N, int K, int max_split, bool swiglu, int* slot
   return p.us;
 }
 
+ManyRowsPlan gemm_tile_plan(int M, int N, int K, int max_split, bool swiglu) {
+  const TilePlan p = plan_tile(M, N, K, max_split, swiglu);
+  return ManyRowsPlan{false, p.bm, p.bn, p.ksplit};
+}
+
 // partial-sum slots launch_gemm_tile will write for this problem (sizes the slot workspace)
 int gemm_tile_slots(int M, int N, int K, int max_split) {
   int slots = 1;

@@ -322,6 +322,11 @@ double gemm_wide_cost(int M, int N, int K, int max_split, bool swiglu, int* slot
   return p.us;
 }
 
+ManyRowsPlan gemm_wide_plan(int M, int N, int K, int max_split, bool swiglu) {
+  const WidePlan p = plan_wide(M, N, K, max_split, swiglu);
+  return ManyRowsPlan{true, 64 * p.mt, 256, p.ksplit};
+}
+
 template <typename E, bool SWIGLU, bool ARGMAX = false>
 static int launch_gemm_wide_t(const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp, int64_t part_stride,
                               int max_split, Partials* res, void* U, hipStream_t st, ArgCand* cand = nullptr) {

@@ -5,7 +5,7 @@
 
 #include <atomic>
 
-#include "kernels.h"
+#include "gemm_rows.h"
 
 namespace mdz {
 
@@ -49,7 +49,6 @@ void gemm_mfma_describe(int M, int N, int K, int max_split, Partials* res, int* 
 int launch_gemm_mfma(int dtype, const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp,
                      int64_t part_stride, int max_split, Partials* res, hipStream_t st);
 
-bool gemm_tile_supported(int dtype, int M, int N, int K);
 int gemm_tile_slots(int M, int N, int K, int max_split);
 int launch_gemm_tile(int dtype, const void* X, const void* Wp, float* P, int M, int N, int K, int64_t ldp,
                      int64_t part_stride, int max_split, Partials* res, hipStream_t st);
@@ -394,6 +393,21 @@ int medusa_gemm_slot_count(int dtype, int M, int N, int K, int max_split, int co
   Partials pr = single_slot(nullptr, 0, 0);
   gemm_mfma_describe(M, N, K, max_split, &pr, nullptr);
   return pr.count(col);
+}
+
+int medusa_gemm_many_rows_plan(int dtype, int M, int N, int K, int max_split, int swiglu, int32_t* wide, int32_t* tile_rows,
+                               int32_t* tile_cols, int32_t* k_splits) {
+  MDZ_REQUIRE(swiglu ? gemm_tile_swiglu_supported(dtype, M, N, K) : gemm_tile_supported(dtype, M, N, K), MDZ_EUNSUPPORTED,
+              "gemm plan: [%d,%d] x [%d,%d] is not a many-row GEMM shape", M, K, N, K);
+  MDZ_REQUIRE(max_split >= 1, MDZ_EINVAL, "gemm plan: max_split %d", max_split);
+  if (swiglu) max_split = 1;
+  const ManyRowsPlan p = gemm_wide_preferred(M, N, K, max_split, swiglu != 0) ? gemm_wide_plan(M, N, K, max_split, swiglu != 0)
+                                                                              : gemm_tile_plan(M, N, K, max_split, swiglu != 0);
+  if (wide) *wide = p.wide;
+  if (tile_rows) *tile_rows = p.tile_rows;
+  if (tile_cols) *tile_cols = p.tile_cols;
+  if (k_splits) *k_splits = p.k_splits;
+  return MDZ_OK;
 }
 
 int64_t medusa_packed_bytes(int dtype, int64_t n_rows, int64_t k) {
