@@ -31,17 +31,9 @@ constexpr int kHD = 128;
 constexpr int kQRow = kHD * 2 + 16;  // bytes per staged query row
 constexpr int kORow = kHD + 4;       // floats per merged output row
 
-__device__ inline float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
-
-template <typename E>
-__device__ inline u32x4 fp8x8_to_elem16(u32x4 v, int half) {  // 8 E4M3 codes (words 2 * half, 2 * half + 1) -> 8 elements
-  const uint32_t w0 = half ? v.z : v.x, w1 = half ? v.w : v.y;
-  return u32x4{Elem16<E>::from_fp8x2(w0, false), Elem16<E>::from_fp8x2(w0, true), Elem16<E>::from_fp8x2(w1, false),
-               Elem16<E>::from_fp8x2(w1, true)};
-}
-
 // Two adjacent columns and their rotary partners (64 columns on) of one row of the QKV partial sums.  load() requests the
-// first kEarly slots, sum() adds the slots in order (and fetches what lies beyond kEarly, which one row never needs).
+// first kEarly slots, sum() adds the slots in order and fetches what lies beyond kEarly, behind the first K / V block.  (A 4096-wide
+// model's product has two slots; narrow ones have more, e.g. eight at 1024, and pay that second round trip.)
 struct PairSums {
   static constexpr int kEarly = 4;
   float2 a[kEarly], p[kEarly];
@@ -308,7 +300,7 @@ __global__ void __launch_bounds__(256, 2)
     for (int r = 0; r < 16; ++r) sc[r] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-      const u32x4 ka = Q8 ? fp8x8_to_elem16<E>(kd[ks >> 1], ks & 1) : kd[ks];
+      const u32x4 ka = Q8 ? fp8x8_to_elem<E>(kd[ks >> 1], ks & 1) : kd[ks];
       sc = Elem16<E>::mfma(ka, *reinterpret_cast<const u32x4*>(qfrag + ks * 32), sc);
     }
     // register r is key 8*(r/4) + 4*gh + r%4 of the block; its scale is component r%4 of scale piece r/4
@@ -323,10 +315,10 @@ __global__ void __launch_bounds__(256, 2)
     }
     bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));  // finite: a block in range holds at least one visible slot
     const float m_new = fmaxf(m_run, bmax);
-    const float alpha = exp2_fast(m_run - m_new);
+    const float alpha = fast_exp2(m_run - m_new);
     float sum = 0.f, p[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) p[r] = exp2_fast(sc[r] - m_new) * WeightTerms<VE>::kScale;
+    for (int r = 0; r < 16; ++r) p[r] = fast_exp2(sc[r] - m_new) * WeightTerms<VE>::kScale;
 #pragma unroll
     for (int r = 0; r < 16; r += 2) sum += p[r] + p[r + 1];
     if constexpr (Q8) {  // a slot that no row was ever written to may hold any finite scale; its probability is zero
@@ -349,7 +341,7 @@ __global__ void __launch_bounds__(256, 2)
       for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
-          const u32x4 va = Q8 ? fp8x8_to_elem16<VE>(vd[t], s2) : vd[t * 2 + s2];
+          const u32x4 va = Q8 ? fp8x8_to_elem<VE>(vd[t], s2) : vd[t * 2 + s2];
           o[t] = Elem16<VE>::mfma(va, pf[s2], o[t]);
         }
     }
@@ -398,7 +390,7 @@ __global__ void __launch_bounds__(256, 2)
     float4 a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float wt = exp2_fast(m_lds[w * nq + qq] - M_safe);
+      const float wt = fast_exp2(m_lds[w * nq + qq] - M_safe);
       const float4 v = *reinterpret_cast<const float4*>(o_lds + (w * nq + qq) * kORow + f);
       L += wt * l_lds[w * nq + qq];
       a.x += wt * v.x, a.y += wt * v.y, a.z += wt * v.z, a.w += wt * v.w;
@@ -521,7 +513,7 @@ __global__ void __launch_bounds__(256, 4)
 #pragma unroll
     for (int x = 16; x > 0; x >>= 1) bmax = fmaxf(bmax, __shfl_xor(bmax, x, 64));
     const float m_new = fmaxf(m_run, bmax);  // finite: a block in range holds at least one visible slot
-    const float alpha = exp2_fast(m_run - m_new), p = exp2_fast(s - m_new);
+    const float alpha = fast_exp2(m_run - m_new), p = fast_exp2(s - m_new);
     l_run = l_run * alpha + p;
     m_run = m_new;
     p_lds[wave][key] = Q8 ? p * v_scale : p;  // (a slot that no row was ever written to may hold any finite scale; its p is zero)
@@ -570,7 +562,7 @@ __global__ void __launch_bounds__(256, 4)
   const float M_safe = M == -INFINITY ? 0.f : M;
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    const float wt = exp2_fast(m_lds[w] - M_safe);
+    const float wt = fast_exp2(m_lds[w] - M_safe);
     L += wt * l_lds[w], a += wt * o_lds[w][tid];
   }
   if (n_splits == 1) {
@@ -601,13 +593,13 @@ __global__ void __launch_bounds__(128)
     float Mg = M;
 #pragma unroll
     for (int s = 0; s < kTogether; ++s) Mg = fmaxf(Mg, ms[s]);
-    const float r = M == -INFINITY ? 0.f : exp2_fast(M - Mg);
+    const float r = M == -INFINITY ? 0.f : fast_exp2(M - Mg);
     L *= r, acc *= r;
     M = Mg;
 #pragma unroll
     for (int s = 0; s < kTogether; ++s)
       if (s0 + s < n_splits) {
-        const float w = ms[s] == -INFINITY ? 0.f : exp2_fast(ms[s] - M);  // (an empty split, possibly before any other)
+        const float w = ms[s] == -INFINITY ? 0.f : fast_exp2(ms[s] - M);  // (an empty split, possibly before any other)
         L += w * ls[s];
         acc += w * v[s];
       }
@@ -619,8 +611,11 @@ bool attn_decode_supported(int dtype, int tree, const KvGeom& g) {
   return is_16bit(dtype) && g.tiled && g.head_dim == kHD && host_tree(tree)->T == 1;
 }
 
-// Key-splits: enough workgroups to give every CU two (they fit), but at least seven blocks each, i.e. two per wave (one
-// sequence of 1024 keys, 32 heads: 12.5 us with 5 splits, 13.7 with 2, 13.9 with 3, 15.1 with 9, merge included).
+// Key-splits: enough workgroups to give every CU two (they fit), but no more than one per seven blocks at max_prefix, i.e. up to
+// two blocks per wave (one sequence of 1024 keys, 32 heads: 12.5 us with 5 splits, 13.7 with 2, 13.9 with 3, 15.1 with 9, merge
+// included).  The number of sevens is rounded up: a split and the merge launch more just past a multiple cost less than a wave's
+// third block (whole layer, rounded up / down: one sequence at 150 keys 56.7 / 59.1 us, at 600 59.6 / 62.3; eight at 440 64.6 / 66.9,
+// though at 300 63.5 / 61.9).
 // Dealing equal parts of a ragged batch out by its device-side lengths was measured too: 24 sequences of 90 .. 3000 keys
 // gain 1 us of 37 (the HBM stream bounds them), a single sequence loses 1 us to finding its part.
 static int decode_splits(int B, int kv_heads, int max_prefix) {

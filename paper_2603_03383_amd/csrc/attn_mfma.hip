@@ -29,16 +29,6 @@ constexpr int kHD = 128;         // head_dim
 constexpr int kQRow = kHD * 2 + 16;  // bytes per staged Q row
 constexpr float kLazyLog2 = 8.f;  // see the key loop: how far a block's maximum may exceed the running reference
 
-__device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// 8 E4M3 codes (words 2*half, 2*half+1 of v) -> 8 elements
-template <typename E>
-__device__ inline u32x4 fp8x8_to_elem(u32x4 v, int half) {
-  const uint32_t w0 = half ? v.z : v.x, w1 = half ? v.w : v.y;
-  return u32x4{Elem16<E>::from_fp8x2(w0, false), Elem16<E>::from_fp8x2(w0, true), Elem16<E>::from_fp8x2(w1, false),
-               Elem16<E>::from_fp8x2(w1, true)};
-}
-
 template <typename E>
 __device__ inline u32x4 pack8(const float* v) {
   return u32x4{Elem16<E>::pack2(v[0], v[1]), Elem16<E>::pack2(v[2], v[3]), Elem16<E>::pack2(v[4], v[5]),

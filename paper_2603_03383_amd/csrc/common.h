@@ -160,6 +160,15 @@ struct Elem16<f16_t> {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
   }
 };
+__device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+// 8 E4M3 codes (words 2*half, 2*half+1 of v) -> 8 elements
+template <typename E>
+__device__ inline u32x4_t fp8x8_to_elem(u32x4_t v, int half) {
+  const uint32_t w0 = half ? v.z : v.x, w1 = half ? v.w : v.y;
+  return u32x4_t{Elem16<E>::from_fp8x2(w0, false), Elem16<E>::from_fp8x2(w0, true), Elem16<E>::from_fp8x2(w1, false),
+                 Elem16<E>::from_fp8x2(w1, true)};
+}
+
 // A softmax weight as a sum of 16-bit terms, so that an MFMA over 16-bit operands multiplies V by the fp32 weight: term i is the
 // rounded rest after terms 0 .. i - 1.  Three bf16 terms are the 24 bits of an fp32 number.  Two binary16 terms are 22, and the
 // weights (at most 1) come scaled by 2^15, which keeps the terms of everything above 2^-29 out of binary16's subnormals and the

@@ -12,7 +12,8 @@
 // What bounds it now: power.  The clock falls from 2.4 to ~1.65 GHz and the loop then runs at 75 % of the MFMA rate of that
 // clock; fewer busy CUs run faster, so a launch takes no more of them than its rounds need.  Measured, us per launch, gemm_tile / this one:
 // 1024 rows: 12288 x 4096: 117 / 100 (and one partial sum instead of two), 22016 x 4096 with SwiGLU: 187 / 178, 128000 x 4096:
-// 1082 / 957 (1.12 PFLOP/s); 512 rows: 65 / 58, 118 / 101, 602 / 539; 320 rows: 48 / 46, 95 / 84, 476 / 435.
+// 1082 / 957 (1.12 PFLOP/s); 512 rows: 65 / 58, 118 / 101, 602 / 539; 320 rows: 48 / 46, 95 / 84, 476 / 435.  (The choice between the
+// two is by modelled times, which are close at some of these: at 512 rows they put 12288 x 4096 on gemm_tile, 78.2 us against 79.1.)
 #include "gemm_rows.h"
 
 namespace mdz {

@@ -45,3 +45,13 @@ def test_eight_bit_rows(n_heads):
 @pytest.mark.parametrize("quant,v_std", [("", 1.0), ("fp8e4m3", 1.0), ("fp8e4m3", 1e-4)])
 def test_softmax_weights_are_fp32(dtype, quant, v_std):
     _check("tree1", dtype, 8, 8, [(37 * b) % 300 for b in range(60)] + [40, 0, 5, 100, 640], 640, quant=quant, v_std=v_std)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("n_heads,lengths", [(8, EDGES), (9, EDGES[:15] * 4)], ids=["8x17", "9x60"])  # 540 workgroups: the FMA kernel
+def test_more_partial_sums_than_are_requested_together(dtype, n_heads, lengths):
+    """Narrow models: the QKV product comes in eight and nine slots, the kernels request four before the first K / V block."""
+    d = 128 * n_heads
+    assert P.medusa_gemm_plan(P.DTYPES[dtype], len(lengths), 3 * d, d, 12)["max_slots"] >= 8
+    r = _layer_case(_w(dtype, n_heads, n_heads), lengths, 1000, x_seed="pairs_slots")
+    _check_layer(r, lengths, dtype)
