@@ -14,8 +14,8 @@
 //   * the operands of a k-step are read from LDS while the previous k-step multiplies (two register sets), so that after a
 //     barrier the matrix cores have work while all eight waves read LDS at once;
 //   * X is read row-major, 128 B (one cache line) of eight rows per instruction; the 16-byte chunks of a row are XOR-ed
-//     with the row number on the way in (through the per-lane source addresses), which makes the operand reads bank
-//     conflict free without padding.  W arrives in the packed order (common.h): 4 KiB per tile and round, contiguous;
+//     with the row number on the way in (through the per-lane source addresses), which spreads the operand reads over the
+//     banks without padding (2.6 conflict cycles are counted per 16-byte read).  W arrives in the packed order (common.h): 4 KiB per tile and round, contiguous;
 //   * the MFMA is issued as W x X^T: a lane then holds four consecutive output columns of ONE row per register quad, so
 //     sums leave as 16-byte (fp32) or 8-byte (SwiGLU output) stores.
 // What bounds it: below ~300 rows the loads (a CU keeps about 64 KiB in flight whatever the ring holds: rings of 3, 4 and 6
