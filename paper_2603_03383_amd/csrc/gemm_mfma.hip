@@ -7,6 +7,10 @@
 //     registers: three half stages (CK/2 input features each) stay in flight while it multiplies the
 //     fourth, and every load is unconditional so the hardware wait counters let the prefetch overlap
 //     the MFMAs (a CU then keeps ~100 KB in flight, what the HBM latency asks for).
+//   * W is loaded non-temporally: every weight is used once per pass, and a read stream that does not ask the caches to keep it
+//     runs faster on this card (1 GiB over 256 workgroups 6.1 / 6.8 TB/s, 100 MB launches 5.5 / 5.9).  us, plain / non-temporal
+//     loads: four Medusa heads from one row 763 / 700, a layer at 64 rows 125 / 118.5, a 32-layer step at 1K 4057 / 3977,
+//     of one row 3390 / 3267.
 //   * X (<= 64 x K bf16, L2 resident) is staged per K-stage through LDS, shared by the WPB waves of a
 //     workgroup, rows padded by 16 B so the 16 B-per-lane operand reads are bank-conflict free.
 //   * Work decomposition is flat and persistent: the (column band, K-stage) units are numbered band-major
@@ -136,7 +140,7 @@ __global__ void __launch_bounds__(WPB * 64)
       const int64_t unit = (((int64_t)(tile >> 2) * nst256 + st) * kBandTiles + (tile & 3)) * 16 + kin0;
       const u32x4* p = reinterpret_cast<const u32x4*>(Wp) + unit * 64 + lane;
 #pragma unroll
-      for (int ks = 0; ks < KH; ++ks) dst[nt][ks] = p[ks * 64];
+      for (int ks = 0; ks < KH; ++ks) dst[nt][ks] = __builtin_nontemporal_load(p + ks * 64);
     }
   };
   auto compute = [&](int buf, int hf, const u32x4 (&wv)[NT][KH]) {
