@@ -99,7 +99,12 @@ __device__ inline void rope16(const float* cs_row, int seg, float (&lo)[16], flo
 // never stored.  Six sequences of 40 .. 1500 keys x 32 heads take 30 us per layer; the portable kernel took 928 us
 // for them).  Its softmax weights enter the product with V as the 16-bit terms of their fp32 values (WeightTerms, common.h): the
 // portable kernel multiplies fp32 weights, and a tree is served with the same precision whichever of the two its shape takes.
-template <typename E, bool Q8, int NU, int TQ>
+// ONCE: no other workgroup reads this one's K and V blocks (it carries all queries of an ungrouped head), so they are loaded
+// non-temporally: the stream then runs faster (as the weights', gemm_mfma.hip).  us per layer, plain / non-temporal: one sequence at
+// 16K keys 65 / 59.6, 16 sequences of 256 .. 4096 keys 148 / 132,
+// a step of 12 of 300 .. 4000 on the 15-node tree, 4 layers 1201 / 1173.  Where two halves share the blocks through L2 it costs (3
+// sequences of 200 .. 2500 keys 31.2 / 34.9).
+template <typename E, bool Q8, int NU, int TQ, bool ONCE>
 __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
     attn_tree_mfma_kernel(int tree, const E* __restrict__ q, const Partials qkv, const float* __restrict__ cs,
                           KvGeom g, E* __restrict__ kc, E* __restrict__ vc, int layer,
@@ -162,13 +167,14 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
   // are in-order, so a wave then keeps a whole block (16 KiB of 16-bit rows) in flight while it works on the
   // previous one, which is what the HBM latency asks for at one wave per SIMD.
   u32x4 kb[2][8], vb[2][8];
+  auto unit = [](const u32x4* p) { return ONCE ? __builtin_nontemporal_load(p) : *p; };
   auto load_kv = [&](int blk, u32x4 (&kd)[8], u32x4 (&vd)[8]) {  // 8-bit rows: [0..3] codes, [4..7] the lane's 16 scales
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      kd[i] = (Q8 && i >= 4) ? ks_p[(int64_t)blk * kBlkPieces + 2 * (i - 4)] : kp[(int64_t)blk * kBlkPieces + i * 64];
+      kd[i] = (Q8 && i >= 4) ? ks_p[(int64_t)blk * kBlkPieces + 2 * (i - 4)] : unit(kp + (int64_t)blk * kBlkPieces + i * 64);
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      vd[i] = (Q8 && i >= 4) ? vs_p[(int64_t)blk * kBlkPieces + 2 * (i - 4)] : vp[(int64_t)blk * kBlkPieces + i * 64];
+      vd[i] = (Q8 && i >= 4) ? vs_p[(int64_t)blk * kBlkPieces + 2 * (i - 4)] : unit(vp + (int64_t)blk * kBlkPieces + i * 64);
   };
   // this wave's blocks: blk_begin + wave, + 4, ... ; two per trip so that the buffers alternate statically
   const int n_mine = blk_begin + wave < blk_end ? (blk_end - blk_begin - wave + 3) >> 2 : 0;
@@ -607,7 +613,7 @@ int64_t attn_mfma_scratch_bytes(int B, int n_heads, int T, int max_prefix) {
   return s == 1 ? 0 : (int64_t)B * n_heads * s * (T * kHD + 2 * T) * 4;
 }
 
-template <typename E, bool Q8, int NU, int TQ>
+template <typename E, bool Q8, int NU, int TQ, bool ONCE>
 static int launch_attention_mfma_t(int tree, const void* q, const Partials* qkv, const float* cs, const KvGeom& g, void* kc,
                                    void* vc, int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out,
                                    void* scratch, int64_t scratch_bytes, hipStream_t st) {
@@ -615,7 +621,7 @@ static int launch_attention_mfma_t(int tree, const void* q, const Partials* qkv,
   // the merge buffer [4][128][32 NU + 2] + [4][2][32 NU] floats overlays the staged Q tile
   constexpr int lds_bytes = 4 * kHD * (32 * NU + 2) * 4 + 4 * 2 * 32 * NU * 4;
   static_assert(lds_bytes >= 32 * NU * kQRow && lds_bytes * (3 - NU) <= 160 * 1024, "LDS budget of the tree kernel");
-  MDZ_SET_LDS_ONCE((attn_tree_mfma_kernel<E, Q8, NU, TQ>), lds_bytes);
+  MDZ_SET_LDS_ONCE((attn_tree_mfma_kernel<E, Q8, NU, TQ, ONCE>), lds_bytes);
   const int nq = q_heads(g);
   const int splits = attn_splits(B, nq, max_prefix, qkv != nullptr);
   MDZ_REQUIRE(scratch_bytes >= attn_mfma_scratch_bytes(B, nq, TQ, max_prefix), MDZ_EWORKSPACE,
@@ -634,7 +640,7 @@ static int launch_attention_mfma_t(int tree, const void* q, const Partials* qkv,
   const int64_t wgs = (int64_t)grid.x * grid.y * grid.z;
   const bool ordered = B > 1 && (splits > 1 ? wgs > num_cus() && max_prefix >= 1536
                                             : wgs > (NU == 1 && TQ == 64 ? 2 : 1) * num_cus() && max_prefix >= (TQ == 64 && !Q8 ? 2560 : 1024));
-  launch_timed(PROF_ATTN, attn_tree_mfma_kernel<E, Q8, NU, TQ>, grid, 256, lds_bytes, st, tree, (const E*)q, qkv ? *qkv : none, cs, g,
+  launch_timed(PROF_ATTN, attn_tree_mfma_kernel<E, Q8, NU, TQ, ONCE>, grid, 256, lds_bytes, st, tree, (const E*)q, qkv ? *qkv : none, cs, g,
                (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, ordered);
   MDZ_LAUNCH_CHECK();
   if (splits > 1) {
@@ -655,16 +661,21 @@ int launch_attention_mfma(int dtype, int tree, const void* q, const Partials* qk
   static const char* env = getenv("MDZ_ATTN_HALVES");  // development builds only: 1 = 32 queries per workgroup, 0 = 64
   if (env) halves = atoi(env) != 0;
 #endif
-#define MDZ_ATTN_CASE(Q8, NU, TQ)                                                                                         \
-  MDZ_WITH_ELEM16(dtype, return (launch_attention_mfma_t<E, Q8, NU, TQ>(tree, q, qkv, cs, g, kc, vc, layer, seq_len, B,  \
-                                                                        max_prefix, att_out, scratch, scratch_bytes, st)))
-  if (host_tree(tree)->T == 15) MDZ_ATTN_CASE(false, 1, 15);
-  if (g.quant) {
-    if (halves) MDZ_ATTN_CASE(true, 1, 64);
-    MDZ_ATTN_CASE(true, 2, 64);
+  const bool once = g.group == 1;  // (and not in halves; 8-bit rows run alike: 16K keys 801 / 802 us per step of 4 layers)
+#define MDZ_ATTN_CASE(Q8, NU, TQ, ONCE)                                                                                     \
+  MDZ_WITH_ELEM16(dtype, return (launch_attention_mfma_t<E, Q8, NU, TQ, ONCE>(tree, q, qkv, cs, g, kc, vc, layer, seq_len, B, \
+                                                                              max_prefix, att_out, scratch, scratch_bytes, st)))
+  if (host_tree(tree)->T == 15) {
+    if (once) MDZ_ATTN_CASE(false, 1, 15, true);
+    MDZ_ATTN_CASE(false, 1, 15, false);
   }
-  if (halves) MDZ_ATTN_CASE(false, 1, 64);
-  MDZ_ATTN_CASE(false, 2, 64);
+  if (g.quant) {
+    if (halves) MDZ_ATTN_CASE(true, 1, 64, false);
+    MDZ_ATTN_CASE(true, 2, 64, false);
+  }
+  if (halves) MDZ_ATTN_CASE(false, 1, 64, false);
+  if (once) MDZ_ATTN_CASE(false, 2, 64, true);
+  MDZ_ATTN_CASE(false, 2, 64, false);
 #undef MDZ_ATTN_CASE
 }
 
