@@ -22,12 +22,19 @@ __device__ inline __attribute__((always_inline)) void static_for(F&& f) {
 // The load takes its LDS address from m0, one wait state after a scalar write of it (the compiler inserts that for its own
 // loads; it does not look into assembly).  (clang warns that m0 is a reserved register: it is named so that a value the compiler
 // itself puts there is not taken to outlive the load.)
+// ONCE: the bytes are not wanted again soon (a weight is read once per row block, and row blocks run side by side), so the load is
+// non-temporal (see gemm_mfma.hip).  us, plain / non-temporal W: steps of 4 layers with 4 sequences on 64 nodes 1026 / 993, 12 on 15 nodes 948 / 915;
+// of 8 layers with 90 rows 1367 / 1356, 192 rows 1706 / 1678, 1024 rows 5368 / 5345.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-template <int OFF>
+template <int OFF, bool ONCE = false>
 __device__ inline void load_to_lds(const void* base, uint32_t off, uint32_t lds) {
-  asm volatile("s_add_i32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base), "n"(OFF)
-               : "memory", "scc", "m0");
+  if constexpr (ONCE)
+    asm volatile("s_add_i32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(off), "s"(base), "n"(OFF)
+                 : "memory", "scc", "m0");
+  else
+    asm volatile("s_add_i32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base), "n"(OFF)
+                 : "memory", "scc", "m0");
 }
 #pragma clang diagnostic pop
 template <int N>

@@ -100,7 +100,7 @@ __global__ void __launch_bounds__(512, 2)
     if constexpr (DIRECT) {
       const uint32_t dst = lds0 + slot * kSlot + wave * 1024;
       static_for<LX>([&](auto q) { load_to_lds<decltype(q)::value * 8192>(xp, xoff[decltype(q)::value], dst); });
-      static_for<LW>([&](auto q) { load_to_lds<UX * 1024 + decltype(q)::value * 8192>(wp, woff[decltype(q)::value], dst); });
+      static_for<LW>([&](auto q) { load_to_lds<UX * 1024 + decltype(q)::value * 8192, true>(wp, woff[decltype(q)::value], dst); });
     } else {
       uint8_t* dst = lds_raw + slot * kSlot + wave * 1024 + lane * 16;
 #pragma unroll
