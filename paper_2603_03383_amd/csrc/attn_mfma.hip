@@ -16,8 +16,10 @@
 // load), the K scales multiply the scores and the V scales the probabilities, both in fp32, so the MFMAs are the same.
 // Key-splits: when the kernel starts from the QKV partial sums, the last split owns every block that holds a
 // tree slot (it is the one that has to produce those K / V rows first) and the other splits share the blocks
-// that hold prefix keys only, which need nothing but Q: the long dependent chain (reduce K and V, write them,
-// read them back) then covers three blocks at most instead of an even share of the prefix.
+// that hold prefix keys only, which need nothing but Q: the longer prologue (three matrices reduced instead of one) then
+// falls on a workgroup with few blocks instead of one with an even share of the prefix.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace mdz {
@@ -35,62 +37,79 @@ __device__ inline u32x4 pack8(const float* v) {
                Elem16<E>::pack2(v[6], v[7])};
 }
 
-// NM head-matrices (q, or q k v, of head h) of the QKV GEMM output for the prologue below: thread (row = t/4,
-// seg = t%4) sums the partial-sum slots (in order) of features [16*seg, 16*seg+16) and their rotary partners
-// [64 + 16*seg, ...) of each matrix: lo[m][16], hi[m][16].  The loads of one slot of all NM matrices are issued
-// together (8 float4 per matrix in flight per thread); matrix m starts at column cols[m].
-template <int NM>
-__device__ inline void qkv_gather(const Partials& part, int64_t row, const int (&cols)[NM], int seg, float (&lo)[NM][16],
-                                  float (&hi)[NM][16]) {
-  int n_part[NM], n_max = 0;
+// F features of one row of one head's q, k or v in the QKV GEMM output, and their rotary partners 64 columns on.  load() requests
+// the first two partial-sum slots (all there are for most shapes) so that the loads of several of these can be in flight
+// together; sum() adds the slots in order and fetches what lies beyond.
+template <int F>
+struct RowSums {
+  float4 a[2][F / 4], b[2][F / 4];
+  const float* src;
+  int n;
+  __device__ inline void load(const Partials& part, int64_t row, int col, int f0) {
+    n = part.count(col);
+    src = part.p + row * part.ld + col + f0;
 #pragma unroll
-  for (int m = 0; m < NM; ++m) {
-    n_part[m] = part.count(cols[m]);
-    n_max = n_part[m] > n_max ? n_part[m] : n_max;
+    for (int p = 0; p < 2; ++p)
+      if (p < n) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) lo[m][i] = hi[m][i] = 0.f;
-  }
-  const float* src = part.p + row * part.ld + 16 * seg;
-  for (int p = 0; p < n_max; ++p) {
-    float4 a[NM][4], b[NM][4];
-    const float* sp = src + (int64_t)p * part.stride;
-#pragma unroll
-    for (int m = 0; m < NM; ++m)
-      if (p < n_part[m]) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          a[m][i] = *reinterpret_cast<const float4*>(sp + cols[m] + 4 * i);
-          b[m][i] = *reinterpret_cast<const float4*>(sp + cols[m] + 64 + 4 * i);
-        }
-      }
-#pragma unroll
-    for (int m = 0; m < NM; ++m)
-      if (p < n_part[m]) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          lo[m][4 * i] += a[m][i].x, lo[m][4 * i + 1] += a[m][i].y, lo[m][4 * i + 2] += a[m][i].z, lo[m][4 * i + 3] += a[m][i].w;
-          hi[m][4 * i] += b[m][i].x, hi[m][4 * i + 1] += b[m][i].y, hi[m][4 * i + 2] += b[m][i].z, hi[m][4 * i + 3] += b[m][i].w;
+        for (int i = 0; i < F / 4; ++i) {
+          a[p][i] = *reinterpret_cast<const float4*>(src + p * part.stride + 4 * i);
+          b[p][i] = *reinterpret_cast<const float4*>(src + p * part.stride + 64 + 4 * i);
         }
       }
   }
-}
-
-__device__ inline void rope16(const float* cs_row, int seg, float (&lo)[16], float (&hi)[16]) {
-  const float* c = cs_row + 32 * seg;  // [i][cos, sin] for i = 16*seg ..
+  __device__ inline void sum(const Partials& part, float (&lo)[F], float (&hi)[F]) const {
+    auto add = [](float* s, const float4& v) { s[0] += v.x, s[1] += v.y, s[2] += v.z, s[3] += v.w; };
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    float cv = c[2 * i], sv = c[2 * i + 1];
-    float a = lo[i], b = hi[i];
-    lo[i] = a * cv - b * sv;
-    hi[i] = b * cv + a * sv;
+    for (int i = 0; i < F; ++i) lo[i] = hi[i] = 0.f;
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+      if (p < n) {
+#pragma unroll
+        for (int i = 0; i < F / 4; ++i) add(lo + 4 * i, a[p][i]), add(hi + 4 * i, b[p][i]);
+      }
+    for (int p = 2; p < n; ++p) {
+#pragma unroll
+      for (int i = 0; i < F / 4; ++i) {
+        add(lo + 4 * i, *reinterpret_cast<const float4*>(src + p * part.stride + 4 * i));
+        add(hi + 4 * i, *reinterpret_cast<const float4*>(src + p * part.stride + 64 + 4 * i));
+      }
+    }
+  }
+};
+// cos, sin of F rotary pairs
+template <int F>
+struct RopeRow {
+  float4 cs[F / 2];
+  __device__ inline void load(const float* cs_row, int f0) {
+#pragma unroll
+    for (int i = 0; i < F / 2; ++i) cs[i] = *reinterpret_cast<const float4*>(cs_row + 2 * f0 + 4 * i);
+  }
+  __device__ inline void rotate(float (&lo)[F], float (&hi)[F]) const {
+#pragma unroll
+    for (int i = 0; i < F; ++i) {
+      const float c = i & 1 ? cs[i >> 1].z : cs[i >> 1].x, sn = i & 1 ? cs[i >> 1].w : cs[i >> 1].y;
+      const float x = lo[i], y = hi[i];
+      lo[i] = x * c - y * sn;
+      hi[i] = y * c + x * sn;
+    }
+  }
+};
+// F elements as E to LDS (8 bytes at a time where F is 4)
+template <typename E, int F>
+__device__ inline void stage(uint8_t* dst, const float (&v)[F]) {
+  if constexpr (F == 4) {
+    *reinterpret_cast<uint2*>(dst) = uint2{Elem16<E>::pack2(v[0], v[1]), Elem16<E>::pack2(v[2], v[3])};
+  } else {
+#pragma unroll
+    for (int i = 0; i < F; i += 8) *reinterpret_cast<u32x4*>(dst + 2 * i) = pack8<E>(v + i);
   }
 }
 
 // qkv.p == NULL: q holds the rotated queries and the cache already holds the tree rows (separate RoPE kernel).
 // qkv.p != NULL: the kernel starts from the QKV GEMM's partial sums: it reduces them, rotates q and k (RoPE,
-// cos/sin table cs [row][64][2]), keeps q in LDS, and — if its key range reaches the tree slots — writes the 64
-// tree rows of K and V of its head into the cache before reading them back like any other key.  Workgroups of
-// the same head that both reach the tree slots write identical values.
+// cos/sin table cs [row][64][2]), keeps q in LDS, and — if its key range reaches the tree slots — the tree's rows of K and V of
+// its head too, from where they enter the product; one workgroup per key/value head also writes them into the cache.
 // NU = 2: a workgroup carries all 64 queries (two groups of 32).  NU = 1: it carries 32 of them, the two halves of a
 // (sequence, head, split) being two workgroups (blockIdx.z = 2 * sequence + half): half the accumulators, so two
 // workgroups share a CU and twice as many loads are in flight per CU, at the price of K and V passing through the
@@ -132,10 +151,13 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
   int blk_begin, blk_end;
   if (qkv.p != nullptr && n_splits > 1) {  // last split: every block with a tree slot; the others: prefix-only blocks
     // (With one or two prefix splits the tree split also takes what it has time for at the end of the prefix: its prologue is
-    // worth about 32 blocks of a prefix split.  3 sequences of 200 .. 2500 keys, two splits: 37.8 -> 31.6 us per layer; with
-    // five to seven prefix splits nothing is gained: 29.3 / 28.9 us at 7K keys of 8 bits, 65.3 / 66.6 at 16K of 16 bits.)
+    // worth about 24 blocks of a prefix split, 32 with 8-bit rows.  3 sequences of 200 .. 2500 keys, two splits: 37.8 -> 31.6 us
+    // per layer; with five to seven prefix splits nothing is gained: 29.3 / 28.9 us at 7K keys of 8 bits, 65.3 / 66.6 at 16K of 16 bits.
+    // us per step of 4 layers with 10 / 16 / 24 / 32 blocks: 3 sequences 1020 / 1016 / 1010 / 1016, 4 of 300 .. 3400 1183 / 1188 / 1193 / 1206, one of
+    // 2000 662 / 662 / 657 / 655, 4 of 200 .. 2500 with 8-bit rows 1135 / 1131 / 1125 / 1114.)
+    constexpr int kTreeCost = Q8 ? 32 : 24;
     const int ps = n_splits - 1, all = S >> 5;
-    const int extra = ps == 1 ? max((all - 32) / 2, 0) : ps == 2 ? max((all - 64) / 3, 0) : 0, pb = all - extra;
+    const int extra = ps == 1 ? max((all - kTreeCost) / 2, 0) : ps == 2 ? max((all - 2 * kTreeCost) / 3, 0) : 0, pb = all - extra;
     blk_begin = split == ps ? pb : (int)((int64_t)split * pb / ps);
     blk_end = split == ps ? nb : (int)((int64_t)(split + 1) * pb / ps);
   } else {
@@ -179,16 +201,14 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
   // this wave's blocks: blk_begin + wave, + 4, ... ; two per trip so that the buffers alternate statically
   const int n_mine = blk_begin + wave < blk_end ? (blk_end - blk_begin - wave + 3) >> 2 : 0;
   const int first = blk_begin + wave, last = first + 4 * (n_mine - 1);
-  // A first block that lies wholly in the prefix depends on nothing this kernel computes: it is requested before the
-  // prologue below, whose own loads then wait no longer than this one takes.  (A block with tree slots is written
-  // by the prologue first.)
-  // (not for 8-bit rows with 64 queries: that variant has no registers to hold the block through the prologue)
-  const bool preloaded = !(Q8 && NU == 2) && n_mine > 0 && (first + 1) * 32 <= S;
-  if (preloaded) load_kv(first, kb[0], vb[0]);
-
+  // Fused: does this workgroup's range reach the tree slots?  Its blocks there take the tree's K and V rows from LDS.
+  const bool has_tree = qkv.p != nullptr && split == n_splits - 1;
   // Q tile of this head -> LDS (rows padded by 16 B: the 16 B-per-lane operand reads below are bank-conflict
-  // free).  The region is reused by the wave merge after the key loop.
+  // free), then, where the range reaches the tree slots, the tree's K and V rows (16-bit, or 128 codes and a scale).  The region is
+  // reused by the wave merge after the key loop.
   uint8_t* q_lds = reinterpret_cast<uint8_t*>(lds);
+  uint8_t* k_lds = q_lds + kQW * kQRow;
+  uint8_t* v_lds = k_lds + TQ * kQRow;
   if (qkv.p == nullptr) {
 #pragma unroll
     for (int i = 0; i < 2 * NU; ++i) {
@@ -197,106 +217,87 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
       *reinterpret_cast<u32x4*>(q_lds + row * kQRow + col * 16) =
           *reinterpret_cast<const u32x4*>(q + (int64_t)(b * TQ + q0 + min(row, kRows - 1)) * d + h * kHD + col * 8);
     }
+    if (n_mine > 0) load_kv(first, kb[0], vb[0]);
   } else {
-    // thread (row = t/4, seg = t%4): features [16 seg, +16) and their rotary partners of one row.  K / V rows: tree
-    // node `row` (all TQ, by the first TQ rows of threads); Q rows: query q0 + row (the first 32 NU rows of threads, the
-    // padding as copies of the last query).
-    const int row = threadIdx.x >> 2, seg = threadIdx.x & 3;
-    const int64_t grow_kv = (int64_t)b * TQ + min(row, TQ - 1), grow_q = (int64_t)b * TQ + q0 + min(row, kRows - 1);
-    const float* cs_kv = cs + grow_kv * kHD;  // 64 pairs x 2
-    auto stage_q = [&](float (&lo)[16], float (&hi)[16]) {
-      uint8_t* qrow = q_lds + row * kQRow;
-      rope16(cs + grow_q * kHD, seg, lo, hi);
-      *reinterpret_cast<u32x4*>(qrow + 32 * seg) = pack8<E>(lo);
-      *reinterpret_cast<u32x4*>(qrow + 32 * seg + 16) = pack8<E>(lo + 8);
-      *reinterpret_cast<u32x4*>(qrow + 128 + 32 * seg) = pack8<E>(hi);
-      *reinterpret_cast<u32x4*>(qrow + 128 + 32 * seg + 16) = pack8<E>(hi + 8);
+    // Bound by its round trips to memory, which cost 3 - 4 us each while other workgroups stream: all loads (the partial sums of
+    // q, k and v and their rotations) are requested before the first is used, and nothing is read back from the cache.  One
+    // tree of 64 nodes: 7.8 us with the matrices one after the other, slot by slot, and the rows through the cache.
+    // Thread (row, seg): F features from F * seg on, and their partners, of a row; 256 threads cover the rows.
+    constexpr int kKvThreads = TQ == 15 ? 16 : 4, kKvF = 64 / kKvThreads;
+    constexpr int kQThreads = TQ == 15 ? 16 : 256 / kQW, kQF = 64 / kQThreads;
+    const int kv_row = min((int)threadIdx.x / kKvThreads, TQ - 1), kv_f0 = (threadIdx.x % kKvThreads) * kKvF;
+    const int q_row = threadIdx.x / kQThreads, q_f0 = (threadIdx.x % kQThreads) * kQF;
+    const int64_t grow_kv = (int64_t)b * TQ + kv_row, grow_q = (int64_t)b * TQ + q0 + min(q_row, kRows - 1);
+    RowSums<kQF> qs;
+    RopeRow<kQF> q_rope;
+    auto stage_q = [&]() {
+      float lo[kQF], hi[kQF];
+      qs.sum(qkv, lo, hi);
+      q_rope.rotate(lo, hi);
+      uint8_t* dst = q_lds + q_row * kQRow + 2 * q_f0;
+      stage<E>(dst, lo);
+      stage<E>(dst + 128, hi);
+      if constexpr (TQ == 15) {  // the padding columns of the operand: copies
+        stage<E>(dst + 16 * kQRow, lo);
+        stage<E>(dst + 16 * kQRow + 128, hi);
+      }
     };
-    // rotates the key row and writes the node's K and V rows into the cache
-    auto write_kv = [&](float (&klo)[16], float (&khi)[16], float (&vlo)[16], float (&vhi)[16]) {
-      const int slot = S + row;
-      rope16(cs_kv, seg, klo, khi);
-      if constexpr (Q8) {
-        // row scales: the largest magnitude over the 4 threads (seg) of the row, then codes of this thread's 2 x 16 features
-        float am[2] = {0.f, 0.f};
+    if (has_tree) {
+      RowSums<kKvF> ks, vs;
+      RopeRow<kKvF> k_rope;
+      ks.load(qkv, grow_kv, d + hk * kHD, kv_f0);
+      k_rope.load(cs + grow_kv * kHD, kv_f0);
+      qs.load(qkv, grow_q, h * kHD, q_f0);
+      q_rope.load(cs + grow_q * kHD, q_f0);
+      vs.load(qkv, grow_kv, d + dkv + hk * kHD, kv_f0);
+      __builtin_amdgcn_sched_barrier(0);
+      uint8_t* k_dst = k_lds + kv_row * kQRow;
+      uint8_t* v_dst = v_lds + kv_row * kQRow;
+      auto stage_row = [&](uint8_t* dst, const float (&lo)[kKvF], const float (&hi)[kKvF]) {
+        if constexpr (Q8) {
+          // the row's scale: the largest magnitude over its 4 threads, then codes of this thread's 2 x 16 features
+          float am = 0.f;
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
+          for (int i = 0; i < kKvF; ++i) am = fmaxf(am, fmaxf(fabsf(lo[i]), fabsf(hi[i])));
+          am = fmaxf(am, __shfl_xor(am, 1, 64));
+          am = fmaxf(am, __shfl_xor(am, 2, 64));
+          const float sc = kv8_scale_of(am);
 #pragma unroll
-          for (int i = 0; i < 16; ++i) am[m] = fmaxf(am[m], fmaxf(fabsf((m == 0 ? klo : vlo)[i]), fabsf((m == 0 ? khi : vhi)[i])));
-          am[m] = fmaxf(am[m], __shfl_xor(am[m], 1, 64));
-          am[m] = fmaxf(am[m], __shfl_xor(am[m], 2, 64));
-        }
-        const float ks = kv8_scale_of(am[0]), vs = kv8_scale_of(am[1]);
-        uint8_t* k8 = reinterpret_cast<uint8_t*>(kc) + kv8_head_base(g, layer, b, hk);
-        uint8_t* v8 = reinterpret_cast<uint8_t*>(vc) + kv8_head_base(g, layer, b, hk);
-        // 8 consecutive features of one key are 8 contiguous bytes of the 8-bit K layout
-#pragma unroll
-        for (int gh2 = 0; gh2 < 2; ++gh2) {
-          const float* a = klo + 8 * gh2;
-          const float* c = khi + 8 * gh2;
-          *reinterpret_cast<uint2*>(k8 + kv8_k_code(slot, 16 * seg + 8 * gh2)) =
-              uint2{kv8_pack4(a[0], a[1], a[2], a[3], ks), kv8_pack4(a[4], a[5], a[6], a[7], ks)};
-          *reinterpret_cast<uint2*>(k8 + kv8_k_code(slot, 64 + 16 * seg + 8 * gh2)) =
-              uint2{kv8_pack4(c[0], c[1], c[2], c[3], ks), kv8_pack4(c[4], c[5], c[6], c[7], ks)};
-        }
-#pragma unroll
-        for (int i = 0; i < 16; i += 4) {
-          const uint32_t wl = kv8_pack4(vlo[i], vlo[i + 1], vlo[i + 2], vlo[i + 3], vs);
-          const uint32_t wh = kv8_pack4(vhi[i], vhi[i + 1], vhi[i + 2], vhi[i + 3], vs);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v8[kv8_v_code(slot, 16 * seg + i + e)] = (uint8_t)(wl >> (8 * e));
-            v8[kv8_v_code(slot, 64 + 16 * seg + i + e)] = (uint8_t)(wh >> (8 * e));
+          for (int i = 0; i < kKvF; i += 4) {
+            *reinterpret_cast<uint32_t*>(dst + kv_f0 + i) = kv8_pack4(lo[i], lo[i + 1], lo[i + 2], lo[i + 3], sc);
+            *reinterpret_cast<uint32_t*>(dst + 64 + kv_f0 + i) = kv8_pack4(hi[i], hi[i + 1], hi[i + 2], hi[i + 3], sc);
           }
+          if (kv_f0 == 0) *reinterpret_cast<float*>(dst + 128) = sc;
+        } else {
+          stage<E>(dst + 2 * kv_f0, lo);
+          stage<E>(dst + 128 + 2 * kv_f0, hi);
         }
-        if (seg == 0) {
-          *reinterpret_cast<float*>(k8 + kv8_scale(slot)) = ks;
-          *reinterpret_cast<float*>(v8 + kv8_scale(slot)) = vs;
-        }
-      } else {
-        // 8 consecutive features of one key are 16 contiguous bytes of the tiled K layout
-        *reinterpret_cast<u32x4*>(kc + k_index(g, layer, b, hk, slot, 16 * seg)) = pack8<E>(klo);
-        *reinterpret_cast<u32x4*>(kc + k_index(g, layer, b, hk, slot, 16 * seg + 8)) = pack8<E>(klo + 8);
-        *reinterpret_cast<u32x4*>(kc + k_index(g, layer, b, hk, slot, 64 + 16 * seg)) = pack8<E>(khi);
-        *reinterpret_cast<u32x4*>(kc + k_index(g, layer, b, hk, slot, 64 + 16 * seg + 8)) = pack8<E>(khi + 8);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          vc[v_index(g, layer, b, hk, slot, 16 * seg + i)] = from_float<E>(vlo[i]);
-          vc[v_index(g, layer, b, hk, slot, 64 + 16 * seg + i)] = from_float<E>(vhi[i]);
-        }
+      };
+      {
+        float lo[kKvF], hi[kKvF];
+        ks.sum(qkv, lo, hi);
+        k_rope.rotate(lo, hi);
+        stage_row(k_dst, lo, hi);
       }
-    };
-    if (blk_end * 32 > S && blk_begin < blk_end) {  // this range reaches the tree slots: produce their K / V rows
-      // (workgroups of one key/value head that reach the tree slots all write them: identical values, no ordering needed)
-      if constexpr (NU == 2) {
-        float lo[3][16], hi[3][16];
-        const int cols[3] = {h * kHD, d + hk * kHD, d + dkv + hk * kHD};  // columns of q, k, v in the QKV output
-        qkv_gather<3>(qkv, grow_kv, cols, seg, lo, hi);
-        stage_q(lo[0], hi[0]);
-        write_kv(lo[1], hi[1], lo[2], hi[2]);
-      } else {
-        float lo[2][16], hi[2][16];
-        const int cols[2] = {d + hk * kHD, d + dkv + hk * kHD};
-        if (row < TQ) {
-          qkv_gather<2>(qkv, grow_kv, cols, seg, lo, hi);
-          write_kv(lo[0], hi[0], lo[1], hi[1]);
-        }
-        if (row < kQW) {
-          float ql[1][16], qh[1][16];
-          const int qcols[1] = {h * kHD};
-          qkv_gather<1>(qkv, grow_q, qcols, seg, ql, qh);
-          stage_q(ql[0], qh[0]);
-        }
+      stage_q();
+      {
+        float lo[kKvF], hi[kKvF];
+        vs.sum(qkv, lo, hi);
+        stage_row(v_dst, lo, hi);
       }
-    } else if (row < kQW) {
-      float lo[1][16], hi[1][16];
-      const int cols[1] = {h * kHD};
-      qkv_gather<1>(qkv, grow_q, cols, seg, lo, hi);
-      stage_q(lo[0], hi[0]);
+      if (n_mine > 0) load_kv(first, kb[0], vb[0]);
+    } else {
+      // Prefix splits request their first block first: the loads behind it then wait no longer than this one takes.
+      // (not for 8-bit rows with 64 queries: that variant has no registers to hold the block meanwhile)
+      if (!(Q8 && NU == 2) && n_mine > 0) load_kv(first, kb[0], vb[0]);
+      qs.load(qkv, grow_q, h * kHD, q_f0);
+      q_rope.load(cs + grow_q * kHD, q_f0);
+      stage_q();
+      if (Q8 && NU == 2 && n_mine > 0) load_kv(first, kb[0], vb[0]);
     }
   }
   MDZ_STAMP(1);
-  __syncthreads();  // Q tile complete; the tree rows written above are complete (stores drain before a barrier)
+  __syncthreads();  // Q tile and tree rows complete
   MDZ_STAMP(2);
   // B operand of scores^T: lane holds query 32u + qi, features 16ks + 8gh .. +7
   const uint8_t* qfrag = q_lds + qi * kQRow + gh * 16;
@@ -316,7 +317,7 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[tt][u][r] = 0.f;
 
-  auto process = [&](int blk, const u32x4 (&kd)[8], const u32x4 (&vd)[8]) {
+  auto process = [&](int blk, const u32x4 (&kd)[8], const u32x4 (&vd)[8], auto masked) {
     // Compiler barrier: keeps the (loop-invariant) Q operand reads inside the loop, i.e. in LDS rather
     // than in 64 registers per lane that this kernel does not have to spare.
     asm volatile("" ::: "memory");
@@ -338,7 +339,7 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
     // visible, a tree key S+j is visible iff bit j of the query's ancestor mask is set, keys beyond the
     // tree are not.  rel0 (wave-uniform) = offset of the block's first key from the tree's first slot.
     const int rel0 = blk * 32 - S;
-    const bool need_mask = rel0 + 32 > 0;  // wave-uniform: the block reaches past the prefix
+    constexpr bool need_mask = decltype(masked)::value;  // the block reaches past the prefix
     float alpha[NU];
     u32x4 pf[NU][2];
     float weight[16];  // (fp32 weights: NU is 1)
@@ -346,7 +347,7 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
     for (int u = 0; u < NU; ++u) {
       float bmax = -INFINITY;
       // register r is key 8*(r/4) + 4*gh + r%4 of the block; its scale is component r%4 of scale piece r/4
-      if (need_mask) {  // wave-uniform branch: only the (at most three) blocks that hold tree slots pay for the mask
+      if constexpr (need_mask) {  // only the (at most three) blocks that hold tree slots pay for the mask
         const uint32_t pre = rel0 >= 0 ? 0u : (0xFFFFFFFFu >> (32 + rel0));          // keys below S (rel0 in [-31,-1])
         const uint64_t tr = rel0 >= 0 ? (mq[u] >> rel0) : (mq[u] << (-rel0));        // rel0 in [-31, 63]
         const uint32_t vis = (pre | (uint32_t)tr) >> (4 * gh);
@@ -424,18 +425,100 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
       }
   };
 
+  // Puts the tree's rows of block blk, staged in LDS, into its units (what the cache holds there is not yet written).
+  auto put_tree = [&](int blk, u32x4 (&kd)[8], u32x4 (&vd)[8]) {
+    const int n0 = blk * 32 - S;  // node of the block's first key; nodes outside [0, TQ) stay as loaded
+    const bool mine = (unsigned)(n0 + qi) < (unsigned)TQ;
+    const uint8_t* krow = k_lds + (mine ? n0 + qi : 0) * kQRow;
+    const uint8_t* vcol = v_lds + (Q8 ? qi : 2 * qi);
+    auto node = [&](int key) { return n0 + key + 4 * gh; };  // key: 8 * j + c, c < 4, of the half-wave's numbering
+    auto in_tree = [&](int key) { return (unsigned)node(key) < (unsigned)TQ; };
+    auto row_of = [&](int key) { return min(max(node(key), 0), TQ - 1) * kQRow; };
+    if constexpr (Q8) {
+      if (mine) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const uint2 lo = *reinterpret_cast<const uint2*>(krow + 32 * j + 8 * gh), hi = *reinterpret_cast<const uint2*>(krow + 32 * j + 16 + 8 * gh);
+          kd[j] = u32x4{lo.x, lo.y, hi.x, hi.y};
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)  // keys 8 j + 4 gh + c: byte 4 (j % 2) + c of V's word pair j / 2, component c of scale piece j
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          __builtin_amdgcn_sched_barrier(0);
+          const int key = 8 * j + c, row = row_of(key);
+          const bool in = in_tree(key);
+          const uint32_t ksc = *reinterpret_cast<const uint32_t*>(k_lds + row + 128), vsc = *reinterpret_cast<const uint32_t*>(v_lds + row + 128);
+          kd[4 + j][c] = in ? ksc : kd[4 + j][c];
+          vd[4 + j][c] = in ? vsc : vd[4 + j][c];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const uint32_t code = vcol[row + 32 * t];
+            vd[t][j] = in ? (vd[t][j] & ~(0xFFu << (8 * c))) | code << (8 * c) : vd[t][j];
+          }
+        }
+    } else {
+      if (mine) {
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) kd[ks] = *reinterpret_cast<const u32x4*>(krow + 32 * ks + 16 * gh);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)  // keys 8 j + 4 gh + c: element 4 (j % 2) + c of unit 2 t + j / 2
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          __builtin_amdgcn_sched_barrier(0);
+          const int key = 8 * j + c, row = row_of(key), w = 2 * (j & 1) + (c >> 1);
+          const bool in = in_tree(key);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const uint32_t v = *reinterpret_cast<const uint16_t*>(vcol + row + 64 * t), old = vd[2 * t + (j >> 1)][w];
+            vd[2 * t + (j >> 1)][w] = in ? (c & 1 ? (old & 0xFFFFu) | v << 16 : (old & 0xFFFF0000u) | v) : old;
+          }
+        }
+    }
+  };
+  auto write_tree = [&](int blk, const u32x4 (&kd)[8], const u32x4 (&vd)[8]) {
+    u32x4* kw = const_cast<u32x4*>(kp) + (int64_t)blk * kBlkPieces;
+    u32x4* vw = const_cast<u32x4*>(vp) + (int64_t)blk * kBlkPieces;
+    const bool mine = (unsigned)(blk * 32 - S + qi) < (unsigned)TQ;
+    if (mine) {
+#pragma unroll
+      for (int i = 0; i < (Q8 ? 4 : 8); ++i) kw[i * 64] = kd[i];
+    }
+#pragma unroll
+    for (int i = 0; i < (Q8 ? 4 : 8); ++i) vw[i * 64] = vd[i];
+    if constexpr (Q8) {  // scales: lane gh = 0 of a key
+      if (mine && gh == 0) {
+        const int row = (blk * 32 - S + qi) * kQRow;
+        reinterpret_cast<uint32_t*>(kw - lane + 256)[qi] = *reinterpret_cast<const uint32_t*>(k_lds + row + 128);
+        reinterpret_cast<uint32_t*>(vw - lane + 256)[qi] = *reinterpret_cast<const uint32_t*>(v_lds + row + 128);
+      }
+    }
+  };
+
+  // The blocks wholly in the prefix, then the wave's block with tree slots, if it has one (three at most, so one per wave).
   if (n_mine > 0) {
-    if (!preloaded) load_kv(first, kb[0], vb[0]);
-    for (int it = 0; it < n_mine; it += 2) {
+    const bool tail = last * 32 + 32 > S;
+    const int n_pre = n_mine - (tail ? 1 : 0);
+    for (int it = 0; it < n_pre; it += 2) {
       const int blk = first + 4 * it;
       load_kv(min(blk + 4, last), kb[1], vb[1]);
       __builtin_amdgcn_sched_barrier(0);
-      process(blk, kb[0], vb[0]);
+      process(blk, kb[0], vb[0], std::false_type{});
       __builtin_amdgcn_sched_barrier(0);
       load_kv(min(blk + 8, last), kb[0], vb[0]);
       __builtin_amdgcn_sched_barrier(0);
-      if (it + 1 < n_mine) process(blk + 4, kb[1], vb[1]);
+      if (it + 1 < n_pre) process(blk + 4, kb[1], vb[1], std::false_type{});
       __builtin_amdgcn_sched_barrier(0);
+    }
+    if (tail) {  // (block `last` is in the first buffer: the loop's last load repeats it)
+      if (has_tree) {
+        put_tree(last, kb[0], vb[0]);
+        // one of the workgroups that hold these rows writes them: whole units, prefix keys in them as they were read
+        if (h % g.group == 0 && q0 == 0) write_tree(last, kb[0], vb[0]);
+      }
+      process(last, kb[0], vb[0], std::true_type{});
     }
   }
 
