@@ -100,12 +100,9 @@ int64_t topk_scratch_bytes(int rows);
 int launch_topk(const float* logits, int rows, int V, int64_t ld, int k, int32_t* out, int64_t out_ld, void* scratch,
                 int64_t scratch_bytes, hipStream_t st);
 // Candidate selection of all heads at once from logits [B][K+1][V] (row 0 of a sequence: the base LM head, used
-// only when root_token is NULL): fills cand_flat [B][n_cand].  Needs heads_select_supported().
-bool heads_select_supported(int tree, int B, int V, const void* scratch, int64_t scratch_bytes);
+// only when root_token is NULL): fills cand_flat [B][n_cand].  (scratch as for launch_argmax)
 int launch_heads_select(int tree, const float* logits, int B, int V, const int32_t* root_token, int32_t* cand_flat,
-                        void* scratch, hipStream_t st);
-// dst[i * dst_stride] = src[i]
-int launch_scatter_i32(const int32_t* src, int32_t* dst, int n, int64_t dst_stride, hipStream_t st);
+                        void* scratch, int64_t scratch_bytes, hipStream_t st);
 int launch_tree_tokens(int tree, const int32_t* cand_flat, int32_t* tree_tokens, int B, hipStream_t st);
 int launch_accept(int tree, const int32_t* tree_tokens, const int32_t* node_argmax, int B, int32_t* accept_len,
                   int32_t* best_path, int32_t* acc_nodes, int32_t* acc_tokens, int32_t* next_root,

@@ -508,23 +508,18 @@ int medusa_heads(const mdz_model_desc* model, const mdz_weights* w, const void* 
   if (B == 0) return MDZ_OK;
   hipStream_t st = (hipStream_t)stream;
   char* wsb = (char*)ws;
-  void* h = wsb + L.h;
+  const void* h = wsb + L.h;
   float* part = (float*)(wsb + L.part);
   void* z = wsb + L.z;
   Partials pr;
   const int64_t V = m.vocab;
   const int64_t ld = (int64_t)(t->K + 1) * V;  // row stride of the [B][K+1][V] logits
   float* hl = head_logits_opt ? head_logits_opt : (float*)(wsb + L.hlogits);
-  if ((rc = launch_gather_rows(m.dtype, hidden, src_row, B, Tsrc, m.d, h, st))) return rc;
-  // the heads' candidates are selected in one pair of launches after the last GEMM where the shape allows it
-  const bool batched = heads_select_supported(m.tree, B, m.vocab, wsb + L.sel, L.sel_bytes);
+  // the rows themselves where there is nothing to gather (the GEMMs' fast kernels need rows that start on 16 bytes)
+  if (src_row == nullptr && Tsrc == 1 && aligned16(hidden, hidden)) h = hidden;
+  else if ((rc = launch_gather_rows(m.dtype, hidden, src_row, B, Tsrc, m.d, wsb + L.h, st))) return rc;
   // slot 0: root token
-  if (root_token) {
-    if (!batched && (rc = launch_scatter_i32(root_token, cand_flat, B, t->n_cand, st))) return rc;
-  } else {
-    if ((rc = launch_gemm(m.dtype, h, w->lm_head, hl, B, m.vocab, m.d, ld, 1, &pr, st))) return rc;
-    if (!batched && (rc = launch_topk(hl, B, m.vocab, ld, 1, cand_flat, t->n_cand, wsb + L.sel, L.sel_bytes, st))) return rc;
-  }
+  if (!root_token && (rc = launch_gemm(m.dtype, h, w->lm_head, hl, B, m.vocab, m.d, ld, 1, &pr, st))) return rc;
   // the K first-layer GEMMs (each into its own partial-sum region), one launch for the K residual blocks, then the
   // K vocabulary projections back to back
   const int64_t head_part = gemm_part_elems(m.dtype, B, m.d, m.d);
@@ -548,16 +543,10 @@ int medusa_heads(const mdz_model_desc* model, const mdz_weights* w, const void* 
     pr.p = part;
     if ((rc = launch_head_residual(m.dtype, h, pr, head_part, b1s, t->K, z, B, m.d, st))) return rc;
   }
-  int seg = 1;
-  for (int k = 0; k < t->K; ++k) {
-    float* lk = hl + (int64_t)(k + 1) * V;
-    if ((rc = launch_gemm(m.dtype, (char*)z + k * zrow, w->head_lm[k], lk, B, m.vocab, m.d, ld, 1, &pr, st))) return rc;
-    if (!batched &&
-        (rc = launch_topk(lk, B, m.vocab, ld, t->caps[k], cand_flat + seg, t->n_cand, wsb + L.sel, L.sel_bytes, st)))
-      return rc;
-    seg += t->caps[k];
-  }
-  if (batched && (rc = launch_heads_select(m.tree, hl, B, m.vocab, root_token, cand_flat, wsb + L.sel, st))) return rc;
+  for (int k = 0; k < t->K; ++k)
+    if ((rc = launch_gemm(m.dtype, (char*)z + k * zrow, w->head_lm[k], hl + (int64_t)(k + 1) * V, B, m.vocab, m.d, ld, 1, &pr, st))) return rc;
+  // the candidates of all heads are selected after the last GEMM
+  if ((rc = launch_heads_select(m.tree, hl, B, m.vocab, root_token, cand_flat, wsb + L.sel, L.sel_bytes, st))) return rc;
   return launch_tree_tokens(m.tree, cand_flat, tree_tokens, B, st);
 }
 

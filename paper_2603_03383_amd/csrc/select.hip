@@ -71,44 +71,10 @@ int launch_argmax_merge(const ArgCand* cand, int rows, int n_cand, int32_t* out,
   return MDZ_OK;
 }
 
-// One block per row. Pass p selects the best element that strictly follows the previous pick.
-__global__ void __launch_bounds__(256) topk_kernel(const float* __restrict__ logits, int V, int64_t ld, int k,
-                                                   int32_t* __restrict__ out, int64_t out_ld) {
-  __shared__ Best red[4];
-  const float* row = logits + (int64_t)blockIdx.x * ld;
-  float pv = INFINITY;
-  int pi = -1;
-  for (int p = 0; p < k; ++p) {
-    Best b{-INFINITY, kNoIndex};
-    for (int i = threadIdx.x; i < V; i += 256) {
-      float v = row[i];
-      bool after_prev = (p == 0) || precedes(pv, pi, v, i);
-      if (after_prev && precedes(v, i, b.v, b.i)) {
-        b.v = v;
-        b.i = i;
-      }
-    }
-    b = block_best_256(b, red);
-    if (threadIdx.x == 0) out[(int64_t)blockIdx.x * out_ld + p] = b.i == kNoIndex ? -1 : b.i;
-    pv = b.v;
-    pi = b.i;
-  }
-}
-
-// ---- two-stage variant for long rows ----------------------------------------------------------------------------
-// Stage 1: every wave takes one chunk of 512 columns (8 per lane, in registers) and extracts its top-k, in order, with
-// wave-level exchanges alone (no LDS, no barriers).  Stage 2: one wave per row merges the chunk lists (see below).
-// The top-k of a union of top-k lists is the global top-k and the order is total (value descending, index
-// ascending), so the result equals the single-stage kernel's.
 // Rows come in two flavours: uniform (every row the same k, picks to out + row * out_ld) and heads (row (b, j) of
 // logits [B][K+1][V]: j = 0 the base LM head, whose argmax is the root candidate unless the caller gave root
 // tokens, j = 1..K Medusa head j with its own k = caps[j-1]; picks go straight to the row's segment of
-// cand_flat [B][n_cand] = [root | head 1 | .. | head K]: one pair of launches for all heads of all sequences).
-constexpr int kSelWaveCols = 512;   // columns per stage-1 chunk
-constexpr int kSelMaxChunks = 512;  // rows of up to 262144 columns
-constexpr int kSelMaxK = 16;        // candidates per chunk list (the lists are laid out for this many)
-static int sel_chunks(int V) { return (V + kSelWaveCols - 1) / kSelWaveCols; }
-
+// cand_flat [B][n_cand] = [root | head 1 | .. | head K]: one launch, or one pair, for all heads of all sequences).
 struct SelRows {
   int tree;        // >= 0: heads flavour over this tree; -1: uniform
   int k;           // uniform: picks per row
@@ -122,6 +88,56 @@ __device__ inline int sel_row_k(const SelRows& rs, int row) {
   const int j = row % (t.K + 1);
   return j == 0 ? (rs.have_root ? 0 : 1) : t.caps[j - 1];
 }
+__device__ inline int32_t* sel_row_out(const SelRows& rs, int row, int32_t* out) {
+  if (rs.tree < 0) return out + (int64_t)row * rs.out_ld;
+  const TreeTables& t = c_trees[rs.tree];
+  const int b = row / (t.K + 1), j = row % (t.K + 1);
+  int seg = 0;  // start of row j's segment in the flat candidate buffer
+  for (int i = 1; i <= j; ++i) seg += i == 1 ? 1 : t.caps[i - 2];
+  return out + (int64_t)b * t.n_cand + seg;
+}
+
+// Short rows, one block per row. Pass p selects the best element that strictly follows the previous pick.
+// Latency bound: all heads of a step go in one launch (1024 columns, three heads and the root token: 12.6 us in four launches, 5.0
+// in one; five heads of up to ten candidates: a step of the tiny model 195 / 165 us).
+__global__ void __launch_bounds__(256) topk_kernel(SelRows rs, const float* __restrict__ logits, int V,
+                                                   const int32_t* __restrict__ root_token, int32_t* __restrict__ out) {
+  __shared__ Best red[4];
+  const float* row = logits + (int64_t)blockIdx.x * (rs.tree < 0 ? rs.ld : (int64_t)V);
+  const int k = sel_row_k(rs, blockIdx.x);
+  int32_t* dst = sel_row_out(rs, blockIdx.x, out);
+  if (k == 0) {  // the root candidate is the caller's token
+    if (threadIdx.x == 0) dst[0] = root_token[blockIdx.x / (c_trees[rs.tree].K + 1)];
+    return;
+  }
+  float pv = INFINITY;
+  int pi = -1;
+  for (int p = 0; p < k; ++p) {
+    Best b{-INFINITY, kNoIndex};
+    for (int i = threadIdx.x; i < V; i += 256) {
+      float v = row[i];
+      bool after_prev = (p == 0) || precedes(pv, pi, v, i);
+      if (after_prev && precedes(v, i, b.v, b.i)) {
+        b.v = v;
+        b.i = i;
+      }
+    }
+    b = block_best_256(b, red);
+    if (threadIdx.x == 0) dst[p] = b.i == kNoIndex ? -1 : b.i;
+    pv = b.v;
+    pi = b.i;
+  }
+}
+
+// ---- two-stage variant for long rows ----------------------------------------------------------------------------
+// Stage 1: every wave takes one chunk of 512 columns (8 per lane, in registers) and extracts its top-k, in order, with
+// wave-level exchanges alone (no LDS, no barriers).  Stage 2: one wave per row merges the chunk lists (see below).
+// The top-k of a union of top-k lists is the global top-k and the order is total (value descending, index
+// ascending), so the result equals the single-stage kernel's.
+constexpr int kSelWaveCols = 512;   // columns per stage-1 chunk
+constexpr int kSelMaxChunks = 512;  // rows of up to 262144 columns
+constexpr int kSelMaxK = 16;        // candidates per chunk list (the lists are laid out for this many)
+static int sel_chunks(int V) { return (V + kSelWaveCols - 1) / kSelWaveCols; }
 
 __global__ void __launch_bounds__(256) topk_stage1_kernel(SelRows rs, const float* __restrict__ logits, int V, int n_chunks,
                                                           float* __restrict__ cand_v, int32_t* __restrict__ cand_i) {
@@ -163,19 +179,10 @@ __global__ void __launch_bounds__(64) topk_stage2_kernel(SelRows rs, const float
   extern __shared__ __attribute__((aligned(8))) uint8_t sel_lds[];  // [n_chunks][k] values, then indices
   const int lane = threadIdx.x, row = blockIdx.x;
   const int k = sel_row_k(rs, row);
-  int32_t* dst;
-  if (rs.tree < 0) {
-    dst = out + (int64_t)row * rs.out_ld;
-  } else {
-    const TreeTables& t = c_trees[rs.tree];
-    const int b = row / (t.K + 1), j = row % (t.K + 1);
-    int seg = 0;  // start of row j's segment in the flat candidate buffer
-    for (int i = 1; i <= j; ++i) seg += i == 1 ? 1 : t.caps[i - 2];
-    dst = out + (int64_t)b * t.n_cand + seg;
-    if (k == 0) {
-      if (lane == 0) dst[0] = root_token[b];
-      return;
-    }
+  int32_t* dst = sel_row_out(rs, row, out);
+  if (k == 0) {
+    if (lane == 0) dst[0] = root_token[row / (c_trees[rs.tree].K + 1)];
+    return;
   }
   float* lv = reinterpret_cast<float*>(sel_lds);
   int* li = reinterpret_cast<int*>(sel_lds) + n_chunks * k;
@@ -236,45 +243,29 @@ int launch_topk(const float* logits, int rows, int V, int64_t ld, int k, int32_t
   if (rows == 0 || k == 0) return MDZ_OK;
   if (two_stage_ok(rows, V, k, scratch, scratch_bytes))
     return launch_two_stage(SelRows{-1, k, ld, out_ld, false}, logits, rows, V, nullptr, out, scratch, st);
-  topk_kernel<<<rows, 256, 0, st>>>(logits, V, ld, k, out, out_ld);
+  topk_kernel<<<rows, 256, 0, st>>>(SelRows{-1, k, ld, out_ld, false}, logits, V, nullptr, out);
   MDZ_LAUNCH_CHECK();
   return MDZ_OK;
 }
 
-// true if launch_heads_select can serve this shape with this much scratch (else the caller selects head by head)
-bool heads_select_supported(int tree, int B, int V, const void* scratch, int64_t scratch_bytes) {
-  const TreeTables* t = host_tree(tree);
-  int kmax = 1;
-  for (int k = 0; k < t->K; ++k) kmax = t->caps[k] > kmax ? t->caps[k] : kmax;
-  return two_stage_ok(B * (t->K + 1), V, kmax, scratch, scratch_bytes);
-}
-
 int launch_heads_select(int tree, const float* logits, int B, int V, const int32_t* root_token, int32_t* cand_flat,
-                        void* scratch, hipStream_t st) {
+                        void* scratch, int64_t scratch_bytes, hipStream_t st) {
   ProfScope prof_(PROF_SELECT, st);
   const TreeTables* t = host_tree(tree);
   const int rows = B * (t->K + 1);
   if (rows == 0) return MDZ_OK;
-  return launch_two_stage(SelRows{tree, 0, 0, 0, root_token != nullptr}, logits, rows, V, root_token, cand_flat, scratch, st);
+  int kmax = 1;
+  for (int k = 0; k < t->K; ++k) kmax = t->caps[k] > kmax ? t->caps[k] : kmax;
+  const SelRows rs{tree, 0, 0, 0, root_token != nullptr};
+  if (two_stage_ok(rows, V, kmax, scratch, scratch_bytes)) return launch_two_stage(rs, logits, rows, V, root_token, cand_flat, scratch, st);
+  topk_kernel<<<rows, 256, 0, st>>>(rs, logits, V, root_token, cand_flat);
+  MDZ_LAUNCH_CHECK();
+  return MDZ_OK;
 }
 
 int launch_argmax(const float* logits, int rows, int V, int64_t ld, int32_t* out, void* scratch, int64_t scratch_bytes,
                   hipStream_t st) {
   return launch_topk(logits, rows, V, ld, 1, out, 1, scratch, scratch_bytes, st);
-}
-
-__global__ void scatter_i32_kernel(const int32_t* __restrict__ src, int32_t* __restrict__ dst, int n,
-                                   int64_t dst_stride) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i * dst_stride] = src[i];
-}
-
-int launch_scatter_i32(const int32_t* src, int32_t* dst, int n, int64_t dst_stride, hipStream_t st) {
-  ProfScope prof_(PROF_SELECT, st);
-  if (n == 0) return MDZ_OK;
-  scatter_i32_kernel<<<(n + 63) / 64, 64, 0, st>>>(src, dst, n, dst_stride);
-  MDZ_LAUNCH_CHECK();
-  return MDZ_OK;
 }
 
 __global__ void tree_tokens_kernel(int tree, const int32_t* __restrict__ cand_flat, int32_t* __restrict__ tree_tokens,
