@@ -42,6 +42,10 @@ int launch_attention_generic(int dtype, int tree, const void* q, const KvGeom& g
 
 bool gemm_f32_supported(int dtype, int K);
 int launch_gemm_f32(const void* X, const void* Wp, float* Y, int M, int N, int K, int64_t ldy, hipStream_t st);
+int launch_gemm_f32_heads(const void* X, int64_t x_stride, const void* const* Wp, int n_heads, float* Y, int64_t y_stride, int M, int N,
+                          int K, int64_t ldy, hipStream_t st);
+bool gemm_f32_swiglu_supported(int dtype, int N, int K);
+int launch_gemm_f32_swiglu(const void* X, const void* Wp, float* U, int M, int N, int K, hipStream_t st);
 
 bool gemm_mfma_supported(int dtype, int M, int N, int K);
 int gemm_mfma_slots(int M, int N, int K, int max_split);
@@ -291,6 +295,8 @@ static int run_layer(const mdz_model_desc& m, const mdz_layer_weights& lw, int l
     if ((rc = launch_gemm_tile_swiglu(fdt, xn, lw.wgateup, u, rows, 2 * m.ffn, m.d, st))) return rc;
   } else if (rows <= 64 && gemm_mfma_swiglu_supported(fdt, rows, 2 * m.ffn, m.d)) {
     if ((rc = launch_gemm_mfma_swiglu(fdt, xn, lw.wgateup, u, rows, 2 * m.ffn, m.d, st))) return rc;
+  } else if (gemm_f32_swiglu_supported(fdt, 2 * m.ffn, m.d) && aligned16(xn, lw.wgateup) && aligned16(u, u)) {
+    if ((rc = launch_gemm_f32_swiglu(xn, lw.wgateup, (float*)u, rows, 2 * m.ffn, m.d, st))) return rc;
   } else {
     if ((rc = launch_gemm(fdt, xn, lw.wgateup, part, rows, 2 * m.ffn, m.d, 2 * m.ffn, ms, &pr, st))) return rc;
     if ((rc = launch_swiglu(fdt, pr, u, rows, m.ffn, st))) return rc;
@@ -543,7 +549,12 @@ int medusa_heads(const mdz_model_desc* model, const mdz_weights* w, const void* 
     pr.p = part;
     if ((rc = launch_head_residual(m.dtype, h, pr, head_part, b1s, t->K, z, B, m.d, st))) return rc;
   }
-  for (int k = 0; k < t->K; ++k)
+  bool together = t->K > 1 && gemm_f32_supported(m.dtype, m.d) && V % 4 == 0 && ((int64_t)B * m.d) % 4 == 0 && aligned16(z, z);
+  for (int k = 0; k < t->K; ++k) together = together && aligned16(w->head_lm[k], w->head_lm[k]);
+  if (together) {
+    if ((rc = launch_gemm_f32_heads(z, (int64_t)B * m.d, w->head_lm, t->K, hl + V, V, B, m.vocab, m.d, ld, st))) return rc;
+  }
+  for (int k = 0; k < t->K && !together; ++k)
     if ((rc = launch_gemm(m.dtype, (char*)z + k * zrow, w->head_lm[k], hl + (int64_t)(k + 1) * V, B, m.vocab, m.d, ld, 1, &pr, st))) return rc;
   // the candidates of all heads are selected after the last GEMM
   if ((rc = launch_heads_select(m.tree, hl, B, m.vocab, root_token, cand_flat, wsb + L.sel, L.sel_bytes, st))) return rc;
