@@ -6,7 +6,10 @@
 //   * A wave owns NT tiles of 32 output columns and moves W through a ring of four half K-stages in
 //     registers: three half stages (CK/2 input features each) stay in flight while it multiplies the
 //     fourth, and every load is unconditional so the hardware wait counters let the prefetch overlap
-//     the MFMAs (a CU then keeps ~100 KB in flight, what the HBM latency asks for).
+//     the MFMAs (a CU then keeps ~100 KB in flight, what the HBM latency asks for).  AHEAD = 2 keeps two: with every CU streaming and
+//     nothing but the stream to wait for (up to 32 rows, several whole bands per workgroup: the heads' vocabulary matrices) fewer
+//     requests queue up in front of the memory: four heads from one row 700 / 691 us per call, eight rows 705 / 696; on 172 or
+//     192 workgroups, and at 64 rows, it loses 2 us per launch or changes nothing.
 //   * W is loaded non-temporally: every weight is used once per pass, and a read stream that does not ask the caches to keep it
 //     runs faster on this card (1 GiB over 256 workgroups 6.1 / 6.8 TB/s, 100 MB launches 5.5 / 5.9).  us, plain / non-temporal
 //     loads: four Medusa heads from one row 763 / 700, a layer at 64 rows 125 / 118.5, a 32-layer step at 1K 4057 / 3977,
@@ -37,12 +40,13 @@ typedef u32x4_t u32x4;
 
 __device__ inline float silu_mfma(float v) { return v / (1.0f + expf(-v)); }
 
-template <int WPB, int NT, int MT, int CK, typename E, bool SWIGLU = false, bool ARGMAX = false>
+template <int WPB, int NT, int MT, int CK, typename E, bool SWIGLU = false, bool ARGMAX = false, int AHEAD = 3>
 __global__ void __launch_bounds__(WPB * 64)
     gemm_mfma_kernel(const E* __restrict__ X, int M, int K, const E* __restrict__ Wp, int n_tiles,
                      int n_stages, float* __restrict__ P, int64_t ldp, int64_t part_stride, int whole_bands,
                      E* __restrict__ Uout = nullptr, ArgCand* __restrict__ cand = nullptr) {
   static_assert(!SWIGLU || (WPB == 4 && NT == 1), "the SwiGLU epilogue pairs waves 0/1 and 2/3");
+  static_assert(AHEAD == 3 || AHEAD == 2, "half stages requested ahead");
   static_assert(!ARGMAX || (NT == 1 && !SWIGLU), "the argmax epilogue scans one tile per wave");
   constexpr int ROWS = MT * 32;
   constexpr int KH = CK / 32;                       // MFMA k-steps per half stage
@@ -268,14 +272,18 @@ __global__ void __launch_bounds__(WPB * 64)
   // staged into the other LDS buffer after the unit's MFMAs.
   for (int u = u_lo; u < u_hi; u += 2) {
     load_x();
-    load_w(wb[3]);
+    if constexpr (AHEAD == 3) load_w(wb[3]);
     __builtin_amdgcn_sched_barrier(0);
     compute(0, 0, wb[0]);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (AHEAD == 2) load_w(wb[3]);
+    __builtin_amdgcn_sched_barrier(0);
     if (u == u_lo) MDZ_STAMP(2);
-    load_w(wb[0]);
+    if constexpr (AHEAD == 3) load_w(wb[0]);
     __builtin_amdgcn_sched_barrier(0);
     compute(0, 1, wb[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (AHEAD == 2) load_w(wb[0]);
     __builtin_amdgcn_sched_barrier(0);
     finish_unit(u + 1 == u_hi);
     store_x(1);
@@ -283,14 +291,21 @@ __global__ void __launch_bounds__(WPB * 64)
     // second unit of the trip; past the end of the range its loads repeat the last ones and nothing is multiplied
     const bool live = u + 1 < u_hi;
     load_x();
-    load_w(wb[1]);
+    if constexpr (AHEAD == 3) load_w(wb[1]);
     __builtin_amdgcn_sched_barrier(0);
     if (live) compute(1, 0, wb[2]);
     __builtin_amdgcn_sched_barrier(0);
-    load_w(wb[2]);
+    if constexpr (AHEAD == 2) load_w(wb[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (AHEAD == 3) load_w(wb[2]);
     __builtin_amdgcn_sched_barrier(0);
     if (live) {
       compute(1, 1, wb[3]);
+      if constexpr (AHEAD == 2) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_w(wb[2]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       finish_unit(u + 2 == u_hi);
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -407,6 +422,14 @@ static int launch_gemm_mfma_t(const void* X, const void* Wp, float* P, int M, in
   gemm_mfma_describe(M, N, K, max_split, res, nullptr);
   const E* x = (const E*)X;
   const E* w = (const E*)Wp;
+  if (p.whole && p.wpb == 4 && p.nt == 1 && p.mt == 1 && p.ck == 128 && bands >= 2 * num_cus()) {
+    constexpr int lds_bytes = 2 * 32 * (128 * 2 + 16);
+    MDZ_SET_LDS_ONCE((gemm_mfma_kernel<4, 1, 1, 128, E, false, false, 2>), lds_bytes);
+    launch_timed(tag, gemm_mfma_kernel<4, 1, 1, 128, E, false, false, 2>, p.grid, 256, lds_bytes, st, x, M, K, w, n_tiles, n_stages, P, ldp,
+                 part_stride, p.whole, nullptr, nullptr);
+    MDZ_LAUNCH_CHECK();
+    return MDZ_OK;
+  }
 #define MDZ_GEMM_CASE(WPB, NT, MT, CK)                                                                       \
   if (p.wpb == WPB && p.nt == NT && p.mt == MT && p.ck == CK) {                                              \
     constexpr int lds_bytes = 2 * MT * 32 * (CK * 2 + 16);                                                   \
