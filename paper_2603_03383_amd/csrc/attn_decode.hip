@@ -435,16 +435,19 @@ __global__ void __launch_bounds__(256, 4)
   const uint8_t* vbase = reinterpret_cast<const uint8_t*>(vc) + (Q8 ? kv8_head_base(g, layer, b, h) : kv_head_base(g, layer, b, h) * 2);
   const u32x4* kp = reinterpret_cast<const u32x4*>(kbase) + lane;
   const u32x4* vp = reinterpret_cast<const u32x4*>(vbase) + lane;
+  // Read once per pass, by no other workgroup, so non-temporally (us per step of 4 layers, plain / non-temporal: 20 sequences of 200 .. 2000
+  // keys 818 / 791, 64 of 40 .. 400 798 / 783, 90 of 300 .. 3000 at 16 heads 1223 / 1152).  Not so in attn_decode_kernel, whose
+  // calls have fewer keys to stream: one sequence of 6000 keys 623 / 627, of 200 at 16 heads 235.6 / 239.1, of 1024 over 32 layers 3252 / 3211.
   u32x4 kd[kUnits], vd[kUnits];
   float k_scale = 1.f, v_scale = 1.f;  // 8-bit rows: of key `key`
   auto load_k = [&](int blk) {
 #pragma unroll
-    for (int i = 0; i < kUnits; ++i) kd[i] = kp[(int64_t)blk * kBlkPieces + i * 64];
+    for (int i = 0; i < kUnits; ++i) kd[i] = __builtin_nontemporal_load(kp + (int64_t)blk * kBlkPieces + i * 64);
     if constexpr (Q8) k_scale = *reinterpret_cast<const float*>(kbase + (int64_t)blk * kKv8BlockBytes + 4096 + key * 4);
   };
   auto load_v = [&](int blk) {
 #pragma unroll
-    for (int i = 0; i < kUnits; ++i) vd[i] = vp[(int64_t)blk * kBlkPieces + i * 64];
+    for (int i = 0; i < kUnits; ++i) vd[i] = __builtin_nontemporal_load(vp + (int64_t)blk * kBlkPieces + i * 64);
     if constexpr (Q8) v_scale = *reinterpret_cast<const float*>(vbase + (int64_t)blk * kKv8BlockBytes + 4096 + key * 4);
   };
 
