@@ -701,9 +701,9 @@ static int launch_attention_mfma_t(int tree, const void* q, const Partials* qkv,
                                    void* vc, int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out,
                                    void* scratch, int64_t scratch_bytes, hipStream_t st) {
   if (B == 0) return MDZ_OK;
-  // the merge buffer [4][128][32 NU + 2] + [4][2][32 NU] floats overlays the staged Q tile
+  // the merge buffer [4][128][32 NU + 2] + [4][2][32 NU] floats overlays the staged Q tile and tree rows
   constexpr int lds_bytes = 4 * kHD * (32 * NU + 2) * 4 + 4 * 2 * 32 * NU * 4;
-  static_assert(lds_bytes >= 32 * NU * kQRow && lds_bytes * (3 - NU) <= 160 * 1024, "LDS budget of the tree kernel");
+  static_assert(lds_bytes >= (32 * NU + 2 * TQ) * kQRow && lds_bytes * (3 - NU) <= 160 * 1024, "LDS budget of the tree kernel");
   MDZ_SET_LDS_ONCE((attn_tree_mfma_kernel<E, Q8, NU, TQ, ONCE>), lds_bytes);
   const int nq = q_heads(g);
   const int splits = attn_splits(B, nq, max_prefix, qkv != nullptr);
