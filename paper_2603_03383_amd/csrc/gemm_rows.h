@@ -22,9 +22,10 @@ __device__ inline __attribute__((always_inline)) void static_for(F&& f) {
 // The load takes its LDS address from m0, one wait state after a scalar write of it (the compiler inserts that for its own
 // loads; it does not look into assembly).  (clang warns that m0 is a reserved register: it is named so that a value the compiler
 // itself puts there is not taken to outlive the load.)
-// ONCE: the bytes are not wanted again soon (a weight is read once per row block, and row blocks run side by side), so the load is
-// non-temporal (see gemm_mfma.hip).  us, plain / non-temporal W: steps of 4 layers with 4 sequences on 64 nodes 1026 / 993, 12 on 15 nodes 948 / 915;
-// of 8 layers with 90 rows 1367 / 1356, 192 rows 1706 / 1678, 1024 rows 5368 / 5345.
+// ONCE: the bytes are not wanted again soon (gemm_tile.hip: W is read once per row block, of which there are few), so the load is
+// non-temporal (see gemm_mfma.hip).  us, plain / non-temporal W there: steps of 4 layers with 4 sequences on 64 nodes 1026 / 993, 12 on 15
+// nodes 948 / 915; of 8 layers with 90 rows 1367 / 1356, 192 rows 1706 / 1678.  gemm_wide.hip keeps plain loads: its many row blocks meet in
+// L2 at their own pace (5 layers, 832 rows 3136 / 3193, 640 rows 2925 / 2942, 1024 rows 3617 / 3601).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 template <int OFF, bool ONCE = false>

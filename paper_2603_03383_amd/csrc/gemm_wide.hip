@@ -100,7 +100,7 @@ __global__ void __launch_bounds__(256, 1)
   };
   w_band();
   auto load_x = [&](auto q) { load_to_lds<decltype(q)::value * 4096>(xp, xoff[decltype(q)::value], x_lds); };
-  auto load_w = [&](auto q) { load_to_lds<decltype(q)::value * 4096, true>(wp, woff[decltype(q)::value], w_lds); };
+  auto load_w = [&](auto q) { load_to_lds<decltype(q)::value * 4096>(wp, woff[decltype(q)::value], w_lds); };
   auto next_x = [&]() {
     if (x_left > 0) {
       --x_left, ++xr, xp += kRound;
