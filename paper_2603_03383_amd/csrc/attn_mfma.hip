@@ -31,12 +31,6 @@ constexpr int kHD = 128;         // head_dim
 constexpr int kQRow = kHD * 2 + 16;  // bytes per staged Q row
 constexpr float kLazyLog2 = 8.f;  // see the key loop: how far a block's maximum may exceed the running reference
 
-template <typename E>
-__device__ inline u32x4 pack8(const float* v) {
-  return u32x4{Elem16<E>::pack2(v[0], v[1]), Elem16<E>::pack2(v[2], v[3]), Elem16<E>::pack2(v[4], v[5]),
-               Elem16<E>::pack2(v[6], v[7])};
-}
-
 // F features of one row of one head's q, k or v in the QKV GEMM output, and their rotary partners 64 columns on.  load() requests
 // the first two partial-sum slots (all there are for most shapes) so that the loads of several of these can be in flight
 // together; sum() adds the slots in order and fetches what lies beyond.
@@ -85,24 +79,43 @@ struct RopeRow {
 #pragma unroll
     for (int i = 0; i < F / 2; ++i) cs[i] = *reinterpret_cast<const float4*>(cs_row + 2 * f0 + 4 * i);
   }
+  __device__ inline float cos(int i) const { return i & 1 ? cs[i >> 1].z : cs[i >> 1].x; }
+  __device__ inline float sin(int i) const { return i & 1 ? cs[i >> 1].w : cs[i >> 1].y; }
+  // Every product and rounding is written out: left to the compiler, which of a rotation's two products is rounded first, and
+  // whether a binary16 result passes through fp32, differs from one instantiation to the next, and a node's K row with it.
+  __device__ inline float low(float x, float y, int i) const { return fmaf(x, cos(i), -(y * sin(i))); }
+  __device__ inline float high(float x, float y, int i) const { return fmaf(y, cos(i), x * sin(i)); }
   __device__ inline void rotate(float (&lo)[F], float (&hi)[F]) const {
 #pragma unroll
     for (int i = 0; i < F; ++i) {
-      const float c = i & 1 ? cs[i >> 1].z : cs[i >> 1].x, sn = i & 1 ? cs[i >> 1].w : cs[i >> 1].y;
       const float x = lo[i], y = hi[i];
-      lo[i] = x * c - y * sn;
-      hi[i] = y * c + x * sn;
+      lo[i] = low(x, y, i), hi[i] = high(x, y, i);
+    }
+  }
+  // rotated pairs as E, two to a word.  (KEY: the upper features through fp32, as K rows have always had them.)
+  template <typename E, bool KEY>
+  __device__ inline void rotate_to(const float (&x)[F], const float (&y)[F], uint32_t (&lo)[F / 2], uint32_t (&hi)[F / 2]) const {
+#pragma unroll
+    for (int i = 0; i < F; i += 2) {
+      lo[i / 2] = Elem16<E>::fma_pack2(x[i], cos(i), -(y[i] * sin(i)), x[i + 1], cos(i + 1), -(y[i + 1] * sin(i + 1)));
+      if constexpr (KEY) {
+        float h0 = high(x[i], y[i], i), h1 = high(x[i + 1], y[i + 1], i + 1);
+        asm("" : "+v"(h0), "+v"(h1));
+        hi[i / 2] = Elem16<E>::pack2(h0, h1);
+      } else {
+        hi[i / 2] = Elem16<E>::fma_pack2(y[i], cos(i), x[i] * sin(i), y[i + 1], cos(i + 1), x[i + 1] * sin(i + 1));
+      }
     }
   }
 };
-// F elements as E to LDS (8 bytes at a time where F is 4)
-template <typename E, int F>
-__device__ inline void stage(uint8_t* dst, const float (&v)[F]) {
-  if constexpr (F == 4) {
-    *reinterpret_cast<uint2*>(dst) = uint2{Elem16<E>::pack2(v[0], v[1]), Elem16<E>::pack2(v[2], v[3])};
+// F elements, two to a word, to LDS (8 bytes at a time where F is 4)
+template <int N>
+__device__ inline void stage(uint8_t* dst, const uint32_t (&w)[N]) {
+  if constexpr (N == 2) {
+    *reinterpret_cast<uint2*>(dst) = uint2{w[0], w[1]};
   } else {
 #pragma unroll
-    for (int i = 0; i < F; i += 8) *reinterpret_cast<u32x4*>(dst + 2 * i) = pack8<E>(v + i);
+    for (int i = 0; i < N; i += 4) *reinterpret_cast<u32x4*>(dst + 4 * i) = u32x4{w[i], w[i + 1], w[i + 2], w[i + 3]};
   }
 }
 
@@ -231,15 +244,16 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
     RowSums<kQF> qs;
     RopeRow<kQF> q_rope;
     auto stage_q = [&]() {
-      float lo[kQF], hi[kQF];
-      qs.sum(qkv, lo, hi);
-      q_rope.rotate(lo, hi);
+      float x[kQF], y[kQF];
+      uint32_t lo[kQF / 2], hi[kQF / 2];
+      qs.sum(qkv, x, y);
+      q_rope.template rotate_to<E, false>(x, y, lo, hi);
       uint8_t* dst = q_lds + q_row * kQRow + 2 * q_f0;
-      stage<E>(dst, lo);
-      stage<E>(dst + 128, hi);
+      stage(dst, lo);
+      stage(dst + 128, hi);
       if constexpr (TQ == 15) {  // the padding columns of the operand: copies
-        stage<E>(dst + 16 * kQRow, lo);
-        stage<E>(dst + 16 * kQRow + 128, hi);
+        stage(dst + 16 * kQRow, lo);
+        stage(dst + 16 * kQRow + 128, hi);
       }
     };
     if (has_tree) {
@@ -253,37 +267,49 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
       __builtin_amdgcn_sched_barrier(0);
       uint8_t* k_dst = k_lds + kv_row * kQRow;
       uint8_t* v_dst = v_lds + kv_row * kQRow;
-      auto stage_row = [&](uint8_t* dst, const float (&lo)[kKvF], const float (&hi)[kKvF]) {
-        if constexpr (Q8) {
-          // the row's scale: the largest magnitude over its 4 threads, then codes of this thread's 2 x 16 features
-          float am = 0.f;
+      // an 8-bit row: its scale, from the largest magnitude over its 4 threads, and the codes of this thread's 2 x 16 features
+      auto stage_codes = [&](uint8_t* dst, const float (&lo)[kKvF], const float (&hi)[kKvF]) {
+        float am = 0.f;
 #pragma unroll
-          for (int i = 0; i < kKvF; ++i) am = fmaxf(am, fmaxf(fabsf(lo[i]), fabsf(hi[i])));
-          am = fmaxf(am, __shfl_xor(am, 1, 64));
-          am = fmaxf(am, __shfl_xor(am, 2, 64));
-          const float sc = kv8_scale_of(am);
+        for (int i = 0; i < kKvF; ++i) am = fmaxf(am, fmaxf(fabsf(lo[i]), fabsf(hi[i])));
+        am = fmaxf(am, __shfl_xor(am, 1, 64));
+        am = fmaxf(am, __shfl_xor(am, 2, 64));
+        const float sc = kv8_scale_of(am);
 #pragma unroll
-          for (int i = 0; i < kKvF; i += 4) {
-            *reinterpret_cast<uint32_t*>(dst + kv_f0 + i) = kv8_pack4(lo[i], lo[i + 1], lo[i + 2], lo[i + 3], sc);
-            *reinterpret_cast<uint32_t*>(dst + 64 + kv_f0 + i) = kv8_pack4(hi[i], hi[i + 1], hi[i + 2], hi[i + 3], sc);
-          }
-          if (kv_f0 == 0) *reinterpret_cast<float*>(dst + 128) = sc;
-        } else {
-          stage<E>(dst + 2 * kv_f0, lo);
-          stage<E>(dst + 128 + 2 * kv_f0, hi);
+        for (int i = 0; i < kKvF; i += 4) {
+          *reinterpret_cast<uint32_t*>(dst + kv_f0 + i) = kv8_pack4(lo[i], lo[i + 1], lo[i + 2], lo[i + 3], sc);
+          *reinterpret_cast<uint32_t*>(dst + 64 + kv_f0 + i) = kv8_pack4(hi[i], hi[i + 1], hi[i + 2], hi[i + 3], sc);
         }
+        if (kv_f0 == 0) *reinterpret_cast<float*>(dst + 128) = sc;
+      };
+      auto stage_words = [&](uint8_t* dst, const uint32_t (&lo)[kKvF / 2], const uint32_t (&hi)[kKvF / 2]) {
+        stage(dst + 2 * kv_f0, lo);
+        stage(dst + 128 + 2 * kv_f0, hi);
       };
       {
-        float lo[kKvF], hi[kKvF];
-        ks.sum(qkv, lo, hi);
-        k_rope.rotate(lo, hi);
-        stage_row(k_dst, lo, hi);
+        float x[kKvF], y[kKvF];
+        ks.sum(qkv, x, y);
+        if constexpr (Q8) {
+          k_rope.rotate(x, y);
+          stage_codes(k_dst, x, y);
+        } else {
+          uint32_t lo[kKvF / 2], hi[kKvF / 2];
+          k_rope.template rotate_to<E, true>(x, y, lo, hi);
+          stage_words(k_dst, lo, hi);
+        }
       }
       stage_q();
       {
-        float lo[kKvF], hi[kKvF];
-        vs.sum(qkv, lo, hi);
-        stage_row(v_dst, lo, hi);
+        float x[kKvF], y[kKvF];
+        vs.sum(qkv, x, y);
+        if constexpr (Q8) {
+          stage_codes(v_dst, x, y);
+        } else {
+          uint32_t lo[kKvF / 2], hi[kKvF / 2];
+#pragma unroll
+          for (int i = 0; i < kKvF; i += 2) lo[i / 2] = Elem16<E>::pack2(x[i], x[i + 1]), hi[i / 2] = Elem16<E>::pack2(y[i], y[i + 1]);
+          stage_words(v_dst, lo, hi);
+        }
       }
       if (n_mine > 0) load_kv(first, kb[0], vb[0]);
     } else {

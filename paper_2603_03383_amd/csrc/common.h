@@ -131,6 +131,10 @@ struct Elem16<bf16_t> {
     typedef __bf16 v2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{a, b}, v2));
   }
+  // a[i] * b[i] + c[i]
+  __device__ static inline uint32_t fma_pack2(float a0, float b0, float c0, float a1, float b1, float c1) {
+    return pack2(fmaf(a0, b0, c0), fmaf(a1, b1, c1));
+  }
   __device__ static inline float lo(uint32_t w) { return __uint_as_float(w << 16); }
   __device__ static inline float hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
   __device__ static inline uint32_t from_fp8x2(uint32_t src, bool hi_word) {  // two E4M3 codes -> two elements (exact)
@@ -148,6 +152,13 @@ struct Elem16<f16_t> {
   typedef _Float16 h2 __attribute__((ext_vector_type(2)));
   __device__ static inline uint32_t pack2(float a, float b) {
     return __builtin_bit_cast(uint32_t, h2{(_Float16)a, (_Float16)b});
+  }
+  // a[i] * b[i] + c[i], rounded once.  (For a conversion of fmaf the compiler takes either these instructions or a fused multiply-add
+  // and a conversion, which round twice, as it sees fit.)
+  __device__ static inline uint32_t fma_pack2(float a0, float b0, float c0, float a1, float b1, float c1) {
+    uint32_t w;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3\n\tv_fma_mixhi_f16 %0, %4, %5, %6" : "=&v"(w) : "v"(a0), "v"(b0), "v"(c0), "v"(a1), "v"(b1), "v"(c1));
+    return w;
   }
   __device__ static inline float lo(uint32_t w) { return (float)__builtin_bit_cast(h2, w).x; }
   __device__ static inline float hi(uint32_t w) { return (float)__builtin_bit_cast(h2, w).y; }
