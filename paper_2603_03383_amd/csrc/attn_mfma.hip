@@ -504,19 +504,52 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
         }
     }
   };
+  // Stores the tree's rows of block blk and nothing else: other slots of the block may be written from another stream meanwhile.
   auto write_tree = [&](int blk, const u32x4 (&kd)[8], const u32x4 (&vd)[8]) {
     u32x4* kw = const_cast<u32x4*>(kp) + (int64_t)blk * kBlkPieces;
     u32x4* vw = const_cast<u32x4*>(vp) + (int64_t)blk * kBlkPieces;
-    const bool mine = (unsigned)(blk * 32 - S + qi) < (unsigned)TQ;
+    const int n0 = blk * 32 - S;
+    const bool mine = (unsigned)(n0 + qi) < (unsigned)TQ;
     if (mine) {
 #pragma unroll
       for (int i = 0; i < (Q8 ? 4 : 8); ++i) kw[i * 64] = kd[i];
     }
+    if (n0 >= 0 && n0 + 32 <= TQ) {  // every key of the block is a node
 #pragma unroll
-    for (int i = 0; i < (Q8 ? 4 : 8); ++i) vw[i * 64] = vd[i];
+      for (int i = 0; i < (Q8 ? 4 : 8); ++i) vw[i * 64] = vd[i];
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {  // the lane's keys 8 j + 4 gh .. + 3 lie together, in word j of a unit or in a pair of words
+        const int node = n0 + 8 * j + 4 * gh;
+        if (node >= 0 && node + 4 <= TQ) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            if constexpr (Q8) {
+              reinterpret_cast<uint32_t*>(vw + t * 64)[j] = vd[t][j];
+            } else {
+              const u32x4 v = vd[2 * t + (j >> 1)];
+              reinterpret_cast<uint2*>(vw + (2 * t + (j >> 1)) * 64)[j & 1] = j & 1 ? uint2{v.z, v.w} : uint2{v.x, v.y};
+            }
+          }
+        } else {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            if ((unsigned)(node + c) < (unsigned)TQ) {
+#pragma unroll
+              for (int t = 0; t < 4; ++t) {
+                if constexpr (Q8)
+                  reinterpret_cast<uint8_t*>(vw + t * 64)[4 * j + c] = (uint8_t)(vd[t][j] >> (8 * c));
+                else
+                  reinterpret_cast<uint16_t*>(vw + (2 * t + (j >> 1)) * 64)[4 * (j & 1) + c] =
+                      (uint16_t)(vd[2 * t + (j >> 1)][2 * (j & 1) + (c >> 1)] >> (16 * (c & 1)));
+              }
+            }
+        }
+      }
+    }
     if constexpr (Q8) {  // scales: lane gh = 0 of a key
       if (mine && gh == 0) {
-        const int row = (blk * 32 - S + qi) * kQRow;
+        const int row = (n0 + qi) * kQRow;
         reinterpret_cast<uint32_t*>(kw - lane + 256)[qi] = *reinterpret_cast<const uint32_t*>(k_lds + row + 128);
         reinterpret_cast<uint32_t*>(vw - lane + 256)[qi] = *reinterpret_cast<const uint32_t*>(v_lds + row + 128);
       }
@@ -541,7 +574,7 @@ __global__ void __launch_bounds__(256, NU == 1 ? 2 : 1)
     if (tail) {  // (block `last` is in the first buffer: the loop's last load repeats it)
       if (has_tree) {
         put_tree(last, kb[0], vb[0]);
-        // one of the workgroups that hold these rows writes them: whole units, prefix keys in them as they were read
+        // one of the workgroups that hold these rows writes them
         if (h % g.group == 0 && q0 == 0) write_tree(last, kb[0], vb[0]);
       }
       process(last, kb[0], vb[0], std::true_type{});

@@ -1,12 +1,15 @@
-"""The tree's own K and V rows in the fused tree attention: they enter the product from LDS and reach the cache as whole 1 KiB units
-that may also hold prefix keys or slots behind the tree.  Lengths that put the first and last tree slot on every kind of place in
+"""The tree's own K and V rows in the fused tree attention: they enter the product from LDS and reach the cache, whose 1 KiB units
+may also hold prefix keys or slots behind the tree.  Lengths that put the first and last tree slot on every kind of place in
 a block of 32 keys; sequences beside each other; more partial-sum slots than are requested together (narrow models); grouped heads
 (one workgroup of a group writes); both numbers of queries per workgroup.  Output, tree rows and the untouched prefix rows are
-checked; bounds: the layer parity tests'."""
+checked; bounds: the layer parity tests'.  Slots behind the tree keep their bytes, also those that another stream writes during the
+pass."""
 import pytest
+import torch
 
 import paper_2603_03383_amd as P
 import workload as W
+from tests import gpu_util as G
 from tests.test_gpu_kv8 import check_layer_kv8
 from tests.test_gpu_parity import _check_layer, _layer_case
 
@@ -45,3 +48,69 @@ def test_layer_rows_with_64_queries_per_workgroup():
 
 def test_the_narrow_models_have_more_slots_than_are_requested_together():
     assert P.medusa_gemm_plan(P.MDZ_BF16, 64, 3 * 512, 512, 12)["max_slots"] > 2
+
+
+FORMATS = [(W.TREE15, "bf16", ""), (W.TREE64, "bf16", ""), (W.TREE64, "fp16", ""), (W.TREE64, "bf16", "fp8e4m3")]
+
+
+def _pass_over_a_full_cache(tree, dtype, quant, max_prefix, kv_heads=2, n_heads=4, behind=40):
+    """A layer call over one sequence per length of EDGES, every slot of the cache holding a row; and those rows as read back."""
+    w = _w(tree, dtype, n_heads, n_kv_heads=kv_heads)
+    dm = G.device_model(w.with_(vocab=64), heads=False, n_layers=1)
+    T, B = dm.tree_info["T"], len(EDGES)
+    cap = max_prefix + T + behind
+    kv = P.DeviceKV(dm, B, cap, n_layers=1, quant=quant)
+    gen = torch.Generator(G.DEV).manual_seed(5)
+    rows = lambda n: torch.empty(kv_heads, n, 128, device=G.DEV).normal_(generator=gen).to(dm.tdtype)  # noqa: E731
+    for b in range(B):
+        kv.write(0, b, 0, rows(cap), rows(cap))
+    before = [kv.read(0, b, 0, cap) for b in range(B)]
+    x = W.hidden_state(w, "full_x", B * T, device=G.DEV).float()
+    lens = torch.tensor(EDGES, dtype=torch.int32, device=G.DEV)
+    ws = dm.workspace(B, max_prefix)
+
+    def run():
+        P.tree_verify_layer(dm.desc, dm.layer(0), 0, x.clone(), kv.desc, lens, B, max_prefix, ws)
+    return kv, T, before, run, rows
+
+
+@pytest.mark.parametrize("max_prefix", [97, 14400], ids=["32 queries", "64 queries"])
+@pytest.mark.parametrize("tree,dtype,quant", FORMATS, ids=lambda v: getattr(v, "name", v))
+def test_slots_outside_the_tree_keep_their_bytes(tree, dtype, quant, max_prefix):
+    kv, T, before, run, _ = _pass_over_a_full_cache(tree, dtype, quant, max_prefix)
+    run()
+    torch.cuda.synchronize()
+    for b, S in enumerate(EDGES):
+        for old, new in zip(before[b], kv.read(0, b, 0, before[b][0].shape[1])):
+            assert torch.equal(old[:, :S], new[:, :S]) and torch.equal(old[:, S + T:], new[:, S + T:])
+            assert not torch.equal(old[:, S:S + T], new[:, S:S + T])
+
+
+@pytest.mark.parametrize("tree,dtype,quant", FORMATS, ids=lambda v: getattr(v, "name", v))
+def test_rows_written_behind_the_tree_during_a_pass_stay(tree, dtype, quant):
+    behind = 40
+    kv, T, before, run, rows = _pass_over_a_full_cache(tree, dtype, quant, 97, behind=behind)
+    run()
+    torch.cuda.synchronize()
+    tree_rows = [[t.clone() for t in kv.read(0, b, S, T)] for b, S in enumerate(EDGES)]
+    side = torch.cuda.Stream()
+    kept = []
+    for _ in range(4):
+        new = [(rows(behind), rows(behind)) for _ in EDGES]
+        kept.append(new)
+        torch.cuda.synchronize()
+        for i in range(6):
+            run()
+            with torch.cuda.stream(side):
+                for b, S in enumerate(EDGES[2 * i:2 * i + 2], 2 * i):
+                    P.medusa_kv_write(kv.desc, 0, b, S + T, behind, *new[b])
+        torch.cuda.synchronize()
+        ref = P.DeviceKV(kv.model, len(EDGES), behind, n_layers=1, quant=quant)
+        for b, S in enumerate(EDGES):
+            ref.write(0, b, 0, *new[b])
+            for got, want in zip(kv.read(0, b, S + T, behind), ref.read(0, b, 0, behind)):
+                assert torch.equal(got, want)
+            for got, want in zip(kv.read(0, b, S, T), tree_rows[b]):
+                assert torch.equal(got, want)
+            for got, want in zip(kv.read(0, b, 0, S + T), before[b]):
+                assert torch.equal(got[:, :S], want[:, :S])
