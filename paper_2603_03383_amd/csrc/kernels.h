@@ -96,9 +96,6 @@ int launch_argmax_merge(const ArgCand* cand, int rows, int n_cand, int32_t* out,
 int launch_argmax(const float* logits, int rows, int V, int64_t ld, int32_t* out, void* scratch, int64_t scratch_bytes,
                   hipStream_t st);
 int64_t topk_scratch_bytes(int rows);
-// out[r][0..k) = indices of the k largest of logits[r][:], descending, ties -> lower index
-int launch_topk(const float* logits, int rows, int V, int64_t ld, int k, int32_t* out, int64_t out_ld, void* scratch,
-                int64_t scratch_bytes, hipStream_t st);
 // Candidate selection of all heads at once from logits [B][K+1][V] (row 0 of a sequence: the base LM head, used
 // only when root_token is NULL): fills cand_flat [B][n_cand].  (scratch as for launch_argmax)
 int launch_heads_select(int tree, const float* logits, int B, int V, const int32_t* root_token, int32_t* cand_flat,

@@ -71,25 +71,23 @@ int launch_argmax_merge(const ArgCand* cand, int rows, int n_cand, int32_t* out,
   return MDZ_OK;
 }
 
-// Rows come in two flavours: uniform (every row the same k, picks to out + row * out_ld) and heads (row (b, j) of
+// Rows come in two flavours: uniform (the best element of every row, to out[row]) and heads (row (b, j) of
 // logits [B][K+1][V]: j = 0 the base LM head, whose argmax is the root candidate unless the caller gave root
 // tokens, j = 1..K Medusa head j with its own k = caps[j-1]; picks go straight to the row's segment of
 // cand_flat [B][n_cand] = [root | head 1 | .. | head K]: one launch, or one pair, for all heads of all sequences).
 struct SelRows {
   int tree;        // >= 0: heads flavour over this tree; -1: uniform
-  int k;           // uniform: picks per row
-  int64_t ld;      // uniform: row stride of the logits (heads: V)
-  int64_t out_ld;  // uniform: row stride of the output
+  int64_t ld;      // row stride of the logits
   bool have_root;  // heads: the caller supplies the root candidates
 };
 __device__ inline int sel_row_k(const SelRows& rs, int row) {
-  if (rs.tree < 0) return rs.k;
+  if (rs.tree < 0) return 1;
   const TreeTables& t = c_trees[rs.tree];
   const int j = row % (t.K + 1);
   return j == 0 ? (rs.have_root ? 0 : 1) : t.caps[j - 1];
 }
 __device__ inline int32_t* sel_row_out(const SelRows& rs, int row, int32_t* out) {
-  if (rs.tree < 0) return out + (int64_t)row * rs.out_ld;
+  if (rs.tree < 0) return out + row;
   const TreeTables& t = c_trees[rs.tree];
   const int b = row / (t.K + 1), j = row % (t.K + 1);
   int seg = 0;  // start of row j's segment in the flat candidate buffer
@@ -103,7 +101,7 @@ __device__ inline int32_t* sel_row_out(const SelRows& rs, int row, int32_t* out)
 __global__ void __launch_bounds__(256) topk_kernel(SelRows rs, const float* __restrict__ logits, int V,
                                                    const int32_t* __restrict__ root_token, int32_t* __restrict__ out) {
   __shared__ Best red[4];
-  const float* row = logits + (int64_t)blockIdx.x * (rs.tree < 0 ? rs.ld : (int64_t)V);
+  const float* row = logits + blockIdx.x * rs.ld;
   const int k = sel_row_k(rs, blockIdx.x);
   int32_t* dst = sel_row_out(rs, blockIdx.x, out);
   if (k == 0) {  // the root candidate is the caller's token
@@ -145,7 +143,7 @@ __global__ void __launch_bounds__(256) topk_stage1_kernel(SelRows rs, const floa
   const int k = sel_row_k(rs, row);
   if (chunk >= n_chunks || k == 0) return;
   const int c0 = chunk * kSelWaveCols;
-  const float* src = logits + (int64_t)row * (rs.tree < 0 ? rs.ld : (int64_t)V);
+  const float* src = logits + row * rs.ld;
   float v[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -231,19 +229,8 @@ static int launch_two_stage(const SelRows& rs, const float* logits, int rows, in
   int32_t* ci = (int32_t*)(cv + (int64_t)rows * n_chunks * kSelMaxK);
   topk_stage1_kernel<<<dim3((n_chunks + 3) / 4, rows), 256, 0, st>>>(rs, logits, V, n_chunks, cv, ci);
   MDZ_LAUNCH_CHECK();
-  const int kmax = rs.tree < 0 ? rs.k : kSelMaxK;
+  const int kmax = rs.tree < 0 ? 1 : kSelMaxK;
   topk_stage2_kernel<<<rows, 64, (size_t)n_chunks * kmax * 8, st>>>(rs, cv, ci, n_chunks, root_token, out);
-  MDZ_LAUNCH_CHECK();
-  return MDZ_OK;
-}
-
-int launch_topk(const float* logits, int rows, int V, int64_t ld, int k, int32_t* out, int64_t out_ld, void* scratch,
-                int64_t scratch_bytes, hipStream_t st) {
-  ProfScope prof_(PROF_SELECT, st);
-  if (rows == 0 || k == 0) return MDZ_OK;
-  if (two_stage_ok(rows, V, k, scratch, scratch_bytes))
-    return launch_two_stage(SelRows{-1, k, ld, out_ld, false}, logits, rows, V, nullptr, out, scratch, st);
-  topk_kernel<<<rows, 256, 0, st>>>(SelRows{-1, k, ld, out_ld, false}, logits, V, nullptr, out);
   MDZ_LAUNCH_CHECK();
   return MDZ_OK;
 }
@@ -256,7 +243,7 @@ int launch_heads_select(int tree, const float* logits, int B, int V, const int32
   if (rows == 0) return MDZ_OK;
   int kmax = 1;
   for (int k = 0; k < t->K; ++k) kmax = t->caps[k] > kmax ? t->caps[k] : kmax;
-  const SelRows rs{tree, 0, 0, 0, root_token != nullptr};
+  const SelRows rs{tree, V, root_token != nullptr};
   if (two_stage_ok(rows, V, kmax, scratch, scratch_bytes)) return launch_two_stage(rs, logits, rows, V, root_token, cand_flat, scratch, st);
   topk_kernel<<<rows, 256, 0, st>>>(rs, logits, V, root_token, cand_flat);
   MDZ_LAUNCH_CHECK();
@@ -265,7 +252,13 @@ int launch_heads_select(int tree, const float* logits, int B, int V, const int32
 
 int launch_argmax(const float* logits, int rows, int V, int64_t ld, int32_t* out, void* scratch, int64_t scratch_bytes,
                   hipStream_t st) {
-  return launch_topk(logits, rows, V, ld, 1, out, 1, scratch, scratch_bytes, st);
+  ProfScope prof_(PROF_SELECT, st);
+  if (rows == 0) return MDZ_OK;
+  const SelRows rs{-1, ld, false};
+  if (two_stage_ok(rows, V, 1, scratch, scratch_bytes)) return launch_two_stage(rs, logits, rows, V, nullptr, out, scratch, st);
+  topk_kernel<<<rows, 256, 0, st>>>(rs, logits, V, nullptr, out);
+  MDZ_LAUNCH_CHECK();
+  return MDZ_OK;
 }
 
 __global__ void tree_tokens_kernel(int tree, const int32_t* __restrict__ cand_flat, int32_t* __restrict__ tree_tokens,
