@@ -7,9 +7,10 @@
 //     registers: three half stages (CK/2 input features each) stay in flight while it multiplies the
 //     fourth, and every load is unconditional so the hardware wait counters let the prefetch overlap
 //     the MFMAs (a CU then keeps ~100 KB in flight, what the HBM latency asks for).  AHEAD = 2 keeps two: with every CU streaming and
-//     nothing but the stream to wait for (up to 32 rows, several whole bands per workgroup: the heads' vocabulary matrices) fewer
-//     requests queue up in front of the memory: four heads from one row 700 / 691 us per call, eight rows 705 / 696; on 172 or
-//     192 workgroups, and at 64 rows, it loses 2 us per launch or changes nothing.
+//     nothing but the stream to wait for (up to 32 rows, several whole bands per workgroup: the vocabulary matrices of the heads, and
+//     that of a verify pass that writes logits) fewer requests queue up in front of the memory: four heads from one row 683 / 672 us
+//     per call, eight rows 702 / 693, sixteen 730 / 726; a one-layer pass with logits, one row 264 / 261, eight 270 / 269, 15 rows 282
+//     / 281, 30 and 32 rows the same; on 172 or 192 workgroups, and at 64 rows, it loses 2 us per launch or changes nothing.
 //   * W is loaded non-temporally: every weight is used once per pass, and a read stream that does not ask the caches to keep it
 //     runs faster on this card (1 GiB over 256 workgroups 6.1 / 6.8 TB/s, 100 MB launches 5.5 / 5.9).  us, plain / non-temporal
 //     loads: four Medusa heads from one row 763 / 700, a layer at 64 rows 125 / 118.5, a 32-layer step at 1K 4057 / 3977,
@@ -422,27 +423,22 @@ static int launch_gemm_mfma_t(const void* X, const void* Wp, float* P, int M, in
   gemm_mfma_describe(M, N, K, max_split, res, nullptr);
   const E* x = (const E*)X;
   const E* w = (const E*)Wp;
-  if (p.whole && p.wpb == 4 && p.nt == 1 && p.mt == 1 && p.ck == 128 && bands >= 2 * num_cus()) {
-    constexpr int lds_bytes = 2 * 32 * (128 * 2 + 16);
-    MDZ_SET_LDS_ONCE((gemm_mfma_kernel<4, 1, 1, 128, E, false, false, 2>), lds_bytes);
-    launch_timed(tag, gemm_mfma_kernel<4, 1, 1, 128, E, false, false, 2>, p.grid, 256, lds_bytes, st, x, M, K, w, n_tiles, n_stages, P, ldp,
-                 part_stride, p.whole, nullptr, nullptr);
-    MDZ_LAUNCH_CHECK();
-    return MDZ_OK;
-  }
-#define MDZ_GEMM_CASE(WPB, NT, MT, CK)                                                                       \
-  if (p.wpb == WPB && p.nt == NT && p.mt == MT && p.ck == CK) {                                              \
+  // half stages of W in flight: see AHEAD at the top
+  const int ahead = p.whole && p.wpb == 4 && p.mt == 1 && p.ck == 128 && bands >= 2 * num_cus() ? 2 : 3;
+#define MDZ_GEMM_CASE(WPB, NT, MT, CK, AHEAD)                                                                \
+  if (p.wpb == WPB && p.nt == NT && p.mt == MT && p.ck == CK && ahead == AHEAD) {                            \
     constexpr int lds_bytes = 2 * MT * 32 * (CK * 2 + 16);                                                   \
-    MDZ_SET_LDS_ONCE((gemm_mfma_kernel<WPB, NT, MT, CK, E>), lds_bytes);                                     \
-    launch_timed(tag, gemm_mfma_kernel<WPB, NT, MT, CK, E>, p.grid, WPB * 64, lds_bytes, st, x, M, K, w, n_tiles, \
-                 n_stages, P, ldp, part_stride, p.whole, nullptr, nullptr);                                       \
+    MDZ_SET_LDS_ONCE((gemm_mfma_kernel<WPB, NT, MT, CK, E, false, false, AHEAD>), lds_bytes);                \
+    launch_timed(tag, gemm_mfma_kernel<WPB, NT, MT, CK, E, false, false, AHEAD>, p.grid, WPB * 64, lds_bytes, st, x, M, K, w, n_tiles, \
+                 n_stages, P, ldp, part_stride, p.whole, nullptr, nullptr);                                  \
   } else
-  MDZ_GEMM_CASE(4, 1, 2, 128)
-  MDZ_GEMM_CASE(4, 1, 1, 128)
-  MDZ_GEMM_CASE(2, 1, 2, 128)
-  MDZ_GEMM_CASE(2, 1, 1, 128)
-  MDZ_GEMM_CASE(4, 1, 2, 256)
-  MDZ_GEMM_CASE(4, 1, 1, 256) {
+  MDZ_GEMM_CASE(4, 1, 2, 128, 3)
+  MDZ_GEMM_CASE(4, 1, 1, 128, 2)
+  MDZ_GEMM_CASE(4, 1, 1, 128, 3)
+  MDZ_GEMM_CASE(2, 1, 2, 128, 3)
+  MDZ_GEMM_CASE(2, 1, 1, 128, 3)
+  MDZ_GEMM_CASE(4, 1, 2, 256, 3)
+  MDZ_GEMM_CASE(4, 1, 1, 256, 3) {
     MDZ_FAIL(MDZ_EUNSUPPORTED, "gemm: no kernel for plan %d,%d,%d,%d", p.wpb, p.nt, p.mt, p.ck);
   }
 #undef MDZ_GEMM_CASE
