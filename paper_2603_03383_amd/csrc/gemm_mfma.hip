@@ -25,9 +25,11 @@
 //     to numbered slots of a workspace and the consumer adds slots 0..count-1 in that fixed order, so the
 //     result is deterministic (no floating-point atomics).
 //   * SWIGLU (the gate/up matrix, whose gate and up tiles alternate in the packed order, run with whole bands per
-//     workgroup): waves 0/2 hold the gate columns and waves 1/3 the up columns of the same 32 features; at the end of
-//     a band the two exchange half of their sums through LDS and SiLU(gate) * up is written as E, so neither the
-//     fp32 sums nor a second kernel are needed.
+//     workgroup): a wave's 32 columns are 16 gate and the 16 up columns of the same features, picked by the lanes' addresses, so
+//     SiLU(gate) * up needs one exchange between lanes and is written as E: neither the fp32 sums nor a second kernel are needed.
+//     What bounds such a launch is that the vector memory path of a CU returns in order and holds some 32 KiB of requests: X (L2
+//     hits) and W (HBM) together come in at ~52 GB/s, so the CUs that a launch leaves idle are lost.  A workgroup therefore takes as
+//     few waves of 32 columns as still leave one workgroup per CU (swiglu_waves).
 //   * ARGMAX (the LM head of a verify pass, whole bands per workgroup, when the caller wants no logits): at the end
 //     of a band a wave turns its 64 x 32 sums through LDS so that lane m holds row m, scans the 32 columns and keeps
 //     the row's best (value, column) so far in two registers; at the end of its range it writes one candidate per
@@ -46,13 +48,14 @@ __global__ void __launch_bounds__(WPB * 64)
     gemm_mfma_kernel(const E* __restrict__ X, int M, int K, const E* __restrict__ Wp, int n_tiles,
                      int n_stages, float* __restrict__ P, int64_t ldp, int64_t part_stride, int whole_bands,
                      E* __restrict__ Uout = nullptr, ArgCand* __restrict__ cand = nullptr) {
-  static_assert(!SWIGLU || (WPB == 4 && NT == 1), "the SwiGLU epilogue pairs waves 0/1 and 2/3");
+  static_assert(!SWIGLU || NT == 1, "the SwiGLU epilogue finishes one set of 32 columns per wave");
   static_assert(AHEAD == 3 || AHEAD == 2, "half stages requested ahead");
   static_assert(!ARGMAX || (NT == 1 && !SWIGLU), "the argmax epilogue scans one tile per wave");
   constexpr int ROWS = MT * 32;
   constexpr int KH = CK / 32;                       // MFMA k-steps per half stage
   constexpr int LROW = CK * 2 + 16;                 // bytes per staged X row (16 B pad)
-  constexpr int XL = ROWS * (CK / 8) / (WPB * 64);  // 16-byte X loads per thread per stage
+  constexpr int XN = ROWS * (CK / 8);               // 16-byte pieces of a stage of X
+  constexpr int XL = (XN + WPB * 64 - 1) / (WPB * 64);  // X loads per thread per stage (three waves: the last ones repeat a piece)
   extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];  // 2 stages of ROWS x LROW bytes
   uint8_t(*lds)[ROWS * LROW] = reinterpret_cast<uint8_t(*)[ROWS * LROW]>(lds_raw);
 
@@ -106,6 +109,10 @@ __global__ void __launch_bounds__(WPB * 64)
   int lb = u_lo / n_stages, lc = u_lo % n_stages, lh = 0, l_left = 2 * (u_hi - u_lo) - 1;  // advances left
   int xc = lc, x_left = u_hi - u_lo - 1;
   int cb = lb, cc = lc;
+  auto x_piece = [&](int i) {
+    const int idx = threadIdx.x + i * (WPB * 64);
+    return XN % (WPB * 64) == 0 || idx < XN ? idx : XN - 1;
+  };
   auto load_x = [&]() {  // loads the X columns of the stage under the X cursor, then advances it
     const int c = xc;
     const int adv = x_left > 0;
@@ -113,7 +120,7 @@ __global__ void __launch_bounds__(WPB * 64)
     xc = (xc + adv == n_stages) ? 0 : xc + adv;
 #pragma unroll
     for (int i = 0; i < XL; ++i) {
-      int idx = threadIdx.x + i * (WPB * 64);
+      int idx = x_piece(i);
       int row = idx / (CK / 8), col = idx % (CK / 8);
       int rr = row < M ? row : M - 1;
       xr[i] = *reinterpret_cast<const u32x4*>(X + (int64_t)rr * K + (int64_t)c * CK + col * 8);
@@ -122,7 +129,7 @@ __global__ void __launch_bounds__(WPB * 64)
   auto store_x = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < XL; ++i) {
-      int idx = threadIdx.x + i * (WPB * 64);
+      int idx = x_piece(i);
       int row = idx / (CK / 8), col = idx % (CK / 8);
       *reinterpret_cast<u32x4*>(&lds[buf][row * LROW + col * 16]) = xr[i];
     }
@@ -142,8 +149,11 @@ __global__ void __launch_bounds__(WPB * 64)
       tile = tile < n_tiles ? tile : 0;
       // packed order [band of 4 tiles][stage of 256 features][tile in band][16 k-steps][lane]
       const int st = CK == 256 ? c : (c >> 1), kin0 = (CK == 256 ? 0 : (c & 1) * 8) + hf * KH;
-      const int64_t unit = (((int64_t)(tile >> 2) * nst256 + st) * kBandTiles + (tile & 3)) * 16 + kin0;
-      const u32x4* p = reinterpret_cast<const u32x4*>(Wp) + unit * 64 + lane;
+      // (SWIGLU: half tile & 1 of the gate tile's and of the up tile's rows; the up tile follows 16 KiB after the gate tile)
+      const int t0 = SWIGLU ? tile & ~1 : tile;
+      const int64_t unit = (((int64_t)(t0 >> 2) * nst256 + st) * kBandTiles + (t0 & 3)) * 16 + kin0;
+      const u32x4* p = reinterpret_cast<const u32x4*>(Wp) + unit * 64 +
+                       (SWIGLU ? (tile & 1) * 16 + (lane & 15) + (lane & 16) * 64 + (lane & 32) : lane);
 #pragma unroll
       for (int ks = 0; ks < KH; ++ks) dst[nt][ks] = __builtin_nontemporal_load(p + ks * 64);
     }
@@ -168,30 +178,24 @@ __global__ void __launch_bounds__(WPB * 64)
   auto flush = [&]() {
     const int b = cb;
     if constexpr (SWIGLU) {
-      // exchange buffer behind the two X stages: [pair][row][33] floats.  Each wave of a pair finishes one half of the rows (with the
-      // gate wave finishing all of them, the up wave idle meanwhile, 22016 x 4096 at 64 rows takes 37.5 us, now 36.4).
-      float* xch = reinterpret_cast<float*>(lds_raw + 2 * ROWS * LROW) + (wave >> 1) * ROWS * 33;
-      const int col = lane & 31, rbase = (lane >> 5) * 4;
-      const int own = wave & 1;  // the half of the rows that this wave finishes: 0 gate, 1 up
-      constexpr int HR = 8 * MT;  // registers of a half
-      auto half = [&](int which, int r) { return MT == 2 ? acc[0][which][r] : acc[0][0][8 * which + r]; };
-      auto row_of = [&](int which, int r) { return which * 16 * MT + 8 * (r >> 2) + rbase + (r & 3); };
-#pragma unroll
-      for (int r = 0; r < HR; ++r) xch[row_of(own ^ 1, r) * 33 + col] = own ? half(0, r) : half(1, r);
-      __syncthreads();
-      const int tile = b * WPB + (wave & ~1);  // the pair's gate tile; its features are 16 * tile .. + 31
-      if (tile + 1 < n_tiles) {
+      // Lane columns 0 .. 15 hold gate, 16 .. 31 up sums of the same features.  One exchange of two registers' 16-lane rows leaves a
+      // lane with gate and up of one row: register r for the lanes that held gate, r + 1 for the others.
+      const int tile = b * WPB + wave;  // the wave's features: 16 tile .. + 15
+      if (tile < n_tiles) {
         int F = n_tiles * 16;  // (M * F < 2^31: checked on the host; opaque so that the row offsets are not hoisted)
         asm volatile("" : "+s"(F));
-        E* urow = Uout + tile * 16 + col;
+        E* urow = Uout + tile * 16 + (lane & 15);
+        const int m0 = (lane >> 5) * 4 + ((lane >> 4) & 1);
 #pragma unroll
-        for (int r = 0; r < HR; ++r) {
-          const int m = row_of(own, r);
-          const float mine = own ? half(1, r) : half(0, r), other = xch[m * 33 + col];
-          if (m < M) urow[m * F] = from_float<E>(silu_mfma(own ? other : mine) * (own ? mine : other));
-        }
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int r = 0; r < 16; r += 2) {
+            const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[0][mt][r]), __float_as_uint(acc[0][mt][r + 1]), false, false);
+            const float gate = __uint_as_float(sw[0]), up = __uint_as_float(sw[1]);
+            const int m = mt * 32 + 8 * (r >> 2) + (r & 3) + m0;
+            if (m < M) urow[m * F] = from_float<E>(silu_mfma(gate) * up);
+          }
       }
-      __syncthreads();
       zero_acc();
       return;
     }
@@ -454,21 +458,31 @@ bool gemm_mfma_swiglu_supported(int dtype, int M, int N, int K) {
   return (bands >= kNumCU * 5 / 8 && bands <= kNumCU) || (bands > kNumCU && bands % kNumCU == 0);
 }
 
+// Waves (of 32 columns) per workgroup of that launch: three where that still is at most one workgroup per CU.  22016 x 4096 on 230
+// workgroups of three, 172 of four: 64 rows (a layer at 512 keys) 111.8 / 115.8 us, one row (a 32-layer step at 1K keys) 3328 / 3362.
+static int swiglu_waves(int M, int N) { return (N / 32 + 2) / 3 <= num_cus() ? 3 : 4; }
+
 template <typename E>
 static int launch_gemm_mfma_swiglu_t(const void* X, const void* Wp, void* U, int M, int N, int K, hipStream_t st) {
   const int tag = M <= 32 ? PROF_GEMM_W32 : PROF_GEMM_W64;
-  const int n_tiles = N / 32, n_stages = K / 128, bands = N / 128, kNumCU = num_cus();
+  const int wpb = swiglu_waves(M, N);
+  const int n_tiles = N / 32, n_stages = K / 128, bands = (n_tiles + wpb - 1) / wpb, kNumCU = num_cus();
   const int grid = bands < kNumCU ? bands : kNumCU;
   MDZ_REQUIRE((int64_t)bands * n_stages * grid < (int64_t)1 << 31 && (int64_t)M * N < (int64_t)1 << 31, MDZ_ESHAPE,
               "gemm: %d x %d units overflow", bands, n_stages);
-#define MDZ_SWIGLU_CASE(MT)                                                                                         \
-  {                                                                                                                  \
-    constexpr int lds_bytes = 2 * MT * 32 * (128 * 2 + 16) + 2 * MT * 32 * 33 * 4;                                   \
-    MDZ_SET_LDS_ONCE((gemm_mfma_kernel<4, 1, MT, 128, E, true>), lds_bytes);                                         \
-    launch_timed(tag, gemm_mfma_kernel<4, 1, MT, 128, E, true>, grid, 256, lds_bytes, st, (const E*)X, M, K,         \
-                 (const E*)Wp, n_tiles, n_stages, nullptr, 0, 0, 1, (E*)U, nullptr);                                  \
+#define MDZ_SWIGLU_CASE(WPB, MT)                                                                                     \
+  if (wpb == WPB && (M + 31) / 32 == MT) {                                                                           \
+    constexpr int lds_bytes = 2 * MT * 32 * (128 * 2 + 16);                                                          \
+    MDZ_SET_LDS_ONCE((gemm_mfma_kernel<WPB, 1, MT, 128, E, true>), lds_bytes);                                       \
+    launch_timed(tag, gemm_mfma_kernel<WPB, 1, MT, 128, E, true>, grid, WPB * 64, lds_bytes, st, (const E*)X, M, K,  \
+                 (const E*)Wp, n_tiles, n_stages, nullptr, 0, 0, 1, (E*)U, nullptr);                                 \
+  } else
+  MDZ_SWIGLU_CASE(3, 1)
+  MDZ_SWIGLU_CASE(3, 2)
+  MDZ_SWIGLU_CASE(4, 1)
+  MDZ_SWIGLU_CASE(4, 2) {
+    MDZ_FAIL(MDZ_EUNSUPPORTED, "gemm: no SwiGLU kernel for %d rows", M);
   }
-  if (M <= 32) MDZ_SWIGLU_CASE(1) else MDZ_SWIGLU_CASE(2)
 #undef MDZ_SWIGLU_CASE
   MDZ_LAUNCH_CHECK();
   return MDZ_OK;

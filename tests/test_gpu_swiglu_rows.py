@@ -1,5 +1,5 @@
-"""SwiGLU in the epilogue of the streaming gate/up GEMM (wide feed-forward blocks, up to 64 rows), whose two waves of a pair each finish
-one half of the rows: row counts at the edges of the halves of a 32-row and of a 64-row tile.  Bounds: the layer parity tests'."""
+"""SwiGLU in the epilogue of the streaming gate/up GEMM (wide feed-forward blocks, up to 64 rows), whose waves finish 16 features each:
+row counts at the edges of a 32-row and of a 64-row tile, three and four waves per workgroup.  Bounds: the layer parity tests'."""
 import pytest
 
 import workload as W
@@ -16,3 +16,15 @@ def test_layer_with_a_wide_feed_forward_block(tree, batches, dtype):
     for n in batches:
         S_list = [(7 * b) % 40 for b in range(n)]
         _check_layer(_layer_case(w, S_list, 40, x_seed=f"wide_ffn_x{n}"), S_list, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("ffn", [10272, 11008, 12288, 12320, 16384, 32768])
+def test_waves_per_workgroup(ffn, dtype):
+    """10272: an odd number of gate/up tile pairs, which the fused launch does not take; 11008: 688 waves of 32 columns, 229 workgroups of
+    three and one with a single one; 12288: 768, the most that three waves serve; 12320 not fused; 16384, 32768: four waves, one band
+    and two bands per workgroup."""
+    w = W.CONFIGS["cfg2_layer_bf16"].with_(d=256, n_heads=2, head_dim=128, ffn=ffn, dtype=dtype, tree=W.TREE15, name=f"swiglu_waves_{ffn}")
+    for n in (2, 3):
+        S_list = [(7 * b) % 40 for b in range(n)]
+        _check_layer(_layer_case(w, S_list, 40, x_seed=f"swiglu_waves_x{n}"), S_list, dtype)
