@@ -284,7 +284,11 @@ static int run_layer(const mdz_model_desc& m, const mdz_layer_weights& lw, int l
   // operand type of the feed-forward block: binary16 for a bf16 model that asks for it (wgateup and wdown are then
   // packed as binary16 and the block's two activations are rounded to binary16), else the storage type
   const int fdt = ffn_dtype(m);
-  if ((rc = launch_gemm(m.dtype, xn, lw.wqkv, part, rows, qkv_cols, m.d, qkv_cols, ms, &pr, st))) return rc;
+  // The 64-node attention fetches q's, k's and v's partial sums beyond the second one after the other, so over more rows than the
+  // streaming GEMM takes the product is split in two at most.  us, steps of 4 layers, any split / at most two: 4096-wide with 8 key/value heads,
+  // 128 rows 854 / 838, 192 rows 1079 / 1056; 2048-wide, 192 rows 444 / 433, 128 rows 389 / 390 (15 nodes, 90 rows: 771 / 775, left as it is).
+  const int qkv_split = rows > 64 && t->T == 64 && ms > 2 ? 2 : ms;
+  if ((rc = launch_gemm(m.dtype, xn, lw.wqkv, part, rows, qkv_cols, m.d, qkv_cols, qkv_split, &pr, st))) return rc;
   if ((rc = launch_rope_attention(m.dtype, m.tree, pr, cs, q, g, kv->k, kv->v, layer, seq_len, B, max_prefix, att,
                                   ws + w.attn_scratch, w.total - w.attn_scratch, st)))
     return rc;
