@@ -725,52 +725,89 @@ bool attn_mfma_supported(int dtype, int tree, const KvGeom& g) {
          (host_tree(tree)->T == 64 || (host_tree(tree)->T == 15 && !g.quant));
 }
 
-// Key-splits per (sequence, head).  fused: the kernel starts from the QKV partial sums, so one split is the tree
-// split and the rest share the prefix: at most as many as keep every workgroup resident at once (one per CU: the
-// merge buffer takes most of a CU's LDS).  Every further split costs about a microsecond per layer (its reduce of
-// the Q partial sums, its share of the merge) and saves the blocks it takes off the others, so the best count grows
-// with the square root of the prefix: measured best 1 / 3 / 5 / 8 splits at prefixes 128 / 1K / 4K / 16K.
-static int attn_splits(int B, int n_heads, int max_prefix, bool fused) {
-#ifdef MDZ_DEV_KNOBS
-  static const char* env = getenv("MDZ_ATTN_SPLITS");  // development builds only
-  if (env && atoi(env) > 0) return atoi(env) > 32 ? 32 : atoi(env);
-#endif
-  const int pairs = B * n_heads;
-  if (fused) {
-    int ps = num_cus() / pairs - 1;
-    const int by_len = (int)sqrtf((float)(max_prefix >> 5) / 8.0f);
-    if (ps > by_len) ps = by_len;
-    if (ps > 31) ps = 31;
-    return ps >= 1 ? ps + 1 : 1;
+// Queries per workgroup and key-splits per (sequence, head) of a launch.
+struct AttnPlan {
+  bool halves;  // 32 queries per workgroup (two fit a CU), else 64
+  int splits;
+};
+
+// fused: the kernel starts from the QKV partial sums, so one split is the tree split and the rest share the prefix.  Every further split
+// costs about a microsecond per layer (its reduce of the Q partial sums, its share of the merge) and saves the blocks it takes off the
+// others, so the best count grows with the square root of the prefix, up to a workgroup on every CU: 32 queries per workgroup (B = 1: one per
+// CU; a CU with two beside CUs with one is the last to end), 64 queries: four fifths of the CUs (at all of them, with 8 splits, every split of
+// a head lies on an XCD of its own, and the tree splits' XCD idles).  With 32 queries K and V pass through the CUs twice, which costs more than
+// the shorter chain of a workgroup saves once they are many.  us, steps of 4 layers, 64 nodes (h: 32 queries; s: splits):
+//   32 heads, one sequence: 1024 keys h s2 617, h s3 614, h s4 618; 4000 keys s4 691, s6 679, h s4 657; 5500 s6 687, h s4 687; 7000 s6 701, s8 711,
+//     h s4 711; 16384 s6 800, s7 803, s8 818, h s4 844.  16 heads: 4000 s4 405, h s4 353; 7000 s6 413, s12 393, h s4 370, h s6 355; 10000 s8 419,
+//     h s8 398; 14000 s8 441, s12 422, h s8 425.  40 heads: 4000 s4 725, h s3 707, h s4 728; 7000 s5 753, s6 758, h s3 754; 14000 s5 832, s6 853.
+//   8-bit rows, 32 heads: 7000 h s6 665, h s4 659, s8 670; 10000 h s7 705, h s4 696, s8 703; 14000 h s4 732, s6 756, s8 729.
+//   four query heads to a key/value head (their blocks come from L2): 4000 s4 728, h s4 677; 7000 s6 719, h s4 694; 14000 s8 759, h s4 752; 16384 s6 811,
+//     s8 779, h s4 799.
+//   several sequences (n / 8 .. n keys; the longest is the last to end, so long ones take twice the splits): 2 at 1500 h s2 802, h s3 811; 4000 s4 880,
+//     h s4 867; 8000 s3 941, s4 945, h s4 941; 3 at 1500 h s1 944, h s2 945; 2500 h s1 990, h s2 966; 8000 s2 1146, s3 1105; 4 at 600 h s1 1045, h s2 1069.
+//   15 nodes, one sequence: 1000 s3 590, s5 572, s6 571; 4000 s4 635, s6 598; 8000 s6 637; two 4000 s4 654, s6 636; three 2000 s2 674, s5 653; six 2000 s1
+//     815, s2 835.
+static AttnPlan attn_plan(int T, const KvGeom& g, int B, int max_prefix, bool fused) {
+  const int pairs = B * q_heads(g), cus = num_cus(), nb = max_prefix >> 5;
+  const int by_len = 1 + (int)sqrtf((float)nb / 8.0f);
+  AttnPlan p{true, 1};
+  auto at_most = [](int a, int b) { return a < b ? a : b; };
+  if (T == 64) {
+    const double through = (double)pairs * max_prefix * (g.quant ? 264 : 512);  // bytes of K and V that a launch takes through the CUs once
+    p.halves = pairs <= cus && through <= (B == 1 ? 96e6 : 160e6) * (g.group > 1 ? 2.5 : g.quant ? 1.3 : 1.0);
   }
-  int nb = (max_prefix + 64 + 31) / 32;
-  int by_len = nb / 8;                        // >= 2 blocks per wave
-  int by_fill = (512 + pairs - 1) / pairs;    // aim at ~512 workgroups
-  int s = by_len < by_fill ? by_len : by_fill;
-  if (s > 32) s = 32;
-  if (s < 1) s = 1;
-  return s;
+  if (!fused) {
+    const int most = (max_prefix + T + 31) / 32 / 8;       // >= 2 blocks per wave
+    const int by_fill = (512 + pairs - 1) / pairs;         // aim at ~512 workgroups
+    p.splits = at_most(most, by_fill);
+  } else if (T == 15 && 5 * pairs <= 2 * cus) {
+    p.splits = at_most(nb / 6, at_most(6, 2 * cus / pairs));
+  } else if (2 * pairs <= cus) {
+    if (T == 15)
+      p.splits = at_most(by_len, cus / pairs);
+    else if (p.halves)
+      p.splits = at_most(by_len, B == 1 || max_prefix < 2048 ? cus / (2 * pairs) : cus / pairs);
+    else
+      p.splits = at_most(1 + (int)sqrtf((float)nb / 4.0f), g.quant || g.group > 1 ? cus / pairs : cus * 4 / 5 / pairs + (B > 1));
+  }
+#ifdef MDZ_DEV_KNOBS
+  static const char* env_s = getenv("MDZ_ATTN_SPLITS");  // development builds only
+  if (env_s && atoi(env_s) > 0) p.splits = atoi(env_s);
+  static const char* env_h = getenv("MDZ_ATTN_HALVES");  // 1 = 32 queries per workgroup, 0 = 64
+  if (env_h && T == 64) p.halves = atoi(env_h) != 0;
+#endif
+  p.splits = p.splits < 1 ? 1 : p.splits > 32 ? 32 : p.splits;
+  return p;
 }
 
-int64_t attn_mfma_scratch_bytes(int B, int n_heads, int T, int max_prefix) {
-  int s = attn_splits(B, n_heads, max_prefix, true), s2 = attn_splits(B, n_heads, max_prefix, false);
-  s = s > s2 ? s : s2;
-  return s == 1 ? 0 : (int64_t)B * n_heads * s * (T * kHD + 2 * T) * 4;
+// Scratch of the splits' partial outputs.  A workspace is sized before the cache's row type is known and may serve shorter prefixes than it was
+// sized for, so this is a bound on every plan's splits that grows with the prefix.
+int64_t attn_mfma_scratch_bytes(int B, const KvGeom& g, int T, int max_prefix) {
+  const int pairs = B * q_heads(g), cus = num_cus(), nb = max_prefix >> 5;
+  int most = attn_plan(T, g, B, max_prefix, false).splits;
+  auto at_least = [&](int by_len, int cap) {
+    const int s = by_len < cap ? by_len : cap;
+    if (s > most) most = s;
+  };
+  if (T == 15 && 5 * pairs <= 2 * cus) at_least(nb / 6, 6);
+  if (2 * pairs <= cus) at_least(1 + (int)sqrtf((float)nb / 4.0f), cus / pairs + (B > 1));
+#ifdef MDZ_DEV_KNOBS
+  at_least(32, 32);
+#endif
+  if (most > 32) most = 32;
+  return most == 1 ? 0 : (int64_t)pairs * most * (T * kHD + 2 * T) * 4;
 }
 
 template <typename E, bool Q8, int NU, int TQ, bool ONCE>
 static int launch_attention_mfma_t(int tree, const void* q, const Partials* qkv, const float* cs, const KvGeom& g, void* kc,
-                                   void* vc, int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out,
+                                   void* vc, int layer, const int32_t* seq_len, int B, int max_prefix, int splits, void* att_out,
                                    void* scratch, int64_t scratch_bytes, hipStream_t st) {
-  if (B == 0) return MDZ_OK;
   // the merge buffer [4][128][32 NU + 2] + [4][2][32 NU] floats overlays the staged Q tile and tree rows
   constexpr int lds_bytes = 4 * kHD * (32 * NU + 2) * 4 + 4 * 2 * 32 * NU * 4;
   static_assert(lds_bytes >= (32 * NU + 2 * TQ) * kQRow && lds_bytes * (3 - NU) <= 160 * 1024, "LDS budget of the tree kernel");
   MDZ_SET_LDS_ONCE((attn_tree_mfma_kernel<E, Q8, NU, TQ, ONCE>), lds_bytes);
   const int nq = q_heads(g);
-  const int splits = attn_splits(B, nq, max_prefix, qkv != nullptr);
-  MDZ_REQUIRE(scratch_bytes >= attn_mfma_scratch_bytes(B, nq, TQ, max_prefix), MDZ_EWORKSPACE,
-              "attention: scratch too small");
+  MDZ_REQUIRE(scratch_bytes >= attn_mfma_scratch_bytes(B, g, TQ, max_prefix), MDZ_EWORKSPACE, "attention: scratch too small");
   float* part_o = (float*)scratch;
   float* part_ml = part_o + (int64_t)B * nq * splits * TQ * kHD;
   dim3 grid(splits, nq, B * (TQ > 32 * NU ? 2 : 1));  // two workgroups share a sequence: blockIdx.z = 2 * sequence + half
@@ -798,27 +835,22 @@ static int launch_attention_mfma_t(int tree, const void* q, const Partials* qkv,
 int launch_attention_mfma(int dtype, int tree, const void* q, const Partials* qkv, const float* cs, const KvGeom& g,
                           void* kc, void* vc, int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out,
                           void* scratch, int64_t scratch_bytes, hipStream_t st) {
-  // 32 queries per workgroup (two workgroups per CU) where the kernel's time is its fixed chain and the machine has
-  // room for twice the workgroups; 64 where K and V are long enough that passing them through the CUs twice costs
-  // more (measured crossover: between 3K and 4K keys for 16-bit rows, between 12K and 16K for 8-bit rows).
-  bool halves = B * q_heads(g) <= num_cus() && max_prefix < (g.quant ? 14336 : 3584);
-#ifdef MDZ_DEV_KNOBS
-  static const char* env = getenv("MDZ_ATTN_HALVES");  // development builds only: 1 = 32 queries per workgroup, 0 = 64
-  if (env) halves = atoi(env) != 0;
-#endif
+  if (B == 0) return MDZ_OK;
+  const int T = host_tree(tree)->T;
+  const AttnPlan p = attn_plan(T, g, B, max_prefix, qkv != nullptr);
   const bool once = g.group == 1;  // (and not in halves; 8-bit rows run alike: 16K keys 801 / 802 us per step of 4 layers)
 #define MDZ_ATTN_CASE(Q8, NU, TQ, ONCE)                                                                                     \
   MDZ_WITH_ELEM16(dtype, return (launch_attention_mfma_t<E, Q8, NU, TQ, ONCE>(tree, q, qkv, cs, g, kc, vc, layer, seq_len, B, \
-                                                                              max_prefix, att_out, scratch, scratch_bytes, st)))
-  if (host_tree(tree)->T == 15) {
+                                                                              max_prefix, p.splits, att_out, scratch, scratch_bytes, st)))
+  if (T == 15) {
     if (once) MDZ_ATTN_CASE(false, 1, 15, true);
     MDZ_ATTN_CASE(false, 1, 15, false);
   }
   if (g.quant) {
-    if (halves) MDZ_ATTN_CASE(true, 1, 64, false);
+    if (p.halves) MDZ_ATTN_CASE(true, 1, 64, false);
     MDZ_ATTN_CASE(true, 2, 64, false);
   }
-  if (halves) MDZ_ATTN_CASE(false, 1, 64, false);
+  if (p.halves) MDZ_ATTN_CASE(false, 1, 64, false);
   if (once) MDZ_ATTN_CASE(false, 2, 64, true);
   MDZ_ATTN_CASE(false, 2, 64, false);
 #undef MDZ_ATTN_CASE

@@ -94,7 +94,7 @@ static int64_t gemm_part_elems(int dtype, int rows, int N, int K, int max_slots 
 }
 
 bool attn_mfma_supported(int dtype, int tree, const KvGeom& g);
-int64_t attn_mfma_scratch_bytes(int B, int n_heads, int T, int max_prefix);
+int64_t attn_mfma_scratch_bytes(int B, const KvGeom& g, int T, int max_prefix);
 int launch_attention_mfma(int dtype, int tree, const void* q, const Partials* qkv, const float* cs, const KvGeom& g, void* kc,
                           void* vc, int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out,
                           void* scratch, int64_t scratch_bytes, hipStream_t st);
@@ -107,7 +107,7 @@ int launch_attention_decode(int dtype, const void* q, const Partials* qkv, const
 
 int64_t tree_attention_scratch_bytes(int dtype, int tree, const KvGeom& g, int B, int max_prefix) {
   if (attn_decode_supported(dtype, tree, g)) return attn_decode_scratch_bytes(B, q_heads(g), g.n_heads, max_prefix);
-  return attn_mfma_supported(dtype, tree, g) ? attn_mfma_scratch_bytes(B, q_heads(g), host_tree(tree)->T, max_prefix) : 0;
+  return attn_mfma_supported(dtype, tree, g) ? attn_mfma_scratch_bytes(B, g, host_tree(tree)->T, max_prefix) : 0;
 }
 
 int launch_tree_attention(int dtype, int tree, const void* q, const KvGeom& g, const void* kc, const void* vc,

@@ -156,7 +156,7 @@ int main() {
     CK(hipMalloc(&seq, 4));
     CK(hipMemcpy(seq, &S, 4, hipMemcpyHostToDevice));
     CK(hipMalloc(&att, (size_t)T * D * 2));
-    const int64_t sb = attn_mfma_scratch_bytes(1, H, T, S);
+    const int64_t sb = attn_mfma_scratch_bytes(1, g, T, S);
     CK(hipMalloc(&scratch, sb > 0 ? sb : 256));
     // the QKV launch's own plan: 96 bands x 32 stages on 192 workgroups, two partial-sum slots per band
     Partials qkv{part, 2, (int64_t)T * 3 * D, 3 * D, 128, 32, 96 * 32, 192};
