@@ -175,7 +175,7 @@ __device__ inline void unpack8_fp8(u32x4 v, int half, float (&f)[8]) {
 }  // namespace
 
 // qkv.p == NULL: q [B][d] holds the rotated queries and the cache already holds the node's row (separate RoPE kernel).
-template <typename E, bool Q8>
+template <typename E, bool Q8, bool ONCE>
 __global__ void __launch_bounds__(256, 2)
     attn_decode_kernel(const E* __restrict__ q, const Partials qkv, const float* __restrict__ cs, KvGeom g, E* __restrict__ kc,
                        E* __restrict__ vc, int layer, const int32_t* __restrict__ seq_len, int max_prefix,
@@ -213,13 +213,14 @@ __global__ void __launch_bounds__(256, 2)
   }
   // K and V double buffered one block ahead; every load is unconditional (past the wave's last block it repeats it)
   u32x4 kb[2][8], vb[2][8];
+  auto unit = [](const u32x4* p) { return ONCE ? __builtin_nontemporal_load(p) : *p; };
   auto load_kv = [&](int blk, u32x4 (&kd)[8], u32x4 (&vd)[8]) {
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      kd[i] = (Q8 && i >= 4) ? ks_p[(int64_t)blk * kBlkPieces + 2 * (i - 4)] : kp[(int64_t)blk * kBlkPieces + i * 64];
+      kd[i] = (Q8 && i >= 4) ? ks_p[(int64_t)blk * kBlkPieces + 2 * (i - 4)] : unit(kp + (int64_t)blk * kBlkPieces + i * 64);
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      vd[i] = (Q8 && i >= 4) ? vs_p[(int64_t)blk * kBlkPieces + 2 * (i - 4)] : vp[(int64_t)blk * kBlkPieces + i * 64];
+      vd[i] = (Q8 && i >= 4) ? vs_p[(int64_t)blk * kBlkPieces + 2 * (i - 4)] : unit(vp + (int64_t)blk * kBlkPieces + i * 64);
   };
   // Requested first (loads return in order): the partial sums of two rotary pairs of one query head per thread, and, in the
   // split that owns the block of slot S, the node's K row (threads 192 .. 223) and V row (224 .. 255).
@@ -436,8 +437,7 @@ __global__ void __launch_bounds__(256, 4)
   const u32x4* kp = reinterpret_cast<const u32x4*>(kbase) + lane;
   const u32x4* vp = reinterpret_cast<const u32x4*>(vbase) + lane;
   // Read once per pass, by no other workgroup, so non-temporally (us per step of 4 layers, plain / non-temporal: 20 sequences of 200 .. 2000
-  // keys 818 / 791, 64 of 40 .. 400 798 / 783, 90 of 300 .. 3000 at 16 heads 1223 / 1152).  Not so in attn_decode_kernel, whose
-  // calls have fewer keys to stream: one sequence of 6000 keys 623 / 627, of 200 at 16 heads 235.6 / 239.1, of 1024 over 32 layers 3252 / 3211.
+  // keys 818 / 791, 64 of 40 .. 400 798 / 783, 90 of 300 .. 3000 at 16 heads 1223 / 1152).
   u32x4 kd[kUnits], vd[kUnits];
   float k_scale = 1.f, v_scale = 1.f;  // 8-bit rows: of key `key`
   auto load_k = [&](int blk) {
@@ -614,22 +614,35 @@ bool attn_decode_supported(int dtype, int tree, const KvGeom& g) {
   return is_16bit(dtype) && g.tiled && g.head_dim == kHD && host_tree(tree)->T == 1;
 }
 
-// Key-splits: enough workgroups to give every CU two (they fit), but no more than one per seven blocks at max_prefix, i.e. up to
-// two blocks per wave (one sequence of 1024 keys, 32 heads: 12.5 us with 5 splits, 13.7 with 2, 13.9 with 3, 15.1 with 9, merge
-// included).  The number of sevens is rounded up: a split and the merge launch more just past a multiple cost less than a wave's
-// third block (whole layer, rounded up / down: one sequence at 150 keys 56.7 / 59.1 us, at 600 59.6 / 62.3; eight at 440 64.6 / 66.9,
-// though at 300 63.5 / 61.9).
+// Key-splits.  A split costs its start, its share of the merge and, the first of them, the merge launch; it is worth the blocks that it takes off
+// the others: one up to twelve blocks, then by the square root of the length (at 600 keys 3 splits 59.6 us per layer, 2 62.3).  Beyond about
+// three quarters of a workgroup per CU more splits only add up, but for many keys, where a CU with two workgroups of long sequences beside CUs with one
+// of short ones is the last to end.  Ungrouped heads are then better off with several workgroups per CU in the other kernel.
+// us, steps of 4 layers, lengths n / 9 .. n, splits of the former rule (one per seven blocks, two workgroups per CU) / of this one:
+//   32 heads: one sequence of 300 keys 541 / 535, 3000 575 / 565, 6000 620 / 597, 16384 735 / 690; four at 1000 564 / 557, 3000 626 / 606, 6000 701 / 672;
+//     eight at 300 559 / 548, 3000 708 / 677, 6000 870 / 806; twelve at 300 569 / 558, 3000 760 / 750
+//   16 heads: one at 4000 280 / 271, eight at 4000 364 / 345.  8 key/value heads: twelve at 1000 599 / 593, 24 at 300 598 / 584, 1000 626 / 606, 3000
+//     718 / 706, 40 at 300 636 / 613, 1000 693 / 682 (at 3000 one split 833, two 821; 24 at 6000 829, three 816)
 // Dealing equal parts of a ragged batch out by its device-side lengths was measured too: 24 sequences of 90 .. 3000 keys
 // gain 1 us of 37 (the HBM stream bounds them), a single sequence loses 1 us to finding its part.
-static int decode_splits(int B, int kv_heads, int max_prefix) {
-  const int nb = (max_prefix + 1 + 31) / 32, pairs = B * kv_heads;
-  const int by_len = (nb + 6) / 7, by_fill = (2 * num_cus() + pairs - 1) / pairs;
-  const int s = by_len < by_fill ? by_len : by_fill;
+static int decode_splits(int B, int kv_heads, int n_heads, int max_prefix) {
+  const int nb = (max_prefix + 1 + 31) / 32, pairs = B * kv_heads, cus = num_cus();
+  const int by_len = nb <= 12 ? 1 : (int)sqrtf(0.5f * (float)nb), by_fill = (2 * cus + pairs - 1) / pairs;
+  int most;
+  if (n_heads != kv_heads)
+    most = pairs <= cus ? (max_prefix < 4096 ? cus / pairs : by_fill) : max_prefix < 2048 ? 1 : by_fill;
+  else if (pairs > cus)
+    most = pairs >= 2 * cus ? 1 : max_prefix < 2048 ? 2 : 3;
+  else if (2 * pairs >= cus && max_prefix >= 2048)
+    most = (5 * cus / 2 + pairs - 1) / pairs;
+  else
+    most = cus * 3 / 4 / pairs + (B > 1);
+  const int s = by_len < most ? by_len : most;
   return s > 32 ? 32 : s < 1 ? 1 : s;
 }
 
 int64_t attn_decode_scratch_bytes(int B, int n_heads, int kv_heads, int max_prefix) {
-  const int s = decode_splits(B, kv_heads, max_prefix);
+  const int s = decode_splits(B, kv_heads, n_heads, max_prefix);
   return s == 1 ? 0 : (int64_t)B * n_heads * s * (kHD + 2) * 4;
 }
 
@@ -638,7 +651,7 @@ static int launch_attention_decode_t(const void* q, const Partials* qkv, const f
                                      int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out, void* scratch,
                                      int64_t scratch_bytes, hipStream_t st) {
   if (B == 0) return MDZ_OK;
-  const int nq = q_heads(g), splits = decode_splits(B, g.n_heads, max_prefix), chunks = (g.group + 31) / 32;
+  const int nq = q_heads(g), splits = decode_splits(B, g.n_heads, nq, max_prefix), chunks = (g.group + 31) / 32;
   MDZ_REQUIRE(scratch_bytes >= attn_decode_scratch_bytes(B, nq, g.n_heads, max_prefix), MDZ_EWORKSPACE,
               "decode attention: scratch too small");
   float* part_o = (float*)scratch;
@@ -646,7 +659,8 @@ static int launch_attention_decode_t(const void* q, const Partials* qkv, const f
   const int cols = g.group < 32 ? g.group : 32;
   const int merge_bytes = 4 * cols * (kORow + 2) * 4, q_bytes = 34 * kQRow;
   const int lds_bytes = merge_bytes > q_bytes ? merge_bytes : q_bytes;
-  MDZ_SET_LDS_ONCE((attn_decode_kernel<E, Q8>), 4 * 32 * (kORow + 2) * 4);
+  MDZ_SET_LDS_ONCE((attn_decode_kernel<E, Q8, false>), 4 * 32 * (kORow + 2) * 4);
+  MDZ_SET_LDS_ONCE((attn_decode_kernel<E, Q8, true>), 4 * 32 * (kORow + 2) * 4);
   const Partials none = single_slot(nullptr, 0, 0);
   // More workgroups than fit at once: long sequences first, from 1536 keys on.  (Finding its place costs a workgroup 1 - 2 us: per layer,
   // lengths S / 4 .. S, in order / not: 64 sequences x 32 heads at S = 100 83.1 / 77.9 us, 500 140.2 / 139.3, 1000 199.3 / 200.1, 2000
@@ -655,11 +669,16 @@ static int launch_attention_decode_t(const void* q, const Partials* qkv, const f
   // Ungrouped heads and more workgroups than the matrix-core kernel keeps resident: FMAs.  (Per layer with small GEMMs, matrix cores /
   // FMAs: 64 sequences x 32 heads of S / 4 .. S keys, S = 16 94.2 / 77.9 us, 100 100.3 / 83.0, 500 149.0 / 140.4, 2000 309.8 / 308.3;
   // 8-bit rows 95.3 / 76.8, 98.4 / 79.0, 124.3 / 105.1, 203.7 / 199.2; 32 at 4000 291.3 / 293.3, 8-bit 185.4 / 183.0.)
+  // Non-temporal K and V once a pass reads more of them than the caches hold from one pass to the next.  (us, steps of 4 layers, plain / non-temporal:
+  // one sequence x 32 heads at 3000 keys (200 MB) 563 / 568, 6000 610 / 595; 24 x 8 at 300 .. 1000 606 / 620, 3000 (at most 1.2 GB) 719 / 706, 64 x 8 at
+  // 1000 (1.1 GB) 735 / 738, 3000 957 / 934, 90 x 8 at 3000 1282 / 1241, but at 500, 6 layers, 1131 / 1142.  More than one key/value head's workgroup per block: plain.)
+  const double stream = (double)g.n_layers * B * g.n_heads * max_prefix * (Q8 ? 264 : 512);
+  const bool once = chunks == 1 && max_prefix >= 1024 && stream >= (B == 1 ? 350e6 : 640e6);
   if (g.group == 1 && (int64_t)splits * g.n_heads * B > 2 * num_cus())
     launch_timed(PROF_ATTN, attn_decode_one_kernel<E, Q8>, dim3(splits, g.n_heads, B), 256, 0, st, (const E*)q, qkv ? *qkv : none, cs,
                  g, (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, ordered);
   else
-    launch_timed(PROF_ATTN, attn_decode_kernel<E, Q8>, dim3(splits, g.n_heads * chunks, B), 256, lds_bytes, st, (const E*)q,
+    launch_timed(PROF_ATTN, once ? attn_decode_kernel<E, Q8, true> : attn_decode_kernel<E, Q8, false>, dim3(splits, g.n_heads * chunks, B), 256, lds_bytes, st, (const E*)q,
                  qkv ? *qkv : none, cs, g, (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, ordered);
   MDZ_LAUNCH_CHECK();
   if (splits > 1) {

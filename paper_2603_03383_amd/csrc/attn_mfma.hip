@@ -743,10 +743,10 @@ struct AttnPlan {
 //   8-bit rows, 32 heads: 7000 h s6 665, h s4 659, s8 670; 10000 h s7 705, h s4 696, s8 703; 14000 h s4 732, s6 756, s8 729.
 //   four query heads to a key/value head (their blocks come from L2): 4000 s4 728, h s4 677; 7000 s6 719, h s4 694; 14000 s8 759, h s4 752; 16384 s6 811,
 //     s8 779, h s4 799.
-//   several sequences (n / 8 .. n keys; the longest is the last to end, so long ones take twice the splits): 2 at 1500 h s2 802, h s3 811; 4000 s4 880,
-//     h s4 867; 8000 s3 941, s4 945, h s4 941; 3 at 1500 h s1 944, h s2 945; 2500 h s1 990, h s2 966; 8000 s2 1146, s3 1105; 4 at 600 h s1 1045, h s2 1069.
-//   15 nodes, one sequence: 1000 s3 590, s5 572, s6 571; 4000 s4 635, s6 598; 8000 s6 637; two 4000 s4 654, s6 636; three 2000 s2 674, s5 653; six 2000 s1
-//     815, s2 835.
+//   several sequences (n / 8 .. n keys; the longest is the last to end, so long ones take twice the splits): 2 at 1500 h s2 788, h s3 802; 4000 s4 864,
+//     h s4 853; 8000 s3 922, s4 923, h s4 926; 3 at 1500 h s1 892, h s2 901; 2500 h s1 931, h s2 922; 8000 s2 1091, s3 1060; 4 at 600 h s1 1002, h s2 1025.
+//   15 nodes, one sequence: 1000 s3 573, s5 568; 4000 s4 609, s6 595; 8000 s4 664, s6 632; two 2000 s3 613, s4 604, s6 614; 8000 s4 688, s6 673; three 2000 s2
+//     650, s4 644; 8000 s2 779, s4 759, s5 780; four 2000 s2 666, s4 678; six 2000 s1 784, s2 802.
 static AttnPlan attn_plan(int T, const KvGeom& g, int B, int max_prefix, bool fused) {
   const int pairs = B * q_heads(g), cus = num_cus(), nb = max_prefix >> 5;
   const int by_len = 1 + (int)sqrtf((float)nb / 8.0f);
@@ -760,8 +760,8 @@ static AttnPlan attn_plan(int T, const KvGeom& g, int B, int max_prefix, bool fu
     const int most = (max_prefix + T + 31) / 32 / 8;       // >= 2 blocks per wave
     const int by_fill = (512 + pairs - 1) / pairs;         // aim at ~512 workgroups
     p.splits = at_most(most, by_fill);
-  } else if (T == 15 && 5 * pairs <= 2 * cus) {
-    p.splits = at_most(nb / 6, at_most(6, 2 * cus / pairs));
+  } else if (T == 15 && 8 * pairs <= 3 * cus) {
+    p.splits = at_most(nb / 6, 8 * pairs <= cus || (4 * pairs <= cus && max_prefix >= 4096) ? 6 : 4);
   } else if (2 * pairs <= cus) {
     if (T == 15)
       p.splits = at_most(by_len, cus / pairs);
@@ -789,7 +789,7 @@ int64_t attn_mfma_scratch_bytes(int B, const KvGeom& g, int T, int max_prefix) {
     const int s = by_len < cap ? by_len : cap;
     if (s > most) most = s;
   };
-  if (T == 15 && 5 * pairs <= 2 * cus) at_least(nb / 6, 6);
+  if (T == 15 && 8 * pairs <= 3 * cus) at_least(nb / 6, 6);
   if (2 * pairs <= cus) at_least(1 + (int)sqrtf((float)nb / 4.0f), cus / pairs + (B > 1));
 #ifdef MDZ_DEV_KNOBS
   at_least(32, 32);
