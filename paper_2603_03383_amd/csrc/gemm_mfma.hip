@@ -450,22 +450,24 @@ static int launch_gemm_mfma_t(const void* X, const void* Wp, float* P, int M, in
   return MDZ_OK;
 }
 
-// The gate/up GEMM with the SwiGLU in its epilogue: U [M][N / 2] of the storage type.  Whole bands per workgroup, so
-// it is taken only where the bands nearly fill the chip (or fill it a whole number of times).
+// The gate/up GEMM with the SwiGLU in its epilogue: U [M][N / 2] of the storage type.
+// Waves (of 32 columns) per workgroup of that launch: as few, from two on, as leave at most one workgroup per CU.  22016 x 4096 on 230
+// workgroups of three, 172 of four: 64 rows (a layer at 512 keys) 111.8 / 115.8 us, one row (a 32-layer step at 1K keys) 3328 / 3362.
+static int swiglu_waves(int N) {
+  const int n_tiles = N / 32, cus = num_cus();
+  return n_tiles <= 2 * cus ? 2 : n_tiles <= 3 * cus ? 3 : 4;
+}
+// Whole bands per workgroup, so it is taken only where the bands nearly fill the chip (or fill it a whole number of times).
 bool gemm_mfma_swiglu_supported(int dtype, int M, int N, int K) {
   if (!gemm_mfma_supported(dtype, M, N, K) || N % 128 != 0) return false;
-  const int bands = N / 128, kNumCU = num_cus();
-  return (bands >= kNumCU * 5 / 8 && bands <= kNumCU) || (bands > kNumCU && bands % kNumCU == 0);
+  const int wpb = swiglu_waves(N), bands = (N / 32 + wpb - 1) / wpb, cus = num_cus();
+  return (bands >= cus * 5 / 8 && bands <= cus) || (bands > cus && bands % cus == 0);
 }
-
-// Waves (of 32 columns) per workgroup of that launch: three where that still is at most one workgroup per CU.  22016 x 4096 on 230
-// workgroups of three, 172 of four: 64 rows (a layer at 512 keys) 111.8 / 115.8 us, one row (a 32-layer step at 1K keys) 3328 / 3362.
-static int swiglu_waves(int M, int N) { return (N / 32 + 2) / 3 <= num_cus() ? 3 : 4; }
 
 template <typename E>
 static int launch_gemm_mfma_swiglu_t(const void* X, const void* Wp, void* U, int M, int N, int K, hipStream_t st) {
   const int tag = M <= 32 ? PROF_GEMM_W32 : PROF_GEMM_W64;
-  const int wpb = swiglu_waves(M, N);
+  const int wpb = swiglu_waves(N);
   const int n_tiles = N / 32, n_stages = K / 128, bands = (n_tiles + wpb - 1) / wpb, kNumCU = num_cus();
   const int grid = bands < kNumCU ? bands : kNumCU;
   MDZ_REQUIRE((int64_t)bands * n_stages * grid < (int64_t)1 << 31 && (int64_t)M * N < (int64_t)1 << 31, MDZ_ESHAPE,
@@ -477,6 +479,8 @@ static int launch_gemm_mfma_swiglu_t(const void* X, const void* Wp, void* U, int
     launch_timed(tag, gemm_mfma_kernel<WPB, 1, MT, 128, E, true>, grid, WPB * 64, lds_bytes, st, (const E*)X, M, K,  \
                  (const E*)Wp, n_tiles, n_stages, nullptr, 0, 0, 1, (E*)U, nullptr);                                 \
   } else
+  MDZ_SWIGLU_CASE(2, 1)
+  MDZ_SWIGLU_CASE(2, 2)
   MDZ_SWIGLU_CASE(3, 1)
   MDZ_SWIGLU_CASE(3, 2)
   MDZ_SWIGLU_CASE(4, 1)
