@@ -38,7 +38,7 @@ typedef u32x4_t u32x4;
 // DIRECT = false: X or W does not start on 16 bytes (a caller's buffer; the C interface asks for no alignment).  The same ring is
 // filled through registers, from ordinary loads that are requested a round before they are written to LDS.  (128000 x 4096, us,
 // aligned / not: 135 rows 217 / 329, 192 rows 228 / 344, 1024 rows 882 (gemm_wide.hip) / 1561; the portable kernel takes 3854, 3990, 18800.)
-template <typename E, int WR, int WC, int MT, int NT, int NS, bool SWIGLU, bool DIRECT>
+template <typename E, int WR, int WC, int MT, int NT, int NS, bool SWIGLU, bool DIRECT, bool BURSTS>
 __global__ void __launch_bounds__(2 * WR * WC * 64, (2 * WR * WC + 3) / 4)
     gemm_tile_kernel(const E* __restrict__ X, int M, int K, const E* __restrict__ Wp, int n_tiles, float* __restrict__ P,
                      int64_t ldp, int64_t part_stride, int nb_m, int nb_n, int ksplit, E* __restrict__ U) {
@@ -48,7 +48,10 @@ __global__ void __launch_bounds__(2 * WR * WC * 64, (2 * WR * WC + 3) / 4)
   // among W requests take as long as those.  With a ring of four rounds the X of two rounds is requested in one round and the W of two
   // in the next: 24 + 16 KiB a round (192 x 128) then stream at 62 GB/s per CU instead of 56, 16 + 16 KiB at 52 instead of 48.
   // us per launch, mixed / in bursts: 192 rows, 22016 x 4096 52.3 / 50.9, 12288 x 4096 33.9 / 33.2; 128 rows, a step of 4 layers 814 / 793.
-  constexpr bool BURSTS = DIRECT && NS == 4;
+  // That holds where a round asks for about as much of X as of W and W comes from HBM.  Rows beyond M repeat a row and come at once, tiles of 64
+  // columns ask for little W, and several row blocks share it through L2: there whole rounds are requested, up to four ahead (70 rows on
+  // 128 x 128: 27648 x 5120 51.7 / 52.5, 15360 x 5120 32.3 / 32.9; 384 rows on 192 x 128, 4096 x 4096 and 4096 x 11008 32.8 / 33.3).
+  static_assert(!BURSTS || (DIRECT && NS == 4), "bursts: the wait counts below are for a ring of four rounds");
   constexpr bool MIXED = SWIGLU && NT == 1;            // a tile is 16 gate and the 16 up columns of the same features
   constexpr int XT = WR * MT, WT = WC * NT;            // 32-row and 32-column tiles of the workgroup
   constexpr int UX = XT * 4, UT = (XT + WT) * 4;       // 1 KiB pieces of a round: X (8 rows x 128 B each), then W
@@ -344,25 +347,30 @@ static int launch_gemm_tile_t(const void* X, const void* Wp, float* P, int M, in
     res->split_units = 0;
   }
   const dim3 grid((p.nb_n + 7) / 8 * 8 * p.nb_m, 1, p.ksplit);
-#define MDZ_TILE_CASE(WR, WC, MT, NT, NS)                                                                                \
-  if (p.bm == 32 * WR * MT && p.bn == 32 * WC * NT) {                                                                     \
+  // X and W in bursts (see the kernel): one row block, at least four fifths as many rows as columns
+  const bool full = p.nb_m == 1 && 5 * M >= 4 * p.bn;
+#define MDZ_TILE_CASE(WR, WC, MT, NT, NS, BURSTS, TAKEN)                                                                  \
+  if (p.bm == 32 * WR * MT && p.bn == 32 * WC * NT && (TAKEN)) {                                                          \
     constexpr int lds_bytes = NS * (WR * MT + WC * NT) * 4 * 1024;                                                        \
     static_assert(lds_bytes <= 160 * 1024, "LDS of a CU");                                                                \
-    MDZ_SET_LDS_ONCE((gemm_tile_kernel<E, WR, WC, MT, NT, NS, SWIGLU, DIRECT>), lds_bytes);                               \
-    launch_timed(PROF_GEMM_LARGE, gemm_tile_kernel<E, WR, WC, MT, NT, NS, SWIGLU, DIRECT>, grid, 2 * WR * WC * 64, lds_bytes, st, \
-                 (const E*)X, M, K, (const E*)Wp, N / 32, P, ldp, part_stride, p.nb_m, p.nb_n, p.ksplit, (E*)U);           \
+    constexpr auto kernel = gemm_tile_kernel<E, WR, WC, MT, NT, NS, SWIGLU, DIRECT, DIRECT && BURSTS>;                    \
+    MDZ_SET_LDS_ONCE(kernel, lds_bytes);                                                                                  \
+    launch_timed(PROF_GEMM_LARGE, kernel, grid, 2 * WR * WC * 64, lds_bytes, st, (const E*)X, M, K, (const E*)Wp, N / 32, P, ldp, \
+                 part_stride, p.nb_m, p.nb_n, p.ksplit, (E*)U);                                                           \
     MDZ_LAUNCH_CHECK();                                                                                                   \
     return MDZ_OK;                                                                                                        \
   }
-  MDZ_TILE_CASE(1, 3, 3, 1, 4)
-  MDZ_TILE_CASE(2, 3, 3, 1, 4)
-  MDZ_TILE_CASE(2, 2, 2, 2, 4)
-  MDZ_TILE_CASE(2, 2, 3, 2, 4)
-  MDZ_TILE_CASE(2, 2, 4, 2, 3)
+  MDZ_TILE_CASE(1, 3, 3, 1, 4, true, true)
+  MDZ_TILE_CASE(2, 3, 3, 1, 4, true, true)
+  if constexpr (DIRECT) MDZ_TILE_CASE(2, 2, 2, 2, 4, true, full)
+  MDZ_TILE_CASE(2, 2, 2, 2, 4, false, true)
+  if constexpr (DIRECT) MDZ_TILE_CASE(2, 2, 3, 2, 4, true, full)
+  MDZ_TILE_CASE(2, 2, 3, 2, 3, false, true)
+  MDZ_TILE_CASE(2, 2, 4, 2, 3, false, true)
   if constexpr (!SWIGLU) {
-    MDZ_TILE_CASE(2, 2, 2, 1, 4)
-    MDZ_TILE_CASE(2, 2, 3, 1, 4)
-    MDZ_TILE_CASE(2, 2, 4, 1, 4)
+    MDZ_TILE_CASE(2, 2, 2, 1, 5, false, true)
+    MDZ_TILE_CASE(2, 2, 3, 1, 4, false, true)
+    MDZ_TILE_CASE(2, 2, 4, 1, 4, false, true)
   }
 #undef MDZ_TILE_CASE
   MDZ_FAIL(MDZ_EUNSUPPORTED, "gemm: no tile kernel for a %d x %d tile", p.bm, p.bn);
