@@ -619,8 +619,9 @@ bool attn_decode_supported(int dtype, int tree, const KvGeom& g) {
 // three quarters of a workgroup per CU more splits only add up, but for many keys, where a CU with two workgroups of long sequences beside CUs with one
 // of short ones is the last to end.  Ungrouped heads are then better off with several workgroups per CU in the other kernel.
 // us, steps of 4 layers, lengths n / 9 .. n, splits of the former rule (one per seven blocks, two workgroups per CU) / of this one:
-//   32 heads: one sequence of 300 keys 541 / 535, 3000 575 / 565, 6000 620 / 597, 16384 735 / 690; four at 1000 564 / 557, 3000 626 / 606, 6000 701 / 672;
-//     eight at 300 559 / 548, 3000 708 / 677, 6000 870 / 806; twelve at 300 569 / 558, 3000 760 / 750
+//   32 heads: one sequence of 300 keys 541 / 535, 3000 575 / 565, 6000 620 / 597, 16384 735 / 690; three at 3000 605 / 587, 6000 665 / 641 (two splits
+//     685); four at 1000 564 / 557, 3000 626 / 606, 6000 701 / 672; eight at 300 559 / 548, 3000 708 / 677, 6000 870 / 806; twelve at 300 569 / 558,
+//     3000 760 / 750; 18 at 3000 883 / 858.  40 heads, 8-bit rows: two at 4000 602 / 598, three 607 / 607 (two splits 636)
 //   16 heads: one at 4000 280 / 271, eight at 4000 364 / 345.  8 key/value heads: twelve at 1000 599 / 593, 24 at 300 598 / 584, 1000 626 / 606, 3000
 //     718 / 706, 40 at 300 636 / 613, 1000 693 / 682 (at 3000 one split 833, two 821; 24 at 6000 829, three 816)
 // Dealing equal parts of a ragged batch out by its device-side lengths was measured too: 24 sequences of 90 .. 3000 keys
@@ -632,9 +633,9 @@ static int decode_splits(int B, int kv_heads, int n_heads, int max_prefix) {
   if (n_heads != kv_heads)
     most = pairs <= cus ? (max_prefix < 4096 ? cus / pairs : by_fill) : max_prefix < 2048 ? 1 : by_fill;
   else if (pairs > cus)
-    most = pairs >= 2 * cus ? 1 : max_prefix < 2048 ? 2 : 3;
-  else if (2 * pairs >= cus && max_prefix >= 2048)
-    most = (5 * cus / 2 + pairs - 1) / pairs;
+    most = pairs >= 3 * cus ? 1 : max_prefix >= 2048 ? 3 : pairs >= 2 * cus ? 1 : 2;
+  else if (const int many = 2 * cus / pairs + 1; B > 1 && by_len >= many && max_prefix >= 1536)
+    most = many;  // the fewest that the FMA kernel takes
   else
     most = cus * 3 / 4 / pairs + (B > 1);
   const int s = by_len < most ? by_len : most;

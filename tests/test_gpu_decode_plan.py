@@ -19,9 +19,10 @@ def _w(n_heads, dtype="bf16", **kw):
 @pytest.mark.parametrize("n_heads,kv_heads,batch,max_prefix", [
     (4, 0, 1, 383), (4, 0, 1, 384),        # twelve blocks, thirteen
     (4, 0, 3, 3000),                       # splits by length
-    (2, 0, 63, 2100), (2, 0, 64, 2100),    # three workgroups in two CUs; five splits, FMA kernel
-    (2, 0, 64, 2047),                      # below
+    (2, 0, 48, 2270), (2, 0, 48, 2271),    # three splits; six, FMA kernel
+    (2, 0, 64, 1535), (2, 0, 64, 2100),    # two; five, FMA kernel
     (2, 0, 129, 2047), (2, 0, 129, 2048),  # more pairs than CUs: two and three splits
+    (2, 0, 260, 2048),                     # 520 pairs: three
     (4, 2, 64, 4095), (4, 2, 64, 4096),    # grouped: two and four splits
     (4, 2, 129, 2047), (4, 2, 129, 2048),  # one and two
 ])
