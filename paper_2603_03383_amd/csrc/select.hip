@@ -168,48 +168,67 @@ __global__ void __launch_bounds__(256) topk_stage1_kernel(SelRows rs, const floa
   }
 }
 
-// One wave per row.  Every chunk list is already in order, so the row's next pick is the best of the lists' current
-// heads: the lists are staged in LDS, every lane owns up to 8 of them (512 lists at most), offers the best of its
-// heads, the wave picks, and the lane that owned the pick advances that list.
-__global__ void __launch_bounds__(64) topk_stage2_kernel(SelRows rs, const float* __restrict__ cand_v,
-                                                         const int32_t* __restrict__ cand_i, int n_chunks,
-                                                         const int32_t* __restrict__ root_token, int32_t* __restrict__ out) {
+// One workgroup per row.  Every chunk list is already in order, so the row's next pick is the best of the lists' current
+// heads: the workgroup brings the lists to LDS in one round trip (a thread a list, 16 bytes at a time), then its first wave picks: every lane
+// holds the heads of up to 8 lists (512 at most) in registers, offers the best, and the lane that owned the wave's pick advances that list.
+// Latency bound: ten picks of 250 lists 11 - 13 us; 16 - 18 with one wave, an entry at a time and the heads read from LDS for every pick.
+__global__ void __launch_bounds__(256) topk_stage2_kernel(SelRows rs, const float* __restrict__ cand_v,
+                                                          const int32_t* __restrict__ cand_i, int n_chunks,
+                                                          const int32_t* __restrict__ root_token, int32_t* __restrict__ out) {
   extern __shared__ __attribute__((aligned(8))) uint8_t sel_lds[];  // [n_chunks][k] values, then indices
-  const int lane = threadIdx.x, row = blockIdx.x;
+  const int row = blockIdx.x;
   const int k = sel_row_k(rs, row);
   int32_t* dst = sel_row_out(rs, row, out);
   if (k == 0) {
-    if (lane == 0) dst[0] = root_token[row / (c_trees[rs.tree].K + 1)];
+    if (threadIdx.x == 0) dst[0] = root_token[row / (c_trees[rs.tree].K + 1)];
     return;
   }
   float* lv = reinterpret_cast<float*>(sel_lds);
   int* li = reinterpret_cast<int*>(sel_lds) + n_chunks * k;
   const float* cv = cand_v + (int64_t)row * n_chunks * kSelMaxK;
   const int32_t* ci = cand_i + (int64_t)row * n_chunks * kSelMaxK;
-  for (int c = lane; c < n_chunks; c += 64)
-    for (int q = 0; q < k; ++q) lv[c * k + q] = cv[c * kSelMaxK + q], li[c * k + q] = ci[c * kSelMaxK + q];
-  __syncthreads();
-  int pos[kSelMaxChunks / 64];  // next entry of the lane's lists lane, lane + 64, ...
+  for (int c = threadIdx.x; c < n_chunks; c += 256) {
+    float4 v[kSelMaxK / 4];
+    int4 x[kSelMaxK / 4];
 #pragma unroll
-  for (int j = 0; j < kSelMaxChunks / 64; ++j) pos[j] = 0;
+    for (int q = 0; q < kSelMaxK / 4; ++q)  // (lists start on 64 bytes; entries from k on were not written and are not used)
+      if (4 * q < k) {
+        v[q] = *reinterpret_cast<const float4*>(cv + c * kSelMaxK + 4 * q);
+        x[q] = *reinterpret_cast<const int4*>(ci + c * kSelMaxK + 4 * q);
+      }
+#pragma unroll
+    for (int q = 0; q < kSelMaxK; ++q)
+      if (q < k) {
+        lv[c * k + q] = reinterpret_cast<const float*>(&v[q / 4])[q % 4];
+        li[c * k + q] = reinterpret_cast<const int*>(&x[q / 4])[q % 4];
+      }
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const int lane = threadIdx.x;
+  constexpr int kLists = kSelMaxChunks / 64;
+  Best head[kLists];  // of the lane's lists lane, lane + 64, ...
+  int pos[kLists];
+#pragma unroll
+  for (int j = 0; j < kLists; ++j) {
+    const int c = lane + 64 * j;
+    pos[j] = c * k;
+    head[j] = c < n_chunks ? Best{lv[c * k], li[c * k]} : Best{-INFINITY, kNoIndex};
+  }
   for (int p = 0; p < k; ++p) {
     Best b{-INFINITY, kNoIndex};
 #pragma unroll
-    for (int j = 0; j < kSelMaxChunks / 64; ++j) {
-      const int c = lane + 64 * j;
-      if (c < n_chunks && pos[j] < k) {
-        const Best h{lv[c * k + pos[j]], li[c * k + pos[j]]};
-        if (h.i != kNoIndex && precedes(h.v, h.i, b.v, b.i)) b = h;
-      }
-    }
+    for (int j = 0; j < kLists; ++j)
+      if (head[j].i != kNoIndex && precedes(head[j].v, head[j].i, b.v, b.i)) b = head[j];
     const Best w = wave_best(b);
     if (lane == 0) dst[p] = w.i == kNoIndex ? -1 : w.i;
     if (w.i != kNoIndex && w.i == b.i) {  // column ids are unique: this lane owns the pick; advance its list
 #pragma unroll
-      for (int j = 0; j < kSelMaxChunks / 64; ++j) {
-        const int c = lane + 64 * j;
-        if (c < n_chunks && pos[j] < k && li[c * k + pos[j]] == w.i) ++pos[j];
-      }
+      for (int j = 0; j < kLists; ++j)
+        if (head[j].i == w.i) {
+          const bool more = ++pos[j] < (lane + 64 * j + 1) * k;
+          head[j] = more ? Best{lv[pos[j]], li[pos[j]]} : Best{-INFINITY, kNoIndex};
+        }
     }
   }
 }
@@ -230,7 +249,7 @@ static int launch_two_stage(const SelRows& rs, const float* logits, int rows, in
   topk_stage1_kernel<<<dim3((n_chunks + 3) / 4, rows), 256, 0, st>>>(rs, logits, V, n_chunks, cv, ci);
   MDZ_LAUNCH_CHECK();
   const int kmax = rs.tree < 0 ? 1 : kSelMaxK;
-  topk_stage2_kernel<<<rows, 64, (size_t)n_chunks * kmax * 8, st>>>(rs, cv, ci, n_chunks, root_token, out);
+  topk_stage2_kernel<<<rows, 256, (size_t)n_chunks * kmax * 8, st>>>(rs, cv, ci, n_chunks, root_token, out);
   MDZ_LAUNCH_CHECK();
   return MDZ_OK;
 }
