@@ -725,6 +725,13 @@ bool attn_mfma_supported(int dtype, int tree, const KvGeom& g) {
          (host_tree(tree)->T == 64 || (host_tree(tree)->T == 15 && !g.quant));
 }
 
+// Key-splits of a launch with 32 queries per workgroup (see attn_plan)
+static int halves_splits(int B, int pairs, int max_prefix) {
+  const int by_len = 1 + (int)sqrtf((float)(max_prefix >> 5) / 8.0f), cus = num_cus();
+  const int most = B == 1 || max_prefix < 2048 ? cus / (2 * pairs) : cus / pairs;
+  return most < 1 ? 1 : by_len < most ? by_len : most;
+}
+
 // Queries per workgroup and key-splits per (sequence, head) of a launch.
 struct AttnPlan {
   bool halves;  // 32 queries per workgroup (two fit a CU), else 64
@@ -766,7 +773,7 @@ static AttnPlan attn_plan(int T, const KvGeom& g, int B, int max_prefix, bool fu
     if (T == 15)
       p.splits = at_most(by_len, cus / pairs);
     else if (p.halves)
-      p.splits = at_most(by_len, B == 1 || max_prefix < 2048 ? cus / (2 * pairs) : cus / pairs);
+      p.splits = halves_splits(B, pairs, max_prefix);
     else
       p.splits = at_most(1 + (int)sqrtf((float)nb / 4.0f), g.quant || g.group > 1 ? cus / pairs : cus * 4 / 5 / pairs + (B > 1));
   }
@@ -781,20 +788,23 @@ static AttnPlan attn_plan(int T, const KvGeom& g, int B, int max_prefix, bool fu
 }
 
 // Scratch of the splits' partial outputs.  A workspace is sized before the cache's row type is known and may serve shorter prefixes than it was
-// sized for, so this is a bound on every plan's splits that grows with the prefix.
+// sized for: the most splits of any plan for up to max_prefix keys.  Each rule's count grows with the prefix; only from 32 to 64 queries it may fall.
 int64_t attn_mfma_scratch_bytes(int B, const KvGeom& g, int T, int max_prefix) {
-  const int pairs = B * q_heads(g), cus = num_cus(), nb = max_prefix >> 5;
+  const int pairs = B * q_heads(g);
   int most = attn_plan(T, g, B, max_prefix, false).splits;
-  auto at_least = [&](int by_len, int cap) {
-    const int s = by_len < cap ? by_len : cap;
+  for (int quant = 0; quant < 2; ++quant) {
+    KvGeom gq = g;
+    gq.quant = quant;
+    const int s = attn_plan(T, gq, B, max_prefix, true).splits;
     if (s > most) most = s;
-  };
-  if (T == 15 && 8 * pairs <= 3 * cus) at_least(nb / 6, 6);
-  if (2 * pairs <= cus) at_least(1 + (int)sqrtf((float)nb / 4.0f), cus / pairs + (B > 1));
+  }
+  if (T == 64 && 2 * pairs <= num_cus()) {
+    const int s = halves_splits(B, pairs, max_prefix);
+    if (s > most) most = s;
+  }
 #ifdef MDZ_DEV_KNOBS
-  at_least(32, 32);
+  most = 32;
 #endif
-  if (most > 32) most = 32;
   return most == 1 ? 0 : (int64_t)pairs * most * (T * kHD + 2 * T) * 4;
 }
 

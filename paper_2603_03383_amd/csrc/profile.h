@@ -12,9 +12,9 @@ namespace mdz {
 
 enum ProfTag {
   PROF_GEMM = 0,     // portable GEMM
-  PROF_GEMM_W64,     // gemm_mfma_kernel<4,1,2,*>: 128-column bands, 64 rows (every layer GEMM and the LM head)
+  PROF_GEMM_W64,     // gemm_mfma_kernel<4,1,2,*>: 128-column bands, 64 rows (every layer GEMM and the LM head; gate/up: two to four waves)
   PROF_GEMM_N64,     // gemm_mfma_kernel<2,1,2,*>: 64-column bands, 64 rows (development plans only)
-  PROF_GEMM_W32,     // gemm_mfma_kernel<4,1,1,*>: <= 32 rows (Medusa heads, autoregressive step)
+  PROF_GEMM_W32,     // gemm_mfma_kernel<4,1,1,*>: <= 32 rows (Medusa heads, autoregressive step; gate/up: two to four waves)
   PROF_GEMM_N32,     // gemm_mfma_kernel<2,1,1,*>: <= 32 rows (development plans only)
   PROF_GEMM_LARGE,   // gemm_tile_kernel, gemm_wide_kernel: more than 64 rows (several sequences)
   PROF_ATTN,         // tree-masked attention (+ its combine pass)
