@@ -437,7 +437,7 @@ def main():
         ab["gemm"] = ab["weights_layers"]
         ab["gemm_w64"] -= ab["lm_head"]
         ab["total"] = ab["weights_layers"] + ab["kv_prefix"] + ab["kv_tree"]
-    # dominant kernel: gemm_mfma_kernel<4,1,2,128,E> (every 64-row GEMM launch: 128-column bands, 128-feature stages)
+    # dominant kernel: gemm_mfma_kernel<4,1,2,128,E> (every 64-row GEMM launch: 128-column bands, 128-feature stages; gate/up: two to four waves of 32 columns)
     gemm = prof.get("gemm_w64", dict(launches=0, total_us=0.0))
     gemm_us_per_step = gemm["total_us"] / args.steps
     gemm_gbps = ab["gemm_w64"] / (gemm_us_per_step * 1e-6) / 1e9 if gemm_us_per_step else 0.0
@@ -455,7 +455,7 @@ def main():
         "hbm": {"algorithmic_bytes_per_step": ab["total"], "achieved_GBps": step_gbps,
                 "frac_of_peak": step_gbps / HBM_PEAK_GBPS,
                 "kv_share_of_bytes": (ab["kv_prefix"] + ab["kv_tree"]) / ab["total"]},
-        "roofline": {"kernel": "gemm_mfma_kernel<4,1,2,128," + ("f16_t" if w.dtype == "fp16" else "bf16_t") + ",*> (gemm_w64: the QKV, O, gate/up, down launches of every layer and the LM head; the last template argument selects the epilogue: partial sums, or SwiGLU for gate/up)",
+        "roofline": {"kernel": "gemm_mfma_kernel<4,1,2,128," + ("f16_t" if w.dtype == "fp16" else "bf16_t") + ",*> (gemm_w64: the QKV, O, gate/up, down launches of every layer and the LM head; template arguments select the epilogue: partial sums, SwiGLU for gate/up (two to four waves per workgroup), or the argmax)",
                      "bound": "hbm", "achieved": gemm_gbps, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": gemm_gbps / HBM_PEAK_GBPS,
                      "traffic": (traffic["fetch_bytes_per_launch"] + traffic["write_bytes_per_launch"]) if traffic else None,
