@@ -57,6 +57,13 @@ int medusa_gemm_slot_count(int dtype, int M, int N, int K, int max_split, int co
 int medusa_gemm_many_rows_plan(int dtype, int M, int N, int K, int max_split, int swiglu, int32_t* wide, int32_t* tile_rows,
                                int32_t* tile_cols, int32_t* k_splits);
 
+/* How the attention of a pass over B sequences with prefixes of up to max_prefix keys is cut: `kernel` (0 = portable, 1 = tree on the
+ * matrix cores, 2 = single query on the matrix cores, 3 = single query with FMAs), `queries` of a tree a workgroup carries, key-`splits` per
+ * sequence and head, and whether workgroups take the longest sequences first.  kv_quant: the cache's row type (mdz_kv_desc.quant);
+ * fused: RoPE and cache write in the attention kernel (the normal order).  Needs no device. */
+int medusa_attention_plan(const mdz_model_desc* model, int kv_quant, int B, int max_prefix, int fused, int32_t* kernel, int32_t* queries,
+                          int32_t* splits, int32_t* ordered);
+
 /* ---- test hook --------------------------------------------------------------------------------------- */
 
 /* The layer runs RoPE + cache write either fused into the attention kernel's prologue (default) or as a kernel of

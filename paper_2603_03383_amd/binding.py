@@ -63,6 +63,7 @@ _SIGNATURES = {
     "medusa_tree_tables": (C.c_int, [C.c_int] + [C.c_void_p] * 5),
     "medusa_gemm_plan": (C.c_int, [C.c_int] * 5 + [C.c_void_p] * 4),
     "medusa_gemm_slot_count": (C.c_int, [C.c_int] * 6),
+    "medusa_attention_plan": (C.c_int, [C.POINTER(ModelDesc)] + [C.c_int] * 4 + [C.c_void_p] * 4),
     "medusa_gemm_many_rows_plan": (C.c_int, [C.c_int] * 6 + [C.c_void_p] * 4),
     "medusa_last_error": (C.c_char_p, []),
     "medusa_profile_begin": (C.c_int, [C.c_int]),
@@ -163,6 +164,13 @@ def medusa_gemm_many_rows_plan(dtype: int, M: int, N: int, K: int, max_split: in
     vals = [C.c_int32() for _ in range(4)]
     _check(lib().medusa_gemm_many_rows_plan(dtype, M, N, K, max_split, int(swiglu), *[C.byref(v) for v in vals]))
     return dict(zip(("wide", "tile_rows", "tile_cols", "k_splits"), [v.value for v in vals]))
+
+
+def medusa_attention_plan(model: "ModelDesc", B: int, max_prefix: int, kv_quant: str = "", fused: bool = True) -> dict:
+    vals = [C.c_int32() for _ in range(4)]
+    _check(lib().medusa_attention_plan(C.byref(model), KV_QUANT[kv_quant], B, max_prefix, int(fused), *[C.byref(v) for v in vals]))
+    kernel, queries, splits, ordered = (v.value for v in vals)
+    return dict(kernel=("portable", "tree", "one_mfma", "one_fma")[kernel], queries=queries, splits=splits, ordered=bool(ordered))
 
 
 def medusa_tree_tables(tree: int) -> dict:

@@ -642,6 +642,32 @@ static int decode_splits(int B, int kv_heads, int n_heads, int max_prefix) {
   return s > 32 ? 32 : s < 1 ? 1 : s;
 }
 
+// What launch_attention_decode does with a batch.
+struct DecodePlan {
+  int splits;
+  bool fma;      // attn_decode_one_kernel, else attn_decode_kernel
+  bool ordered;  // the longest sequences first
+};
+static DecodePlan decode_plan(const KvGeom& g, int B, int max_prefix) {
+  DecodePlan p;
+  p.splits = decode_splits(B, g.n_heads, q_heads(g), max_prefix);
+  const int chunks = (g.group + 31) / 32;
+  // Ungrouped heads and more workgroups than the matrix-core kernel keeps resident: FMAs.  (Per layer with small GEMMs, matrix cores /
+  // FMAs: 64 sequences x 32 heads of S / 4 .. S keys, S = 16 94.2 / 77.9 us, 100 100.3 / 83.0, 500 149.0 / 140.4, 2000 309.8 / 308.3;
+  // 8-bit rows 95.3 / 76.8, 98.4 / 79.0, 124.3 / 105.1, 203.7 / 199.2; 32 at 4000 291.3 / 293.3, 8-bit 185.4 / 183.0.)
+  p.fma = g.group == 1 && (int64_t)p.splits * g.n_heads * B > 2 * num_cus();
+  // More workgroups than fit at once: long sequences first, from 1536 keys on.  (Finding its place costs a workgroup 1 - 2 us: per layer,
+  // lengths S / 4 .. S, in order / not: 64 sequences x 32 heads at S = 100 83.1 / 77.9 us, 500 140.2 / 139.3, 1000 199.3 / 200.1, 2000
+  // 309.5 / 313.0; 49 at 2000 246.6 / 256.0; 49 x 8 key/value heads of 4 query heads at 500 77.6 / 73.1, 1000 84.7 / 80.1, 2000 110.9 / 111.2.)
+  p.ordered = B > 1 && max_prefix >= 1536 && (int64_t)p.splits * g.n_heads * chunks * B > 2 * num_cus();
+  return p;
+}
+
+AttentionPlan attn_decode_plan(const KvGeom& g, int B, int max_prefix) {
+  const DecodePlan p = decode_plan(g, B, max_prefix);
+  return AttentionPlan{p.fma ? ATTN_ONE_FMA : ATTN_ONE_MFMA, 1, p.splits, p.ordered};
+}
+
 int64_t attn_decode_scratch_bytes(int B, int n_heads, int kv_heads, int max_prefix) {
   const int s = decode_splits(B, kv_heads, n_heads, max_prefix);
   return s == 1 ? 0 : (int64_t)B * n_heads * s * (kHD + 2) * 4;
@@ -652,7 +678,8 @@ static int launch_attention_decode_t(const void* q, const Partials* qkv, const f
                                      int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out, void* scratch,
                                      int64_t scratch_bytes, hipStream_t st) {
   if (B == 0) return MDZ_OK;
-  const int nq = q_heads(g), splits = decode_splits(B, g.n_heads, nq, max_prefix), chunks = (g.group + 31) / 32;
+  const DecodePlan plan = decode_plan(g, B, max_prefix);
+  const int nq = q_heads(g), splits = plan.splits, chunks = (g.group + 31) / 32;
   MDZ_REQUIRE(scratch_bytes >= attn_decode_scratch_bytes(B, nq, g.n_heads, max_prefix), MDZ_EWORKSPACE,
               "decode attention: scratch too small");
   float* part_o = (float*)scratch;
@@ -663,24 +690,17 @@ static int launch_attention_decode_t(const void* q, const Partials* qkv, const f
   MDZ_SET_LDS_ONCE((attn_decode_kernel<E, Q8, false>), 4 * 32 * (kORow + 2) * 4);
   MDZ_SET_LDS_ONCE((attn_decode_kernel<E, Q8, true>), 4 * 32 * (kORow + 2) * 4);
   const Partials none = single_slot(nullptr, 0, 0);
-  // More workgroups than fit at once: long sequences first, from 1536 keys on.  (Finding its place costs a workgroup 1 - 2 us: per layer,
-  // lengths S / 4 .. S, in order / not: 64 sequences x 32 heads at S = 100 83.1 / 77.9 us, 500 140.2 / 139.3, 1000 199.3 / 200.1, 2000
-  // 309.5 / 313.0; 49 at 2000 246.6 / 256.0; 49 x 8 key/value heads of 4 query heads at 500 77.6 / 73.1, 1000 84.7 / 80.1, 2000 110.9 / 111.2.)
-  const bool ordered = B > 1 && max_prefix >= 1536 && (int64_t)splits * g.n_heads * chunks * B > 2 * num_cus();
-  // Ungrouped heads and more workgroups than the matrix-core kernel keeps resident: FMAs.  (Per layer with small GEMMs, matrix cores /
-  // FMAs: 64 sequences x 32 heads of S / 4 .. S keys, S = 16 94.2 / 77.9 us, 100 100.3 / 83.0, 500 149.0 / 140.4, 2000 309.8 / 308.3;
-  // 8-bit rows 95.3 / 76.8, 98.4 / 79.0, 124.3 / 105.1, 203.7 / 199.2; 32 at 4000 291.3 / 293.3, 8-bit 185.4 / 183.0.)
   // Non-temporal K and V once a pass reads more of them than the caches hold from one pass to the next.  (us, steps of 4 layers, plain / non-temporal:
   // one sequence x 32 heads at 3000 keys (200 MB) 563 / 568, 6000 610 / 595; 24 x 8 at 300 .. 1000 606 / 620, 3000 (at most 1.2 GB) 719 / 706, 64 x 8 at
   // 1000 (1.1 GB) 735 / 738, 3000 957 / 934, 90 x 8 at 3000 1282 / 1241, but at 500, 6 layers, 1131 / 1142.  More than one key/value head's workgroup per block: plain.)
   const double stream = (double)g.n_layers * B * g.n_heads * max_prefix * (Q8 ? 264 : 512);
   const bool once = chunks == 1 && max_prefix >= 1024 && stream >= (B == 1 ? 350e6 : 640e6);
-  if (g.group == 1 && (int64_t)splits * g.n_heads * B > 2 * num_cus())
+  if (plan.fma)
     launch_timed(PROF_ATTN, attn_decode_one_kernel<E, Q8>, dim3(splits, g.n_heads, B), 256, 0, st, (const E*)q, qkv ? *qkv : none, cs,
-                 g, (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, ordered);
+                 g, (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, plan.ordered);
   else
     launch_timed(PROF_ATTN, once ? attn_decode_kernel<E, Q8, true> : attn_decode_kernel<E, Q8, false>, dim3(splits, g.n_heads * chunks, B), 256, lds_bytes, st, (const E*)q,
-                 qkv ? *qkv : none, cs, g, (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, ordered);
+                 qkv ? *qkv : none, cs, g, (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, plan.ordered);
   MDZ_LAUNCH_CHECK();
   if (splits > 1) {
     launch_timed(PROF_ATTN, attn_decode_combine_kernel<E>, dim3(nq, B), 128, 0, st, nq, splits, part_o, part_ml, (E*)att_out);

@@ -736,6 +736,7 @@ static int halves_splits(int B, int pairs, int max_prefix) {
 struct AttnPlan {
   bool halves;  // 32 queries per workgroup (two fit a CU), else 64
   int splits;
+  bool ordered;  // the longest sequences first
 };
 
 // fused: the kernel starts from the QKV partial sums, so one split is the tree split and the rest share the prefix.  Every further split
@@ -757,7 +758,7 @@ struct AttnPlan {
 static AttnPlan attn_plan(int T, const KvGeom& g, int B, int max_prefix, bool fused) {
   const int pairs = B * q_heads(g), cus = num_cus(), nb = max_prefix >> 5;
   const int by_len = 1 + (int)sqrtf((float)nb / 8.0f);
-  AttnPlan p{true, 1};
+  AttnPlan p{true, 1, false};
   auto at_most = [](int a, int b) { return a < b ? a : b; };
   if (T == 64) {
     const double through = (double)pairs * max_prefix * (g.quant ? 264 : 512);  // bytes of K and V that a launch takes through the CUs once
@@ -784,7 +785,23 @@ static AttnPlan attn_plan(int T, const KvGeom& g, int B, int max_prefix, bool fu
   if (env_h && T == 64) p.halves = atoi(env_h) != 0;
 #endif
   p.splits = p.splits < 1 ? 1 : p.splits > 32 ? 32 : p.splits;
+  // Long sequences first, where the launch gains by it: finding its place costs a workgroup 1 - 2 us, and where all workgroups run at
+  // once the hardware's order pairs them better.  us per layer, lengths S / 4 .. S, in order / not, 64 nodes unless said otherwise:
+  //   one split, more workgroups than fit (32 heads): 32 sequences at S = 1000 135 / 124, 2000 194 / 188, 3000 255 / 256, 4000 315 / 328;
+  //     16 at 1000 64 / 62, 3000 131 / 134, 4000 168 / 174; 8-bit rows: 32 at 1000 119 / 117, 2000 157 / 162, 16 at 1000 57 / 59, 2000 75 / 84;
+  //     15 nodes, 32 at 250 35 / 33, 1000 81 / 85, 4000 257 / 268;
+  //   one split, all at once: 6 at 1000 31 / 27, 3000 64 / 58 (15 nodes gain: 12 at 1000 32 / 33, 3000 87 / 92);
+  //   several splits: 3 at 1000 24.5 / 23.6, 2000 26.9 / 28.9, 3000 34.5 / 38.0, 8-bit rows at 6000 38 / 44.
+  const int halves_of_tree = T == 64 && p.halves ? 2 : 1;
+  const int64_t wgs = (int64_t)p.splits * pairs * halves_of_tree;
+  p.ordered = B > 1 && (p.splits > 1 ? wgs > cus && max_prefix >= 1536
+                                     : wgs > halves_of_tree * cus && max_prefix >= (T == 64 && !g.quant ? 2560 : 1024));
   return p;
+}
+
+AttentionPlan attn_mfma_plan(int tree, const KvGeom& g, int B, int max_prefix, bool fused) {
+  const AttnPlan p = attn_plan(host_tree(tree)->T, g, B, max_prefix, fused);
+  return AttentionPlan{ATTN_TREE, host_tree(tree)->T == 64 && !p.halves ? 64 : 32, p.splits, p.ordered};
 }
 
 // Scratch of the splits' partial outputs.  A workspace is sized before the cache's row type is known and may serve shorter prefixes than it was
@@ -810,30 +827,20 @@ int64_t attn_mfma_scratch_bytes(int B, const KvGeom& g, int T, int max_prefix) {
 
 template <typename E, bool Q8, int NU, int TQ, bool ONCE>
 static int launch_attention_mfma_t(int tree, const void* q, const Partials* qkv, const float* cs, const KvGeom& g, void* kc,
-                                   void* vc, int layer, const int32_t* seq_len, int B, int max_prefix, int splits, void* att_out,
+                                   void* vc, int layer, const int32_t* seq_len, int B, int max_prefix, const AttnPlan& p, void* att_out,
                                    void* scratch, int64_t scratch_bytes, hipStream_t st) {
   // the merge buffer [4][128][32 NU + 2] + [4][2][32 NU] floats overlays the staged Q tile and tree rows
   constexpr int lds_bytes = 4 * kHD * (32 * NU + 2) * 4 + 4 * 2 * 32 * NU * 4;
   static_assert(lds_bytes >= (32 * NU + 2 * TQ) * kQRow && lds_bytes * (3 - NU) <= 160 * 1024, "LDS budget of the tree kernel");
   MDZ_SET_LDS_ONCE((attn_tree_mfma_kernel<E, Q8, NU, TQ, ONCE>), lds_bytes);
-  const int nq = q_heads(g);
+  const int nq = q_heads(g), splits = p.splits;
   MDZ_REQUIRE(scratch_bytes >= attn_mfma_scratch_bytes(B, g, TQ, max_prefix), MDZ_EWORKSPACE, "attention: scratch too small");
   float* part_o = (float*)scratch;
   float* part_ml = part_o + (int64_t)B * nq * splits * TQ * kHD;
   dim3 grid(splits, nq, B * (TQ > 32 * NU ? 2 : 1));  // two workgroups share a sequence: blockIdx.z = 2 * sequence + half
   const Partials none = single_slot(nullptr, 0, 0);
-  // Long sequences first, where the launch gains by it: finding its place costs a workgroup 1 - 2 us, and where all workgroups run at
-  // once the hardware's order pairs them better.  us per layer, lengths S / 4 .. S, in order / not, 64 nodes unless said otherwise:
-  //   one split, more workgroups than fit (32 heads): 32 sequences at S = 1000 135 / 124, 2000 194 / 188, 3000 255 / 256, 4000 315 / 328;
-  //     16 at 1000 64 / 62, 3000 131 / 134, 4000 168 / 174; 8-bit rows: 32 at 1000 119 / 117, 2000 157 / 162, 16 at 1000 57 / 59, 2000 75 / 84;
-  //     15 nodes, 32 at 250 35 / 33, 1000 81 / 85, 4000 257 / 268;
-  //   one split, all at once: 6 at 1000 31 / 27, 3000 64 / 58 (15 nodes gain: 12 at 1000 32 / 33, 3000 87 / 92);
-  //   several splits: 3 at 1000 24.5 / 23.6, 2000 26.9 / 28.9, 3000 34.5 / 38.0, 8-bit rows at 6000 38 / 44.
-  const int64_t wgs = (int64_t)grid.x * grid.y * grid.z;
-  const bool ordered = B > 1 && (splits > 1 ? wgs > num_cus() && max_prefix >= 1536
-                                            : wgs > (NU == 1 && TQ == 64 ? 2 : 1) * num_cus() && max_prefix >= (TQ == 64 && !Q8 ? 2560 : 1024));
   launch_timed(PROF_ATTN, attn_tree_mfma_kernel<E, Q8, NU, TQ, ONCE>, grid, 256, lds_bytes, st, tree, (const E*)q, qkv ? *qkv : none, cs, g,
-               (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, ordered);
+               (E*)kc, (E*)vc, layer, seq_len, max_prefix, (E*)att_out, part_o, part_ml, p.ordered);
   MDZ_LAUNCH_CHECK();
   if (splits > 1) {
     launch_timed(PROF_ATTN, attn_combine_kernel<E, TQ>, dim3(nq, B, (TQ + 15) / 16), 256, 0, st, nq, splits, part_o, part_ml, (E*)att_out);
@@ -851,7 +858,7 @@ int launch_attention_mfma(int dtype, int tree, const void* q, const Partials* qk
   const bool once = g.group == 1;  // (and not in halves; 8-bit rows run alike: 16K keys 801 / 802 us per step of 4 layers)
 #define MDZ_ATTN_CASE(Q8, NU, TQ, ONCE)                                                                                     \
   MDZ_WITH_ELEM16(dtype, return (launch_attention_mfma_t<E, Q8, NU, TQ, ONCE>(tree, q, qkv, cs, g, kc, vc, layer, seq_len, B, \
-                                                                              max_prefix, p.splits, att_out, scratch, scratch_bytes, st)))
+                                                                              max_prefix, p, att_out, scratch, scratch_bytes, st)))
   if (T == 15) {
     if (once) MDZ_ATTN_CASE(false, 1, 15, true);
     MDZ_ATTN_CASE(false, 1, 15, false);

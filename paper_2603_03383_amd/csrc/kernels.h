@@ -116,6 +116,14 @@ int launch_gemm(int dtype, const void* X, const void* Wp, float* out, int M, int
 int launch_tree_attention(int dtype, int tree, const void* q, const KvGeom& g, const void* kc, const void* vc,
                           int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out, void* scratch,
                           int64_t scratch_bytes, hipStream_t st);
+// How a launch over B sequences of up to max_prefix keys is cut (for tests; numbers as in medusa_attention_plan).
+enum { ATTN_PORTABLE = 0, ATTN_TREE, ATTN_ONE_MFMA, ATTN_ONE_FMA };
+struct AttentionPlan {
+  int kernel;   // one of the above
+  int queries;  // of a workgroup
+  int splits;   // key-splits per sequence and head
+  bool ordered;  // the longest sequences first
+};
 int64_t tree_attention_scratch_bytes(int dtype, int tree, const KvGeom& g, int B, int max_prefix);
 
 }  // namespace mdz

@@ -95,12 +95,14 @@ static int64_t gemm_part_elems(int dtype, int rows, int N, int K, int max_slots 
 
 bool attn_mfma_supported(int dtype, int tree, const KvGeom& g);
 int64_t attn_mfma_scratch_bytes(int B, const KvGeom& g, int T, int max_prefix);
+AttentionPlan attn_mfma_plan(int tree, const KvGeom& g, int B, int max_prefix, bool fused);
 int launch_attention_mfma(int dtype, int tree, const void* q, const Partials* qkv, const float* cs, const KvGeom& g, void* kc,
                           void* vc, int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out,
                           void* scratch, int64_t scratch_bytes, hipStream_t st);
 
 bool attn_decode_supported(int dtype, int tree, const KvGeom& g);
 int64_t attn_decode_scratch_bytes(int B, int n_heads, int kv_heads, int max_prefix);
+AttentionPlan attn_decode_plan(const KvGeom& g, int B, int max_prefix);
 int launch_attention_decode(int dtype, const void* q, const Partials* qkv, const float* cs, const KvGeom& g, void* kc, void* vc,
                             int layer, const int32_t* seq_len, int B, int max_prefix, void* att_out, void* scratch,
                             int64_t scratch_bytes, hipStream_t st);
@@ -417,6 +419,27 @@ int medusa_gemm_many_rows_plan(int dtype, int M, int N, int K, int max_split, in
   if (tile_rows) *tile_rows = p.tile_rows;
   if (tile_cols) *tile_cols = p.tile_cols;
   if (k_splits) *k_splits = p.k_splits;
+  return MDZ_OK;
+}
+
+int medusa_attention_plan(const mdz_model_desc* model, int kv_quant, int B, int max_prefix, int fused, int32_t* kernel, int32_t* queries,
+                          int32_t* splits, int32_t* ordered) {
+  int rc = check_model(model);
+  if (rc) return rc;
+  MDZ_REQUIRE(B >= 1 && max_prefix >= 0, MDZ_EINVAL, "attention plan: B %d, max_prefix %d", B, max_prefix);
+  mdz_kv_desc kv{};
+  kv.n_layers = model->n_layers, kv.batch = B, kv.n_heads = kv_heads(*model), kv.head_dim = model->head_dim;
+  kv.cap = max_prefix + host_tree(model->tree)->T, kv.dtype = model->dtype, kv.quant = kv_quant;
+  if ((rc = check_kv_quant(&kv))) return rc;
+  MDZ_REQUIRE(kv_quant == MDZ_KV_PLAIN || host_tree(model->tree)->T != 15, MDZ_EUNSUPPORTED, "8-bit kv rows need a tree of 64 nodes or 1 node");
+  const KvGeom g = geom(&kv, model->n_heads / kv_heads(*model));
+  AttentionPlan p{ATTN_PORTABLE, 1, 1, false};
+  if (attn_decode_supported(model->dtype, model->tree, g)) p = attn_decode_plan(g, B, max_prefix);
+  else if (attn_mfma_supported(model->dtype, model->tree, g)) p = attn_mfma_plan(model->tree, g, B, max_prefix, fused != 0);
+  if (kernel) *kernel = p.kernel;
+  if (queries) *queries = p.queries;
+  if (splits) *splits = p.splits;
+  if (ordered) *ordered = p.ordered;
   return MDZ_OK;
 }
 

@@ -1,0 +1,32 @@
+"""CPU tests of the attention's host-side plan (no GPU work; 256 CUs): kernel, queries per workgroup, key-splits and the order of the
+sequences."""
+import pytest
+
+import paper_2603_03383_amd as P
+
+
+def _model(n_heads, kv_heads=0, tree="tree64", head_dim=128, dtype="bf16"):
+    return P.ModelDesc(n_heads * head_dim, n_heads, head_dim, 704, 1024, 2, P.DTYPES[dtype], P.TREES[tree], 1e-5, 1e4, kv_heads)
+
+
+def _plan(m, B, max_prefix, quant="", fused=True):
+    p = P.medusa_attention_plan(m, B, max_prefix, quant, fused)
+    return p["kernel"], p["queries"], p["splits"]
+
+
+def test_kernels():
+    assert _plan(_model(4, head_dim=64, dtype="fp32"), 1, 100) == ("portable", 1, 1)
+    assert _plan(_model(32), 1, 1024) == ("tree", 32, 3)
+    assert _plan(_model(32), 1, 16384) == ("tree", 64, 6)
+    assert _plan(_model(32), 1, 16384, fused=False) == ("tree", 64, 16)
+    assert _plan(_model(32, tree="tree15"), 1, 1024) == ("tree", 32, 5)
+    assert _plan(_model(32, tree="tree1"), 1, 1024) == ("one_mfma", 1, 4)
+    assert _plan(_model(32, tree="tree1"), 64, 100) == ("one_fma", 1, 1)
+    assert not P.medusa_attention_plan(_model(32), 16, 1500)["ordered"] and P.medusa_attention_plan(_model(32), 16, 2560)["ordered"]
+
+
+def test_errors():
+    for args in [(_model(32), 0, 100), (_model(32), 1, -1), (_model(32, tree="tree15"), 1, 100, "fp8e4m3"),
+                 (_model(4, head_dim=64), 1, 100, "fp8e4m3"), (_model(32, 5), 1, 100)]:
+        with pytest.raises(P.MedusaError):
+            P.medusa_attention_plan(*args)
