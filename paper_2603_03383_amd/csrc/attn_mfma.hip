@@ -753,6 +753,12 @@ struct AttnPlan {
 //     s8 779, h s4 799.
 //   several sequences (n / 8 .. n keys; the longest is the last to end, so long ones take twice the splits): 2 at 1500 h s2 788, h s3 802; 4000 s4 864,
 //     h s4 853; 8000 s3 922, s4 923, h s4 926; 3 at 1500 h s1 892, h s2 901; 2500 h s1 931, h s2 922; 8000 s2 1091, s3 1060; 4 at 600 h s1 1002, h s2 1025.
+//   8-bit rows of several sequences are converted by more CUs with 32 queries, whatever the length (2 layers, h / 64 queries): 2 at 14000 374 / 420, 3 at
+//     11000 435 / 498, 4 at 8000 482 / 513, 5 at 6000 557 / 631, 22000 782 / 1010, 8 at 8000 748 / 796, of equal length within 1 % or better.
+//   more pairs than half the CUs, hence one split (3 layers, h / 64 queries, lengths n / 8 .. n and n / 2 .. n): 5 x 32 heads at 2500 739 / 741 and 771 / 751,
+//     6 at 3400 814 / 813 and 869 / 835, 7 at 3200 (4 layers) 1316 / 1263 and 1365 / 1291, 9 x 16 at 3000 500 / 500 and 539 / 501, 11 at 3000 598 / 546 and
+//     604 / 553, 4 x 40 at 2500 866 / 840 and 886 / 848 (32 queries are ahead by at most 1 %, where five or six lengths spread from n / 20);
+//     grouped heads (2 layers): 5 at 3000 503 / 521 and 523 / 526, 8 at 3000 627 / 632 and 649 / 654.
 //   15 nodes, one sequence: 1000 s3 573, s5 568; 4000 s4 609, s6 595; 8000 s4 664, s6 632; two 2000 s3 613, s4 604, s6 614; 8000 s4 688, s6 673; three 2000 s2
 //     650, s4 644; 8000 s2 779, s4 759, s5 780; four 2000 s2 666, s4 678; six 2000 s1 784, s2 802.
 static AttnPlan attn_plan(int T, const KvGeom& g, int B, int max_prefix, bool fused) {
@@ -762,7 +768,8 @@ static AttnPlan attn_plan(int T, const KvGeom& g, int B, int max_prefix, bool fu
   auto at_most = [](int a, int b) { return a < b ? a : b; };
   if (T == 64) {
     const double through = (double)pairs * max_prefix * (g.quant ? 264 : 512);  // bytes of K and V that a launch takes through the CUs once
-    p.halves = pairs <= cus && through <= (B == 1 ? 96e6 : 160e6) * (g.group > 1 ? 2.5 : g.quant ? 1.3 : 1.0);
+    p.halves = pairs <= cus && ((g.quant && B > 1) || (g.group > 1 && max_prefix < 3584) ||
+                                through <= (B == 1 ? 96e6 : 160e6) * (g.group > 1 ? 2.5 : g.quant ? 1.3 : 1.0));
   }
   if (!fused) {
     const int most = (max_prefix + T + 31) / 32 / 8;       // >= 2 blocks per wave

@@ -30,3 +30,16 @@ def test_errors():
                  (_model(4, head_dim=64), 1, 100, "fp8e4m3"), (_model(32, 5), 1, 100)]:
         with pytest.raises(P.MedusaError):
             P.medusa_attention_plan(*args)
+
+
+@pytest.mark.parametrize("n_heads,kv_heads", [(16, 0), (32, 0), (40, 0), (32, 8)])
+def test_8bit_rows_of_several_sequences_take_32_queries(n_heads, kv_heads):
+    for B in range(2, 256 // n_heads + 1):
+        for max_prefix in (300, 4900, 4930, 6600, 8200, 9900, 12400, 14335, 14336, 22000):
+            assert _plan(_model(n_heads, kv_heads), B, max_prefix, "fp8e4m3")[:2] == ("tree", 32), (B, max_prefix)
+
+
+def test_one_split_of_grouped_heads_takes_32_queries():
+    for B in (5, 6, 7, 8):
+        for max_prefix in (1000, 3052, 3583):
+            assert _plan(_model(32, 8), B, max_prefix) == ("tree", 32, 1), (B, max_prefix)

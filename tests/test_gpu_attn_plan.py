@@ -39,6 +39,15 @@ def test_one_sequence_8bit(max_prefix):
     check_layer_kv8(_layer_case(w, [S], max_prefix, x_seed=f"plan8_x{max_prefix}"), [S], w, f"plan8_x{max_prefix}")
 
 
+@pytest.mark.parametrize("n_heads,batch,max_prefix", [(2, 3, 22000), (32, 3, 9000), (32, 5, 5000)])
+def test_several_sequences_8bit(n_heads, batch, max_prefix):
+    """32 queries per workgroup whatever the length; ten splits, two and one."""
+    S_list = [1300, 0, 700, 33, 64][:batch]
+    w = _w(n_heads, kv_quant="fp8e4m3").with_(prefix=tuple(S_list))
+    seed = f"plan8_x{n_heads}_{batch}"
+    check_layer_kv8(_layer_case(w, S_list, max_prefix, x_seed=seed), S_list, w, seed)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
 @pytest.mark.parametrize("n_heads,batch,lengths", [(32, 1, [1200]), (32, 3, [1184, 32, 700]), (32, 4, [200, 1000, 0, 31]), (2, 48, None), (2, 49, None),
                                                    (2, 2, [4100, 40])])
