@@ -624,18 +624,28 @@ bool attn_decode_supported(int dtype, int tree, const KvGeom& g) {
 //     3000 760 / 750; 18 at 3000 883 / 858.  40 heads, 8-bit rows: two at 4000 602 / 598, three 607 / 607 (two splits 636)
 //   16 heads: one at 4000 280 / 271, eight at 4000 364 / 345.  8 key/value heads: twelve at 1000 599 / 593, 24 at 300 598 / 584, 1000 626 / 606, 3000
 //     718 / 706, 40 at 300 636 / 613, 1000 693 / 682 (at 3000 one split 833, two 821; 24 at 6000 829, three 816)
+// 8-bit rows cost conversions, i.e. vector work that wants more splits: several sequences of ungrouped heads take the other kernel's fewest splits as
+// soon as they are seven blocks long, a single sequence one workgroup per CU.  us, steps of 3 layers, one per seven blocks as above / the rule
+// of 16-bit rows / this: 32 heads: one sequence of 5000 keys 342 / 329 / 326, three at 900 322 / 320 / 312, 1300 317 / 325 / 314, 2000 321 / 331 / 318,
+// five at 1300 322 / 329 / 319, eight at 900 337 / 327 / 324 (at 500 326 / 315 / 318, left as it is).  40 heads: one at 9000 460 / 472 / 458, 14000 490 / 508
+// / 492, two at 3000 426 / 434 / 426, four at 1300 425 / 440 / 425.  16 heads: one at 1300 178 / 179 / 176, two at 14000 216 / 223 / 210, three at 5000 193 /
+// 199 / 191, twelve at 900 194 / 200 / 189.
 // Dealing equal parts of a ragged batch out by its device-side lengths was measured too: 24 sequences of 90 .. 3000 keys
 // gain 1 us of 37 (the HBM stream bounds them), a single sequence loses 1 us to finding its part.
-static int decode_splits(int B, int kv_heads, int n_heads, int max_prefix) {
+static int decode_splits(int B, int kv_heads, int n_heads, int max_prefix, bool q8) {
   const int nb = (max_prefix + 1 + 31) / 32, pairs = B * kv_heads, cus = num_cus();
-  const int by_len = nb <= 12 ? 1 : (int)sqrtf(0.5f * (float)nb), by_fill = (2 * cus + pairs - 1) / pairs;
-  int most;
+  int by_len = nb <= 12 ? 1 : (int)sqrtf(0.5f * (float)nb), most;
+  const int by_fill = (2 * cus + pairs - 1) / pairs, many = 2 * cus / pairs + 1;  // many: the fewest that the FMA kernel takes
   if (n_heads != kv_heads)
     most = pairs <= cus ? (max_prefix < 4096 ? cus / pairs : by_fill) : max_prefix < 2048 ? 1 : by_fill;
   else if (pairs > cus)
     most = pairs >= 3 * cus ? 1 : max_prefix >= 2048 ? 3 : pairs >= 2 * cus ? 1 : 2;
-  else if (const int many = 2 * cus / pairs + 1; B > 1 && by_len >= many && max_prefix >= 1536)
-    most = many;  // the fewest that the FMA kernel takes
+  else if (q8 && B == 1)
+    most = cus / pairs, by_len = nb <= 12 ? 1 : (int)sqrtf((float)nb);
+  else if (q8 && many <= 32 && (nb + 6) / 7 >= many && (4 * pairs <= 3 * cus || max_prefix >= 640))
+    by_len = most = many;
+  else if (B > 1 && by_len >= many && max_prefix >= 1536)
+    most = many;
   else
     most = cus * 3 / 4 / pairs + (B > 1);
   const int s = by_len < most ? by_len : most;
@@ -650,7 +660,7 @@ struct DecodePlan {
 };
 static DecodePlan decode_plan(const KvGeom& g, int B, int max_prefix) {
   DecodePlan p;
-  p.splits = decode_splits(B, g.n_heads, q_heads(g), max_prefix);
+  p.splits = decode_splits(B, g.n_heads, q_heads(g), max_prefix, g.quant != 0);
   const int chunks = (g.group + 31) / 32;
   // Ungrouped heads and more workgroups than the matrix-core kernel keeps resident: FMAs.  (Per layer with small GEMMs, matrix cores /
   // FMAs: 64 sequences x 32 heads of S / 4 .. S keys, S = 16 94.2 / 77.9 us, 100 100.3 / 83.0, 500 149.0 / 140.4, 2000 309.8 / 308.3;
@@ -668,8 +678,10 @@ AttentionPlan attn_decode_plan(const KvGeom& g, int B, int max_prefix) {
   return AttentionPlan{p.fma ? ATTN_ONE_FMA : ATTN_ONE_MFMA, 1, p.splits, p.ordered};
 }
 
+// (a workspace is sized before the cache's row type is known)
 int64_t attn_decode_scratch_bytes(int B, int n_heads, int kv_heads, int max_prefix) {
-  const int s = decode_splits(B, kv_heads, n_heads, max_prefix);
+  const int s16 = decode_splits(B, kv_heads, n_heads, max_prefix, false), s8 = decode_splits(B, kv_heads, n_heads, max_prefix, true);
+  const int s = s16 > s8 ? s16 : s8;
   return s == 1 ? 0 : (int64_t)B * n_heads * s * (kHD + 2) * 4;
 }
 

@@ -43,3 +43,16 @@ def test_one_split_of_grouped_heads_takes_32_queries():
     for B in (5, 6, 7, 8):
         for max_prefix in (1000, 3052, 3583):
             assert _plan(_model(32, 8), B, max_prefix) == ("tree", 32, 1), (B, max_prefix)
+
+
+@pytest.mark.parametrize("n_heads,B,max_prefix,kernel,splits", [
+    (32, 3, 1119, "one_mfma", 3), (32, 3, 1120, "one_fma", 6), (32, 3, 2064, "one_fma", 6), (32, 5, 1364, "one_fma", 4),
+    (32, 8, 564, "one_mfma", 1), (32, 8, 964, "one_fma", 3), (40, 2, 1664, "one_fma", 7), (40, 4, 1164, "one_fma", 4),
+    (16, 2, 14064, "one_fma", 17), (16, 3, 4564, "one_fma", 11), (16, 12, 964, "one_fma", 3),
+    (40, 1, 9064, "one_mfma", 6), (16, 1, 1364, "one_mfma", 6), (32, 1, 14064, "one_mfma", 8)])
+def test_single_query_splits_of_8bit_rows(n_heads, B, max_prefix, kernel, splits):
+    """As many as the conversions pay for; the workspace holds them (it is sized before the row type is known)."""
+    m = _model(n_heads, tree="tree1")
+    assert _plan(m, B, max_prefix, "fp8e4m3") == (kernel, 1, splits)
+    scratch = (B * n_heads * splits * 130 * 4 + 255) // 256 * 256
+    assert P.medusa_workspace_bytes(m, B, max_prefix) - P.medusa_workspace_bytes(m, B, 0) >= scratch * (splits > 1)

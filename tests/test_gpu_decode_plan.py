@@ -3,6 +3,7 @@ twelve blocks; many sequences of ungrouped heads, in the other kernel from 2048 
 non-temporally once a pass reads 350 MB of them.  Bounds: the layer parity tests'."""
 import pytest
 
+import paper_2603_03383_amd as P
 import workload as W
 from tests.test_gpu_kv8 import check_layer_kv8
 from tests.test_gpu_parity import _check_layer, _layer_case
@@ -44,3 +45,17 @@ def test_non_temporal_loads(kv_heads):
 def test_non_temporal_loads_8bit():
     w = _w(32, kv_quant="fp8e4m3").with_(prefix=(700,))
     check_layer_kv8(_layer_case(w, [700], 41500, x_seed="decode_nt8_x"), [700], w, "decode_nt8_x")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("n_heads,batch,max_prefix,splits", [(2, 48, 1119, 3), (2, 48, 1120, 6), (2, 16, 3600, 17), (2, 128, 640, 3), (4, 1, 1400, 6)])
+def test_8bit_splits(n_heads, batch, max_prefix, splits, dtype):
+    """Several sequences around the length where the FMA kernel takes them, in seventeen splits and at the most pairs; one sequence."""
+    S_list = [(211 * b) % 600 for b in range(batch)]
+    S_list[-1] = min(max_prefix, 1100)
+    w = _w(n_heads, dtype, kv_quant="fp8e4m3").with_(prefix=tuple(S_list))
+    seed = f"decode_plan8_x{batch}_{max_prefix}"
+    r = _layer_case(w, S_list, max_prefix, x_seed=seed)
+    plan = P.medusa_attention_plan(r["kv"].model.desc, batch, max_prefix, "fp8e4m3")
+    assert plan["splits"] == splits and plan["kernel"] == ("one_fma" if splits * batch * n_heads > 512 else "one_mfma")
+    check_layer_kv8(r, S_list, w, seed)
