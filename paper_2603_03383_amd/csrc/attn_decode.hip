@@ -630,14 +630,27 @@ bool attn_decode_supported(int dtype, int tree, const KvGeom& g) {
 // five at 1300 322 / 329 / 319, eight at 900 337 / 327 / 324 (at 500 326 / 315 / 318, left as it is).  40 heads: one at 9000 460 / 472 / 458, 14000 490 / 508
 // / 492, two at 3000 426 / 434 / 426, four at 1300 425 / 440 / 425.  16 heads: one at 1300 178 / 179 / 176, two at 14000 216 / 223 / 210, three at 5000 193 /
 // 199 / 191, twelve at 900 194 / 200 / 189.
+// Grouped heads: where two workgroups per CU take over.  us, steps of 3 layers, lengths n / 9 .. n, a workgroup per CU / two: 8 key/value heads, 17
+// sequences at 2000 350 / 360, 2500 375 / 368, 4000 420 / 407, 18 at 2500 377 / 371, 20 at 3000 400 / 408, 24 at 4000 437 / 447, 16 at 4000 388 / 397; 8-bit rows: 17 at
+// 2500 366 / 352, 4000 405 / 362, 24 at 2500 374 / 372, 4000 414 / 393, 28 at 2500 380 / 384, 4000 423 / 417, 12 at 2500 340 / 346, 4000 358 / 353, 10 layers: 7 at 3500
+// 1036 / 1049, 20 at 2100 1135 / 1145.
+// Few pairs take seven and eight splits early (one sequence at 2000 5 splits 311, 8 307, 16 313), and no more than eight beyond 16 pairs: eight lie on an XCD each
+// (steps of 10 layers: 4 sequences at 6000 8 splits 1046, 9 1094, 16 1083, 5 at 8000 8 1110, 10 1124, 12 1159, 3 at 8000 8 1055, 11 1095, 16 1074; but one at 12000
+// 8 1082, 12 1048, 16 1045).
 // Dealing equal parts of a ragged batch out by its device-side lengths was measured too: 24 sequences of 90 .. 3000 keys
 // gain 1 us of 37 (the HBM stream bounds them), a single sequence loses 1 us to finding its part.
 static int decode_splits(int B, int kv_heads, int n_heads, int max_prefix, bool q8) {
   const int nb = (max_prefix + 1 + 31) / 32, pairs = B * kv_heads, cus = num_cus();
   int by_len = nb <= 12 ? 1 : (int)sqrtf(0.5f * (float)nb), most;
   const int by_fill = (2 * cus + pairs - 1) / pairs, many = 2 * cus / pairs + 1;  // many: the fewest that the FMA kernel takes
-  if (n_heads != kv_heads)
-    most = pairs <= cus ? (max_prefix < 4096 ? cus / pairs : by_fill) : max_prefix < 2048 ? 1 : by_fill;
+  if (n_heads != kv_heads) {
+    // (beyond half as many pairs as CUs, a workgroup per CU leaves no room for a second split)
+    const bool few = 2 * pairs <= cus, half = !few && 16 * pairs <= 9 * cus;
+    const int fill_from = pairs > cus ? 2048 : q8 ? (few ? 3584 : half ? 2112 : 4 * pairs <= 3 * cus ? 2304 : 3072) : half ? 2304 : 4096;
+    most = max_prefix >= fill_from ? by_fill : pairs <= cus ? cus / pairs : 1;
+    if (8 * pairs <= cus && nb >= 48 && nb < 128) by_len = nb < 64 ? 7 : 8;
+    if (16 * pairs > cus && most > 8) most = 8;
+  }
   else if (pairs > cus)
     most = pairs >= 3 * cus ? 1 : max_prefix >= 2048 ? 3 : pairs >= 2 * cus ? 1 : 2;
   else if (q8 && B == 1)

@@ -56,3 +56,13 @@ def test_single_query_splits_of_8bit_rows(n_heads, B, max_prefix, kernel, splits
     assert _plan(m, B, max_prefix, "fp8e4m3") == (kernel, 1, splits)
     scratch = (B * n_heads * splits * 130 * 4 + 255) // 256 * 256
     assert P.medusa_workspace_bytes(m, B, max_prefix) - P.medusa_workspace_bytes(m, B, 0) >= scratch * (splits > 1)
+
+
+@pytest.mark.parametrize("B,max_prefix,quant,splits", [
+    (17, 2303, "", 1), (17, 2304, "", 4), (18, 4064, "", 4), (20, 4064, "", 1), (20, 4096, "", 4), (16, 4064, "", 2), (8, 4064, "", 4),
+    (17, 2111, "fp8e4m3", 1), (17, 2112, "fp8e4m3", 4), (24, 2303, "fp8e4m3", 1), (24, 2304, "fp8e4m3", 3), (28, 3064, "fp8e4m3", 1), (28, 3072, "fp8e4m3", 3),
+    (32, 4064, "fp8e4m3", 2), (12, 3583, "fp8e4m3", 2), (12, 3584, "fp8e4m3", 6), (14, 4064, "fp8e4m3", 5), (16, 3584, "fp8e4m3", 4),
+    (1, 1503, "", 4), (1, 1504, "", 7), (1, 2064, "", 8), (1, 12064, "", 13), (3, 8064, "", 8), (4, 6064, "", 8), (5, 12064, "", 8), (7, 6064, "fp8e4m3", 8),
+    (40, 2047, "", 1), (40, 2048, "", 2)])
+def test_single_query_splits_of_grouped_heads(B, max_prefix, quant, splits):
+    assert _plan(_model(32, 8, tree="tree1"), B, max_prefix, quant) == ("one_mfma", 1, splits)

@@ -25,6 +25,7 @@ def _w(n_heads, dtype="bf16", **kw):
     (2, 0, 129, 2047), (2, 0, 129, 2048),  # more pairs than CUs: two and three splits
     (2, 0, 260, 2048),                     # 520 pairs: three
     (4, 2, 64, 4095), (4, 2, 64, 4096),    # grouped: two and four splits
+    (4, 2, 68, 2303), (4, 2, 68, 2304),    # one and four
     (4, 2, 129, 2047), (4, 2, 129, 2048),  # one and two
 ])
 def test_layer(n_heads, kv_heads, batch, max_prefix, dtype):
@@ -48,14 +49,16 @@ def test_non_temporal_loads_8bit():
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
-@pytest.mark.parametrize("n_heads,batch,max_prefix,splits", [(2, 48, 1119, 3), (2, 48, 1120, 6), (2, 16, 3600, 17), (2, 128, 640, 3), (4, 1, 1400, 6)])
-def test_8bit_splits(n_heads, batch, max_prefix, splits, dtype):
-    """Several sequences around the length where the FMA kernel takes them, in seventeen splits and at the most pairs; one sequence."""
+@pytest.mark.parametrize("n_heads,kv_heads,batch,max_prefix,splits", [
+    (2, 0, 48, 1119, 3), (2, 0, 48, 1120, 6), (2, 0, 16, 3600, 17), (2, 0, 128, 640, 3), (4, 0, 1, 1400, 6), (4, 2, 68, 2304, 4), (4, 2, 48, 3584, 6)])
+def test_8bit_splits(n_heads, kv_heads, batch, max_prefix, splits, dtype):
+    """Several sequences around the length where the FMA kernel takes them, in seventeen splits and at the most pairs; one sequence; grouped
+    heads from the lengths on where they take two workgroups per CU."""
     S_list = [(211 * b) % 600 for b in range(batch)]
     S_list[-1] = min(max_prefix, 1100)
-    w = _w(n_heads, dtype, kv_quant="fp8e4m3").with_(prefix=tuple(S_list))
+    w = _w(n_heads, dtype, kv_quant="fp8e4m3", n_kv_heads=kv_heads).with_(prefix=tuple(S_list))
     seed = f"decode_plan8_x{batch}_{max_prefix}"
     r = _layer_case(w, S_list, max_prefix, x_seed=seed)
     plan = P.medusa_attention_plan(r["kv"].model.desc, batch, max_prefix, "fp8e4m3")
-    assert plan["splits"] == splits and plan["kernel"] == ("one_fma" if splits * batch * n_heads > 512 else "one_mfma")
+    assert plan["splits"] == splits and plan["kernel"] == ("one_fma" if not kv_heads and splits * batch * n_heads > 512 else "one_mfma")
     check_layer_kv8(r, S_list, w, seed)
