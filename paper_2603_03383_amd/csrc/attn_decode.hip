@@ -624,12 +624,13 @@ bool attn_decode_supported(int dtype, int tree, const KvGeom& g) {
 //     3000 760 / 750; 18 at 3000 883 / 858.  40 heads, 8-bit rows: two at 4000 602 / 598, three 607 / 607 (two splits 636)
 //   16 heads: one at 4000 280 / 271, eight at 4000 364 / 345.  8 key/value heads: twelve at 1000 599 / 593, 24 at 300 598 / 584, 1000 626 / 606, 3000
 //     718 / 706, 40 at 300 636 / 613, 1000 693 / 682 (at 3000 one split 833, two 821; 24 at 6000 829, three 816)
-// 8-bit rows cost conversions, i.e. vector work that wants more splits: several sequences of ungrouped heads take the other kernel's fewest splits as
-// soon as they are seven blocks long, a single sequence one workgroup per CU.  us, steps of 3 layers, one per seven blocks as above / the rule
-// of 16-bit rows / this: 32 heads: one sequence of 5000 keys 342 / 329 / 326, three at 900 322 / 320 / 312, 1300 317 / 325 / 314, 2000 321 / 331 / 318,
-// five at 1300 322 / 329 / 319, eight at 900 337 / 327 / 324 (at 500 326 / 315 / 318, left as it is).  40 heads: one at 9000 460 / 472 / 458, 14000 490 / 508
-// / 492, two at 3000 426 / 434 / 426, four at 1300 425 / 440 / 425.  16 heads: one at 1300 178 / 179 / 176, two at 14000 216 / 223 / 210, three at 5000 193 /
-// 199 / 191, twelve at 900 194 / 200 / 189.
+// Several sequences of ungrouped heads take the other kernel's fewest splits as soon as these are seven blocks long: with K and V from HBM its four
+// workgroups per CU ask for more at once.  us, lengths n / 9 .. n, matrix cores / the other kernel, steps of 10 layers: 3 x 32 heads at 900 1009 / 984,
+// 1600 1052 / 1010, 2100 1089 / 1022, 5 at 1100 1042 / 1013, 6 at 1100 1073 / 1036, 8 at 900 1073 / 1040 (at 350 976 / 985); 8 layers: 4 x 40 at 1100 1132 / 1102;
+// 16 layers: 4 x 16 at 4000 1037 / 997, 5 at 2800 1016 / 976, 10 at 700 984 / 931, 13 at 1100 1013 / 1023; but 2 x 16 (17 splits) at 2800 895 / 926.
+// 8-bit rows cost conversions, i.e. vector work: any count of splits pays for them there, and a single sequence takes one workgroup per CU (long ones of 33 heads
+// or more the other kernel).  Steps of 3 layers, by the square root / so: 32 heads: one sequence at 5000 329 / 326, three at 900 320 / 312, 2000 331 / 318; 40 heads: four at
+// 1300 440 / 425; 16 heads: one at 1300 179 / 176, two at 14000 223 / 210; 8 layers: one of 40 heads at 4000 1121 / 1095, 9000 1206 / 1170 (6 splits 1181).
 // Grouped heads: where two workgroups per CU take over.  us, steps of 3 layers, lengths n / 9 .. n, a workgroup per CU / two: 8 key/value heads, 17
 // sequences at 2000 350 / 360, 2500 375 / 368, 4000 420 / 407, 18 at 2500 377 / 371, 20 at 3000 400 / 408, 24 at 4000 437 / 447, 16 at 4000 388 / 397; 8-bit rows: 17 at
 // 2500 366 / 352, 4000 405 / 362, 24 at 2500 374 / 372, 4000 414 / 393, 28 at 2500 380 / 384, 4000 423 / 417, 12 at 2500 340 / 346, 4000 358 / 353, 10 layers: 7 at 3500
@@ -653,10 +654,11 @@ static int decode_splits(int B, int kv_heads, int n_heads, int max_prefix, bool 
   }
   else if (pairs > cus)
     most = pairs >= 3 * cus ? 1 : max_prefix >= 2048 ? 3 : pairs >= 2 * cus ? 1 : 2;
+  else if ((B > 1 ? many <= (q8 ? 32 : 12) : q8 && many <= 16) && (nb + 6) / 7 >= many &&
+           max_prefix >= (B == 1 ? 3584 : 4 * pairs <= 3 * cus ? 0 : 640))
+    by_len = most = many;
   else if (q8 && B == 1)
     most = cus / pairs, by_len = nb <= 12 ? 1 : (int)sqrtf((float)nb);
-  else if (q8 && many <= 32 && (nb + 6) / 7 >= many && (4 * pairs <= 3 * cus || max_prefix >= 640))
-    by_len = most = many;
   else if (B > 1 && by_len >= many && max_prefix >= 1536)
     most = many;
   else

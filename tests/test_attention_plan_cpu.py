@@ -49,7 +49,7 @@ def test_one_split_of_grouped_heads_takes_32_queries():
     (32, 3, 1119, "one_mfma", 3), (32, 3, 1120, "one_fma", 6), (32, 3, 2064, "one_fma", 6), (32, 5, 1364, "one_fma", 4),
     (32, 8, 564, "one_mfma", 1), (32, 8, 964, "one_fma", 3), (40, 2, 1664, "one_fma", 7), (40, 4, 1164, "one_fma", 4),
     (16, 2, 14064, "one_fma", 17), (16, 3, 4564, "one_fma", 11), (16, 12, 964, "one_fma", 3),
-    (40, 1, 9064, "one_mfma", 6), (16, 1, 1364, "one_mfma", 6), (32, 1, 14064, "one_mfma", 8)])
+    (40, 1, 3583, "one_mfma", 6), (40, 1, 3584, "one_fma", 13), (16, 1, 1364, "one_mfma", 6), (32, 1, 14064, "one_mfma", 8)])
 def test_single_query_splits_of_8bit_rows(n_heads, B, max_prefix, kernel, splits):
     """As many as the conversions pay for; the workspace holds them (it is sized before the row type is known)."""
     m = _model(n_heads, tree="tree1")
@@ -66,3 +66,11 @@ def test_single_query_splits_of_8bit_rows(n_heads, B, max_prefix, kernel, splits
     (40, 2047, "", 1), (40, 2048, "", 2)])
 def test_single_query_splits_of_grouped_heads(B, max_prefix, quant, splits):
     assert _plan(_model(32, 8, tree="tree1"), B, max_prefix, quant) == ("one_mfma", 1, splits)
+
+
+@pytest.mark.parametrize("n_heads,B,max_prefix,kernel,splits", [
+    (32, 2, 1791, "one_mfma", 4), (32, 2, 1792, "one_fma", 9), (32, 3, 1119, "one_mfma", 3), (32, 3, 1120, "one_fma", 6), (32, 5, 764, "one_fma", 4),
+    (32, 6, 564, "one_fma", 3), (32, 8, 639, "one_mfma", 1), (32, 8, 640, "one_fma", 3), (40, 3, 1164, "one_fma", 5), (16, 3, 4064, "one_fma", 11),
+    (16, 2, 6064, "one_mfma", 7), (16, 10, 764, "one_fma", 4), (32, 1, 9064, "one_mfma", 6), (40, 1, 9064, "one_mfma", 4)])
+def test_single_query_splits_of_16bit_rows(n_heads, B, max_prefix, kernel, splits):
+    assert _plan(_model(n_heads, tree="tree1"), B, max_prefix) == (kernel, 1, splits)

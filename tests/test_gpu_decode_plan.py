@@ -20,8 +20,9 @@ def _w(n_heads, dtype="bf16", **kw):
 @pytest.mark.parametrize("n_heads,kv_heads,batch,max_prefix", [
     (4, 0, 1, 383), (4, 0, 1, 384),        # twelve blocks, thirteen
     (4, 0, 3, 3000),                       # splits by length
-    (2, 0, 48, 2270), (2, 0, 48, 2271),    # three splits; six, FMA kernel
-    (2, 0, 64, 1535), (2, 0, 64, 2100),    # two; five, FMA kernel
+    (2, 0, 48, 1119), (2, 0, 48, 1120),    # three splits; six, FMA kernel
+    (2, 0, 64, 895), (2, 0, 64, 896),      # two; five, FMA kernel
+    (2, 0, 112, 639), (2, 0, 112, 640),    # one; three, FMA kernel
     (2, 0, 129, 2047), (2, 0, 129, 2048),  # more pairs than CUs: two and three splits
     (2, 0, 260, 2048),                     # 520 pairs: three
     (4, 2, 64, 4095), (4, 2, 64, 4096),    # grouped: two and four splits
@@ -30,7 +31,7 @@ def _w(n_heads, dtype="bf16", **kw):
 ])
 def test_layer(n_heads, kv_heads, batch, max_prefix, dtype):
     w = _w(n_heads, dtype, n_kv_heads=kv_heads)
-    S_list = [max_prefix if batch == 1 else (611 * b) % 1500 for b in range(batch)]
+    S_list = [max_prefix if batch == 1 else (611 * b) % min(1500, max_prefix) for b in range(batch)]
     S_list[-1] = min(max_prefix, 2000)
     _check_layer(_layer_case(w, S_list, max_prefix, x_seed=f"decode_plan_x{batch}_{max_prefix}"), S_list, dtype)
 
