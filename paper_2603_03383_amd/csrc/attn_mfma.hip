@@ -728,8 +728,13 @@ bool attn_mfma_supported(int dtype, int tree, const KvGeom& g) {
 // Key-splits of a launch with 32 queries per workgroup (see attn_plan)
 static int halves_splits(int B, int pairs, int max_prefix) {
   const int by_len = 1 + (int)sqrtf((float)(max_prefix >> 5) / 8.0f), cus = num_cus();
-  const int most = B == 1 || max_prefix < 2048 ? cus / (2 * pairs) : cus / pairs;
+  const int most = B == 1 || max_prefix < 1536 ? cus / (2 * pairs) : max_prefix < 2048 ? cus * 9 / 8 / (2 * pairs) : cus / pairs;
   return most < 1 ? 1 : by_len < most ? by_len : most;
+}
+
+// Key-splits that fill the CUs with a workgroup each: ungrouped heads four fifths of them (see attn_plan)
+static int full_splits(const KvGeom& g, int B, int pairs) {
+  return g.group > 1 ? num_cus() / pairs : num_cus() * 4 / 5 / pairs + (B > 1);
 }
 
 // Queries per workgroup and key-splits per (sequence, head) of a launch.
@@ -752,7 +757,8 @@ struct AttnPlan {
 //   four query heads to a key/value head (their blocks come from L2): 4000 s4 728, h s4 677; 7000 s6 719, h s4 694; 14000 s8 759, h s4 752; 16384 s6 811,
 //     s8 779, h s4 799.
 //   several sequences (n / 8 .. n keys; the longest is the last to end, so long ones take twice the splits): 2 at 1500 h s2 788, h s3 802; 4000 s4 864,
-//     h s4 853; 8000 s3 922, s4 923, h s4 926; 3 at 1500 h s1 892, h s2 901; 2500 h s1 931, h s2 922; 8000 s2 1091, s3 1060; 4 at 600 h s1 1002, h s2 1025.
+//     h s4 853; 8000 s3 922, s4 923, h s4 926; 3 at 1500 h s1 892, h s2 901 (3 x 16 heads, 16 layers, 1100 h s2
+//     1520, h s3 1519, 1700 h s2 1573, h s3 1556); 2500 h s1 931, h s2 922; 8000 s2 1091, s3 1060; 4 at 600 h s1 1002, h s2 1025.
 //   8-bit rows of several sequences are converted by more CUs with 32 queries, whatever the length (2 layers, h / 64 queries): 2 at 14000 374 / 420, 3 at
 //     11000 435 / 498, 4 at 8000 482 / 513, 5 at 6000 557 / 631, 22000 782 / 1010, 8 at 8000 748 / 796, of equal length within 1 % or better.
 //   more pairs than half the CUs, hence one split (3 layers, h / 64 queries, lengths n / 8 .. n and n / 2 .. n): 5 x 32 heads at 2500 739 / 741 and 771 / 751,
@@ -760,12 +766,16 @@ struct AttnPlan {
 //     604 / 553, 4 x 40 at 2500 866 / 840 and 886 / 848 (32 queries are ahead by at most 1 %, where five or six lengths spread from n / 20);
 //     grouped heads (2 layers): 5 at 3000 503 / 521 and 523 / 526, 8 at 3000 627 / 632 and 649 / 654.
 //   15 nodes, one sequence: 1000 s3 573, s5 568; 4000 s4 609, s6 595; 8000 s4 664, s6 632; two 2000 s3 613, s4 604, s6 614; 8000 s4 688, s6 673; three 2000 s2
-//     650, s4 644; 8000 s2 779, s4 759, s5 780; four 2000 s2 666, s4 678; six 2000 s1 784, s2 802.
+//     650, s4 644; 8000 s2 779, s4 759, s5 780; four 2000 s2 666, s4 678; six 2000 s1 784, s2 802.  10 layers, grouped heads, one: 14000 s6 1277, s7 1283, s8 1170 (two
+//     at 4500 s6 1134, s8 1095, one at 7000 s6 1129, s8 1081: left, the count is of the length); 32 heads 14000 s6 1318, s8 1365.  16 layers of 16 heads: one 10000 s6 1180,
+//     s7 1138, 14000 s6 1310, s8 1220; two 14000 s6 1395, s7 1335; three 4500 s4 1287, s5 1244, s6 1279; four 4500 s4 1366, s6 1418; five 4500 s3 1496, s4 1519 (2100 1338,
+//     1336); six 4500 s2 1649, s4 1617.  8 layers of 40 heads: two 4500 s3 1248, s4 1263.
 static AttnPlan attn_plan(int T, const KvGeom& g, int B, int max_prefix, bool fused) {
   const int pairs = B * q_heads(g), cus = num_cus(), nb = max_prefix >> 5;
   const int by_len = 1 + (int)sqrtf((float)nb / 8.0f);
   AttnPlan p{true, 1, false};
   auto at_most = [](int a, int b) { return a < b ? a : b; };
+  auto at_least = [](int a, int b) { return a > b ? a : b; };
   if (T == 64) {
     const double through = (double)pairs * max_prefix * (g.quant ? 264 : 512);  // bytes of K and V that a launch takes through the CUs once
     p.halves = pairs <= cus && ((g.quant && B > 1) || (g.group > 1 && max_prefix < 3584) ||
@@ -776,14 +786,18 @@ static AttnPlan attn_plan(int T, const KvGeom& g, int B, int max_prefix, bool fu
     const int by_fill = (512 + pairs - 1) / pairs;         // aim at ~512 workgroups
     p.splits = at_most(most, by_fill);
   } else if (T == 15 && 8 * pairs <= 3 * cus) {
-    p.splits = at_most(nb / 6, 8 * pairs <= cus || (4 * pairs <= cus && max_prefix >= 4096) ? 6 : 4);
+    int most = 4;
+    if (8 * pairs <= cus) most = at_least(6, at_most(by_len, full_splits(g, B, pairs)));
+    else if (B <= 2 && 4 * pairs <= cus && max_prefix >= 4096) most = at_least(6, cus / pairs);
+    else if (3 * pairs <= cus && max_prefix >= 2560) most = cus / pairs;
+    p.splits = at_most(nb / 6, most);
   } else if (2 * pairs <= cus) {
     if (T == 15)
       p.splits = at_most(by_len, cus / pairs);
     else if (p.halves)
       p.splits = halves_splits(B, pairs, max_prefix);
     else
-      p.splits = at_most(1 + (int)sqrtf((float)nb / 4.0f), g.quant || g.group > 1 ? cus / pairs : cus * 4 / 5 / pairs + (B > 1));
+      p.splits = at_most(1 + (int)sqrtf((float)nb / 4.0f), g.quant ? cus / pairs : full_splits(g, B, pairs));
   }
 #ifdef MDZ_DEV_KNOBS
   static const char* env_s = getenv("MDZ_ATTN_SPLITS");  // development builds only
@@ -812,7 +826,8 @@ AttentionPlan attn_mfma_plan(int tree, const KvGeom& g, int B, int max_prefix, b
 }
 
 // Scratch of the splits' partial outputs.  A workspace is sized before the cache's row type is known and may serve shorter prefixes than it was
-// sized for: the most splits of any plan for up to max_prefix keys.  Each rule's count grows with the prefix; only from 32 to 64 queries it may fall.
+// sized for: the most splits of any plan for up to max_prefix keys.  Each rule's count grows with the prefix, but from 32 to 64 queries and, for
+// 15 nodes, at 2560 keys.
 int64_t attn_mfma_scratch_bytes(int B, const KvGeom& g, int T, int max_prefix) {
   const int pairs = B * q_heads(g);
   int most = attn_plan(T, g, B, max_prefix, false).splits;
@@ -824,6 +839,10 @@ int64_t attn_mfma_scratch_bytes(int B, const KvGeom& g, int T, int max_prefix) {
   }
   if (T == 64 && 2 * pairs <= num_cus()) {
     const int s = halves_splits(B, pairs, max_prefix);
+    if (s > most) most = s;
+  }
+  if (T == 15 && max_prefix >= 2560) {
+    const int s = attn_plan(T, g, B, 2559, true).splits;
     if (s > most) most = s;
   }
 #ifdef MDZ_DEV_KNOBS

@@ -74,3 +74,34 @@ def test_single_query_splits_of_grouped_heads(B, max_prefix, quant, splits):
     (16, 2, 6064, "one_mfma", 7), (16, 10, 764, "one_fma", 4), (32, 1, 9064, "one_mfma", 6), (40, 1, 9064, "one_mfma", 4)])
 def test_single_query_splits_of_16bit_rows(n_heads, B, max_prefix, kernel, splits):
     assert _plan(_model(n_heads, tree="tree1"), B, max_prefix) == (kernel, 1, splits)
+
+
+@pytest.mark.parametrize("n_heads,kv_heads,B,max_prefix,splits", [
+    (32, 0, 1, 14064, 6), (32, 8, 1, 14064, 8), (16, 0, 1, 9064, 6), (16, 0, 1, 9216, 7), (16, 0, 1, 14064, 8), (16, 0, 2, 14064, 7), (16, 0, 3, 2559, 4),
+    (16, 0, 3, 4564, 5), (16, 0, 4, 4564, 4), (32, 0, 2, 4095, 4), (32, 0, 2, 4564, 6), (16, 0, 5, 2559, 4), (16, 0, 5, 2560, 3), (40, 0, 2, 4564, 3),
+    (32, 0, 3, 4564, 4), (16, 0, 6, 4564, 4), (16, 0, 7, 4564, 2), (16, 0, 1, 200, 1), (40, 0, 1, 7064, 6)])
+def test_splits_of_the_15_node_tree(n_heads, kv_heads, B, max_prefix, splits):
+    assert _plan(_model(n_heads, kv_heads, "tree15"), B, max_prefix) == ("tree", 32, splits)
+
+
+def test_splits_of_48_pairs():
+    """(288 workgroups of 32 queries where the launch takes the longest sequences first)"""
+    assert [_plan(_model(16), 3, n) for n in (1400, 1535, 1536, 2047, 2048)] == [("tree", 32, 2)] * 2 + [("tree", 32, 3)] * 3
+
+
+@pytest.mark.parametrize("tree", ["tree15", "tree64", "tree1"])
+@pytest.mark.parametrize("n_heads,kv_heads", [(1, 0), (2, 0), (5, 0), (16, 0), (32, 0), (32, 8), (40, 0), (48, 12), (64, 0), (80, 0)])
+def test_a_workspace_serves_shorter_prefixes_and_both_row_types(tree, n_heads, kv_heads):
+    m = _model(n_heads, kv_heads, tree)
+    T = P.medusa_tree_info(P.TREES[tree])["T"]
+    row = 130 if tree == "tree1" else T * 130  # floats of one split's partial output and its two statistics
+    for B in (1, 2, 3, 4, 5, 7, 9, 17, 40):
+        base, before = P.medusa_workspace_bytes(m, B, 0), 0
+        for max_prefix in sorted(list(range(0, 6000, 61)) + [2559, 2560, 3583, 3584, 4095, 4096] + list(range(6000, 40000, 977))):
+            ws = P.medusa_workspace_bytes(m, B, max_prefix)
+            assert ws >= before, (B, max_prefix)
+            before = ws
+            for quant in ("",) if tree == "tree15" else ("", "fp8e4m3"):
+                for fused in (True, False):
+                    splits = _plan(m, B, max_prefix, quant, fused)[2]
+                    assert splits == 1 or ws - base >= B * n_heads * splits * row * 4, (B, max_prefix, quant, fused)

@@ -50,7 +50,7 @@ def test_several_sequences_8bit(n_heads, batch, max_prefix):
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
 @pytest.mark.parametrize("n_heads,batch,lengths", [(32, 1, [1200]), (32, 3, [1184, 32, 700]), (32, 4, [200, 1000, 0, 31]), (2, 48, None), (2, 49, None),
-                                                   (2, 2, [4100, 40])])
+                                                   (2, 2, [4100, 40]), (16, 5, [2560, 100, 0, 31, 700]), (16, 3, [2561, 64, 33])])
 def test_15_nodes(n_heads, batch, lengths, dtype):
     w = _w(n_heads, dtype, W.TREE15)
     S_list = lengths or [(131 * b) % 1200 for b in range(batch)]
