@@ -1,10 +1,11 @@
-"""Key-splits of the single-query attention (decode_splits in attn_decode.hip) at the lengths and batches where they change: one split up to
-twelve blocks; many sequences of ungrouped heads, in the other kernel from 2048 keys on; grouped heads below and from 4096 keys on; K and V loaded
-non-temporally once a pass reads 350 MB of them.  Bounds: the layer parity tests'."""
+"""Key-splits and kernel of the single-query attention (decode_splits in attn_decode.hip) at the lengths and batches where they change: one split
+up to twelve blocks; several sequences of ungrouped heads, in the FMA kernel from seven blocks per split on; more pairs than CUs; grouped heads, a
+workgroup per CU and two; 8-bit rows; K and V loaded non-temporally once a pass reads 350 MB of them.  Every case asserts the plan it is
+written for.  Bounds: the layer parity tests'."""
 import pytest
 
-import paper_2603_03383_amd as P
 import workload as W
+from tests import gpu_util as G
 from tests.test_gpu_kv8 import check_layer_kv8
 from tests.test_gpu_parity import _check_layer, _layer_case
 
@@ -17,20 +18,23 @@ def _w(n_heads, dtype="bf16", **kw):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
-@pytest.mark.parametrize("n_heads,kv_heads,batch,max_prefix", [
-    (4, 0, 1, 383), (4, 0, 1, 384),        # twelve blocks, thirteen
-    (4, 0, 3, 3000),                       # splits by length
-    (2, 0, 48, 1119), (2, 0, 48, 1120),    # three splits; six, FMA kernel
-    (2, 0, 64, 895), (2, 0, 64, 896),      # two; five, FMA kernel
-    (2, 0, 112, 639), (2, 0, 112, 640),    # one; three, FMA kernel
-    (2, 0, 129, 2047), (2, 0, 129, 2048),  # more pairs than CUs: two and three splits
-    (2, 0, 260, 2048),                     # 520 pairs: three
-    (4, 2, 64, 4095), (4, 2, 64, 4096),    # grouped: two and four splits
-    (4, 2, 68, 2303), (4, 2, 68, 2304),    # one and four
-    (4, 2, 129, 2047), (4, 2, 129, 2048),  # one and two
+@pytest.mark.parametrize("n_heads,kv_heads,batch,max_prefix,kernel,splits", [
+    (4, 0, 1, 383, "one_mfma", 1), (4, 0, 1, 384, "one_mfma", 2),      # twelve blocks, thirteen
+    (4, 0, 3, 3000, "one_mfma", 6),                                    # by length
+    (2, 0, 48, 1119, "one_mfma", 3), (2, 0, 48, 1120, "one_fma", 6), (2, 0, 48, 2272, "one_fma", 6),
+    (2, 0, 64, 895, "one_mfma", 2), (2, 0, 64, 896, "one_fma", 5),
+    (2, 0, 112, 639, "one_mfma", 1), (2, 0, 112, 640, "one_fma", 3),   # nearly as many pairs as CUs
+    (2, 0, 129, 2047, "one_fma", 2), (2, 0, 129, 2048, "one_fma", 3),  # more
+    (2, 0, 260, 2048, "one_fma", 3),
+    (4, 2, 64, 4095, "one_mfma", 2), (4, 2, 64, 4096, "one_mfma", 4),
+    (4, 2, 68, 2303, "one_mfma", 1), (4, 2, 68, 2304, "one_mfma", 4),
+    (4, 2, 129, 2047, "one_mfma", 1), (4, 2, 129, 2048, "one_mfma", 2),
+    (4, 2, 8, 2064, "one_mfma", 8), (4, 2, 8, 3000, "one_mfma", 8),    # few pairs
 ])
-def test_layer(n_heads, kv_heads, batch, max_prefix, dtype):
+def test_layer(n_heads, kv_heads, batch, max_prefix, kernel, splits, dtype):
     w = _w(n_heads, dtype, n_kv_heads=kv_heads)
+    plan = G.attention_plan(w, batch, max_prefix)
+    assert (plan["kernel"], plan["splits"]) == (kernel, splits)
     S_list = [max_prefix if batch == 1 else (611 * b) % min(1500, max_prefix) for b in range(batch)]
     S_list[-1] = min(max_prefix, 2000)
     _check_layer(_layer_case(w, S_list, max_prefix, x_seed=f"decode_plan_x{batch}_{max_prefix}"), S_list, dtype)
@@ -50,16 +54,16 @@ def test_non_temporal_loads_8bit():
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
-@pytest.mark.parametrize("n_heads,kv_heads,batch,max_prefix,splits", [
-    (2, 0, 48, 1119, 3), (2, 0, 48, 1120, 6), (2, 0, 16, 3600, 17), (2, 0, 128, 640, 3), (4, 0, 1, 1400, 6), (4, 2, 68, 2304, 4), (4, 2, 48, 3584, 6)])
-def test_8bit_splits(n_heads, kv_heads, batch, max_prefix, splits, dtype):
-    """Several sequences around the length where the FMA kernel takes them, in seventeen splits and at the most pairs; one sequence; grouped
-    heads from the lengths on where they take two workgroups per CU."""
+@pytest.mark.parametrize("n_heads,kv_heads,batch,max_prefix,kernel,splits", [
+    (2, 0, 48, 1119, "one_mfma", 3), (2, 0, 48, 1120, "one_fma", 6), (2, 0, 16, 3600, "one_fma", 17), (2, 0, 128, 640, "one_fma", 3),
+    (4, 0, 1, 1400, "one_mfma", 6), (40, 0, 1, 3584, "one_fma", 13), (4, 2, 68, 2304, "one_mfma", 4), (4, 2, 48, 3584, "one_mfma", 6)])
+def test_8bit_splits(n_heads, kv_heads, batch, max_prefix, kernel, splits, dtype):
+    """Several sequences around the length where the FMA kernel takes them, in seventeen splits and at the most pairs; one sequence, a long one of
+    40 heads; grouped heads from the lengths on where they take two workgroups per CU."""
     S_list = [(211 * b) % 600 for b in range(batch)]
     S_list[-1] = min(max_prefix, 1100)
     w = _w(n_heads, dtype, kv_quant="fp8e4m3", n_kv_heads=kv_heads).with_(prefix=tuple(S_list))
     seed = f"decode_plan8_x{batch}_{max_prefix}"
-    r = _layer_case(w, S_list, max_prefix, x_seed=seed)
-    plan = P.medusa_attention_plan(r["kv"].model.desc, batch, max_prefix, "fp8e4m3")
-    assert plan["splits"] == splits and plan["kernel"] == ("one_fma" if not kv_heads and splits * batch * n_heads > 512 else "one_mfma")
-    check_layer_kv8(r, S_list, w, seed)
+    plan = G.attention_plan(w, batch, max_prefix)
+    assert (plan["kernel"], plan["splits"]) == (kernel, splits)
+    check_layer_kv8(_layer_case(w, S_list, max_prefix, x_seed=seed), S_list, w, seed)

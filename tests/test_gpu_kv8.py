@@ -124,13 +124,14 @@ def check_layer_kv8(r, S_list, w, x_seed):
     return err / _scale(r["ref"]), err2 / _scale(ref2), worst_frac
 
 
-# (14400 keys: beyond the prefix up to which a workgroup carries 32 of the 64 queries, so both kernel variants run)
+# (a launch planned for 28500 keys: beyond the prefix up to which a workgroup carries 32 of the 64 queries, so both kernel variants run)
 @pytest.mark.parametrize("S_list,max_prefix", [([0], 0), ([77], 100), ([1024], 1024), ([300, 0, 45], 300), ([5000], 5003),
-                                                ([14400], 14400)])
+                                                ([14400], 14400), ([2000], 28500)])
 @pytest.mark.parametrize("kv_heads,dtype", [(0, "bf16"), (8, "bf16"), (8, "fp16")], ids=["mha-bf16", "gqa8-bf16", "gqa8-fp16"])
 def test_7b_width_layer_8bit_rows(S_list, max_prefix, kv_heads, dtype):
     w = W.CONFIGS["cfg2_layer_bf16"].with_(name="layer_kv8", dtype=dtype, n_kv_heads=kv_heads, prefix=tuple(S_list),
                                             kv_quant="fp8e4m3")
+    assert G.attention_plan(w, len(S_list), max_prefix)["queries"] == (64 if max_prefix == 28500 else 32)
     r = _layer_case(w, S_list, max_prefix, x_seed="kv8_layer_x")
     rel, rel2, frac = check_layer_kv8(r, S_list, w, "kv8_layer_x")
     print(f"kv8 layer {S_list} kv_heads={kv_heads} {dtype}: err/scale {rel:.3e}, with the GPU's rows substituted {rel2:.3e}, "

@@ -634,10 +634,12 @@ def ragged_batch_case(w):
 
 def test_cfg4_full_depth_32_layers_at_16k_prefix():
     """Config 4's longest point as a whole step: 32 layers at a 16384-token prefix (K and V of 4.3 GB each, so layer
-    offsets pass 2^32 bytes; 64 queries per workgroup and 8 key-splits in every layer), every logit, the hidden
+    offsets pass 2^32 bytes; 64 queries per workgroup and six key-splits in every layer), every logit, the hidden
     states, node_argmax, acceptance, and the KV rows written by layers 0, 16 and 31 against the oracle."""
     w = W.CONFIGS["cfg4_step_16k"]
     S = w.prefix[0]
+    plan = G.attention_plan(w, 1, S)
+    assert (plan["queries"], plan["splits"]) == (64, 6)
     tol = TOL["bf16"]
     tree = U.oracle_tree(w)
     T = tree["T"]

@@ -35,6 +35,7 @@ def _k_rows(tree, dtype, wk, kv_heads, max_prefix):
     dm.add_layer(zero(D, D), wk.to(td), wk.to(td), zero(D, D), zero(704, D), zero(704, D), zero(D, 704), one, one)
     dm.finalize()
     T = dm.tree_info["T"]
+    assert P.medusa_attention_plan(dm.desc, 1, max_prefix)["queries"] == (64 if max_prefix > 512 else 32)
     kv = P.DeviceKV(dm, 1, max_prefix + T)
     x = torch.ones(T, D, dtype=torch.float32, device=G.DEV)
     P.tree_verify_layer(dm.desc, dm.layer(0), 0, x, kv.desc, torch.tensor([S], dtype=torch.int32, device=G.DEV), 1, max_prefix,
@@ -54,7 +55,7 @@ def test_k_row_does_not_depend_on_the_kernel(dtype, kv_heads):
         wk[h * HD:h * HD + 64, 0], wk[h * HD + 64:(h + 1) * HD, 0] = torch.from_numpy(x), torch.from_numpy(y)
     node_at = {t: [P.medusa_tree_tables(P.TREES[t])["depth"].tolist().index(e) for e in range(4)] for t in ("tree15", "tree64")}
     ref = _k_rows("tree64", dtype, wk, kv_heads, 512)[:, node_at["tree64"]]
-    wide = _k_rows("tree64", dtype, wk, kv_heads, 4000)[:, node_at["tree64"]]
+    wide = _k_rows("tree64", dtype, wk, kv_heads, 60000)[:, node_at["tree64"]]
     small = _k_rows("tree15", dtype, wk, kv_heads, 512)[:, node_at["tree15"]]
     assert torch.equal(ref, wide), int((ref != wide).sum())
     assert torch.equal(ref, small), int((ref != small).sum())

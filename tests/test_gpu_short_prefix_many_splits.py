@@ -1,11 +1,12 @@
 """Short sequences in a launch planned for a long prefix: the key-splits of the tree attention are chosen by max_prefix, so most of
 them get no block of a short sequence, and the merge, which takes the splits eight at a time, meets a whole group of empty ones
-before the split of the tree slots (9 splits at 16384 keys, 10 at 20736).  Both 16-bit types and both orders of RoPE; lengths
+before the split of the tree slots (9 to 12 splits at 16384 keys, 10 to 12 at 20736).  Both 16-bit types and both orders of RoPE; lengths
 around the first two key blocks.  Bounds: the layer parity tests'."""
 import pytest
 
 import paper_2603_03383_amd as P
 import workload as W
+from tests import gpu_util as G
 from tests.test_gpu_parity import _check_layer, _layer_case
 
 pytestmark = pytest.mark.gpu
@@ -18,7 +19,8 @@ def _w(tree, n_heads, dtype="bf16", **kw):
                                               name=f"short_{tree.name}_{n_heads}", **kw)
 
 
-def _run(w, S_list, max_prefix):
+def _run(w, S_list, max_prefix, fused=True):
+    assert G.attention_plan(w, len(S_list), max_prefix, fused)["splits"] >= 9
     r = _layer_case(w, S_list, max_prefix, x_seed=f"short_x{max_prefix}_{len(S_list)}")
     _check_layer(r, S_list, w.dtype)
 
@@ -42,6 +44,6 @@ def test_separate_rope_kernel(tree):
     was = P.medusa_test_force_unfused_rope(True)
     try:
         for S in (0, 40):
-            _run(_w(tree, 2), [S], 20736)
+            _run(_w(tree, 2), [S], 20736, fused=False)
     finally:
         P.medusa_test_force_unfused_rope(was)

@@ -9,10 +9,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("ffn", [8192, 10240, 16384])  # two, three and four waves
 @pytest.mark.parametrize("tree,batches", [(W.TREE1, [1, 15, 16, 17, 31, 32, 33, 63, 64]), (W.TREE15, [1, 2, 3, 4]), (W.TREE64, [1])],
                          ids=["1 node", "15 nodes", "64 nodes"])
-def test_layer_with_a_wide_feed_forward_block(tree, batches, dtype):
-    w = W.CONFIGS["cfg2_layer_bf16"].with_(d=256, n_heads=2, head_dim=128, ffn=10240, dtype=dtype, tree=tree, name=f"wide_ffn_{tree.name}")
+def test_layer_with_a_wide_feed_forward_block(tree, batches, ffn, dtype):
+    w = W.CONFIGS["cfg2_layer_bf16"].with_(d=256, n_heads=2, head_dim=128, ffn=ffn, dtype=dtype, tree=tree, name=f"wide_ffn_{tree.name}")
     for n in batches:
         S_list = [(7 * b) % 40 for b in range(n)]
         _check_layer(_layer_case(w, S_list, 40, x_seed=f"wide_ffn_x{n}"), S_list, dtype)

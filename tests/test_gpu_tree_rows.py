@@ -33,17 +33,19 @@ def test_layer_rows_at_block_edges(tree, dtype, n_heads, kv_heads):
     _check_layer(_layer_case(w, EDGES, 97, x_seed="rows_xb"), EDGES, dtype)
 
 
-@pytest.mark.parametrize("max_prefix", [97, 14400], ids=["32 queries", "64 queries"])
-def test_layer_rows_at_block_edges_8bit(max_prefix):
-    w = _w(W.TREE64, n_kv_heads=2, kv_quant="fp8e4m3")
+@pytest.mark.parametrize("max_prefix,queries", [(97, 32), (118500, 64)])
+def test_layer_rows_at_block_edges_8bit(max_prefix, queries):
+    w = _w(W.TREE64, kv_quant="fp8e4m3")
+    assert G.attention_plan(w, 1, max_prefix)["queries"] == queries
     for S in (0, 1, 15, 31, 33, 63):
         check_layer_kv8(_layer_case(w.with_(prefix=(S,)), [S], max_prefix, x_seed=f"rows8_x{S}"), [S], w.with_(prefix=(S,)), f"rows8_x{S}")
 
 
 def test_layer_rows_with_64_queries_per_workgroup():
     w = _w(W.TREE64)
+    assert G.attention_plan(w, 1, 47000)["queries"] == 64
     for S in (0, 17, 33):
-        _check_layer(_layer_case(w, [S], 4000, x_seed=f"rows64_x{S}"), [S], "bf16")
+        _check_layer(_layer_case(w, [S], 47000, x_seed=f"rows64_x{S}"), [S], "bf16")
 
 
 def test_the_narrow_models_have_more_slots_than_are_requested_together():
@@ -74,10 +76,13 @@ def _pass_over_a_full_cache(tree, dtype, quant, max_prefix, kv_heads=2, n_heads=
     return kv, T, before, run, rows
 
 
-@pytest.mark.parametrize("max_prefix", [97, 14400], ids=["32 queries", "64 queries"])
+@pytest.mark.parametrize("queries", [32, 64])
 @pytest.mark.parametrize("tree,dtype,quant", FORMATS, ids=lambda v: getattr(v, "name", v))
-def test_slots_outside_the_tree_keep_their_bytes(tree, dtype, quant, max_prefix):
-    kv, T, before, run, _ = _pass_over_a_full_cache(tree, dtype, quant, max_prefix)
+def test_slots_outside_the_tree_keep_their_bytes(tree, dtype, quant, queries):
+    """64 queries per workgroup: five key-splits of a long prefix; with 8-bit rows one split of more heads than CUs."""
+    n_heads, max_prefix = (4, 97) if queries == 32 else (24, 97) if quant else (4, 17000)
+    kv, T, before, run, _ = _pass_over_a_full_cache(tree, dtype, quant, max_prefix, n_heads=n_heads)
+    assert T == 15 or P.medusa_attention_plan(kv.model.desc, len(EDGES), max_prefix, quant)["queries"] == queries
     run()
     torch.cuda.synchronize()
     for b, S in enumerate(EDGES):

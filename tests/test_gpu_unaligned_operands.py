@@ -63,7 +63,22 @@ def test_lm_head_on_an_unaligned_hidden_out(dtype, tree, batch, vocab, want_logi
 @pytest.mark.parametrize("tree,batch", [(W.TREE1, 65), (W.TREE15, 6), (W.TREE15, 13), (W.TREE64, 5)], ids=lambda v: getattr(v, "name", v))
 @pytest.mark.parametrize("shape", [dict(), dict(d=320, n_heads=5, head_dim=64, ffn=64), dict(d=2048, n_heads=16, ffn=5632)], ids=str)
 def test_layer_on_unaligned_weights(dtype, tree, batch, shape):
-    w = _w(tree, dtype, **shape)
+    _check_layer_on_unaligned_weights(_w(tree, dtype, **shape), batch)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("tree,batch,tile_rows", [(W.TREE1, 65, 96), (W.TREE15, 6, 96), (W.TREE1, 129, 192), (W.TREE64, 3, 192)],
+                         ids=lambda v: getattr(v, "name", v))
+def test_layer_on_unaligned_weights_in_tiles_of_96_columns(dtype, tree, batch, tile_rows):
+    """The gate/up product (22016 columns) with its mixed gate and up columns, gathered into registers."""
+    w = _w(tree, dtype, ffn=11008)
+    plan = P.medusa_gemm_many_rows_plan(P.DTYPES[dtype], batch * P.medusa_tree_info(P.TREES[tree.name])["T"], 2 * w.ffn, w.d, 1, True)
+    assert (plan["tile_rows"], plan["tile_cols"]) == (tile_rows, 96)
+    _check_layer_on_unaligned_weights(w, batch)
+
+
+def _check_layer_on_unaligned_weights(w, batch):
+    tree, dtype = w.tree, w.dtype
     dm = G.device_model(w.with_(vocab=64), heads=False, n_layers=1)
     T = dm.tree_info["T"]
     lw = dm.layer(0)

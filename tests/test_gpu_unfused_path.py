@@ -23,8 +23,10 @@ TP.test_small_bf16_layer_ragged_and_empty_prefix([77], 100)
 prof = P.medusa_profile_end()
 assert prof.get("rope", dict(launches=0))["launches"] >= 1, prof   # the separate RoPE + cache-write kernel did run
 print("unfused path taken", flush=True)
-for S_list, max_prefix in [([0], 0), ([77], 100), ([300, 0, 45], 300), ([5000, 131], 5003), ([33], 33)]:
+for S_list, max_prefix in [([0], 0), ([77], 100), ([300, 0, 45], 300), ([5000, 131], 5003), ([33], 33), ([500, 131], 80000)]:
     TP.test_small_bf16_layer_ragged_and_empty_prefix(S_list, max_prefix)
+    plan = P.medusa_attention_plan(P.ModelDesc(256, 2, 128, 704, 1024, 1, P.MDZ_BF16, P.MDZ_TREE_64, 1e-5, 1e4), len(S_list), max_prefix, fused=False)
+    assert plan["queries"] == (64 if max_prefix == 80000 else 32)
     print("small layer", S_list, "ok", flush=True)
 TP.test_cfg2_full_size_layer_bf16()
 print("full-size layer ok", flush=True)
