@@ -618,7 +618,8 @@ bool attn_decode_supported(int dtype, int tree, const KvGeom& g) {
 // the others: one up to twelve blocks, then by the square root of the length (at 600 keys 3 splits 59.6 us per layer, 2 62.3).  Beyond about
 // three quarters of a workgroup per CU more splits only add up, but for many keys, where a CU with two workgroups of long sequences beside CUs with one
 // of short ones is the last to end.  Ungrouped heads are then better off with several workgroups per CU in the other kernel.
-// us, steps of 4 layers, lengths n / 9 .. n, splits of the former rule (one per seven blocks, two workgroups per CU) / of this one:
+// us, steps of 4 layers (the memory-side cache holds the shorter ones' K and V), lengths n / 9 .. n, one split per seven blocks and two workgroups
+// per CU / by the square root:
 //   32 heads: one sequence of 300 keys 541 / 535, 3000 575 / 565, 6000 620 / 597, 16384 735 / 690; three at 3000 605 / 587, 6000 665 / 641 (two splits
 //     685); four at 1000 564 / 557, 3000 626 / 606, 6000 701 / 672; eight at 300 559 / 548, 3000 708 / 677, 6000 870 / 806; twelve at 300 569 / 558,
 //     3000 760 / 750; 18 at 3000 883 / 858.  40 heads, 8-bit rows: two at 4000 602 / 598, three 607 / 607 (two splits 636)

@@ -6,7 +6,7 @@
 //   * A wave owns NT tiles of 32 output columns and moves W through a ring of four half K-stages in
 //     registers: three half stages (CK/2 input features each) stay in flight while it multiplies the
 //     fourth, and every load is unconditional so the hardware wait counters let the prefetch overlap
-//     the MFMAs (a CU then keeps ~100 KB in flight, what the HBM latency asks for).  AHEAD = 2 keeps two: with every CU streaming and
+//     the MFMAs (12 KiB per wave, 24 .. 48 KiB per CU; from some 32 KiB on a CU takes in no more).  AHEAD = 2 keeps two: with every CU streaming and
 //     nothing but the stream to wait for (up to 32 rows, several whole bands per workgroup: the vocabulary matrices of the heads, and
 //     that of a verify pass that writes logits) fewer requests queue up in front of the memory: four heads from one row 683 / 672 us
 //     per call, eight rows 702 / 693, sixteen 730 / 726; a one-layer pass with logits, one row 264 / 261, eight 270 / 269, 15 rows 282
@@ -27,7 +27,7 @@
 //   * SWIGLU (the gate/up matrix, whose gate and up tiles alternate in the packed order, run with whole bands per
 //     workgroup): a wave's 32 columns are 16 gate and the 16 up columns of the same features, picked by the lanes' addresses, so
 //     SiLU(gate) * up needs one exchange between lanes and is written as E: neither the fp32 sums nor a second kernel are needed.
-//     What bounds such a launch is that the vector memory path of a CU returns in order and holds some 32 KiB of requests: X (L2
+//     What bounds such a launch is that the vector memory path of a CU returns in order and takes in no more from some 32 KiB of requests on: X (L2
 //     hits) and W (HBM) together come in at ~52 GB/s, so the CUs that a launch leaves idle are lost.  A workgroup therefore takes as
 //     few waves of 32 columns as still leave one workgroup per CU (swiglu_waves).
 //   * ARGMAX (the LM head of a verify pass, whole bands per workgroup, when the caller wants no logits): at the end
@@ -262,7 +262,7 @@ __global__ void __launch_bounds__(WPB * 64)
   // that comes from HBM, and the first barrier passes while the first W half stages are still in flight.
   load_x();
   __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_barrier();  // all four waves' X requests enter the CU's memory pipeline ahead of any W request
+  __builtin_amdgcn_s_barrier();  // all waves' X requests enter the CU's memory pipeline ahead of any W request
   __builtin_amdgcn_sched_barrier(0);
   load_w(wb[0]);
   load_w(wb[1]);

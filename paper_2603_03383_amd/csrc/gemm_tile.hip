@@ -18,7 +18,7 @@
 //     banks without padding (2.6 conflict cycles are counted per 16-byte read).  W arrives in the packed order (common.h): 4 KiB per tile and round, contiguous;
 //   * the MFMA is issued as W x X^T: a lane then holds four consecutive output columns of ONE row per register quad, so
 //     sums leave as 16-byte (fp32) or 8-byte (SwiGLU output) stores.
-// What bounds it: below ~300 rows the loads (a CU takes in 45 - 60 GB/s of X and W whatever the ring holds, the chip some 10 TB/s: see
+// What bounds it: below ~300 rows the loads (a CU takes in 45 - 62 GB/s of X and W whatever the ring holds, the chip some 10 TB/s: see
 // BURSTS below), hence the tall tiles; at 1024 rows the LDS, which a round of the 256 x 128 tile asks for 96 KiB of
 // operand reads and 48 KiB of incoming loads beside 1024 clocks of MFMAs (1024 x 22016 x 4096: 196 us; without the loads
 // 145, without the MFMAs 146).  Measured on [M, K] x [N, K]^T, us per launch, before (128 x 256 tiles, operands through registers) / now:
@@ -44,7 +44,7 @@ __global__ void __launch_bounds__(2 * WR * WC * 64, (2 * WR * WC + 3) / 4)
                      int64_t ldp, int64_t part_stride, int nb_m, int nb_n, int ksplit, E* __restrict__ U) {
   static_assert(!SWIGLU || NT <= 2, "a wave holds the gate and the up columns of its features: two tiles, or the halves of one");
   constexpr int GW = WR * WC, NW = 2 * GW;             // waves of a group and of the workgroup
-  // X comes from L2 and W from HBM, but a CU's vector memory path returns in order and holds ~32 KiB of requests, so X requests queued
+  // X comes from L2 and W from HBM, but a CU's vector memory path returns in order and takes in no more from ~32 KiB of requests on, so X requests queued
   // among W requests take as long as those.  With a ring of four rounds the X of two rounds is requested in one round and the W of two
   // in the next: 24 + 16 KiB a round (192 x 128) then stream at 62 GB/s per CU instead of 56, 16 + 16 KiB at 52 instead of 48.
   // us per launch, mixed / in bursts: 192 rows, 22016 x 4096 52.3 / 50.9, 12288 x 4096 33.9 / 33.2; 128 rows, a step of 4 layers 814 / 793.
