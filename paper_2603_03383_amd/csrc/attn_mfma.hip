@@ -726,8 +726,9 @@ bool attn_mfma_supported(int dtype, int tree, const KvGeom& g) {
 }
 
 // Key-splits of a launch with 32 queries per workgroup (see attn_plan)
-static int halves_splits(int B, int pairs, int max_prefix) {
+static int halves_splits(int B, int pairs, int max_prefix, bool grouped) {
   const int by_len = 1 + (int)sqrtf((float)(max_prefix >> 5) / 8.0f), cus = num_cus();
+  if (B == 1 && grouped && by_len * pairs >= cus) return cus / pairs;
   const int most = B == 1 || max_prefix < 1536 ? cus / (2 * pairs) : max_prefix < 2048 ? cus * 9 / 8 / (2 * pairs) : cus / pairs;
   return most < 1 ? 1 : by_len < most ? by_len : most;
 }
@@ -754,8 +755,9 @@ struct AttnPlan {
 //     h s4 711; 16384 s6 800, s7 803, s8 818, h s4 844.  16 heads: 4000 s4 405, h s4 353; 7000 s6 413, s12 393, h s4 370, h s6 355; 10000 s8 419,
 //     h s8 398; 14000 s8 441, s12 422, h s8 425.  40 heads: 4000 s4 725, h s3 707, h s4 728; 7000 s5 753, s6 758, h s3 754; 14000 s5 832, s6 853.
 //   8-bit rows, 32 heads: 7000 h s6 665, h s4 659, s8 670; 10000 h s7 705, h s4 696, s8 703; 14000 h s4 732, s6 756, s8 729.
-//   four query heads to a key/value head (their blocks come from L2): 4000 s4 728, h s4 677; 7000 s6 719, h s4 694; 14000 s8 759, h s4 752; 16384 s6 811,
-//     s8 779, h s4 799.
+//   four query heads to a key/value head (their blocks come from L2, the better for a workgroup per CU, i.e. a split on each XCD): 4000 s4 728, h s4 677; 7000 s6
+//     719, h s4 694; 10 layers: 8000 s8 1316, h s4 1313, h s8 1304, 11500 s8 1368, h s4 1390, h s8 1367, 13500 s8 1396, h s4 1440, h s8 1406; 8-bit rows 13000 s8 1417,
+//     h s4 1367, h s8 1351, 20000 s8 1531, h s4 1494, h s8 1455.
 //   several sequences (n / 8 .. n keys; the longest is the last to end, so long ones take twice the splits): 2 at 1500 h s2 788, h s3 802; 4000 s4 864,
 //     h s4 853; 8000 s3 922, s4 923, h s4 926; 3 at 1500 h s1 892, h s2 901 (3 x 16 heads, 16 layers, 1100 h s2
 //     1520, h s3 1519, 1700 h s2 1573, h s3 1556); 2500 h s1 931, h s2 922; 8000 s2 1091, s3 1060; 4 at 600 h s1 1002, h s2 1025.
@@ -779,7 +781,7 @@ static AttnPlan attn_plan(int T, const KvGeom& g, int B, int max_prefix, bool fu
   if (T == 64) {
     const double through = (double)pairs * max_prefix * (g.quant ? 264 : 512);  // bytes of K and V that a launch takes through the CUs once
     p.halves = pairs <= cus && ((g.quant && B > 1) || (g.group > 1 && max_prefix < 3584) ||
-                                through <= (B == 1 ? 96e6 : 160e6) * (g.group > 1 ? 2.5 : g.quant ? 1.3 : 1.0));
+                                through <= (B == 1 ? 96e6 : 160e6) * (g.group > 1 ? (B == 1 && !g.quant ? 2.0 : 2.5) : g.quant ? 1.3 : 1.0));
   }
   if (!fused) {
     const int most = (max_prefix + T + 31) / 32 / 8;       // >= 2 blocks per wave
@@ -795,7 +797,7 @@ static AttnPlan attn_plan(int T, const KvGeom& g, int B, int max_prefix, bool fu
     if (T == 15)
       p.splits = at_most(by_len, cus / pairs);
     else if (p.halves)
-      p.splits = halves_splits(B, pairs, max_prefix);
+      p.splits = halves_splits(B, pairs, max_prefix, g.group > 1);
     else
       p.splits = at_most(1 + (int)sqrtf((float)nb / 4.0f), g.quant ? cus / pairs : full_splits(g, B, pairs));
   }
@@ -838,7 +840,7 @@ int64_t attn_mfma_scratch_bytes(int B, const KvGeom& g, int T, int max_prefix) {
     if (s > most) most = s;
   }
   if (T == 64 && 2 * pairs <= num_cus()) {
-    const int s = halves_splits(B, pairs, max_prefix);
+    const int s = halves_splits(B, pairs, max_prefix, g.group > 1);
     if (s > most) most = s;
   }
   if (T == 15 && max_prefix >= 2560) {

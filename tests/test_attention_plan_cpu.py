@@ -105,3 +105,10 @@ def test_a_workspace_serves_shorter_prefixes_and_both_row_types(tree, n_heads, k
                 for fused in (True, False):
                     splits = _plan(m, B, max_prefix, quant, fused)[2]
                     assert splits == 1 or ws - base >= B * n_heads * splits * row * 4, (B, max_prefix, quant, fused)
+
+
+@pytest.mark.parametrize("max_prefix,quant,plan", [
+    (8064, "", (32, 4)), (11718, "", (32, 4)), (11719, "", (64, 8)), (13564, "", (64, 8)), (12543, "fp8e4m3", (32, 4)), (12544, "fp8e4m3", (32, 8)),
+    (20064, "fp8e4m3", (32, 8))])
+def test_one_long_sequence_of_grouped_heads_takes_eight_splits(max_prefix, quant, plan):
+    assert _plan(_model(32, 8), 1, max_prefix, quant)[1:] == plan

@@ -23,7 +23,7 @@ def _plan(w, batch, max_prefix):
 
 @pytest.mark.parametrize("n_heads,kv_heads,max_prefix,plan", [
     (32, 0, 5859, (32, 4)), (32, 0, 5860, (64, 6)), (16, 0, 11718, (32, 7)), (16, 0, 11719, (64, 10)), (16, 0, 16384, (64, 12)), (40, 0, 4000, (32, 3)),
-    (32, 8, 14648, (32, 4)), (32, 8, 14649, (64, 8)), (4, 0, 4000, (32, 4))])
+    (32, 8, 11718, (32, 4)), (32, 8, 11719, (64, 8)), (4, 0, 4000, (32, 4))])
 def test_one_sequence(n_heads, kv_heads, max_prefix, plan):
     w = _w(n_heads, n_kv_heads=kv_heads)
     assert _plan(w, 1, max_prefix) == plan
@@ -31,10 +31,10 @@ def test_one_sequence(n_heads, kv_heads, max_prefix, plan):
         _check_layer(_layer_case(w, [S], max_prefix, x_seed=f"plan_x{n_heads}_{max_prefix}_{S}"), [S], "bf16")
 
 
-@pytest.mark.parametrize("max_prefix,plan", [(9000, (32, 4)), (14773, (64, 8))])
-def test_one_sequence_8bit(max_prefix, plan):
+@pytest.mark.parametrize("kv_heads,max_prefix,plan", [(0, 9000, (32, 4)), (0, 14773, (64, 8)), (8, 12543, (32, 4)), (8, 12544, (32, 8))])
+def test_one_sequence_8bit(kv_heads, max_prefix, plan):
     S = 2000
-    w = _w(32, kv_quant="fp8e4m3").with_(prefix=(S,))
+    w = _w(32, kv_quant="fp8e4m3", n_kv_heads=kv_heads).with_(prefix=(S,))
     assert _plan(w, 1, max_prefix) == plan
     check_layer_kv8(_layer_case(w, [S], max_prefix, x_seed=f"plan8_x{max_prefix}"), [S], w, f"plan8_x{max_prefix}")
 
